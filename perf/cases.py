@@ -336,10 +336,13 @@ def work(case):
 def tolerance(case):
     """Encode: masks, offsets, scales, radius codes and payload are whole or exactly defined; the index of a chunk
     whose two best codewords score within 1e-6 of one another may be either, about one chunk in 3000 has such a pair
-    and one in 40 of those is resolved the other way, a chunk touching one or two words.  Decode and attention: fp16
-    results, about four times the distance from 64-bit arithmetic."""
-    if case["op"] in ("encode", "append"):
-        return {"rel": 0.0, "differ": 1e-4}
+    and one in 40 of those is resolved the other way, a chunk touching one or two words: up to 1.6e-5 of the words
+    differ from 64-bit arithmetic (seen), in a small tensor a word or two.  Decode and attention: fp16 results, about
+    four times the distance from 64-bit arithmetic."""
+    c = case
+    if c["op"] in ("encode", "append"):
+        words = c["n"] * c["B"] * c["H"] * c["T"] * ((c["D"] + 3) // 4) * (_index_bits(c["S"]) + c["b_r"]) / 32
+        return {"rel": 0.0, "differ": min(0.01, 6e-5 + 4 / words)}
     return {"rel": 1e-3, "max": 4e-3}
 
 
