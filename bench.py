@@ -4,7 +4,7 @@
 A step is one pass of the whole hot path over the workload: every (layer, role) tensor is
 encoded (median select, search + quantise + pack, outlier scan + gather) and then decoded, inputs and
 outputs resident in HBM.  Prints ONE JSON line: whole-path elems/s, the encode / decode
-split, the roofline position of the dominant kernel (the MFMA search) and of the decode
+split, the roofline position of the dominant kernel (the search) and of the decode
 kernel, measured with HIP events on the launch stream, and the CPU oracle timed on a bounded
 sample of the same workload.
 
@@ -24,7 +24,6 @@ if ROOT not in sys.path:
 
 METRIC = "HQMQ encode/decode elems/sec at 1 GPU; % of fp32-compute (enc) / HBM (dec) roofline"
 PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 matrix (and packed vector) peak
-PEAK_F16_TFLOPS = 2500.0     # MI355X dense fp16 matrix peak
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E peak
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # plain (unpacked) VALU lane-operations per second, in 1e12
 
@@ -49,11 +48,16 @@ def profile_figures(workload: str) -> dict:
 
 
 def search_flops_per_chunk(S: int) -> float:
-    """Flops the implemented search formulation spends per chunk: per secondary one 4x4
-    matrix-vector product on the MFMA unit (16 FMA = 32 flop) and the closed-form nearest
-    24-cell vertex on the VALU (3 adds + 1 multiply); S rounded up to the loop's group of 16."""
+    """Flops per chunk of the exhaustive search in its cheapest closed form, the metric's yardstick: per secondary one
+    4x4 matrix-vector product (16 FMA = 32 flop) and the nearest 24-cell vertex (3 adds + 1 multiply); S rounded up to
+    groups of 16.  The search kernel reaches the same result by point location and does a small part of them."""
     s16 = (S + 15) // 16 * 16
     return 36.0 * s16
+
+
+def search_bytes_per_chunk(chunks_per_row: int, words_per_row: int) -> float:
+    """Algorithmic HBM bytes of the search per chunk: 8 read; code words, flag word, scale and offset of a row written."""
+    return 8.0 + (4.0 * words_per_row + 4.0 + 2.0 + 4.0) / chunks_per_row
 
 
 def decode_bytes_per_chunk(w: int, p_out: float, chunks_per_row: int = 32, words_per_row: int | None = None) -> float:
@@ -188,15 +192,14 @@ def main() -> int:
     status = max(int(e.status.item()) for e in encs)
 
     import statistics
-    S16 = (wl.S + 15) // 16
-    search_kernel = "k_search" if wl.D == 128 else "k_search_flat"
+    cells = wl.S <= 512 and chunks_per_tensor // wl.H >= (32768 if wl.S > 128 else 65536)  # the library's rule
+    search_kernel = "k_search_cells" if cells else "k_search" if wl.D == 128 else "k_search_flat"
     decode_kernel = "k_decode" if wl.D in (64, 96, 128) else "k_decode_rows"
     prof = profile_figures(wl.name)
     flops_launch = search_flops_per_chunk(wl.S) * chunks_per_tensor * tensors_per_enc_launch
     search_tflops = flops_launch / (search_ms * 1e-3) / 1e12
-    closed_form_per_chunk = 5.5 * 16 * S16          # VALU lane-operations of the closed form, per chunk
-    valu_tops = closed_form_per_chunk * chunks_per_tensor * tensors_per_enc_launch / (search_ms * 1e-3) / 1e12
-    mfma_tflops = 128.0 * S16 * 16 * chunks_per_tensor * tensors_per_enc_launch / (search_ms * 1e-3) / 1e12
+    search_bytes_chunk = search_bytes_per_chunk(info.chunks_per_row, info.code_words_per_row)
+    search_gbs = search_bytes_chunk * chunks_per_tensor * tensors_per_enc_launch / (search_ms * 1e-3) / 1e9
     dec_bytes_chunk = decode_bytes_per_chunk(info.code_bits, p_out, info.chunks_per_row, info.code_words_per_row)
     dec_bytes_launch = dec_bytes_chunk * chunks_per_tensor * tensors_per_dec_launch
     dec_gbs = dec_bytes_launch / (decode_ms * 1e-3) / 1e9
@@ -205,21 +208,14 @@ def main() -> int:
         v = prof.get((kernel, "traffic_bytes_per_tensor"))
         return None if v is None else v * per_launch
 
-    # What the search kernel executes, from the committed instruction counters (per pass of 64 chunks, one per
-    # lane): every VALU instruction it issues against the instructions of the closed form alone, and the
-    # matrix instructions; priced at the measured launch time this gives the share of the chip's VALU issue
-    # slots the kernel fills (the bound) next to the share that is the algorithm (the headline fraction).
-    valu_pass = prof.get((search_kernel, "valu_instructions_per_pass"))
-    mfma_pass = prof.get((search_kernel, "mfma_instructions_per_pass"))
-    passes_launch = chunks_per_tensor * tensors_per_enc_launch / 64.0
-    executed = {"source": prof.get(("source", "instruction_counters")),
-                "valu_instructions_per_pass": valu_pass, "mfma_instructions_per_pass": mfma_pass,
-                "closed_form_instructions_per_pass": closed_form_per_chunk,
-                "analytic_mfma_per_pass": 4.0 * S16 + 1.0,
-                "valu_issue_frac": None, "closed_form_share_of_executed": None}
-    if valu_pass:
-        executed["valu_issue_frac"] = valu_pass * passes_launch * 64 / (search_ms * 1e-3) / 1e12 / PEAK_VALU_TOPS
-        executed["closed_form_share_of_executed"] = closed_form_per_chunk / valu_pass
+    # What the search kernel executes, from the committed instruction counters: the share of the chip's VALU issue
+    # slots it fills at the measured launch time (256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, plain instructions).
+    valu_chunk = prof.get((search_kernel, "valu_lane_operations_per_chunk"))
+    executed = {"source": prof.get(("source", "instruction_counters")), "valu_lane_operations_per_chunk": valu_chunk,
+                "valu_issue_frac": None}
+    if valu_chunk:
+        executed["valu_issue_frac"] = (valu_chunk * chunks_per_tensor * tensors_per_enc_launch
+                                       / (search_ms * 1e-3) / 1e12 / PEAK_VALU_TOPS)
 
     result = {
         "metric": METRIC,
@@ -232,7 +228,7 @@ def main() -> int:
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (search: screened on the matrix cores with fp32 factors as 2-part fp16 splits and fp32 accumulation, decided on fp32 VALU scores)",
+        "dtype": "f32 (search: fp32 scores of the codewords that can be nearest in the chunk's box; near ties by fp32 scores of all)",
         "data": "synthetic",
         "config": {"workload": wl.name, "layers": layers, "B": wl.B, "kv_heads": wl.H, "T": wl.T, "D": wl.D,
                    "S": wl.S, "b_r": wl.b_r, "C": wl.C, "tensors_per_step": n_t,
@@ -253,25 +249,17 @@ def main() -> int:
         "status_bits": status,
         "bits_per_element_stored": (encs[0].nbytes() - encs[0].outliers.numel() * 2 + 8 * n_out / n_t) * 8
         / wl.elems_per_tensor,
-        # The search kernel is bound by VALU issue (its vector ALUs are busy for the whole kernel: "executed"
-        # below, from the committed rocprofv3 counters), so that is the roofline reported first.  `achieved` is
-        # ALGORITHMIC work over the measured average launch time: the closed-form scoring, 5.5 VALU
-        # lane-operations per (chunk, secondary) pair (3 additions and 2.5 three-input maxima; no FMA among
-        # them, so one operation counts as one flop); `peak` is the rate at which the chip issues plain wave64
-        # VALU instructions, 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (packed fp32 forms are switched off in this
-        # build).  "fp32_equivalent" is the metric's own yardstick, the fp32 flops of the whole search
-        # formulation (36 S per chunk) against the 157.3 TFLOP/s fp32 peak: it is NOT a roofline fraction (it
-        # can exceed 1) because the K = 4 contraction runs on the fp16 matrix path as a 2-part split of every
-        # fp32 factor, whose peak is 16 times the fp32 one; "executed_mfma" prices those instructions against
-        # their own peak.
-        "roofline": {"kernel": search_kernel, "bound": "alu",
-                     "achieved": valu_tops, "peak": PEAK_VALU_TOPS, "unit": "TFLOP/s", "frac": valu_tops / PEAK_VALU_TOPS,
+        # The search reads every chunk once and writes its code: that is what it cannot do without, so its roofline is
+        # HBM; what it spends the time on is VALU issue ("executed", from the committed rocprofv3 counters; the phase
+        # also holds the launch that builds the box index).  "fp32_equivalent" is the metric's own yardstick, the fp32
+        # flops of the exhaustive search in closed form (36 S per chunk) against the 157.3 TFLOP/s fp32 peak: NOT a
+        # roofline fraction, since point location reaches the same result without doing them.
+        "roofline": {"kernel": search_kernel, "bound": "hbm",
+                     "achieved": search_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": search_gbs / PEAK_HBM_GBS,
                      "traffic": traffic(search_kernel, tensors_per_enc_launch),
                      "traffic_source": prof.get(("source", "hbm_traffic")),
                      "tensors_per_launch": tensors_per_enc_launch,
-                     "flops_per_chunk": closed_form_per_chunk,
-                     "flop": "one VALU lane-operation of the closed-form scoring (add, three-input max, multiply)",
-                     "peak_derivation": "256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, plain (unpacked) VALU issue",
+                     "bytes_per_chunk": search_bytes_chunk,
                      "avg_launch_ms": search_ms,
                      "median_launch_ms": statistics.median(search_launch_ms), "min_launch_ms": min(search_launch_ms),
                      "launches_timed": len(search_launch_ms),
@@ -280,12 +268,9 @@ def main() -> int:
                                          "ratio_to_fp32_peak": search_tflops / PEAK_FP32_TFLOPS,
                                          "flops_per_chunk": search_flops_per_chunk(wl.S),
                                          "formulation": "W_min (36 S flop/chunk)",
-                                         "note": "not a roofline fraction: the fp32-accurate contraction runs as 4 fp16 "
-                                                 "products per term on the matrix cores; the fp32 peak is the metric's "
-                                                 "yardstick (target >= 0.5), not a bound on this formulation"},
-                     "executed_mfma": {"instruction": "v_mfma_f32_32x32x16_f16", "flops_per_chunk": 128.0 * S16 * 16,
-                                       "achieved": mfma_tflops, "peak": PEAK_F16_TFLOPS, "unit": "TFLOP/s",
-                                       "frac": mfma_tflops / PEAK_F16_TFLOPS}},
+                                         "note": "not a roofline fraction: the flops of the exhaustive closed form, most of "
+                                                 "which point location does not do; the fp32 peak is the metric's "
+                                                 "yardstick (target >= 0.5)"}},
         "roofline_decode": {"kernel": decode_kernel, "bound": "hbm", "achieved": dec_gbs, "peak": PEAK_HBM_GBS,
                             "unit": "GB/s", "frac": dec_gbs / PEAK_HBM_GBS,
                             "traffic": traffic(decode_kernel, tensors_per_dec_launch),

@@ -137,9 +137,21 @@ static Geometry make_geometry(const hqmq_params *p)
         const uint64_t want = (n_h / 32 + 1023) / 1024 * 1024;
         g.cand_cap = (int32_t)(want > (uint64_t)kCandCap ? want : (uint64_t)kCandCap);
     }
+    g.cell_n = g.cell_groups = g.cell_used = g.cell_words = 0;
     g.search_rows = search_rows_for(p->T, g.S16, g.A16, g.D, g.row_words);
     g.n_search_blocks_per_seg = (uint32_t)((p->T + g.search_rows - 1) / g.search_rows);
     return g;
+}
+
+// The search of the general path.  With the box index from 65536 chunks per head on (32768 with more than 128
+// secondaries): the index costs 20 to 35 us per call (1.2 us per head beyond some 30 heads), the search behind it a
+// sixth of the matrix screen's time at S = 256, two thirds at S = 16.  Measured, whole encode of one or two tensors
+// with 8 heads, without / with: 234 / 90 and 130 / 81 and 105 / 78 us at T = 2048, D = 128, S = 256, 64, 16; below the line
+// 71 / 74 us at T = 1024, S = 64, and 97 / 129 with 64 heads.
+static bool use_cells(const Geometry &g)
+{
+    const uint64_t chunks = (uint64_t)g.B * g.T * g.n_c;
+    return g.A16 > 0 && chunks >= (g.S > 128 ? 32768u : 65536u);
 }
 
 struct WorkspaceLayout {
@@ -366,17 +378,35 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
                 return hip_failed(err);
             continue;
         }
-        err = launch_select_median(g, wo, batch, n, params->C, no_outliers || thr_given != nullptr, st);
+        Geometry gs = g;
+        WorkspaceOffsets wos = wo;
+        if (use_cells(g)) {
+            const CellShape c = cell_shape_for(g.S);
+            gs.cell_n = c.n;
+            gs.cell_groups = c.groups;
+            gs.cell_used = c.used;
+            gs.cell_words = (24 * g.S + 31) / 32;
+            // never fewer rows than search_rows_for says, which sized the arrays of the workgroups' totals
+            gs.search_rows = g.T >= kSearchRowsSwitchHuge ? kSearchRowsHuge : g.T >= kSearchRowsSwitch ? kSearchRowsLarge : kSearchRowsSmall;
+        } else if (g.search_rows != kSearchRowsSmall) {
+            // 64 rows per workgroup, whose totals take the memory of the candidate lists (the select is done with them):
+            // 8 bytes per 64 of at most 65536 rows of a head
+            gs.search_rows = kSearchRowsSmall;
+            wos.block_sum = wo.cand;
+            wos.block_pre = wo.cand + (uint32_t)align_up((uint64_t)g.B * g.H * ((g.T + kSearchRowsSmall - 1) / kSearchRowsSmall) * 4, 256);
+        }
+        gs.n_search_blocks_per_seg = (uint32_t)((g.T + gs.search_rows - 1) / gs.search_rows);
+        err = launch_select_median(gs, wo, batch, n, params->C, no_outliers || thr_given != nullptr, st);
         if (err == hipSuccess)
             err = mark(1);
         if (err != hipSuccess)
             return hip_failed(err);
-        err = launch_search(g, wo, batch, n, st);
+        err = launch_search(gs, wos, batch, n, st);
         if (err == hipSuccess)
             err = mark(2);
         if (err != hipSuccess)
             return hip_failed(err);
-        err = launch_outlier_list(g, wo, batch, n, st);
+        err = launch_outlier_list(gs, wos, batch, n, st);
         if (err == hipSuccess)
             err = mark(3);
         if (err != hipSuccess)

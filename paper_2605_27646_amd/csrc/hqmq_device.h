@@ -10,9 +10,9 @@
 namespace hqmq {
 
 constexpr int kChunksPerRow = 32;    // chunks of a row of D = 128 elements, and the most a row may have
-constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan:
-constexpr int kSearchRowsLarge = 256;  // 64 for short segments (more workgroups), 256 from 2048 rows on,
-constexpr int kSearchRowsHuge = 512;   // 512 from 4096 rows on (16-wave workgroups)
+constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64 for short
+constexpr int kSearchRowsLarge = 256;  // segments (more workgroups); the search with the box index takes 256 rows from
+constexpr int kSearchRowsHuge = 512;   // kSearchRowsSwitch on and 512 from kSearchRowsSwitchHuge on (1024: no faster)
 constexpr int kSearchRowsSwitch = 2048;
 constexpr int kSearchRowsSwitchHuge = 4096;
 constexpr int kThreads = 256;        // default workgroup: 4 wave64
@@ -76,6 +76,10 @@ struct Geometry {
     int32_t cand_cap;     // candidate keys kept per head: kCandCap, or 1/32 of the head's chunks if that is more
     int32_t select_sampled;  // the median select predicts the median's bin from a sample of the rows (large heads only)
     int32_t fused_by_head;  // fused search only: one workgroup per head takes the rows of all batch entries (B T <= 64)
+    int32_t cell_n;       // boxes per axis of the search's index (0: no index, see hqmq_search.hip)
+    int32_t cell_groups;  // list groups it may have, group 0 included
+    int32_t cell_used;    // codewords its lists may name
+    int32_t cell_words;   // 32-bit words of a bit per codeword
     int32_t search_rows;               // rows per search workgroup (kSearchRowsSmall or kSearchRowsLarge)
     uint32_t n_search_blocks_per_seg;  // ceil(T / search_rows)
 };
@@ -93,12 +97,29 @@ inline size_t search_lds_bytes(int S16, int A16, int D, int row_words, int waves
 }
 constexpr size_t kLdsPerCu = 160 * 1024;
 
-// Waves of a search workgroup.  256 or more rows per workgroup, and tables so large
-// that fewer than four 4-wave workgroups fit a CU's LDS: one workgroup of 16 waves per CU when its LDS
-// fits (four waves on every SIMD sharing one copy of the tables; measured 3 % faster than two
-// workgroups of 4, while four or more small workgroups, where they fit, are 7 to 13 % faster than the large one).
-// Otherwise 4 waves when two workgroups fit a CU's LDS, else one workgroup of 8, which keeps two waves
-// on every SIMD.
+// Shape of the search's box index for S secondaries: boxes per axis, list groups and codewords (a random codebook of
+// unit quaternions needs 3730 groups and 610 codewords at S = 256, 2210 and 360 at 128, 850 and 115 at 24, with a
+// spread of 2 % over codebooks; what does not fit is searched without the index).
+struct CellShape {
+    int n, groups, used;
+};
+inline CellShape cell_shape_for(int S)
+{
+    const int used = ((13 * S) / 5 + 99) / 4 * 4;  // keeps what follows in LDS 16-byte aligned
+    if (S <= 8)
+        return {8, 512, used};
+    if (S <= 32)
+        return {12, 1152, used};
+    if (S <= 128)
+        return {16, 2560, used};
+    return {20, S <= 256 ? 4224 : 5120, used};
+}
+// functions and lists lie in the first 64 KiB of LDS: their addresses fit 16 bits
+static_assert(((13 * kScreenMaxS) / 5 + 99 + 1) * 16 + 5120 * 8 < 65536, "16-bit LDS addresses");
+__host__ __device__ inline size_t cell_head_bytes(int n) { return ((size_t)n * n * n * 2 + 15) / 16 * 16; }
+
+// Waves of a search workgroup of the matrix screen, which has 64 rows: 4 when two workgroups fit a CU's LDS, else one
+// workgroup of 8, which keeps two waves on every SIMD.  (The answers for more rows only size workspaces.)
 inline int search_waves_for(int S16, int A16, int D, int row_words, int rows)
 {
     if (A16 == 0)
@@ -109,10 +130,8 @@ inline int search_waves_for(int S16, int A16, int D, int row_words, int rows)
     return 2 * search_lds_bytes(S16, A16, D, row_words, 4, rows) > kLdsPerCu ? 8 : 4;
 }
 
-// Rows per search workgroup.  Four or more 4-wave workgroups per CU are the fastest shape (measured 3 to
-// 7 % ahead of one 16-wave workgroup): the most rows with which they fit, 256 for long segments (the head's
-// operand table is copied less often) or 64.  With tables too large for that: one 16-wave workgroup of 512
-// or 256 rows per CU, else 64 rows.
+// The rows per workgroup that a workspace is sized for (its arrays of workgroup totals): no launch takes fewer without
+// finding its own place for the totals.  A size that callers have allocated for, so it stays.
 inline int search_rows_for(int T, int S16, int A16, int D, int row_words)
 {
     if (A16 == 0)
@@ -130,6 +149,16 @@ inline int search_rows_for(int T, int S16, int A16, int D, int row_words)
     return kSearchRowsSmall;
 }
 
+// Dynamic LDS of one workgroup of the search with the box index.
+inline size_t cell_lds_bytes(const Geometry &g)
+{
+    const size_t tables = ((size_t)g.cell_used + 1) * 16 + (size_t)g.S * 16 + cell_head_bytes(g.cell_n) +
+                          (size_t)g.cell_groups * 8 + (size_t)g.cell_used * 4 + 24 * 32;
+    const size_t scratch = (size_t)g.cell_words * 8 + 4;
+    const size_t rows = (16 * 64 + (size_t)g.search_rows) * 4;
+    return tables + (rows > scratch ? rows : scratch);
+}
+
 // Workspace carve-up (device pointers into the caller's workspace).
 struct Workspace {
     SelectState *state;            // [H]
@@ -145,6 +174,8 @@ struct Workspace {
     unsigned long long *cand;      // [H][cand_cap]
     uint32_t *block_sum;           // [B*H*n_search_blocks_per_seg] outliers per search workgroup
     uint32_t *block_pre;           // same shape, exclusive prefix
+    uint32_t *cell_state;          // [H][1 + cell_words] counter and used bits of the search's box index; the boxes and
+                                   // lists themselves take the candidate list's memory, which the select is done with
     uint4 *aop;                    // [H][kATiles * S16][64] MFMA A operands of the search, built once per call
 };
 
@@ -191,6 +222,7 @@ __device__ __forceinline__ Workspace carve_workspace(char *base, const Workspace
     ws.cand = reinterpret_cast<unsigned long long *>(base + o.cand);
     ws.block_sum = reinterpret_cast<uint32_t *>(base + o.block_sum);
     ws.block_pre = reinterpret_cast<uint32_t *>(base + o.block_pre);
+    ws.cell_state = reinterpret_cast<uint32_t *>(base + o.aop);
     ws.aop = reinterpret_cast<uint4 *>(base + o.aop);
     return ws;
 }
@@ -256,9 +288,9 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 // of fp16 values are exact in fp64, so only the three additions round.
 __device__ __forceinline__ double chunk_norm2(const half4_t v)
 {
-    double x0 = (double)(float)v[0], x1 = (double)(float)v[1];
-    double x2 = (double)(float)v[2], x3 = (double)(float)v[3];
-    return ((x0 * x0 + x1 * x1) + x2 * x2) + x3 * x3;
+    const double x0 = (double)(float)v[0], x1 = (double)(float)v[1];
+    const double x2 = (double)(float)v[2], x3 = (double)(float)v[3];
+    return fma(x3, x3, fma(x2, x2, fma(x1, x1, x0 * x0)));  // a fused addition of an exact product rounds like the addition
 }
 
 // True when one of the chunk's four fp16 values is an infinity or a NaN (exponent field all ones).  Taken

@@ -116,6 +116,8 @@ __global__ __launch_bounds__(kThreads) void k_init(Geometry g, WorkspaceOffsets 
         ws.hist1[i] = 0;
     if (i < 3u * (uint32_t)g.H)
         ws.cand_count[i] = 0;
+    if (g.cell_n > 0 && i < (uint32_t)g.H * (1u + (uint32_t)g.cell_words))
+        ws.cell_state[i] = 0;
     if (i < (uint32_t)g.H) {
         // +inf: nothing is flagged (replaced by the select, unless the caller supplies the thresholds)
         ws.thr[i] = tn.thr_given ? tn.thr_given[i] : __longlong_as_double(0x7ff0000000000000LL);

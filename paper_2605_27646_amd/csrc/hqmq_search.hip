@@ -27,11 +27,14 @@
 // winning group is not ahead of every other group by 6e-6 of its score is searched again over all S secondaries with
 // plain fp32 arithmetic.  Either way the choice between secondaries is made on fp32 closed-form scores.
 //
-// Work split: a workgroup (4, 8 or 16 wave64) owns 64, 256 or 512 rows of one (b, h) segment, so the A
+// Work split: a workgroup (4 or 8 wave64) owns 64 rows of one (b, h) segment, so the A
 // matrices of the head sit in LDS once per workgroup.  A wave takes 64 chunks, one per lane, at a
 // time and runs them as two 32-chunk MFMA column groups: two whole rows of 128 elements in
 // k_search, 64 consecutive chunks of the workgroup's flattened rows in k_search_flat (any other
 // head dimension).  The per-chunk steps (scale, radius code, direction search) are shared.
+//
+// That is the search of short tensors.  Long ones locate a chunk's direction in a box index over the codewords
+// (k_cells, k_search_cells below), which replaces the scan over all S secondaries.
 #include "hqmq_device.h"
 
 namespace hqmq {
@@ -95,6 +98,25 @@ __device__ __forceinline__ double dpp_move_f64(double v)
     return __longlong_as_double((long long)dpp_move64<kCtrl>((unsigned long long)__double_as_longlong(v)));
 }
 
+template <int kCtrl>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    return dpp_move_f64<kCtrl>(v);
+}
+template <int kCtrl>
+__device__ __forceinline__ float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+
+// Maximum with the lane 16 away (lane ^ 16).
+__device__ __forceinline__ float max_across_16(float v)
+{
+    const auto pair = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(pair[0]), __uint_as_float(pair[1]));
+}
+__device__ __forceinline__ double max_across_16(double v) { return fmax(v, __shfl_xor(v, 16, 64)); }
+
 __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b)
 {
     return a > b ? a : b;
@@ -145,6 +167,21 @@ __device__ __forceinline__ uint16_t sigma_of_row_max(double rmax)
     return sigma16;
 }
 
+// Whether sigma_of_row_max has to take the fp64 recipe: rmax its argument (rounded to fp32), sf the fp32 square root.
+__device__ __forceinline__ bool scale_unsure(float rmax, float sf)
+{
+    const int dist = (int)(__float_as_uint(sf) & 0x1fffu) - 0x1000;
+    return rmax != 0.f && sf < 65504.f && (sf < 0x1.0p-14f || (dist >= -8 && dist <= 8));
+}
+
+__device__ __forceinline__ int radius_code_exact(double r2, uint16_t sigma16, double Lq)
+{
+    const double sigma = half_bits_to_double(sigma16);
+    double q = rint((sqrt(r2) * Lq) / sigma);
+    q = q < 0.0 ? 0.0 : (q > Lq ? Lq : q);
+    return (int)q;
+}
+
 // Radius code r_q = clamp(rint(sqrt(r2) * L / sigma), 0, L), defined in fp64.  An fp32
 // evaluation with the hardware's 1-ulp square root (r_f) and reciprocal is off by at most
 // 6e-7 * L (five roundings of <= 1.2e-7 each); it rounds the same way unless it lands within
@@ -162,12 +199,8 @@ __device__ __forceinline__ int radius_code(double r2, float r_f, uint16_t sigma1
         rq = (int)rintf(qf);
     }
     if (__any(exact_needed)) {
-        if (exact_needed) {
-            const double sigma = half_bits_to_double(sigma16);
-            double q = rint((sqrt(r2) * Lq) / sigma);
-            q = q < 0.0 ? 0.0 : (q > Lq ? Lq : q);
-            rq = (int)q;
-        }
+        if (exact_needed)
+            rq = radius_code_exact(r2, sigma16, Lq);
     }
     return rq;
 }
@@ -458,6 +491,32 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
     return code;
 }
 
+// Outlier offsets local to the workgroup of kRows rows from t0 on, and its total; the global prefix is added by the
+// scan / gather kernels that follow.  Called by one wave.
+template <int kRows>
+__device__ __forceinline__ void write_row_offsets(const Geometry &g, const Workspace &ws, const EncodedPtrs &enc, int lane,
+                                                  int seg, int t0, const uint32_t *rcnt)
+{
+    uint32_t carry = 0;
+#pragma unroll
+    for (int part = 0; part < kRows / 64; ++part) {
+        const int r = 64 * part + lane;
+        const uint32_t cnt = t0 + r < g.T ? rcnt[r] : 0u;
+        uint32_t inc = cnt;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            uint32_t o = __shfl_up(inc, d, 64);
+            if (lane >= d)
+                inc += o;
+        }
+        if (t0 + r < g.T)
+            enc.row_off[(int64_t)seg * g.T + t0 + r] = carry + inc - cnt;
+        carry += __shfl(inc, 63, 64);
+    }
+    if (lane == 0)
+        ws.block_sum[(size_t)seg * g.n_search_blocks_per_seg + blockIdx.x] = carry;
+}
+
 }  // namespace
 
 // The K = 4 contraction v = A(q_s) u on v_mfma_f32_32x32x16_f16: a product covers 8 secondaries (32 rows =
@@ -519,10 +578,8 @@ __global__ __launch_bounds__(kThreads) void k_prepare_operands(Geometry g, Works
         ws.aop[(size_t)h * g.A16 * kATiles * 64 + idx] = operand_entry(tn.sec + (size_t)h * g.S * 4, g.S, idx);
 }
 
-// kWaves: 4 (several workgroups per CU); 16 for workgroups of 256 or 512 rows whose tables would leave
-// room for fewer than four such workgroups (one per CU, four waves on every SIMD); 8 when tables and row
-// state are so large that only one workgroup fits a CU and 16 waves do not: twice the waves then share
-// the tables and keep two waves on every SIMD.
+// kWaves: 4, or 8 when tables and row state are so large that only one workgroup fits a CU: twice the waves then
+// share the tables and keep two waves on every SIMD.
 // This kernel is for rows of 128 elements (32 chunks: two rows per wave); k_search_flat below takes
 // every other head dimension.
 // kFused: the form for tensors of a few rows whose thresholds are known beforehand (appended tokens with
@@ -875,34 +932,780 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
     }
 }
 
-// The search kernels' dynamic LDS exceeds the 64 KiB a kernel gets by default once S > 208: raises the limit
+// ---------------------------------------------------------------------------------------------------------------
+// The search of long tensors: point location instead of a scan over the secondaries.
+//
+// Folding.  The score of codeword P_p q_s is <u, P_p q_s> = <conj(P_0) u, P_p' q_s> with P_p = P_0 P_p' for any P_0 of
+// 2T.  With P_0 the element nearest to u, w = conj(P_0) u lies in the cell of 1: w_0 >= |w_i| and
+// w_0 >= (w_0 + |w_1| + |w_2| + |w_3|) / 2, that is, y = (w_1, w_2, w_3) / w_0 lies in the octahedron
+// |y_1| + |y_2| + |y_3| <= 1 (24-cell: its cells are octahedra).  Scores divided by w_0 > 0 are
+// c_0 + c_1 y_1 + c_2 y_2 + c_3 y_3: linear in y.
+// Cells.  The cube [-1, 1]^3 is cut into n^3 boxes; a box has the list of the codewords that are the best, or within
+// kCellEps of the best, somewhere in it.  Codeword c is left out when another one b is ahead of it all over the box:
+// <b - c, (1, m)> > h sum_i |b_i - c_i| + eps at the centre m with half width h: exact for linear functions, whatever
+// the norms of the secondaries.  About 6 of the 24 S codewords stay (S = 256, n = 20).
+// A chunk then costs the fold, a look-up of its box and 3 FMA and 5 more operations per listed codeword instead of
+// 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
+// is searched again over all S secondaries in fp32, so the outcome is the one of the exhaustive fp32 search.
+// Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 73 us, index
+// included; two tensors in a call: 1017 -> 146 us + 32 us for the index.  Bound by VALU issue (300 instructions per
+// 64 chunks, 115 of them in the list loop: the longest of 64 lists has 3.4 groups of four on average), LDS busy
+// half of the time; 16 % of the HBM peak.
+// ---------------------------------------------------------------------------------------------------------------
+
+namespace {
+
+constexpr int kCellThreads = 256;      // workgroup of the index build: 4 lanes per box
+constexpr int kCoarseCap = 1024;       // codewords of a block of 4^3 boxes
+constexpr int kMidCap = 384;           // codewords of a sub-block of 2^3 boxes
+constexpr int kCellMax = 64;           // codewords of a box before the pairwise test
+// Two codewords whose scores lie closer than this fraction of the best are not told apart by the lists' arithmetic.  The
+// error of a difference of two scores is at most 7.6e-7 |c_a - c_b| (y: fold, reciprocal) + 5e-7 (functions, 3 FMA), the
+// best is at least 0.7: below 1.6e-6 of it for codewords that can be next to one another (3.4e-7 measured on 800,000).
+constexpr float kCellBand = 2.0e-6f;
+constexpr float kCellEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
+                                       // kCellBand times the ratio of two scores of a box plus the rounding of the test
+constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box number of y = 1 below n
+constexpr uint32_t kCellPad = 0x7fffu; // list entry without a codeword; bit 15 marks the last group of a list
+
+// The search numbers the element P_0 that it folds with by what it has at hand (fold_primary), and needs the index of
+// P_0 P_p' in the order of the primaries: [fold][p'], rows of 32 bytes.
+struct FoldTable {
+    alignas(16) uint8_t at[24 * 32];
+};
+// fold < 8: axis element 2 slot + sign; else half-integer element with the sign bits fold - 8.  The bits (slots) 0..3
+// belong to components 2, 0, 3, 1: where the packed sign bits of the four halves end up.
+constexpr int fold_primary(int fold)
+{
+    const int comp[4] = {2, 0, 3, 1};
+    if (fold < 8)
+        return 2 * comp[fold >> 1] + (fold & 1);
+    int p = 8;
+    for (int slot = 0; slot < 4; ++slot)
+        if (((fold - 8) >> slot) & 1)
+            p += 8 >> comp[slot];
+    return p;
+}
+constexpr FoldTable make_fold_table()
+{
+    FoldTable t{};
+    int el[24][4] = {};  // twice the components
+    for (int p = 0; p < 24; ++p)
+        for (int i = 0; i < 4; ++i)
+            el[p][i] = p < 8 ? ((p >> 1) == i ? ((p & 1) ? -2 : 2) : 0) : ((((p - 8) >> (3 - i)) & 1) ? -1 : 1);
+    for (int a = 0; a < 24; ++a)
+        for (int b = 0; b < 24; ++b) {
+            const int *x = el[fold_primary(a)], *y = el[b];
+            const int c[4] = {x[0] * y[0] - x[1] * y[1] - x[2] * y[2] - x[3] * y[3],
+                              x[0] * y[1] + x[1] * y[0] + x[2] * y[3] - x[3] * y[2],
+                              x[0] * y[2] - x[1] * y[3] + x[2] * y[0] + x[3] * y[1],
+                              x[0] * y[3] + x[1] * y[2] - x[2] * y[1] + x[3] * y[0]};
+            for (int p = 0; p < 24; ++p)
+                if (c[0] == 2 * el[p][0] && c[1] == 2 * el[p][1] && c[2] == 2 * el[p][2] && c[3] == 2 * el[p][3])
+                    t.at[32 * a + b] = (uint8_t)p;
+        }
+    return t;
+}
+__constant__ const FoldTable kFoldTable = make_fold_table();
+
+// Component i of primary p.
+__device__ __forceinline__ float primary_component(int p, int i)
+{
+    if (p < 8)
+        return (p >> 1) == i ? ((p & 1) ? -1.f : 1.f) : 0.f;
+    return (((p - 8) >> (3 - i)) & 1) ? -0.5f : 0.5f;
+}
+
+// P_p q as (c_1, c_2, c_3, c_0): the linear function of a box point.
+__device__ __forceinline__ float4_t codeword_function(int p, const float4_t q)
+{
+    const float a = primary_component(p, 0), b = primary_component(p, 1), c = primary_component(p, 2),
+                d = primary_component(p, 3);
+    float4_t f;
+    f[3] = fmaf(-d, q[3], fmaf(-c, q[2], fmaf(-b, q[1], a * q[0])));
+    f[0] = fmaf(-d, q[2], fmaf(c, q[3], fmaf(b, q[0], a * q[1])));
+    f[1] = fmaf(d, q[1], fmaf(c, q[0], fmaf(-b, q[3], a * q[2])));
+    f[2] = fmaf(d, q[0], fmaf(-c, q[1], fmaf(b, q[2], a * q[3])));
+    return f;
+}
+
+__device__ __forceinline__ float value_at(const float4_t f, float m1, float m2, float m3)
+{
+    return fmaf(f[0], m1, fmaf(f[1], m2, fmaf(f[2], m3, f[3])));
+}
+
+// b (value vb at the centre) ahead of c (value vc) by more than eps all over the box of half width h
+__device__ __forceinline__ bool ahead_in_box(const float4_t b, float vb, const float4_t c, float vc, float h, float eps)
+{
+    const float spread = (fabsf(b[0] - c[0]) + fabsf(b[1] - c[1])) + fabsf(b[2] - c[2]);
+    return vb - vc > fmaf(h, spread, eps);
+}
+
+// Box of half width h around m meets the octahedron (with room for the rounding of y).
+__device__ __forceinline__ bool meets_octahedron(float m1, float m2, float m3, float h)
+{
+    return (fmaxf(fabsf(m1) - h, 0.f) + fmaxf(fabsf(m2) - h, 0.f)) + fmaxf(fabsf(m3) - h, 0.f) <= 1.0001f;
+}
+
+struct CellIndex {        // parts of one head's index in the workspace
+    uint16_t *head;       // [n^3] first group of the box's list; 0 = no list
+    uint2 *list;          // [cell_groups] groups of four 16-bit entries k = p S + s; group 0 belongs to no list
+    uint32_t *n_groups;   // groups handed out beyond group 0
+    uint32_t *used;       // [cell_words] bit k: codeword k is in some list
+};
+__device__ __forceinline__ CellIndex cell_index_of(const Geometry &g, const Workspace &ws, int h)
+{
+    CellIndex ix;
+    char *base = reinterpret_cast<char *>(ws.cand + (size_t)h * g.cand_cap);
+    ix.head = reinterpret_cast<uint16_t *>(base);
+    ix.list = reinterpret_cast<uint2 *>(base + cell_head_bytes(g.cell_n));
+    ix.n_groups = ws.cell_state + (size_t)h * (1 + g.cell_words);
+    ix.used = ix.n_groups + 1;
+    return ix;
+}
+
+}  // namespace
+
+// Index build: workgroup (block, head, tensor) does the 4^3 boxes of one block of the grid.
+//   1  the best codeword at the block's centre, and the codewords that it is not ahead of all over the block
+//   2  the same for its 2^3 sub-blocks of 2^3 boxes against that list (32 lanes each)
+//   3  the same for every box against its sub-block's list (4 lanes each), then the survivors against eight strong ones,
+//      the best two of each lane's share (every pair: 2 % fewer entries for three times the work)
+//   4  the lists, four entries to a group, in space handed out by one counter per head
+// A box whose list does not fit any of the arrays gets none; its chunks take the search over all S secondaries.
+// grid = ((n / 4)^3, H, tensors), block = 256.
+__global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+{
+    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const Workspace ws = carve_workspace(tn.ws, wo);
+    const int h = blockIdx.y, S = g.S, n = g.cell_n, nb = n / 4;
+    const float *sec_h = tn.sec + (size_t)h * S * 4;
+    const CellIndex ix = cell_index_of(g, ws, h);
+
+    __shared__ float4_t cf[kCoarseCap];
+    __shared__ uint16_t ck[kCoarseCap];
+    __shared__ uint32_t cused[kCoarseCap / 32];
+    __shared__ uint16_t mid[8][kMidCap];
+    __shared__ uint16_t kept[64][kCellMax];
+    __shared__ uint32_t n_mid[8], n_kept[64], first_group[64];
+    __shared__ unsigned long long wave_key[kCellThreads / 64];
+    __shared__ uint32_t n_coarse, list_base;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int b0 = blockIdx.x / (nb * nb), b1 = (blockIdx.x / nb) % nb, b2 = blockIdx.x % nb;
+    // box of this lane's quad: sub-block tid / 32, box of it (tid / 4) % 8
+    const int cell = tid >> 2, sub = tid & 3, sb = tid >> 5;
+    const int s0 = sb >> 2, s1 = (sb >> 1) & 1, s2 = sb & 1;
+    const int i0 = 4 * b0 + 2 * s0 + ((cell >> 2) & 1), i1 = 4 * b1 + 2 * s1 + ((cell >> 1) & 1), i2 = 4 * b2 + 2 * s2 + (cell & 1);
+    const int cell_id = (i0 * n + i1) * n + i2;
+    const float hf = 1.0f / (float)n;
+    const float margin = 1.2e-5f;  // y and the box number are rounded, the latter by kCellShrink as well
+    const float y1 = (float)(2 * i0 + 1) * hf - 1.f, y2 = (float)(2 * i1 + 1) * hf - 1.f, y3 = (float)(2 * i2 + 1) * hf - 1.f;
+    const float m1 = (float)(8 * b0 + 4) * hf - 1.f, m2 = (float)(8 * b1 + 4) * hf - 1.f, m3 = (float)(8 * b2 + 4) * hf - 1.f;
+    if (blockIdx.x == 0 && tid == 0)
+        ix.list[0] = make_uint2(kCellPad | 0x8000u | (kCellPad << 16), kCellPad | (kCellPad << 16));
+    if (!meets_octahedron(m1, m2, m3, 4.f * hf)) {  // uniform
+        if (sub == 0)
+            ix.head[cell_id] = 0;
+        return;
+    }
+    if (tid == 0)
+        n_coarse = 0;
+    if (tid < 8)
+        n_mid[tid] = 0;
+    if (tid < 64)
+        n_kept[tid] = 0;
+    if (tid < kCoarseCap / 32)
+        cused[tid] = 0;
+
+    // ---- 1: the block ------------------------------------------------------------------------------------------------
+    unsigned long long key = 0ull;
+    for (int s = tid; s < S; s += kCellThreads) {
+        float v0, v1, v2, v3;
+        const float sc = score_secondary(sec_h + 4 * s, 1.f, m1, m2, m3, v0, v1, v2, v3);
+        key = umax64(key, ((unsigned long long)__float_as_uint(sc) << 32) | (0xffffffffu - (uint32_t)s));
+    }
+    key = wave_umax64(key);
+    if (lane == 0)
+        wave_key[tid >> 6] = key;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kCellThreads / 64; ++w)
+        key = umax64(key, wave_key[w]);
+    const int s_best = (int)min(0xffffffffu - (uint32_t)key, (uint32_t)S - 1u);
+    float4_t best;
+    float v_best;
+    {
+        float v0, v1, v2, v3, sc;
+        (void)score_secondary(sec_h + 4 * s_best, 1.f, m1, m2, m3, v0, v1, v2, v3);
+        const int p = nearest_primary(v0, v1, v2, v3, sc);
+        best = codeword_function(p, *reinterpret_cast<const float4_t *>(sec_h + 4 * s_best));
+        v_best = value_at(best, m1, m2, m3);
+    }
+    {
+        const float hb = 4.f * hf + margin, eps = kCellEps * fabsf(v_best);
+        for (int s = tid; s < S; s += kCellThreads) {
+            const float4_t q = *reinterpret_cast<const float4_t *>(sec_h + 4 * s);
+            // c: P_p q as (c_1, c_2, c_3, c_0), v its value at the centre; its negative is tested along with it
+            auto test = [&](const float4_t c, float v, int p, int p_neg) {
+                if (!ahead_in_box(best, v_best, c, v, hb, eps) || !ahead_in_box(best, v_best, -c, -v, hb, eps)) {
+#pragma unroll
+                    for (int sign = 0; sign < 2; ++sign) {
+                        const float4_t f = sign ? -c : c;
+                        if (!ahead_in_box(best, v_best, f, sign ? -v : v, hb, eps)) {
+                            const uint32_t at = atomicAdd(&n_coarse, 1u);
+                            if (at < (uint32_t)kCoarseCap) {
+                                cf[at] = f;
+                                ck[at] = (uint16_t)((sign ? p_neg : p) * S + s);
+                            }
+                        }
+                    }
+                }
+            };
+            const float4_t e0 = {q[1], q[2], q[3], q[0]}, e1 = {q[0], -q[3], q[2], -q[1]};  // q, i q
+            const float4_t e2 = {q[3], q[0], -q[1], -q[2]}, e3 = {-q[2], q[1], q[0], -q[3]};  // j q, k q
+            const float v0 = value_at(e0, m1, m2, m3), v1 = value_at(e1, m1, m2, m3);
+            const float v2 = value_at(e2, m1, m2, m3), v3 = value_at(e3, m1, m2, m3);
+            test(e0, v0, 0, 1);
+            test(e1, v1, 2, 3);
+            test(e2, v2, 4, 5);
+            test(e3, v3, 6, 7);
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const float4_t ea = a ? e0 - e1 : e0 + e1;
+                const float va = a ? v0 - v1 : v0 + v1;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const float4_t eb = (b & 2 ? -e2 : e2) + (b & 1 ? -e3 : e3);
+                    const float vb = (b & 2 ? -v2 : v2) + (b & 1 ? -v3 : v3);
+                    const int p = 8 + 4 * a + b;
+                    test(0.5f * (ea + eb), 0.5f * (va + vb), p, 31 - p);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int nc = n_coarse <= (uint32_t)kCoarseCap ? (int)n_coarse : 0;  // 0: no lists in this block
+
+    // The strongest of `count` entries `entry(j)` at (z1, z2, z3), over `lanes` neighbouring lanes of which this one is number l.
+    auto strongest = [&](auto entry, int count, int l, int lanes, float z1, float z2, float z3, float &v) {
+        float vb = -3.4e38f;
+        int jb = 0;
+        for (int j = l; j < count; j += lanes) {
+            const int i = entry(j);
+            const float w = value_at(cf[i], z1, z2, z3);
+            jb = w > vb ? i : jb;
+            vb = fmaxf(vb, w);
+        }
+        for (int d = 1; d < lanes; d <<= 1) {
+            const float vo = __shfl_xor(vb, d, 64);
+            const int jo = __shfl_xor(jb, d, 64);
+            const bool take = vo > vb || (vo == vb && jo < jb);
+            vb = take ? vo : vb;
+            jb = take ? jo : jb;
+        }
+        v = vb;
+        return jb;
+    };
+
+    // ---- 2: the sub-block ----------------------------------------------------------------------------------------------
+    if (nc > 0) {
+        const float z1 = (float)(8 * b0 + 4 * s0 + 2) * hf - 1.f, z2 = (float)(8 * b1 + 4 * s1 + 2) * hf - 1.f,
+                    z3 = (float)(8 * b2 + 4 * s2 + 2) * hf - 1.f;
+        if (meets_octahedron(z1, z2, z3, 2.f * hf)) {
+            float vb;
+            const int jb = strongest([](int j) { return j; }, nc, tid & 31, 32, z1, z2, z3, vb);
+            const float4_t bf = cf[jb];
+            const float eps = kCellEps * fabsf(vb), hm = 2.f * hf + margin;
+            for (int j = tid & 31; j < nc; j += 32) {
+                const float4_t c = cf[j];
+                if (!ahead_in_box(bf, vb, c, value_at(c, z1, z2, z3), hm, eps)) {
+                    const uint32_t at = atomicAdd(&n_mid[sb], 1u);
+                    if (at < (uint32_t)kMidCap)
+                        mid[sb][at] = (uint16_t)j;
+                }
+            }
+        }
+    }
+    wave_lds_sync();  // the lanes of a sub-block, and of a box, belong to one wave
+    const int nm = n_mid[sb] <= (uint32_t)kMidCap ? (int)n_mid[sb] : 0;
+
+    // ---- 3: the box ------------------------------------------------------------------------------------------------------
+    uint32_t keep = 0;  // bit i: entry sub + 4 i of kept[cell] is in the list
+    if (nm > 0 && meets_octahedron(y1, y2, y3, hf)) {
+        const float hc = hf + margin;
+        const uint16_t *list = mid[sb];
+        float vb;
+        const int jb = strongest([&](int j) { return (int)list[j]; }, nm, sub, 4, y1, y2, y3, vb);
+        const float4_t bf = cf[jb];
+        const float eps = kCellEps * fabsf(vb);
+        float v_own[2] = {-3.4e38f, -3.4e38f};  // the two strongest survivors of this lane's share
+        int j_own[2] = {jb, jb};
+        for (int j = sub; j < nm; j += 4) {
+            const int i = list[j];
+            const float4_t c = cf[i];
+            const float v = value_at(c, y1, y2, y3);
+            if (!ahead_in_box(bf, vb, c, v, hc, eps)) {
+                j_own[1] = v > v_own[0] ? j_own[0] : v > v_own[1] ? i : j_own[1];
+                v_own[1] = __builtin_amdgcn_fmed3f(v, v_own[0], v_own[1]);
+                j_own[0] = v > v_own[0] ? i : j_own[0];
+                v_own[0] = fmaxf(v_own[0], v);
+                const uint32_t at = atomicAdd(&n_kept[cell], 1u);
+                if (at < (uint32_t)kCellMax)
+                    kept[cell][at] = (uint16_t)i;
+            }
+        }
+        float4_t strong[8];
+        float v_strong[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            strong[k] = cf[__shfl(j_own[k & 1], (lane & ~3) + (k >> 1), 64)];
+            v_strong[k] = value_at(strong[k], y1, y2, y3);
+        }
+        wave_lds_sync();
+        const int m = n_kept[cell] <= (uint32_t)kCellMax ? (int)n_kept[cell] : 0;
+        for (int i = sub; i < m; i += 4) {
+            const float4_t c = cf[kept[cell][i]];
+            const float v = value_at(c, y1, y2, y3);
+            bool out = false;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                out |= ahead_in_box(strong[k], v_strong[k], c, v, hc, eps);
+            keep |= out ? 0u : 1u << (i >> 2);
+        }
+    }
+    // ---- 4: space for the lists, entries -----------------------------------------------------------------------------------
+    const uint32_t mine = __popc(keep);
+    uint32_t before = 0, total = 0;  // entries of the quad's lanes in front of this one, and of all four
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t o = __shfl(mine, (lane & ~3) + d, 64);
+        before += d < sub ? o : 0u;
+        total += o;
+    }
+    const uint32_t groups = (total + 3) >> 2;
+    if (sub == 0)
+        first_group[cell] = groups;
+    __syncthreads();
+    if (tid < 64) {
+        const uint32_t v = first_group[tid];
+        uint32_t inc = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, 64);
+            if (lane >= d)
+                inc += o;
+        }
+        const uint32_t all = __shfl(inc, 63, 64);
+        if (tid == 0)
+            list_base = 1u + (all ? atomicAdd(ix.n_groups, all) : 0u);
+        first_group[tid] = inc - v;
+    }
+    __syncthreads();
+    const uint32_t first = list_base + first_group[cell];
+    const bool fits = groups > 0 && first + groups <= (uint32_t)g.cell_groups;
+    if (sub == 0)
+        ix.head[cell_id] = fits ? (uint16_t)first : (uint16_t)0;
+    if (fits) {
+        uint16_t *dst = reinterpret_cast<uint16_t *>(ix.list + first);
+        uint32_t at = before;
+        for (uint32_t left = keep; left; left &= left - 1u) {
+            const int j = kept[cell][sub + 4 * (__ffs((int)left) - 1)];
+            atomicOr(&cused[j >> 5], 1u << (j & 31));
+            dst[at] = (uint16_t)(ck[j] | (at == 4 * (groups - 1) ? 0x8000u : 0u));
+            ++at;
+        }
+        if (sub == 3)  // the last lane's entries end the list
+            for (at = total; at < 4 * groups; ++at)
+                dst[at] = (uint16_t)kCellPad;
+    }
+    __syncthreads();
+    for (int j = tid; j < nc; j += kCellThreads)
+        if ((cused[j >> 5] >> (j & 31)) & 1u)
+            atomicOr(&ix.used[ck[j] >> 5], 1u << (ck[j] & 31));
+}
+
+namespace {
+
+// LDS image of a head's index during the search, at the start of the workgroup's LDS.  List entries and box heads are
+// LDS addresses, so that neither takes arithmetic (the first two arrays end below 2^16, checked by the host).
+struct CellTables {
+    uint32_t base;    // address of the codeword functions (c_1, c_2, c_3, c_0) [cell_used + 1]; the last never wins
+    uint32_t list;    // [cell_groups] groups of four addresses of functions; bit 0 of the first: last group of its list
+    uint32_t head;    // [n^3] u16 address of the box's first group
+    uint32_t id;      // [cell_used] p' << 16 | s of the codeword
+    uint32_t mul;     // [24][32] u8: FoldTable
+    uint32_t sec;     // [S][4] the head's secondaries
+    uint32_t end;
+};
+__host__ __device__ inline CellTables cell_tables(const Geometry &g, uint32_t base)
+{
+    CellTables t;
+    t.base = base;
+    t.list = t.base + ((uint32_t)g.cell_used + 1u) * 16u;
+    t.head = t.list + (uint32_t)g.cell_groups * 8u;
+    t.id = t.head + (uint32_t)cell_head_bytes(g.cell_n);
+    t.mul = t.id + (uint32_t)g.cell_used * 4u;
+    t.sec = t.mul + 24u * 32u;
+    t.end = t.sec + (uint32_t)g.S * 16u;
+    return t;
+}
+template <typename T>
+__device__ __forceinline__ T lds_at(uint32_t address)
+{
+    return *(__attribute__((address_space(3))) const T *)(uintptr_t)address;
+}
+template <typename T>
+__device__ __forceinline__ T *lds_ptr(uint32_t address)
+{
+    return (T *)(__attribute__((address_space(3))) T *)(uintptr_t)address;
+}
+
+typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+
+// Code word of the lane's chunk, as search_codeword returns it (called by all 64 lanes); live: the chunk is neither
+// flagged nor zero nor past the end.
+__device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellTables &ct, int lane, const half4_t xv,
+                                                  double r2, float r_f, bool live, int rq)
+{
+    const float x0 = (float)xv[0], x1 = (float)xv[1], x2 = (float)xv[2], x3 = (float)xv[3];
+    // ---- fold: P_0 nearest to x.  An axis element when twice the largest |x_i| exceeds the sum (never for two at once) ----
+    const float a0 = fabsf(x0), a1 = fabsf(x1), a2 = fabsf(x2), a3 = fabsf(x3);
+    const float big = fmaxf(fmaxf(fmaxf(a0, a1), a2), a3);
+    const bool axis = 2.f * big > ((a0 + a1) + a2) + a3;
+    const float bound = axis ? big : 0.f, mag = axis ? 1.f : 0.5f;
+    const bool h0 = a0 >= bound, h1 = a1 >= bound, h2 = a2 >= bound, h3 = a3 >= bound;
+    const float p0 = h0 ? copysignf(mag, x0) : 0.f, p1 = h1 ? copysignf(mag, x1) : 0.f;
+    const float p2 = h2 ? copysignf(mag, x2) : 0.f, p3 = h3 ? copysignf(mag, x3) : 0.f;
+    const float w0 = fmaf(p3, x3, fmaf(p2, x2, fmaf(p1, x1, p0 * x0)));
+    const float w1 = fmaf(p3, x2, fmaf(-p2, x3, fmaf(-p1, x0, p0 * x1)));
+    const float w2 = fmaf(-p3, x1, fmaf(-p2, x0, fmaf(p1, x3, p0 * x2)));
+    const float w3 = fmaf(-p3, x0, fmaf(p2, x1, fmaf(-p1, x2, p0 * x3)));
+    const float inv = __builtin_amdgcn_rcpf(w0);
+    const float y1 = w1 * inv, y2 = w2 * inv, y3 = w3 * inv;
+    // ---- the box.  The scale keeps y = 1 below n; the last clamp is for inputs that break the contract (a zero chunk's
+    // 0 / 0 converts to 0, a corner box without a list) ---------------------------------------------------------------------
+    const float hn = 0.5f * (float)g.cell_n * kCellShrink;
+    const float n = (float)g.cell_n;
+    const float i0 = floorf(fmaf(y1, hn, hn)), i1 = floorf(fmaf(y2, hn, hn)), i2 = floorf(fmaf(y3, hn, hn));
+    const uint32_t box = min((uint32_t)fmaf(fmaf(i0, n, i1), n, i2), (uint32_t)(g.cell_n * g.cell_n * g.cell_n) - 1u);
+    uint32_t group = lds_at<uint16_t>(ct.head + 2u * box);
+    // ---- best and runner-up of the list ----------------------------------------------------------------------------------
+    float best = 0.f, second = 0.f;
+    uint32_t at = ct.base;
+    uint2v e = lds_at<uint2v>(group);
+    for (;;) {
+        const bool last = (e.x & 1u) != 0u;
+        const uint32_t o[4] = {e.x & 0xfff0u, e.x >> 16, e.y & 0xffffu, e.y >> 16};
+        group += 8u;
+        e = lds_at<uint2v>(group);  // one past the last list is still inside the tables
+        float4_t f[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            f[i] = lds_at<float4_t>(o[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = value_at(f[i], y1, y2, y3);
+            second = __builtin_amdgcn_fmed3f(v, best, second);  // second <= best
+            if (v > best)
+                at = o[i];
+            best = fmaxf(best, v);
+        }
+        if (last)
+            break;
+    }
+    const bool clear = best - second > kCellBand * best;  // false without a list
+    const uint32_t id = lds_at<uint32_t>(ct.id + ((at - ct.base) >> 2));
+    // packed signs of components 2, 0, 3, 1 in bits 0..3
+    const uint2 raw = __builtin_bit_cast(uint2, xv);
+    const uint32_t t = (raw.x & 0x80008000u) | ((raw.y >> 1) & 0x40004000u);
+    const uint32_t signs = ((t >> 14) & 3u) | (t >> 28);
+    const uint32_t slot = h3 ? 2u : h1 ? 3u : h0 ? 1u : 0u;
+    const uint32_t fold = axis ? 2u * slot + ((signs >> slot) & 1u) : 8u + signs;
+    uint32_t p = lds_at<uint8_t>(ct.mul + 32u * fold + (id >> 16));
+    uint32_t s = id & 0xffffu;
+    // ---- the others, one at a time, over all secondaries in fp32 (as in search_codeword) ---------------------------------
+    const bool unclear = live && !clear;
+    unsigned long long todo = __ballot(unclear);
+    if (todo) {
+        const float *secl = lds_ptr<float>(ct.sec);
+        const Direction u = unit_direction(xv, r2, r_f);
+        const float u0 = opaque(u.u0), u1 = opaque(u.u1), u2 = opaque(u.u2), u3 = opaque(u.u3);
+        while (todo) {  // wave-uniform
+            const int src = __ffsll((long long)todo) - 1;
+            todo &= todo - 1ull;
+            const float e0 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u0), src));
+            const float e1 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u1), src));
+            const float e2 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u2), src));
+            const float e3 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u3), src));
+            unsigned long long key = 0ull;
+            for (int j = lane; j < g.S; j += 64) {
+                float v0, v1, v2, v3;
+                const float sc = score_secondary(secl + 4 * j, e0, e1, e2, e3, v0, v1, v2, v3);
+                key = umax64(key, ((unsigned long long)__float_as_uint(sc) << 32) | (0xffffffffu - (uint32_t)j));
+            }
+            key = wave_umax64(key);
+            if (lane == src)
+                s = min(0xffffffffu - (uint32_t)key, (uint32_t)g.S - 1u);
+        }
+        float v0, v1, v2, v3, sc;
+        (void)score_secondary(secl + 4 * min(s, (uint32_t)g.S - 1u), u0, u1, u2, u3, v0, v1, v2, v3);
+        const uint32_t pu = (uint32_t)nearest_primary(v0, v1, v2, v3, sc);
+        p = unclear ? pu : p;
+    }
+    return live ? ((uint32_t)rq << g.w_idx) | (__umul24(p, (uint32_t)g.S) + s) : 0u;
+}
+
+// A head's index from the workspace into LDS: lists (entries k become addresses), boxes, and the functions of the
+// codewords that lists name.  `bits` [2 * cell_words + 1] u32 is scratch.  Ends with a barrier.
+template <int kThreadsS>
+__device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &ws, int h, const float *sec_h,
+                                           const CellTables &ct, uint32_t *bits)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const CellIndex ix = cell_index_of(g, ws, h);
+    const int nw = g.cell_words, used_cap = g.cell_used;
+    uint32_t *pre = bits + nw;  // [nw], then the number of codewords in use
+    float4_t *table = lds_ptr<float4_t>(ct.base), *secl = lds_ptr<float4_t>(ct.sec);
+    uint2 *list = lds_ptr<uint2>(ct.list);
+    uint32_t *head = lds_ptr<uint32_t>(ct.head), *id = lds_ptr<uint32_t>(ct.id);
+    for (int s = tid; s < g.S; s += kThreadsS)
+        secl[s] = reinterpret_cast<const float4_t *>(sec_h)[s];
+    for (int i = tid; i < 24 * 32 / 4; i += kThreadsS)
+        lds_ptr<uint32_t>(ct.mul)[i] = reinterpret_cast<const uint32_t *>(kFoldTable.at)[i];
+    if (tid < 64) {  // exclusive prefix of the used bits, nw <= 6 * 64 words
+        uint32_t w[6], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int i = 6 * lane + j;
+            w[j] = i < nw ? ix.used[i] : 0u;
+            sum += __popc(w[j]);
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, 64);
+            if (lane >= d)
+                inc += o;
+        }
+        uint32_t run = inc - sum;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int i = 6 * lane + j;
+            if (i < nw) {
+                bits[i] = w[j];
+                pre[i] = run;
+            }
+            run += __popc(w[j]);
+        }
+        if (lane == 63)
+            pre[nw] = inc;
+    }
+    __syncthreads();
+    const int n_used = (int)pre[nw];
+    const bool whole = n_used <= used_cap;  // else no box gets a list
+    {
+        const uint2 *src = reinterpret_cast<const uint2 *>(ix.head);
+        const int words = g.cell_n * g.cell_n * g.cell_n / 4;  // n is a multiple of 4
+        auto address = [&](uint32_t group) { return ct.list + 8u * (whole ? min(group, (uint32_t)g.cell_groups - 1u) : 0u); };
+        for (int i = tid; i < words; i += kThreadsS) {
+            const uint2 v = src[i];
+            head[2 * i] = address(v.x & 0xffffu) | (address(v.x >> 16) << 16);
+            head[2 * i + 1] = address(v.y & 0xffffu) | (address(v.y >> 16) << 16);
+        }
+    }
+    const uint32_t S = (uint32_t)g.S, n_code = 24u * S;
+    for (int i = tid; i < nw; i += kThreadsS) {
+        uint32_t left = bits[i], at = pre[i];
+        for (; left; left &= left - 1u, ++at) {
+            const uint32_t k = 32u * (uint32_t)i + (uint32_t)__ffs((int)left) - 1u;
+            const uint32_t p = (uint32_t)((float)k * g.inv_S);  // k / S
+            if (at < (uint32_t)used_cap && k < n_code)
+                id[at] = (p << 16) | (k - p * S);
+        }
+    }
+    const int n_groups = min((int)*ix.n_groups + 1, g.cell_groups);
+    const uint32_t pad = ct.base + 16u * (uint32_t)used_cap;
+    auto address_of = [&](uint32_t k) -> uint32_t {  // a pad, or a group that belongs to no list: the function that never wins
+        if (k >= n_code)
+            return pad;
+        return min(ct.base + 16u * (pre[k >> 5] + (uint32_t)__popc(bits[k >> 5] & ((1u << (k & 31u)) - 1u))), pad);
+    };
+    for (int i = tid; i < n_groups; i += kThreadsS) {
+        const uint2 raw = ix.list[i];
+        list[i] = make_uint2(address_of(raw.x & 0x7fffu) | ((raw.x >> 15) & 1u) | (address_of(raw.x >> 16) << 16),
+                             address_of(raw.y & 0xffffu) | (address_of(raw.y >> 16) << 16));
+    }
+    __syncthreads();
+    for (int i = tid; i <= used_cap; i += kThreadsS) {
+        float4_t f = {0.f, 0.f, 0.f, -1.0e30f};
+        if (i < n_used && i < used_cap) {
+            const uint32_t v = id[i];
+            f = codeword_function((int)(v >> 16), secl[v & 0xffffu]);
+        }
+        table[i] = f;
+    }
+    if (n_used == 0 && tid == 0)
+        id[0] = 0;  // what a chunk without a list reads before the fp32 search
+    __syncthreads();
+}
+
+}  // namespace
+
+// 16 waves and kRows rows per workgroup; a wave takes several whole rows at a time, one lane per chunk: kSlot = 32 or 16
+// lanes per row, the lanes past the row's chunks idle (row maxima are then DPP steps), or kSlot = 0 for rows that would
+// leave many idle: 64 / n_c rows next to one another.
+// kFull: rows of 128 elements.
+// Dynamic LDS: cell_lds_bytes().
+template <int kRows, int kSlot, bool kFull>
+__global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+{
+    constexpr int kWaves = 16;
+    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const Workspace ws = carve_workspace(tn.ws, wo);
+    const EncodedPtrs enc = tn.enc;
+    extern __shared__ float4_t cell_smem[];
+    const CellTables ct = cell_tables(g, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float4_t *)cell_smem);
+    uint32_t *pack = lds_ptr<uint32_t>(ct.end);
+    uint32_t *rcnt = pack + kWaves * 64;  // pack: also the scratch of load_cells
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
+    const int t0 = blockIdx.x * kRows;
+    load_cells<64 * kWaves>(g, ws, h, tn.sec + (size_t)h * g.S * 4, ct, pack);
+
+    const double thr = ws.thr[h];
+    const double Lq = (double)((1 << g.b_r) - 1);
+    const int n_c = kFull ? kChunksPerRow : g.n_c, row_words = kFull ? g.w : g.row_words;
+    const int slot = kSlot ? kSlot : n_c;
+    const int rows_pass = 64 / slot;
+    const int rl = lane / slot, c = lane - rl * slot;  // the lane's row of the pass and chunk of the row
+    const int n_rows = min(kRows, g.T - t0);         // >= 1 by the grid's size
+    uint32_t *my_pack = pack + wv * 64;              // rows_pass * row_words <= 64 words: w <= 22 as S <= kScreenMaxS
+    const _Float16 *row = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * rows_pass + rl) * g.st;
+    const int64_t row_step = (int64_t)(kWaves * rows_pass) * g.st;
+    const int64_t row0 = (int64_t)seg * g.T + t0;
+    const float Lf = (float)Lq;
+    for (int r0 = wv * rows_pass; r0 < n_rows; r0 += kWaves * rows_pass, row += row_step) {  // wave-uniform
+        const int r = r0 + rl;
+        const bool valid = (kFull || (rl < rows_pass && c < n_c)) && r < n_rows;
+        half4_t xv = {0, 0, 0, 0};
+        if (valid)
+            xv = load_row_chunk<kFull>(row, c, g);
+        const double r2 = chunk_norm2(xv);
+        const bool flagged = valid && (r2 > thr);
+        const unsigned long long ballot = __ballot(flagged);
+        const uint32_t word = (uint32_t)(ballot >> ((unsigned)(rl * slot) & 63u)) &
+                              (kFull ? 0xffffffffu : (uint32_t)((1ull << n_c) - 1ull));
+        if (g.check_finite) {  // uniform
+            const bool bad = valid && chunk_nonfinite(xv);
+            if (__ballot(bad) != 0ull && lane == 0)
+                atomicOr(enc.status, HQMQ_STATUS_NONFINITE);
+        }
+        // The row's scale, sigma_of_row_max of the largest r^2: rounding to fp32 is monotone, so the fp32 maximum decides
+        // unless its square root lies next to a rounding boundary; then the fp64 maximum is taken as well.
+        // r^2 is 0 or at least 2^-48: the fp32 value is zero for a zero chunk only.
+        const float r2f = (float)r2;
+        auto row_max = [&](auto v) {
+            if (kSlot) {  // after each step the running maxima are uniform over a block twice as large, so the mirrors pair the right blocks
+                v = fmax(v, dpp_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+                v = fmax(v, dpp_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+                v = fmax(v, dpp_move<0x141>(v));  // row_half_mirror
+                v = fmax(v, dpp_move<0x140>(v));  // row_mirror
+                return kSlot == 32 ? max_across_16(v) : v;
+            }
+            for (int d = 1; d < n_c; d <<= 1) {
+                const auto o = __shfl(v, lane + d, 64);
+                v = c + d < n_c ? fmax(v, o) : v;
+            }
+            return __shfl(v, lane - c, 64);
+        };
+        const float rmax = row_max(flagged ? 0.f : r2f);
+        const float sf = __builtin_amdgcn_sqrtf(rmax);  // 1 ulp
+        uint16_t sigma16 = sf >= 65504.f ? (uint16_t)0x7bff : __builtin_bit_cast(uint16_t, (_Float16)sf);
+        if (__any(scale_unsure(rmax, sf))) {
+            const double exact = row_max(flagged ? 0.0 : r2);
+            if (scale_unsure(rmax, sf))
+                sigma16 = double_to_half_rne_sat(sqrt(exact));
+        }
+        const float r_f = __builtin_amdgcn_sqrtf(r2f);
+        const bool live = r2f != 0.f && valid && !flagged;
+        // radius_code
+        int rq = 0;
+        {
+            const float q = fminf(r_f * Lf * __builtin_amdgcn_rcpf((float)__builtin_bit_cast(_Float16, sigma16)), Lf);
+            const float whole = rintf(q);
+            const bool round = live && sigma16 != 0;
+            const bool unsure = round && fabsf(q - whole) > 0.5f - (6e-7f * Lf + 1e-6f);
+            rq = round ? (int)whole : 0;
+            if (__any(unsure)) {
+                if (unsure)
+                    rq = radius_code_exact(r2, sigma16, Lq);
+            }
+        }
+        my_pack[lane] = 0;  // after the previous pass's reads of it: LDS serves a wave in order
+        const uint32_t code = cell_codeword(g, ct, lane, xv, r2, r_f, live, rq);
+        wave_lds_sync();
+        if (code) {
+            const uint32_t bitpos = (uint32_t)c * g.w;
+            const uint32_t sh = bitpos & 31;
+            uint32_t *d0 = my_pack + rl * row_words + (bitpos >> 5);
+            atomicOr(d0, code << sh);
+            if (sh + g.w > 32)
+                atomicOr(d0 + 1, code >> (32 - sh));
+        }
+        wave_lds_sync();
+        // the pass's rows are neighbours, and so are their code words
+        if (lane < min(rows_pass, n_rows - r0) * row_words)
+            enc.codes[(row0 + r0) * row_words + lane] = my_pack[lane];
+        if (valid && c == 0) {
+            enc.sigma[row0 + r] = sigma16;
+            enc.flags[row0 + r] = word;
+            rcnt[r] = __popc(word);
+        }
+    }
+    __syncthreads();
+    if (wv == 0)
+        write_row_offsets<kRows>(g, ws, enc, lane, seg, t0, rcnt);
+}
+
+// The search kernels' dynamic LDS may exceed the 64 KiB a kernel gets by default: raises the limit
 // of every variant on the current device.  Stateless; the caller (the library's per-device set-up) runs it
 // once per device, before any launch and outside any stream capture.
 hipError_t prepare_search_kernels()
 {
-    const void *variants[17] = {reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, true>),
-                                reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall, true>),
-                                reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, true>),
-                                reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall, true>),
-                                reinterpret_cast<const void *>(k_search_flat<16, kSearchRowsLarge>),
-                                reinterpret_cast<const void *>(k_search_flat<16, kSearchRowsHuge>),
-                                reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall>),
-                                reinterpret_cast<const void *>(k_search<4, kSearchRowsLarge>),
-                                reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall>),
-                                reinterpret_cast<const void *>(k_search<8, kSearchRowsLarge>),
-                                reinterpret_cast<const void *>(k_search<16, kSearchRowsLarge>),
-                                reinterpret_cast<const void *>(k_search<16, kSearchRowsHuge>),
-                                reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall>),
-                                reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsLarge>),
-                                reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall>),
-                                reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, false, false>),
-                                reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, false, false>)};
+    // the fused forms also hold static LDS (the workgroup-wide OR, the merge buffer of the cooperative pass: up to
+    // 6 KiB), which counts against the same 160 KiB
+    const void *fused[] = {reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, true>),
+                           reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall, true>),
+                           reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, true>),
+                           reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall, true>)};
+    const void *variants[] = {reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall>),
+                              reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall>),
+                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall>),
+                              reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall>),
+                              reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, false, false>),
+                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, false, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 0, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, true>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 16, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 0, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, true>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 16, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 0, false>)};
     hipError_t err = hipSuccess;
-    // the first four (the fused forms, only ever launched with 64 rows per workgroup) also hold static LDS (the
-    // workgroup-wide OR, the merge buffer of the cooperative pass: up to 6 KiB), which counts against the same 160 KiB
-    for (int i = 0; i < 17 && err == hipSuccess; ++i)
-        err = hipFuncSetAttribute(variants[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)kLdsPerCu - (i < 4 ? 8192 : 0));
+    for (const void *f : fused)
+        if (err == hipSuccess)
+            err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsPerCu - 8192);
+    for (const void *f : variants)
+        if (err == hipSuccess)
+            err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsPerCu);
     return err;
 }
 
@@ -940,13 +1743,37 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
 {
     dim3 grid((g.T + g.search_rows - 1) / g.search_rows, g.B * g.H, (unsigned)n_tensors);
     const bool full = g.D == 4 * kChunksPerRow;
+    if (g.cell_n > 0) {
+        const int nb = g.cell_n / 4;
+        hipLaunchKernelGGL(k_cells, dim3(nb * nb * nb, g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
+        const size_t lds_cells = cell_lds_bytes(g);
+#define HQMQ_LAUNCH_CELLS(R)                                                                                             \
+    do {                                                                                                             \
+        if (full)                                                                                                    \
+            hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch);    \
+        else if (g.n_c > 21)                                                                                         \
+            hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);   \
+        else if (g.n_c <= 16 && g.n_c > 12)                                                                          \
+            hipLaunchKernelGGL((k_search_cells<R, 16, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);   \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_search_cells<R, 0, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);    \
+    } while (0)
+        if (g.search_rows == kSearchRowsHuge)
+            HQMQ_LAUNCH_CELLS(kSearchRowsHuge);
+        else if (g.search_rows == kSearchRowsLarge)
+            HQMQ_LAUNCH_CELLS(kSearchRowsLarge);
+        else
+            HQMQ_LAUNCH_CELLS(kSearchRowsSmall);
+#undef HQMQ_LAUNCH_CELLS
+        return hipGetLastError();
+    }
     const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
     const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows);
     if (g.A16 > 0)
         hipLaunchKernelGGL(k_prepare_operands, dim3((g.A16 * kATiles * 64 + kThreads - 1) / kThreads, g.H, (unsigned)n_tensors),
                            dim3(kThreads), 0, stream, g, wo, batch);
-    const bool large = g.search_rows == kSearchRowsLarge;
-#define HQMQ_LAUNCH(KERNEL, W, R) hipLaunchKernelGGL((KERNEL<W, R>), grid, dim3(64 * W), lds, stream, g, wo, batch)
+    // 64 rows per workgroup (the caller sees to it)
+#define HQMQ_LAUNCH(KERNEL, W) hipLaunchKernelGGL((KERNEL<W, kSearchRowsSmall>), grid, dim3(64 * W), lds, stream, g, wo, batch)
     if (g.A16 == 0) {
         // more secondaries than the matrix-core screen holds: 64 rows on 4 waves, every chunk scored in fp32
         if (full)
@@ -954,30 +1781,15 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
         else
             hipLaunchKernelGGL((k_search_flat<4, kSearchRowsSmall, false, false>), grid, dim3(256), lds, stream, g, wo, batch);
     } else if (full) {
-        if (g.search_rows == kSearchRowsHuge)  // only chosen together with 16 waves
-            HQMQ_LAUNCH(k_search, 16, kSearchRowsHuge);
-        else if (large && waves == 16)
-            HQMQ_LAUNCH(k_search, 16, kSearchRowsLarge);
-        else if (large && waves == 8)
-            HQMQ_LAUNCH(k_search, 8, kSearchRowsLarge);
-        else if (large)
-            HQMQ_LAUNCH(k_search, 4, kSearchRowsLarge);
-        else if (waves == 8)
-            HQMQ_LAUNCH(k_search, 8, kSearchRowsSmall);
+        if (waves == 8)
+            HQMQ_LAUNCH(k_search, 8);
         else
-            HQMQ_LAUNCH(k_search, 4, kSearchRowsSmall);
+            HQMQ_LAUNCH(k_search, 4);
     } else {
-        // 256 rows per workgroup are only chosen when two 4-wave workgroups fit a CU
-        if (g.search_rows == kSearchRowsHuge)  // only chosen together with 16 waves
-            HQMQ_LAUNCH(k_search_flat, 16, kSearchRowsHuge);
-        else if (large && waves == 16)
-            HQMQ_LAUNCH(k_search_flat, 16, kSearchRowsLarge);
-        else if (large)
-            HQMQ_LAUNCH(k_search_flat, 4, kSearchRowsLarge);
-        else if (waves == 8)
-            HQMQ_LAUNCH(k_search_flat, 8, kSearchRowsSmall);
+        if (waves == 8)
+            HQMQ_LAUNCH(k_search_flat, 8);
         else
-            HQMQ_LAUNCH(k_search_flat, 4, kSearchRowsSmall);
+            HQMQ_LAUNCH(k_search_flat, 4);
     }
 #undef HQMQ_LAUNCH
     return hipGetLastError();

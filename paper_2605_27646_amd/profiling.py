@@ -82,15 +82,13 @@ kernel ({per_launch:g} tensors per launch unless noted)       calls     avg (us)
             nm += " (per layer)"
         out.append(f"{nm:48s} {r['Calls']:>6s} {float(r['AverageNs']) / 1e3:12.1f} {float(r['MinNs']) / 1e3:10.1f} "
                    f"{float(r['MaxNs']) / 1e3:10.1f} {float(r['Percentage']):8.2f} {per}")
-    ex, fe32 = rf["executed_mfma"], rf["fp32_equivalent"]
+    fe32 = rf["fp32_equivalent"]
     out.append(f"""
 (% time is of all GPU kernels in the process, including torch's generators for the synthetic inputs.)
 
 bench.py line of the same build (python bench.py --workload {wl}; {d['warmup']} warm-up + {d['steps']} timed steps; HIP-event times on the launch stream):
-  search kernel: avg launch {rf['avg_launch_ms'] * 1e3:.1f} us for {per_launch:g} tensors (median {rf['median_launch_ms'] * 1e3:.1f}, min {rf['min_launch_ms'] * 1e3:.1f}; {rf['avg_launch_ms'] * 1e3 / per_launch:.1f} us per tensor)  ->  bound by VALU issue:
-      closed-form scoring, {rf['flops_per_chunk']:g} VALU lane-operations per chunk ({chunks:,} chunks per tensor): {rf['achieved']:.1f} T op/s of the {rf['peak']:.1f} the chip issues = {rf['frac'] * 100:.1f} %;
-      fp32-equivalent ({fe32['flops_per_chunk']:g} flop per chunk): {fe32['achieved']:.1f} TFLOP/s = {fe32['ratio_to_fp32_peak']:.3f} x the 157.3 fp32 peak (the metric's yardstick, not a roofline fraction: the contraction runs as fp16 products);
-      executed on the matrix cores: {ex['instruction']}, {ex['achieved']:.0f} TFLOP/s of 2500 = {ex['frac'] * 100:.1f} %
+  search phase (box index and search): avg {rf['avg_launch_ms'] * 1e3:.1f} us for {per_launch:g} tensors (median {rf['median_launch_ms'] * 1e3:.1f}, min {rf['min_launch_ms'] * 1e3:.1f}; {rf['avg_launch_ms'] * 1e3 / per_launch:.1f} us per tensor)  ->  {rf['achieved']:.0f} GB/s of 8000 = {rf['frac'] * 100:.1f} % ({rf['bytes_per_chunk']:.2f} B per chunk, {chunks:,} chunks per tensor);
+      the exhaustive closed form ({fe32['flops_per_chunk']:g} flop per chunk) would run at {fe32['achieved']:.1f} TFLOP/s = {fe32['ratio_to_fp32_peak']:.3f} x the 157.3 fp32 peak (the metric's yardstick, not a roofline fraction)
   decode kernel: avg launch {rd['avg_launch_ms'] * 1e3:.1f} us for {rd['tensors_per_launch']:g} tensors (median {rd['median_launch_ms'] * 1e3:.1f}, min {rd['min_launch_ms'] * 1e3:.1f}; {rd['avg_launch_ms'] * 1e3 / rd['tensors_per_launch']:.1f} us per tensor)  ->  {rd['achieved']:.0f} GB/s of 8000 = {rd['frac'] * 100:.1f} % ({rd['bytes_per_chunk']:.2f} B per chunk)
   encode {d['encode_elems_per_s']:.3e} elems/s, decode {d['decode_elems_per_s']:.3e} elems/s, encode+decode {d['value']:.3e} elems/s ({d['ms_per_step']:.1f} ms per step)
   encode phases per tensor: median select {d['encode_phase_ms_per_tensor']['median_select'] * 1e3:.1f} us ({d['median_select_GBs']:.0f} GB/s over the {d['median_select_reads']:.4g} reads of the tensor it makes), search + quantise + pack {d['encode_phase_ms_per_tensor']['search_quantise_pack'] * 1e3:.1f} us, outlier scan + gather {d['encode_phase_ms_per_tensor']['outlier_scan_gather'] * 1e3:.1f} us
@@ -150,14 +148,13 @@ kernel                                      FETCH (KiB)    WRITE (KiB)   read MB
             per[base(k)] = (r_mb / nt_l, w_mb / nt_l)
             lines.append(f"{short(k):42s} {f:12.1f} {w:14.1f} {r_mb:16.2f} {w_mb:16.2f}   {r_mb / nt_l:8.2f} + {w_mb / nt_l:.2f}"
                          + (" (per layer)" if nt_l == 1 else ""))
-        skey = "k_search" if "k_search" in per else "k_search_flat"
+        skey = rf["kernel"]
         dkey = "k_decode" if "k_decode" in per else "k_decode_rows"
         s, dk = per[skey], per[dkey]
         info_w = rd["bytes_per_chunk"] - 8.0
         x_mb = chunks * 8 / 1e6
         lines.append(f"""
-algorithmic bytes for comparison, per tensor: the search kernel reads the tensor, {x_mb:.1f} MB (8 B per chunk; the flat kernel for
-head dimensions other than 128 reads it twice, the second time from L2) and writes codes, flags, scales and offsets,
+algorithmic bytes for comparison, per tensor: the search kernel reads the tensor, {x_mb:.1f} MB (8 B per chunk), and writes codes, flags, scales and offsets,
 {chunks * (info_w - 8 * d['outlier_fraction']) / 1e6:.1f} MB; the decode kernel reads {chunks * info_w / 1e6:.1f} MB (codes, flags, scales, offsets, payload) and writes {x_mb:.1f} MB.
 measured per tensor: search {s[0] + s[1]:.1f} MB ({s[0]:.1f} read + {s[1]:.1f} written); decode {dk[0] + dk[1]:.1f} MB ({dk[0]:.1f} read + {dk[1]:.1f} written).""")
         akey = "k_attend_joint" if "k_attend_joint" in per else "k_attend_partial"
@@ -195,23 +192,14 @@ kernel                              waves   VALU/wave   MFMA/wave   SALU/wave   
             lines.append(f"{short(k):32s} {wv:8.0f} {c['SQ_INSTS_VALU'] / wv:11.1f} {c['SQ_INSTS_MFMA'] / wv:11.2f} "
                          f"{c['SQ_INSTS_SALU'] / wv:11.1f} {c['SQ_INSTS_LDS'] / wv:11.1f} {busy_us:16.1f} "
                          + (f"{t:24.1f} {busy_us / t:15.2f}" if t else ""))
-            m = re.search(r"(k_search(?:_flat)?)<(\d+), (\d+)(?:, \w+)*>", k)
-            if m:
-                waves_wg, rows_wg = int(m.group(2)), int(m.group(3))
-                # passes of 64 chunks per wave: two rows of 32 chunks per pass in k_search; in k_search_flat the
-                # workgroup's rows as one flat list of chunks shared by its waves
-                passes = rows_wg / (2 * waves_wg) if m.group(1) == "k_search" else -(-rows_wg * n_c // (64 * waves_wg))
-                figs.append((m.group(1), c["SQ_INSTS_VALU"] / wv / passes, c["SQ_INSTS_MFMA"] / wv / passes, passes))
+            if base(k) == rf["kernel"]:
+                figs.append((base(k), 64 * c["SQ_INSTS_VALU"] / (2 * chunks)))
         lines.append("")
-        for name, v, mf, passes in figs:
-            s16 = (cfg["S"] + 15) // 16
-            lines.append(f"{name}: {passes:g} passes of 64 chunks per wave -> {v:.1f} VALU and {mf:.2f} MFMA instructions per pass; the closed form "
-                         f"alone is 5.5 x 16 x {s16} = {5.5 * 16 * s16:g} VALU instructions per pass ({5.5 * 16 * s16 / v * 100:.1f} % of the executed ones), "
-                         f"the analytic MFMA count 4 x {s16} + 1 = {4 * s16 + 1}.")
+        for name, v in figs:
+            lines.append(f"{name}: {v:.1f} VALU lane-operations per chunk over the whole kernel (64 per instruction and wave).")
         lines.append("\nfigures read back by bench.py:")
-        for name, v, mf, passes in figs:
-            lines.append(f"figure {name} valu_instructions_per_pass {v:.1f}")
-            lines.append(f"figure {name} mfma_instructions_per_pass {mf:.2f}")
+        for name, v in figs:
+            lines.append(f"figure {name} valu_lane_operations_per_chunk {v:.1f}")
         open(f"{ROOT}/profiles/instruction_counters_{wl}.txt", "w").write("\n".join(lines) + "\n")
     print("wrote profiles for", wl)
 

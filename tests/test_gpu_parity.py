@@ -591,6 +591,51 @@ def test_codebook_with_nearly_equal_secondaries():
     assert stats["near_ties"] > 100
 
 
+def _index_codebook(kind, S, H):
+    """Secondaries [H, S, 4] that stress the search's box index: random ones, every one twice, all of them within a small
+    cap, all equal, all multiplied by factors between 1/2 and 3/2, the axis directions over and over."""
+    sec = _sec(5, H, S)[1].copy()
+    rng = np.random.default_rng(S)
+    if kind == "twice":
+        sec[:, S // 2: 2 * (S // 2)] = sec[:, : S // 2]
+    elif kind == "cap":
+        sec = sec[:, :1] + np.float32(0.05) * sec
+        sec /= np.linalg.norm(sec, axis=2, keepdims=True)
+    elif kind == "equal":
+        sec[:] = sec[:, :1]
+    elif kind == "scaled":
+        sec *= rng.uniform(0.5, 1.5, (H, S, 1)).astype(np.float32)
+    elif kind == "axes":
+        sec[:] = np.eye(4, dtype=np.float32)[np.arange(S) % 4]
+    return np.ascontiguousarray(sec, np.float32)
+
+
+@pytest.mark.parametrize("S,D,T,kind", [
+    (1, 128, 2048, "random"), (8, 128, 2048, "random"), (9, 64, 4097, "random"), (32, 128, 2049, "random"),
+    (33, 96, 2731, "random"), (128, 128, 2048, "random"), (129, 100, 1311, "random"), (256, 128, 1024, "random"),
+    (257, 128, 1025, "random"), (512, 124, 2050, "random"), (48, 80, 3300, "random"), (16, 45, 5500, "random"),
+    (200, 3, 33000, "random"),                       # one chunk per row, a partial one
+    (256, 128, 1024, "twice"), (64, 128, 2048, "cap"), (256, 128, 1030, "cap"), (192, 128, 1024, "equal"),
+    (96, 64, 4100, "scaled"), (24, 128, 2048, "axes")])
+def test_box_index_search(S, D, T, kind):
+    """The search with the box index (from 65536 chunks per head on, 32768 with more than 128 secondaries) at the edges of
+    its shapes and row layouts, and on codebooks whose lists are long, full of ties, or do not fit.  The tensor mixes
+    Gaussian rows with chunks on the boundaries of the fold: zeros, equal magnitudes, axis directions, subnormals."""
+    H = 2
+    rng = np.random.default_rng(11)
+    x = rng.standard_normal((1, H, T, D)).astype(np.float32)
+    special = rng.integers(-1, 2, (1, H, T, D)).astype(np.float32) * rng.choice([0.5, 1.0, 6e-8, 3000.0], (1, H, T, 1))
+    x = np.where(rng.random((1, H, T, 1)) < 0.1, special, x).astype(np.float16)
+    sec = _index_codebook(kind, S, H)
+    rows = np.zeros(H * T, bool)
+    rows[rng.choice(H * T, 600, replace=False)] = True
+    rows[[0, T - 1, T, H * T - 1]] = True
+    bits = x.view(np.uint16)
+    e = oracle.encode(bits, sec, b_r=6, Cmul=3.0, rows=rows)
+    g = gpu_encode(torch.from_numpy(x).to(DEV), torch.from_numpy(sec).to(DEV), 6, 3.0)
+    print(compare_encode(g, e, bits, sec), flush=True)
+
+
 def test_direction_component_on_a_half_precision_midpoint():
     """Regression: the matrix pass splits every direction component into two fp16 parts; both must be
     taken from the same fp32 value.  Row 630 of this tensor holds a chunk whose fourth component, scaled, is
