@@ -192,7 +192,7 @@ def main() -> int:
     status = max(int(e.status.item()) for e in encs)
 
     import statistics
-    cells = wl.S <= 512 and chunks_per_tensor // wl.H >= (32768 if wl.S > 128 else 65536)  # the library's rule
+    cells = wl.S <= 512 and chunks_per_tensor // wl.H * (wl.S + 32) >= 3 << 21  # the library's rule
     search_kernel = "k_search_cells" if cells else "k_search" if wl.D == 128 else "k_search_flat"
     decode_kernel = "k_decode" if wl.D in (64, 96, 128) else "k_decode_rows"
     prof = profile_figures(wl.name)

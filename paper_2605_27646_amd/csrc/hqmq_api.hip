@@ -143,15 +143,15 @@ static Geometry make_geometry(const hqmq_params *p)
     return g;
 }
 
-// The search of the general path.  With the box index from 65536 chunks per head on (32768 with more than 128
-// secondaries): the index costs 20 to 35 us per call (1.2 us per head beyond some 30 heads), the search behind it a
-// sixth of the matrix screen's time at S = 256, two thirds at S = 16.  Measured, whole encode of one or two tensors
-// with 8 heads, without / with: 234 / 90 and 130 / 81 and 105 / 78 us at T = 2048, D = 128, S = 256, 64, 16; below the line
-// 71 / 74 us at T = 1024, S = 64, and 97 / 129 with 64 heads.
+// The search of the general path: the box index (a launch of 12 to 30 us, 1.1 us per head beyond some 25 heads, then a
+// search that hardly depends on S) from chunks per head x (S + 32) = 6.3 million on, the matrix screen below.  Whole
+// encodes of 4 tensors with 8 heads of 128 elements, screen / index in us: S = 256: 92 / 90 at T = 512, 118 / 102 at
+// 1024, 355 / 199 at 4096; S = 64: 87 / 94 at 1536, 116 / 110 at 3072, 209 / 183 at 4096; S = 16: 90 / 94 at 3072,
+// 176 / 168 at 4096, 272 / 203 at 16384.  With 64 heads the two meet at the same lengths within a fifth, with 8 earlier.
 static bool use_cells(const Geometry &g)
 {
     const uint64_t chunks = (uint64_t)g.B * g.T * g.n_c;
-    return g.A16 > 0 && chunks >= (g.S > 128 ? 32768u : 65536u);
+    return g.A16 > 0 && chunks * (uint64_t)(g.S + 32) >= (3ull << 21);
 }
 
 struct WorkspaceLayout {
@@ -386,16 +386,25 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             gs.cell_groups = c.groups;
             gs.cell_used = c.used;
             gs.cell_words = (24 * g.S + 31) / 32;
-            // never fewer rows than search_rows_for says, which sized the arrays of the workgroups' totals
-            gs.search_rows = g.T >= kSearchRowsSwitchHuge ? kSearchRowsHuge : g.T >= kSearchRowsSwitch ? kSearchRowsLarge : kSearchRowsSmall;
-        } else if (g.search_rows != kSearchRowsSmall) {
-            // 64 rows per workgroup, whose totals take the memory of the candidate lists (the select is done with them):
-            // 8 bytes per 64 of at most 65536 rows of a head
-            gs.search_rows = kSearchRowsSmall;
-            wos.block_sum = wo.cand;
-            wos.block_pre = wo.cand + (uint32_t)align_up((uint64_t)g.B * g.H * ((g.T + kSearchRowsSmall - 1) / kSearchRowsSmall) * 4, 256);
+            // the most rows per workgroup (its copy of the index is made once) that leave 512 workgroups
+            const auto blocks = [&](int rows) { return (int64_t)n * g.B * g.H * ((g.T + rows - 1) / rows); };
+            gs.search_rows = blocks(kSearchRowsHuge) >= 512 ? kSearchRowsHuge : blocks(kSearchRowsLarge) >= 512 ? kSearchRowsLarge : kSearchRowsSmall;
+        } else {
+            gs.search_rows = kSearchRowsSmall;  // 256 at S = 16, T = 4096, one tensor with 8 heads of 96 elements: 96 us, 64: 66
         }
         gs.n_search_blocks_per_seg = (uint32_t)((g.T + gs.search_rows - 1) / gs.search_rows);
+        if (gs.search_rows < g.search_rows) {
+            // more workgroups than the arrays of their totals were sized for: the totals take the histograms' memory, which
+            // the select is done with, where they fit it (8 bytes per workgroup and 32 KiB per head)
+            const uint64_t bytes = align_up((uint64_t)g.B * g.H * gs.n_search_blocks_per_seg * 4, 256);
+            if (2 * bytes <= (uint64_t)g.H * kBins0 * sizeof(uint32_t)) {
+                wos.block_sum = wo.hist0;
+                wos.block_pre = wo.hist0 + (uint32_t)bytes;
+            } else {
+                gs.search_rows = g.search_rows;
+                gs.n_search_blocks_per_seg = g.n_search_blocks_per_seg;
+            }
+        }
         err = launch_select_median(gs, wo, batch, n, params->C, no_outliers || thr_given != nullptr, st);
         if (err == hipSuccess)
             err = mark(1);

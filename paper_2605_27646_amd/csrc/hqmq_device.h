@@ -10,9 +10,9 @@
 namespace hqmq {
 
 constexpr int kChunksPerRow = 32;    // chunks of a row of D = 128 elements, and the most a row may have
-constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64 for short
-constexpr int kSearchRowsLarge = 256;  // segments (more workgroups); the search with the box index takes 256 rows from
-constexpr int kSearchRowsHuge = 512;   // kSearchRowsSwitch on and 512 from kSearchRowsSwitchHuge on (1024: no faster)
+constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64; the search with
+constexpr int kSearchRowsLarge = 256;  // the box index takes 256 or 512 where that leaves 512 workgroups (1024 rows: no
+constexpr int kSearchRowsHuge = 512;   // faster)
 constexpr int kSearchRowsSwitch = 2048;
 constexpr int kSearchRowsSwitchHuge = 4096;
 constexpr int kThreads = 256;        // default workgroup: 4 wave64

@@ -948,7 +948,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32, so the outcome is the one of the exhaustive fp32 search.
 // Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 73 us, index
-// included; two tensors in a call: 1017 -> 146 us + 32 us for the index.  Bound by VALU issue (300 instructions per
+// included; two tensors in a call: 1017 -> 144 us + 28 us for the index.  Bound by VALU issue (300 instructions per
 // 64 chunks, 115 of them in the list loop: the longest of 64 lists has 3.4 groups of four on average), LDS busy
 // half of the time; 16 % of the HBM peak.
 // ---------------------------------------------------------------------------------------------------------------
@@ -1087,7 +1087,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     __shared__ uint32_t cused[kCoarseCap / 32];
     __shared__ uint16_t mid[8][kMidCap];
     __shared__ uint16_t kept[64][kCellMax];
-    __shared__ uint32_t n_mid[8], n_kept[64], first_group[64];
+    __shared__ uint32_t first_group[64];
     __shared__ unsigned long long wave_key[kCellThreads / 64];
     __shared__ uint32_t n_coarse, list_base;
 
@@ -1111,10 +1111,6 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     }
     if (tid == 0)
         n_coarse = 0;
-    if (tid < 8)
-        n_mid[tid] = 0;
-    if (tid < 64)
-        n_kept[tid] = 0;
     if (tid < kCoarseCap / 32)
         cused[tid] = 0;
 
@@ -1144,23 +1140,16 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     }
     {
         const float hb = 4.f * hf + margin, eps = kCellEps * fabsf(v_best);
-        for (int s = tid; s < S; s += kCellThreads) {
-            const float4_t q = *reinterpret_cast<const float4_t *>(sec_h + 4 * s);
+        for (int s0 = 0; s0 < S; s0 += kCellThreads) {  // uniform
+            const int s = s0 + tid;
+            float4_t q = {0.f, 0.f, 0.f, 0.f};
+            if (s < S)
+                q = *reinterpret_cast<const float4_t *>(sec_h + 4 * s);
             // c: P_p q as (c_1, c_2, c_3, c_0), v its value at the centre; its negative is tested along with it
+            uint32_t left = 0;
             auto test = [&](const float4_t c, float v, int p, int p_neg) {
-                if (!ahead_in_box(best, v_best, c, v, hb, eps) || !ahead_in_box(best, v_best, -c, -v, hb, eps)) {
-#pragma unroll
-                    for (int sign = 0; sign < 2; ++sign) {
-                        const float4_t f = sign ? -c : c;
-                        if (!ahead_in_box(best, v_best, f, sign ? -v : v, hb, eps)) {
-                            const uint32_t at = atomicAdd(&n_coarse, 1u);
-                            if (at < (uint32_t)kCoarseCap) {
-                                cf[at] = f;
-                                ck[at] = (uint16_t)((sign ? p_neg : p) * S + s);
-                            }
-                        }
-                    }
-                }
+                left |= ahead_in_box(best, v_best, c, v, hb, eps) ? 0u : 1u << p;
+                left |= ahead_in_box(best, v_best, -c, -v, hb, eps) ? 0u : 1u << p_neg;
             };
             const float4_t e0 = {q[1], q[2], q[3], q[0]}, e1 = {q[0], -q[3], q[2], -q[1]};  // q, i q
             const float4_t e2 = {q[3], q[0], -q[1], -q[2]}, e3 = {-q[2], q[1], q[0], -q[3]};  // j q, k q
@@ -1180,6 +1169,28 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
                     const float vb = (b & 2 ? -v2 : v2) + (b & 1 ? -v3 : v3);
                     const int p = 8 + 4 * a + b;
                     test(0.5f * (ea + eb), 0.5f * (va + vb), p, 31 - p);
+                }
+            }
+            if (s >= S)
+                left = 0;
+            // the wave's survivors take consecutive places
+            const uint32_t count = __popc(left);
+            uint32_t inc = count;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = __shfl_up(inc, d, 64);
+                if (lane >= d)
+                    inc += o;
+            }
+            uint32_t base = 0;
+            if (lane == 63)
+                base = atomicAdd(&n_coarse, inc);
+            uint32_t at = __shfl(base, 63, 64) + inc - count;
+            for (; left; left &= left - 1u, ++at) {
+                const int p = __ffs((int)left) - 1;
+                if (at < (uint32_t)kCoarseCap) {
+                    cf[at] = codeword_function(p, q);
+                    ck[at] = (uint16_t)(p * S + s);
                 }
             }
         }
@@ -1209,6 +1220,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     };
 
     // ---- 2: the sub-block ----------------------------------------------------------------------------------------------
+    int nm = 0;
     if (nc > 0) {
         const float z1 = (float)(8 * b0 + 4 * s0 + 2) * hf - 1.f, z2 = (float)(8 * b1 + 4 * s1 + 2) * hf - 1.f,
                     z3 = (float)(8 * b2 + 4 * s2 + 2) * hf - 1.f;
@@ -1217,18 +1229,24 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
             const int jb = strongest([](int j) { return j; }, nc, tid & 31, 32, z1, z2, z3, vb);
             const float4_t bf = cf[jb];
             const float eps = kCellEps * fabsf(vb), hm = 2.f * hf + margin;
-            for (int j = tid & 31; j < nc; j += 32) {
-                const float4_t c = cf[j];
-                if (!ahead_in_box(bf, vb, c, value_at(c, z1, z2, z3), hm, eps)) {
-                    const uint32_t at = atomicAdd(&n_mid[sb], 1u);
-                    if (at < (uint32_t)kMidCap)
-                        mid[sb][at] = (uint16_t)j;
+            for (int j0 = 0; j0 < nc; j0 += 32) {  // uniform over the half-wave
+                const int j = j0 + (tid & 31);
+                bool stays = false;
+                if (j < nc) {
+                    const float4_t c = cf[j];
+                    stays = !ahead_in_box(bf, vb, c, value_at(c, z1, z2, z3), hm, eps);
                 }
+                const uint32_t votes = (uint32_t)(__ballot(stays) >> (lane & 32));
+                const int at = nm + __popc(votes & ((1u << (lane & 31)) - 1u));
+                if (stays && at < kMidCap)
+                    mid[sb][at] = (uint16_t)j;
+                nm += __popc(votes);
             }
         }
     }
     wave_lds_sync();  // the lanes of a sub-block, and of a box, belong to one wave
-    const int nm = n_mid[sb] <= (uint32_t)kMidCap ? (int)n_mid[sb] : 0;
+    if (nm > kMidCap)
+        nm = 0;
 
     // ---- 3: the box ------------------------------------------------------------------------------------------------------
     uint32_t keep = 0;  // bit i: entry sub + 4 i of kept[cell] is in the list
@@ -1240,21 +1258,31 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
         const float4_t bf = cf[jb];
         const float eps = kCellEps * fabsf(vb);
         float v_own[2] = {-3.4e38f, -3.4e38f};  // the two strongest survivors of this lane's share
-        int j_own[2] = {jb, jb};
-        for (int j = sub; j < nm; j += 4) {
-            const int i = list[j];
-            const float4_t c = cf[i];
-            const float v = value_at(c, y1, y2, y3);
-            if (!ahead_in_box(bf, vb, c, v, hc, eps)) {
-                j_own[1] = v > v_own[0] ? j_own[0] : v > v_own[1] ? i : j_own[1];
-                v_own[1] = __builtin_amdgcn_fmed3f(v, v_own[0], v_own[1]);
-                j_own[0] = v > v_own[0] ? i : j_own[0];
-                v_own[0] = fmaxf(v_own[0], v);
-                const uint32_t at = atomicAdd(&n_kept[cell], 1u);
-                if (at < (uint32_t)kCellMax)
-                    kept[cell][at] = (uint16_t)i;
+        int j_own[2] = {jb, jb}, m = 0;
+        for (int j0 = 0; j0 < nm; j0 += 4) {  // uniform over the quad
+            const int j = j0 + sub;
+            bool stays = false;
+            int i = 0;
+            if (j < nm) {
+                i = list[j];
+                const float4_t c = cf[i];
+                const float v = value_at(c, y1, y2, y3);
+                stays = !ahead_in_box(bf, vb, c, v, hc, eps);
+                if (stays) {
+                    j_own[1] = v > v_own[0] ? j_own[0] : v > v_own[1] ? i : j_own[1];
+                    v_own[1] = __builtin_amdgcn_fmed3f(v, v_own[0], v_own[1]);
+                    j_own[0] = v > v_own[0] ? i : j_own[0];
+                    v_own[0] = fmaxf(v_own[0], v);
+                }
             }
+            const uint32_t votes = (uint32_t)(__ballot(stays) >> (lane & ~3)) & 15u;
+            const int at = m + __popc(votes & ((1u << sub) - 1u));
+            if (stays && at < kCellMax)
+                kept[cell][at] = (uint16_t)i;
+            m += __popc(votes);
         }
+        if (m > kCellMax)
+            m = 0;
         float4_t strong[8];
         float v_strong[8];
 #pragma unroll
@@ -1263,7 +1291,6 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
             v_strong[k] = value_at(strong[k], y1, y2, y3);
         }
         wave_lds_sync();
-        const int m = n_kept[cell] <= (uint32_t)kCellMax ? (int)n_kept[cell] : 0;
         for (int i = sub; i < m; i += 4) {
             const float4_t c = cf[kept[cell][i]];
             const float v = value_at(c, y1, y2, y3);
