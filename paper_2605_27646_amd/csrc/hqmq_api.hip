@@ -130,9 +130,8 @@ static Geometry make_geometry(const hqmq_params *p)
             g.log2_S = j;
     g.check_finite = (p->flags & HQMQ_FLAG_CHECK_FINITE) ? 1 : 0;
     g.fused_by_head = 0;
-    g.select_sampled = 0;
     {
-        // the sampled select keeps the keys of a few bins around the median: about 2 % of a head's chunks
+        // the select of a long head keeps the keys of a narrow range around the median: about 2 % of a head's chunks
         const uint64_t n_h = (uint64_t)p->B * p->T * g.n_c;
         const uint64_t want = (n_h / 32 + 1023) / 1024 * 1024;
         g.cand_cap = (int32_t)(want > (uint64_t)kCandCap ? want : (uint64_t)kCandCap);

@@ -18,23 +18,17 @@ constexpr int kSearchRowsSwitchHuge = 4096;
 constexpr int kThreads = 256;        // default workgroup: 4 wave64
 constexpr int kATiles = 2;           // 64-lane x 16-byte MFMA A operand tiles per 16 secondaries (8 secondaries each)
 
-// Radix select over the 63 value bits of a non-negative IEEE double.  The sequence-sharded select takes
-// bits 62..50, then 10 bits per pass.  The single-tensor select takes exponent and 6 mantissa bits first
-// (17-bit prefix minus kFineBase, clamped to the kBins0 bins: what squares of fp16 data need), collects the
-// keys of that bin as candidates and, should they overflow their list, narrows by bits 45..36.
+// Digits of the keys (the 63 value bits of a non-negative IEEE double).  The sequence-sharded select takes bits 62..50,
+// then 10 bits per pass.  The single-tensor select's first digit is exponent and 6 mantissa bits (17-bit prefix minus
+// kFineBase, clamped to the kBins0 bins: what squares of fp16 data need).
 constexpr int kBits0 = 13, kShift0 = 50, kBins0 = 1 << kBits0;  // bits 62..50
 constexpr int kBits1 = 10, kShift1 = 40, kBins1 = 1 << kBits1;  // bits 49..40
 constexpr int kFineShift = 46;                      // first digit of the single-tensor select: key >> 46 ...
 constexpr uint32_t kFineBase = (975u << 6) - 1u;    // ... minus this: 2^-48, the smallest square of an fp16 value, lands in bin 1
-constexpr int kSecShift = kFineShift - kBits1;      // its second digit: bits 45..36
 constexpr int kCandCap = 32768;      // candidate keys kept per head, at least (Geometry::cand_cap: more for very long heads)
-static_assert(kBins0 * sizeof(uint32_t) <= kCandCap * sizeof(unsigned long long),
-              "the sample histogram borrows the candidate list's memory");
 constexpr int kSelectThreads = 1024; // workgroup of the select sweeps
 constexpr int kSelectRows = 1024;    // rows of one (b, h) segment per select workgroup
 constexpr int kScreenMaxS = 512;      // largest S whose search is screened on the matrix cores (operand tables in LDS)
-constexpr int kSampleStride = 16;     // the sampled select reads every 16th row of a head first ...
-constexpr int kSampleMinChunks = 1 << 17;  // ... when the head has at least this many chunks
 constexpr int kSmallListRows = 4096;   // a tensor of at most this many rows and kSmallListBlocks search workgroups,
 constexpr int kSmallListBlocks = 1024; // with thresholds known beforehand, is encoded by two launches
 
@@ -45,14 +39,10 @@ struct SelectState {
     uint32_t pad;
 };
 
-// Per-head plan of the sampled select: the bins of the first digit whose keys the full sweep keeps as
-// candidates (predicted from a sample of the rows), and what the full histogram then says.
+// Per-head state of the select's sweep.
 struct SelectPlan {
-    uint32_t lo, span;   // candidate bins lo .. lo + span (lo = kBins0: none)
-    uint32_t bin0;       // the bin that holds the median, from the full histogram
-    uint32_t before0;    // keys in the bins below it
-    uint32_t need;       // 1: the prediction missed the bin or the list overflowed; a sweep of its own collects the bin
-    uint32_t pad[3];
+    uint32_t below;  // keys below the predicted range
+    uint32_t pad[7];
 };
 
 // Shape and addressing of one tensor, passed by value to every kernel.
@@ -74,7 +64,6 @@ struct Geometry {
     float inv_S;          // (1/S)(1 + 2^-18): uint(float(k) * inv_S) == k / S for every k < 2^16, S <= 2730
     int32_t check_finite;  // HQMQ_FLAG_CHECK_FINITE: the search reports chunks holding an infinity or a NaN in the status word
     int32_t cand_cap;     // candidate keys kept per head: kCandCap, or 1/32 of the head's chunks if that is more
-    int32_t select_sampled;  // the median select predicts the median's bin from a sample of the rows (large heads only)
     int32_t fused_by_head;  // fused search only: one workgroup per head takes the rows of all batch entries (B T <= 64)
     int32_t cell_n;       // boxes per axis of the search's index (0: no index, see hqmq_search.hip)
     int32_t cell_groups;  // list groups it may have, group 0 included
@@ -165,12 +154,9 @@ struct Workspace {
     double *thr;                   // [H] outlier threshold on squared norms
     uint32_t *hist0;               // [H][kBins0]
     uint32_t *hist1;               // [H][kBins1]
-    uint32_t *hist_s;              // [H][kBins0] first digit of the sampled rows; shares the candidate list's memory (read
-                                   // before the first candidate is written)
-    SelectPlan *plan;              // [H]
-    uint32_t *cand_count;          // [3][H] keys sent to the candidate list (any may exceed cand_cap): by the sweep that
-                                   // collects one bin (or, in the sampled select, the predicted bins), by the sweep after
-                                   // an overflow, by the sampled select's fallback sweep of one bin
+    SelectPlan *plan;              // [H] (the predicted range and the lists' counters are in hist1's memory)
+    uint32_t *cand_count;          // [3][H] where the prediction missed: keys sent to the candidate list (they may exceed
+                                   // cand_cap) and workgroups done with it; the third row is not used
     unsigned long long *cand;      // [H][cand_cap]
     uint32_t *block_sum;           // [B*H*n_search_blocks_per_seg] outliers per search workgroup
     uint32_t *block_pre;           // same shape, exclusive prefix
@@ -216,7 +202,6 @@ __device__ __forceinline__ Workspace carve_workspace(char *base, const Workspace
     ws.thr = reinterpret_cast<double *>(base + o.thr);
     ws.hist0 = reinterpret_cast<uint32_t *>(base + o.hist0);
     ws.hist1 = reinterpret_cast<uint32_t *>(base + o.hist1);
-    ws.hist_s = reinterpret_cast<uint32_t *>(base + o.cand);
     ws.plan = reinterpret_cast<SelectPlan *>(base + o.plan);
     ws.cand_count = reinterpret_cast<uint32_t *>(base + o.cand_count);
     ws.cand = reinterpret_cast<unsigned long long *>(base + o.cand);

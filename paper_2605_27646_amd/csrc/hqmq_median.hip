@@ -3,27 +3,21 @@
 //
 // The median is the lower median (element (n-1)/2 of the sorted norms) of all B*T*ceil(D/4) chunks
 // of a head.  Non-negative IEEE doubles order like their bit patterns read as unsigned integers,
-// so the median is found by a most-significant-digit radix select on the 63 value bits of r^2:
-//   sweep 0  histogram of a first digit made of the exponent and 6 mantissa bits (the squares of fp16
-//            data span 83 binades, which at 64 bins each fit the 8192 bins of a workgroup's LDS)
-//   sweep 1  the keys in the bin that holds the wanted rank (about one in 200 for smooth data) go to a
-//            candidate list, and are counted by their next 10 bits
-//   sweep 2  only for a head whose list overflowed: collects the keys that share both digits; returns
-//            at once otherwise
-//   finish   one workgroup per head selects the wanted rank among the candidates (radix select on
-//            their low 46 or 36 bits) and writes the outlier threshold C^2 * median.
-// Nothing is sorted and no float arithmetic is involved after r^2 itself, so the result is the
-// exact order statistic.  Each sweep recomputes r^2 in registers from the fp16 tensor (8 B per
-// chunk, HBM-bound); the bin choice of the previous sweep is re-derived by every workgroup
-// from the (L2-resident) histogram instead of costing a kernel launch of its own.
-// A head of at least kSampleMinChunks chunks skips sweep 1 (the sampled select): a histogram of every
-// kSampleStride-th row predicts a few bins around the median's, sweep 0 keeps the keys of those bins as
-// candidates while it counts all keys, and only a head whose prediction missed the bin that the full
-// histogram names (or whose list overflowed) goes through sweep 1 after all.  The prediction decides which
-// keys are kept, never the result.
-// If a head has more keys sharing both digits than the list holds (many equal norms: a
-// constant or coarsely quantised tensor), the finishing workgroup falls back to radix-selecting
-// the low bits over the head's raw rows itself: slow, exact, and only for such inputs.
+// and nothing is sorted and no float arithmetic is involved after r^2 itself, so the result is the exact order
+// statistic.  Each sweep recomputes r^2 in registers from the fp16 tensor (8 B per chunk).
+//
+// A sample predicts a narrow range of keys around the median (its ranks within four standard deviations of the middle
+// one).  One sweep then counts the keys below the range and keeps those in it, in 16 lists by where in the range
+// they lie, and the wanted rank is located in the one list that holds it by histograms over ever narrower ranges
+// (select_rank).  The prediction decides which keys are kept, never the result.
+//   heads of at most 1024 rows   one workgroup selects from its registers (k_select_head)
+//   longer heads                 k_select_predict (a workgroup per head), k_select_count (the sweep, HBM-bound),
+//                                k_select_digit (only where the prediction missed), k_select_finish
+// For a head whose prediction missed, or whose list overflowed, k_select_digit makes a histogram of a first digit and
+// k_select_finish collects the keys of the bin that holds the median; every other head's workgroups leave at once.  The
+// first digit is made of the exponent and 6 mantissa bits (the squares of fp16 data span 83 binades, which at 64 bins each
+// fit the 8192 bins of a workgroup's LDS).
+// The sequence-sharded median further down is a plain most-significant-digit radix select on the 63 value bits.
 #include "hqmq_device.h"
 
 namespace hqmq {
@@ -31,12 +25,13 @@ namespace hqmq {
 namespace {
 
 constexpr unsigned long long kKeyMask = 0x7fffffffffffffffull;
+constexpr int kPickScratch = kSelectThreads / 64 + 4;
 
 // Exclusive scan position of `rank` in a histogram: returns the bin holding the rank-th key
 // (0-based) and how many keys lie in earlier bins.  Called by every thread of the block with the
 // same arguments; `hist` may be global memory.  kBins is a multiple of the block size.
 template <int kBins, int kBlock>
-__device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t rank, uint32_t *scratch /* LDS, kBlock + 2 */,
+__device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t rank, uint32_t *scratch /* LDS, kBlock / 64 + 2 */,
                                          uint32_t &bin_out, uint32_t &before_out)
 {
     constexpr int kPer = kBins / kBlock;
@@ -70,8 +65,8 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t rank, ui
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             if (!found && rank < before + local[i]) {
-                scratch[kBlock] = tid * kPer + i;
-                scratch[kBlock + 1] = before;
+                scratch[kBlock / 64] = tid * kPer + i;
+                scratch[kBlock / 64 + 1] = before;
                 found = true;
             }
             if (!found)
@@ -79,14 +74,129 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t rank, ui
         }
     }
     __syncthreads();
-    bin_out = scratch[kBlock];
-    before_out = scratch[kBlock + 1];
+    bin_out = scratch[kBlock / 64];
+    before_out = scratch[kBlock / 64 + 1];
     __syncthreads();
+}
+
+// pick_bin for two ranks of one histogram, which ranks(n, a, b) sets from the number of keys in it.
+template <int kBins, int kBlock, typename Ranks>
+__device__ __forceinline__ void pick_two(const uint32_t *hist, Ranks ranks, uint32_t *scratch /* LDS, kBlock / 64 + 4 */, uint32_t &bin_a,
+                                         uint32_t &before_a, uint32_t &bin_b, uint32_t &before_b)
+{
+    constexpr int kPer = kBins / kBlock, kW = kBlock / 64;
+    static_assert(kBins % kBlock == 0, "bins must tile the block");
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t local[kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        local[i] = hist[tid * kPer + i];
+        sum += local[i];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(inc, d, 64);
+        if (lane >= d)
+            inc += o;
+    }
+    if (lane == 63)
+        scratch[wv] = inc;
+    __syncthreads();
+    uint32_t before = inc - sum, n = 0, rank_a, rank_b;
+#pragma unroll
+    for (int k = 0; k < kW; ++k) {
+        const uint32_t total = scratch[k];
+        before += k < wv ? total : 0u;
+        n += total;
+    }
+    ranks(n, rank_a, rank_b);
+    if (rank_a - before < sum || rank_b - before < sum) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (rank_a - before < local[i]) {
+                scratch[kW] = tid * kPer + i;
+                scratch[kW + 1] = before;
+            }
+            if (rank_b - before < local[i]) {
+                scratch[kW + 2] = tid * kPer + i;
+                scratch[kW + 3] = before;
+            }
+            before += local[i];
+        }
+    }
+    __syncthreads();
+    bin_a = scratch[kW];
+    before_a = scratch[kW + 1];
+    bin_b = scratch[kW + 2];
+    before_b = scratch[kW + 3];
+    __syncthreads();
+}
+
+constexpr int kRankBits = 12, kRankBins = 1 << kRankBits;
+constexpr int kFew = 64;  // keys that one wave ranks by counting
+struct RankScratch {      // LDS
+    unsigned long long few[kFew], result;
+    uint32_t n_few, pick[kPickScratch];
+};
+
+// The key of the given rank (0-based) among those in [lo, hi] that each(f) passes to f, every thread its share; there are
+// more than `rank` of them.  A histogram of 4096 equal parts of the range, then of the part that holds the rank, until few
+// enough keys are left in it (keys spread evenly over the range: at once) or it is a single value.  Called by the whole
+// workgroup; bins: LDS, kRankBins.
+template <typename Each>
+__device__ __forceinline__ unsigned long long select_rank(Each each, unsigned long long lo, unsigned long long hi, uint32_t rank,
+                                                          uint32_t *bins, RankScratch &sc)
+{
+    const int tid = threadIdx.x;
+    for (;;) {  // at most 6 rounds: each fixes 12 bits of the 63
+        if (lo >= hi)
+            return lo;
+        const int width = 64 - __clzll((long long)(hi - lo));
+        const int shift = width > kRankBits ? width - kRankBits : 0;
+        for (int i = tid; i < kRankBins; i += kSelectThreads)
+            bins[i] = 0;
+        if (tid == 0)
+            sc.n_few = 0;
+        __syncthreads();
+        each([&](unsigned long long key) {
+            if (key - lo <= hi - lo)
+                atomicAdd(&bins[(uint32_t)((key - lo) >> shift)], 1u);
+        });
+        __syncthreads();
+        uint32_t bin, before;
+        pick_bin<kRankBins, kSelectThreads>(bins, rank, sc.pick, bin, before);
+        const uint32_t count = bins[bin];
+        rank -= before;
+        lo += (unsigned long long)bin << shift;
+        const unsigned long long top = lo + ((1ull << shift) - 1ull);
+        hi = top < hi ? top : hi;
+        if (count <= (uint32_t)kFew && lo < hi) {
+            each([&](unsigned long long key) {
+                if (key - lo <= hi - lo)
+                    sc.few[atomicAdd(&sc.n_few, 1u)] = key;
+            });
+            __syncthreads();
+            if ((uint32_t)tid < count) {  // one wave
+                const unsigned long long mine = sc.few[tid];
+                uint32_t less = 0;
+                for (uint32_t j = 0; j < count; ++j) {
+                    const unsigned long long other = sc.few[j];
+                    less += other < mine || (other == mine && j < (uint32_t)tid) ? 1u : 0u;
+                }
+                if (less == rank)
+                    sc.result = mine;
+            }
+            __syncthreads();
+            return sc.result;
+        }
+        __syncthreads();  // every thread has read its count
+    }
 }
 
 }  // namespace
 
-// First digit of the two-sweep select: exponent and 6 mantissa bits of r^2, offset so that the squares
+// First digit: exponent and 6 mantissa bits of r^2, offset so that the squares
 // that fp16 data can produce (0, and 2^-48 up to below 2^35) fill bins 0 and 1..5312.  Monotone; bins
 // 1..kBins0-2 each hold exactly the keys of one 17-bit prefix bin + kFineBase; bin 0 holds the keys
 // below 2^-48 (for fp16 data: zero only), the last bin everything from 2^(kBins0-2)/64 binades up
@@ -100,244 +210,463 @@ __device__ __forceinline__ uint32_t fine_bin(unsigned long long key)
 __device__ __forceinline__ bool fine_bin_is_prefix(uint32_t bin) { return bin >= 1u && bin <= (uint32_t)kBins0 - 2u; }
 
 // ---------------------------------------------------------------------------------------
-// reset of the per-call scratch state
+// reset of the per-call state of head h: what the search's index counts in, and the caller's counters
 // ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void reset_head(const Geometry &g, const Workspace &ws, const EncodedPtrs &enc, int h, int tid, int threads)
+{
+    if (g.cell_n > 0)
+        for (int i = tid; i < 1 + g.cell_words; i += threads)
+            ws.cell_state[(size_t)h * (1 + g.cell_words) + i] = 0;
+    if (tid == 0) {
+        enc.n_outliers[h] = 0;
+        if (h == 0) {
+            enc.n_outliers[g.H] = 0;
+            enc.status[0] = 0;
+        }
+    }
+}
+
+// Without a select: thresholds from the caller, or +infinity (nothing is flagged).  grid = (H, 1, tensors).
 __global__ __launch_bounds__(kThreads) void k_init(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    const EncodedPtrs enc = tn.enc;
-    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-    if (i < (uint32_t)g.H * kBins0) {
-        ws.hist0[i] = 0;
-        ws.hist_s[i] = 0;
-    }
-    if (i < (uint32_t)g.H * kBins1)
-        ws.hist1[i] = 0;
-    if (i < 3u * (uint32_t)g.H)
-        ws.cand_count[i] = 0;
-    if (g.cell_n > 0 && i < (uint32_t)g.H * (1u + (uint32_t)g.cell_words))
-        ws.cell_state[i] = 0;
-    if (i < (uint32_t)g.H) {
-        // +inf: nothing is flagged (replaced by the select, unless the caller supplies the thresholds)
-        ws.thr[i] = tn.thr_given ? tn.thr_given[i] : __longlong_as_double(0x7ff0000000000000LL);
-    }
-    if (i <= (uint32_t)g.H)
-        enc.n_outliers[i] = 0;
-    if (i == 0)
-        enc.status[0] = 0;
+    const int h = blockIdx.x;
+    reset_head(g, ws, tn.enc, h, threadIdx.x, kThreads);
+    if (threadIdx.x == 0)
+        ws.thr[h] = tn.thr_given ? tn.thr_given[h] : __longlong_as_double(0x7ff0000000000000LL);
+}
+
+// threshold on squares: fl(fl(C*C) * median), C widened from fp32
+__device__ __forceinline__ double threshold_of(unsigned long long median_bits, float C)
+{
+    const double c = (double)C;
+    const double c2 = c * c;
+    return c2 * __longlong_as_double((long long)median_bits);
 }
 
 // ---------------------------------------------------------------------------------------
-// sweeps.  grid = (ceil(T / kSelectRows), B*H), 1024 threads: one lane per chunk, 32 rows per
-// block iteration, four independent 8-byte loads in flight per lane.
-//   MODE 0: histogram of the first digit (fine_bin), all keys; in the sampled select it also keeps the keys of
-//           the predicted bins as candidates (staged like MODE 1's)
-//   MODE 3: histogram of the first digit over every kSampleStride-th row (sampled select only)
-//   MODE 1: picks the first digit (sampled select: returns at once unless the head needs it); the keys of that bin (about one in 200) go to the head's candidate
-//           list, staged in LDS so that a workgroup costs the list's counter one update, and are
-//           counted by their next 10 bits (45..36) in case the list overflows
-//   MODE 2: returns at once unless the head's list overflowed; then picks both digits and collects the
-//           keys that share them (the list's memory is reused, with a counter of its own)
+// A head of at most 1024 rows (of all batch entries one after the other) in one workgroup, its keys in registers: a lane
+// per chunk and 32 rows per step, all requested before the first is used; the first digit's histogram, then select_rank
+// within the digit that holds the rank.  Bound by that compute unit's instructions and latency: 17 us for 1024 rows, where
+// the sweeps over several workgroups, their histograms in memory, took 40 in five launches.
+// grid = (H, 1, tensors), 1024 threads.
 // ---------------------------------------------------------------------------------------
-// kFull: D = 128 (every lane of a 32-lane row slot holds a chunk); otherwise lanes past the row's
-// chunks are idle and the loads go through the general path.
-constexpr int kStageKeys = 1024;  // candidate keys a workgroup stages in LDS
-constexpr int kFallbackSpan = 8;  // sampled select: a workgroup of MODE 1 or 2 covers this many times kSelectRows rows
-// The counter of the list that holds the keys of the median's bin alone: MODE 1's.
-__device__ __forceinline__ uint32_t *bin_list_counter(const Geometry &g, const Workspace &ws, int h)
-{
-    return ws.cand_count + (g.select_sampled ? 2 * g.H + h : h);
-}
-template <int MODE, bool kFull, bool kCollect = false>
-__global__ __launch_bounds__(kSelectThreads) void k_select_sweep(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+constexpr int kHeadRows = 1024;
+template <int kSteps, bool kFull>
+__global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, float C)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    const _Float16 *__restrict__ x = tn.x;
-    constexpr bool kHist0 = MODE == 0 || MODE == 3;
-    constexpr bool kStages = MODE == 1 || (MODE == 0 && kCollect);
-    constexpr int kLdsBins = kHist0 ? kBins0 : kBins1;
-    __shared__ uint32_t lh[MODE == 2 ? 1 : kLdsBins];
-    __shared__ uint32_t scratch[kSelectThreads + 2];
-    __shared__ unsigned long long staged[kStages ? kStageKeys : 1];
-    __shared__ uint32_t n_staged, list_base;
-
-    const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
-    const uint32_t rank0 = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
-    uint32_t bin0 = 0, before0 = 0, bin1 = 0, before1 = 0;
-    uint32_t keep_lo = 0, keep_span = 0;
-    if (MODE == 0 && kCollect) {
-        keep_lo = ws.plan[h].lo;
-        keep_span = ws.plan[h].span;
-    }
-    if ((MODE == 1 || MODE == 2) && g.select_sampled && !ws.plan[h].need)
-        return;  // the candidates kept by MODE 0 hold the median's bin (uniform over the workgroup)
-    uint32_t *const bin_count = bin_list_counter(g, ws, h);
-    if (MODE == 2 && *bin_count <= (uint32_t)g.cand_cap)
-        return;  // the list of MODE 1 holds every candidate (uniform over the workgroup)
-    if (MODE == 1 || MODE == 2) {
-        pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank0, scratch, bin0, before0);
-        if (!fine_bin_is_prefix(bin0))
-            return;  // the finishing kernel knows the median of such a bin without candidates
-    }
-    if (MODE == 2)
-        pick_bin<kBins1, kSelectThreads>(ws.hist1 + (size_t)h * kBins1, rank0 - before0, scratch, bin1, before1);
-    if (MODE != 2) {
-        for (int i = threadIdx.x; i < kLdsBins; i += kSelectThreads)
-            lh[i] = 0;
-        if (threadIdx.x == 0)
-            n_staged = 0;
-        __syncthreads();
-    }
-
-    const int c = threadIdx.x & 31, sub = threadIdx.x >> 5;  // 32 rows per iteration
-    // MODE 3 walks the sampled rows: row j of its grid is token kSampleStride * j
-    constexpr int kStep = MODE == 3 ? kSampleStride : 1;
-    const int n_t = MODE == 3 ? (g.T + kSampleStride - 1) / kSampleStride : g.T;
-    // the sweeps that a sampled select seldom needs are launched with fewer, longer workgroups
-    const int rows = ((MODE == 1 || MODE == 2) && g.select_sampled) ? kSelectRows * kFallbackSpan : kSelectRows;
-    const int t0 = blockIdx.x * rows;
-    const int t1 = min(n_t, t0 + rows);
-    const _Float16 *base = x + (int64_t)b * g.sb + (int64_t)h * g.sh;
-    const int64_t row_stride = (int64_t)kStep * g.st;
+    const int h = blockIdx.x, tid = threadIdx.x, c = tid & 31;
+    __shared__ uint32_t hist[kBins0];
+    __shared__ RankScratch sc;
+    static_assert(kRankBins <= kBins0, "the histograms share their memory");
+    reset_head(g, ws, tn.enc, h, tid, kSelectThreads);
+    const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
     const bool active = kFull || c < g.n_c;
-    unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
-
-    for (int tb = t0; tb < t1; tb += 128) {  // uniform over the block
-        half4_t v[4];
+    half4_t v[kSteps];
+    {
+        uint32_t r = tid >> 5, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int tt = tb + sub + 32 * u;
-            v[u] = (tt < t1) ? load_row_chunk<kFull>(base + (int64_t)tt * row_stride, c, g) : half4_t{0, 0, 0, 0};
+        for (int u = 0; u < kSteps; ++u) {
+            v[u] = half4_t{0, 0, 0, 0};
+            if (active && r < R)
+                v[u] = load_row_chunk<kFull>(tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, c, g);
+            r += 32;
+            t += 32;
+            while (t >= (uint32_t)g.T && r < R) {
+                t -= (uint32_t)g.T;
+                ++b;
+            }
+        }
+    }
+    for (int i = tid; i < kBins0; i += kSelectThreads)
+        hist[i] = 0;
+    __syncthreads();
+    unsigned long long key[kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const bool in = active && (uint32_t)(tid >> 5) + 32u * u < R;
+        key[u] = in ? key_of(chunk_norm2(v[u])) & kKeyMask : ~0ull;
+        if (in)
+            atomicAdd(&hist[fine_bin(key[u])], 1u);
+    }
+    __syncthreads();
+    const uint32_t rank = (R * (uint32_t)g.n_c - 1u) / 2u;
+    uint32_t bin, before;
+    pick_bin<kBins0, kSelectThreads>(hist, rank, sc.pick, bin, before);
+    unsigned long long median = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; beyond finite fp16 data (not reached)
+    if (fine_bin_is_prefix(bin)) {
+        const unsigned long long lo = (unsigned long long)(bin + kFineBase) << kFineShift;
+        median = select_rank(
+            [&](auto f) {
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u)
+                    f(key[u]);
+            },
+            lo, lo | ((1ull << kFineShift) - 1ull), rank - before, hist, sc);
+    }
+    if (tid == 0)
+        ws.thr[h] = threshold_of(median, C);
+}
+
+// ---------------------------------------------------------------------------------------
+// Longer heads, prediction (and reset): one workgroup per head or, beyond 2^19 chunks, four, bound by their compute
+// unit's instructions and latency (8 us with 8 chunks per thread, 18 with 32: hence four).
+// A workgroup's sample: pieces of 8 chunks (64 bytes) of 128 rows per step, so that chunks of one row, which are alike
+// where the rows differ in scale, are few among it; every row's piece follows the one before, turned once more per round,
+// at an odd stride of rows, so that structures of a power-of-two period in either direction do not alias with the sample.
+// The range ends at the sample's ranks four standard deviations of a binomial count (sqrt(n) / 2 each) below and above its
+// middle one, for n chunks of all parts, whose ends are averaged: the whole head's median falls outside it about once in
+// 16000 heads of independent chunks.
+// In fp32, which only a prediction may be: exponent and 8 mantissa bits (a bin holds about 0.2% of smooth data), the range
+// widened by the rounding of the sum; 10 bits more where those two bins hold more than 1/64 of the sample.
+// A head in one part keeps 4.7% of smooth data, its lists hold at least 6.2%; in four parts 2.6% and 3.1%.
+// grid = (H, parts, tensors).
+// ---------------------------------------------------------------------------------------
+constexpr int kPredictBits = 8, kPredictShift = 23 - kPredictBits;
+constexpr uint32_t kPredictBase = (79u << kPredictBits) - 1u;  // fp32 exponents 79 (2^-48) to 162; bin 0: zero
+constexpr int kPredictBins = 84 << kPredictBits;
+constexpr int kBuckets = 16;
+constexpr int kBucketPitch = kBins1 / kBuckets;  // words between the counters: atomics to one line wait for each other
+__host__ __device__ __forceinline__ int predict_parts(const Geometry &g)
+{
+    return (uint64_t)g.B * g.T * g.n_c <= 1u << 19 ? 1 : 4;
+}
+__device__ __forceinline__ uint32_t *bucket_counts(const Workspace &ws, int h) { return ws.hist1 + (size_t)h * kBins1; }
+__device__ __forceinline__ float2 *predicted_ends(const Workspace &ws, int h)  // between the first two counters
+{
+    return reinterpret_cast<float2 *>(ws.hist1 + (size_t)h * kBins1 + kBucketPitch / 2);
+}
+
+template <bool kFull>
+__global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+{
+    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const Workspace ws = carve_workspace(tn.ws, wo);
+    const int h = blockIdx.x, tid = threadIdx.x;
+    __shared__ __align__(16) uint32_t hist[kPredictBins];
+    __shared__ uint32_t pick[kPickScratch];
+    constexpr int kSteps = 8, kPieceChunks = 8, kPieceRows = kSelectThreads / kPieceChunks;
+    const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
+    half4_t v[kSteps];
+    uint32_t loaded = 0;  // a bit per step
+    const uint32_t parts = gridDim.y, part = blockIdx.y;
+    {
+        const uint32_t samples = kPieceRows * kSteps * parts, stride = (R + samples - 1) / samples | 1u;
+        const uint32_t pieces = (uint32_t)(g.n_c + kPieceChunks - 1) / kPieceChunks;
+        uint32_t i = tid / kPieceChunks * parts + part, r = i * stride, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const uint32_t round = i / pieces, c = (i + round) % pieces * kPieceChunks + tid % kPieceChunks;
+            v[u] = half4_t{0, 0, 0, 0};
+            if (r < R && c < (uint32_t)g.n_c) {
+                v[u] = load_row_chunk<kFull>(tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, (int)c, g);
+                loaded |= 1u << u;
+            }
+            i += kPieceRows * parts;
+            r += kPieceRows * parts * stride;
+            t += kPieceRows * parts * stride;
+            while (t >= (uint32_t)g.T && r < R) {
+                t -= (uint32_t)g.T;
+                ++b;
+            }
+        }
+    }
+    if (part == 0) {
+        reset_head(g, ws, tn.enc, h, tid, kSelectThreads);
+        for (int i = tid; i < kBins0; i += kSelectThreads)
+            ws.hist0[(size_t)h * kBins0 + i] = 0;
+        if (tid < kBuckets)
+            bucket_counts(ws, h)[tid * kBucketPitch] = 0;
+        if (tid < 3)
+            ws.cand_count[tid * g.H + h] = 0;
+        if (tid == 0)
+            ws.plan[h].below = 0;
+    }
+    for (int i = tid; i < kPredictBins / 4; i += kSelectThreads)
+        reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t key[kSteps];
+    auto bin_of = [&](uint32_t k) { return min(max(k >> kPredictShift, kPredictBase) - kPredictBase, (uint32_t)kPredictBins - 1u); };
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const float x0 = (float)v[u][0], x1 = (float)v[u][1], x2 = (float)v[u][2], x3 = (float)v[u][3];
+        key[u] = __float_as_uint(fmaf(x3, x3, fmaf(x2, x2, fmaf(x1, x1, x0 * x0)))) & 0x7fffffffu;
+        if ((loaded >> u) & 1u)
+            atomicAdd(&hist[bin_of(key[u])], 1u);
+    }
+    __syncthreads();
+    uint32_t rank_lo, rank_hi, n, bin_lo, bin_hi, before_lo, before_hi;
+    pick_two<kPredictBins, kSelectThreads>(
+        hist,
+        [&](uint32_t total, uint32_t &a, uint32_t &b) {
+            const uint32_t mid = (total - 1) / 2, margin = (uint32_t)(2.0f * sqrtf((float)total / (float)parts)) + 2u;
+            n = total;
+            a = rank_lo = mid > margin ? mid - margin : 0u;
+            b = rank_hi = min(total - 1, mid + margin);
+        },
+        pick, bin_lo, before_lo, bin_hi, before_hi);
+    uint32_t f_lo = bin_lo == 0u ? 0u : (bin_lo + kPredictBase) << kPredictShift;
+    uint32_t f_hi = bin_hi == 0u ? 0u : ((bin_hi + kPredictBase) << kPredictShift) | ((1u << kPredictShift) - 1u);
+    const uint32_t n_lo = hist[bin_lo];
+    if (n_lo + hist[bin_hi] > n / 64u) {  // uniform: concentrated or coarse data
+        __syncthreads();
+        for (int i = tid; i < 2 * kBins1; i += kSelectThreads)
+            hist[i] = 0;
+        __syncthreads();
+        constexpr int kSubShift = kPredictShift - kBits1;
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            if ((loaded >> u) & 1u) {
+                const uint32_t bin = bin_of(key[u]), digit = (key[u] >> kSubShift) & (kBins1 - 1);
+                if (bin == bin_lo)
+                    atomicAdd(&hist[digit], 1u);
+                if (bin == bin_hi)
+                    atomicAdd(&hist[kBins1 + digit], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t sub_lo, sub_hi, before;
+        pick_two<2 * kBins1, kSelectThreads>(
+            hist,
+            [&](uint32_t, uint32_t &a, uint32_t &b) {
+                a = rank_lo - before_lo;
+                b = n_lo + rank_hi - before_hi;
+            },
+            pick, sub_lo, before, sub_hi, before);
+        if (bin_lo != 0u)
+            f_lo |= sub_lo << kSubShift;
+        if (bin_hi != 0u)
+            f_hi = f_hi >> kPredictShift << kPredictShift | (sub_hi & (kBins1 - 1)) << kSubShift | ((1u << kSubShift) - 1u);
+        // a sample that holds one value between the two ranks: that value alone (a constant or coarsely quantised tensor,
+        // whose squares are exact in fp32: its keys need no list)
+        uint32_t least = 0xffffffffu, most = 0u;
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            if (((loaded >> u) & 1u) && key[u] >= f_lo && key[u] <= f_hi) {
+                least = min(least, key[u]);
+                most = max(most, key[u]);
+            }
+        }
+        if (tid == 0) {
+            pick[0] = 0xffffffffu;
+            pick[1] = 0u;
+        }
+        __syncthreads();
+        if (least <= most) {
+            atomicMin(&pick[0], least);
+            atomicMax(&pick[1], most);
+        }
+        __syncthreads();
+        if (pick[0] == pick[1])
+            f_lo = f_hi = pick[0];
+    }
+    if (tid == 0) {
+        if (f_lo != f_hi) {  // three roundings of 2^-24 each: 4 units of the last place on either side
+            f_lo = f_lo <= 4u ? 0u : f_lo - 4u;
+            f_hi += 4u;
+        }
+        predicted_ends(ws, h)[part] = make_float2(__uint_as_float(f_lo), __uint_as_float(f_hi));
+    }
+}
+
+// The kept keys' lists: 16 equal parts of the range of values (of bit patterns, the parts above a power of two would hold
+// twice what those below it do).
+__device__ __forceinline__ uint32_t bucket_capacity(const Geometry &g) { return (uint32_t)g.cand_cap / kBuckets; }
+struct Buckets {
+    unsigned long long lo, span;  // keys
+    float scale;
+    __device__ __forceinline__ Buckets(const Geometry &g, const Workspace &ws, int h)
+    {
+        const float2 *parts = predicted_ends(ws, h);
+        const int n = predict_parts(g);
+        float first = 0.0f, last = 0.0f;
+        for (int i = 0; i < n; ++i) {
+            first += parts[i].x;
+            last += parts[i].y;
+        }
+        // exact, if the parts agree on a single value; else their ends are 4 units of the last place wide
+        first *= 1.0f / (float)n;
+        last *= 1.0f / (float)n;
+        lo = key_of((double)first);
+        span = key_of((double)last) - lo;
+        scale = (float)kBuckets / (last - first);  // not used for a single value
+    }
+    __device__ __forceinline__ bool holds(unsigned long long key) const { return key - lo <= span; }
+    __device__ __forceinline__ uint32_t of(unsigned long long key) const  // monotone in key
+    {
+        const double past = __longlong_as_double((long long)key) - __longlong_as_double((long long)lo);
+        return min((uint32_t)((float)past * scale), (uint32_t)kBuckets - 1u);
+    }
+};
+
+// Where the key of the given rank is among the kept ones: its list and its rank there.  False: not at all (it lies outside
+// the predicted range), or its list overflowed (a range of one value needs none).
+__device__ __forceinline__ bool find_kept(const Geometry &g, const Workspace &ws, int h, const Buckets &range, uint32_t rank,
+                                          uint32_t &bucket, uint32_t &rank_in, uint32_t &n)
+{
+    const uint32_t below = ws.plan[h].below;
+    const int lane = threadIdx.x & 63;  // every wave for itself: a lane per list
+    const uint32_t mine = lane < kBuckets ? bucket_counts(ws, h)[lane * kBucketPitch] : 0u;
+    uint32_t inc = mine;
+#pragma unroll
+    for (int d = 1; d < kBuckets; d <<= 1) {
+        const uint32_t o = __shfl_up(inc, d, 64);
+        if (lane >= d)
+            inc += o;
+    }
+    const unsigned long long past = __ballot(lane < kBuckets && rank >= below && rank - below < inc);
+    if (past == 0ull)
+        return false;
+    bucket = (uint32_t)__ffsll((long long)past) - 1u;
+    n = (uint32_t)__shfl((int)mine, (int)bucket, 64);
+    rank_in = rank - below - ((uint32_t)__shfl((int)inc, (int)bucket, 64) - n);
+    return n <= bucket_capacity(g) || range.span == 0ull;
+}
+
+// The sweep: keys below the predicted range are counted, those in it kept, staged in LDS so that a workgroup updates each
+// list's counter once.  HBM-bound: two [1, 8, 32768, 128] tensors in 31 us, 4.4 TB/s; one of 131072 rows in 56, 4.8.
+// `rows` of one (b, h) segment per workgroup, grid = (ceil(T / rows), B * H, tensors).
+constexpr int kStageKeys = 128;  // keys a workgroup stages per list
+template <bool kFull>
+__global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows)
+{
+    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const Workspace ws = carve_workspace(tn.ws, wo);
+    __shared__ unsigned long long staged[kBuckets][kStageKeys];
+    __shared__ uint32_t n_staged[kBuckets], n_below;
+    const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
+    const int c = threadIdx.x & 31, sub = threadIdx.x >> 5;
+    const int t0 = blockIdx.x * rows, t1 = min(g.T, t0 + rows);
+    const _Float16 *base = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh;
+    const Buckets range(g, ws, h);
+    const uint32_t cap = bucket_capacity(g);
+    unsigned long long *lists = ws.cand + (size_t)h * g.cand_cap;
+    uint32_t *count = bucket_counts(ws, h);
+    if (threadIdx.x < kBuckets)
+        n_staged[threadIdx.x] = 0;
+    if (threadIdx.x == 0)
+        n_below = 0;
+    __syncthreads();
+    uint32_t below = 0, equal = 0;
+    for (int tb = t0 + sub; tb < t1; tb += 256) {
+        half4_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            v[u] = half4_t{0, 0, 0, 0};
+            if (tb + 32 * u < t1)
+                v[u] = load_row_chunk<kFull>(base + (int64_t)(tb + 32 * u) * g.st, c, g);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool in = active && (tb + sub + 32 * u) < t1;
+        for (int u = 0; u < 8; ++u) {
+            const bool in = (kFull || c < g.n_c) && tb + 32 * u < t1;
             const unsigned long long key = key_of(chunk_norm2(v[u])) & kKeyMask;
-            if (kHist0) {
-                if (in) {
-                    const uint32_t bin = fine_bin(key);
-                    atomicAdd(&lh[bin], 1u);
-                    if (kCollect && bin - keep_lo <= keep_span) {
-                        const uint32_t pos = atomicAdd(&n_staged, 1u);
-                        if (pos < (uint32_t)kStageKeys) {
-                            staged[pos] = key;
-                        } else {
-                            const uint32_t gpos = atomicAdd(&ws.cand_count[h], 1u);
-                            if (gpos < (uint32_t)g.cand_cap)
-                                cand[gpos] = key;
-                        }
-                    }
-                }
-            } else if (MODE == 1) {
-                if (in && fine_bin(key) == bin0) {
-                    atomicAdd(&lh[(uint32_t)(key >> kSecShift) & (kBins1 - 1)], 1u);
-                    const uint32_t pos = atomicAdd(&n_staged, 1u);
+            below += in && key < range.lo ? 1u : 0u;
+            if (in && range.holds(key)) {
+                if (range.span == 0ull) {
+                    ++equal;
+                } else {
+                    const uint32_t k = range.of(key), pos = atomicAdd(&n_staged[k], 1u);
                     if (pos < (uint32_t)kStageKeys) {
-                        staged[pos] = key;
-                    } else {  // more than the stage holds (many equal norms): straight to the list
-                        const uint32_t gpos = atomicAdd(bin_count, 1u);
-                        if (gpos < (uint32_t)g.cand_cap)
-                            cand[gpos] = key;
-                    }
-                }
-            } else {
-                // one counter update per wave: ballot, leader adds, lanes take consecutive slots
-                const bool hit = in && fine_bin(key) == bin0 && ((uint32_t)(key >> kSecShift) & (kBins1 - 1)) == bin1;
-                const unsigned long long m = __ballot(hit);
-                if (m) {
-                    uint32_t basepos = 0;
-                    const int leader = __ffsll((long long)m) - 1;
-                    if ((int)(threadIdx.x & 63) == leader)
-                        basepos = atomicAdd(&ws.cand_count[g.H + h], (uint32_t)__popcll(m));
-                    basepos = __shfl(basepos, leader, 64);
-                    if (hit) {
-                        const uint32_t pos = basepos + __popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
-                        if (pos < (uint32_t)g.cand_cap)
-                            cand[pos] = key;
+                        staged[k][pos] = key;
+                    } else {  // more than the stage holds: straight to the list
+                        const uint32_t at = atomicAdd(&count[k * kBucketPitch], 1u);
+                        if (at < cap)
+                            lists[k * cap + at] = key;
                     }
                 }
             }
         }
     }
-    if (MODE != 2) {
-        __syncthreads();
-        uint32_t *gh = MODE == 0   ? ws.hist0 + (size_t)h * kBins0
-                       : MODE == 3 ? ws.hist_s + (size_t)h * kBins0
-                                   : ws.hist1 + (size_t)h * kBins1;
-        for (int i = threadIdx.x; i < kLdsBins; i += kSelectThreads) {
-            const uint32_t n = lh[i];
-            if (n)
-                atomicAdd(&gh[i], n);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+        below += __shfl_xor(below, d, 64);
+    if ((threadIdx.x & 63) == 0)
+        atomicAdd(&n_below, below);
+    if (equal)
+        atomicAdd(&n_staged[0], equal);
+    __syncthreads();
+    const int k = threadIdx.x / 64;  // a wave per list
+    static_assert(kBuckets * 64 == kSelectThreads, "a wave per list");
+    if (range.span == 0ull) {
+        if (threadIdx.x == 0 && n_staged[0])
+            atomicAdd(&count[0], n_staged[0]);
+    } else {
+        const uint32_t n = min(n_staged[k], (uint32_t)kStageKeys);
+        uint32_t at = 0;
+        if ((threadIdx.x & 63) == 0 && n)
+            at = atomicAdd(&count[k * kBucketPitch], n);
+        at = (uint32_t)__shfl((int)at, 0, 64);
+        for (uint32_t i = threadIdx.x & 63; i < n; i += 64)
+            if (at + i < cap)
+                lists[k * cap + at + i] = staged[k][i];
+    }
+    if (threadIdx.x == 0 && n_below)
+        atomicAdd(&ws.plan[h].below, n_below);
+}
+
+// ---------------------------------------------------------------------------------------
+// For a head whose kept keys do not answer: kParts workgroups share its rows (of all batch entries one after the other).
+// Every other head's workgroups return at once.
+// ---------------------------------------------------------------------------------------
+constexpr int kParts = 16;
+// f of the key of every chunk of the rows [first, last) of head h, a lane per chunk, 128 rows per step in flight.
+template <bool kFull, typename F>
+__device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, int h, uint32_t first, uint32_t last, F f)
+{
+    const int c = threadIdx.x & 31;
+    for (uint32_t r0 = first + (threadIdx.x >> 5); r0 < last; r0 += 128) {
+        half4_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t r = r0 + 32u * u, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
+            v[u] = half4_t{0, 0, 0, 0};
+            if (r < last)
+                v[u] = load_row_chunk<kFull>(x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, c, g);
         }
-    }
-    if (kStages) {
-        const uint32_t n = min(n_staged, (uint32_t)kStageKeys);
-        uint32_t *const counter = MODE == 1 ? bin_count : ws.cand_count + h;
-        if (threadIdx.x == 0)
-            list_base = n ? atomicAdd(counter, n) : 0u;
-        __syncthreads();
-        const uint32_t at = list_base;
-        for (uint32_t i = threadIdx.x; i < n; i += kSelectThreads)
-            if (at + i < (uint32_t)g.cand_cap)
-                cand[at + i] = staged[i];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((kFull || c < g.n_c) && r0 + 32u * u < last)
+                f(key_of(chunk_norm2(v[u])) & kKeyMask);
     }
 }
+__device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t &first, uint32_t &last)
+{
+    const uint64_t R = (uint64_t)g.B * g.T;
+    first = (uint32_t)(R * blockIdx.x / kParts);
+    last = (uint32_t)(R * (blockIdx.x + 1) / kParts);
+}
 
-// ---------------------------------------------------------------------------------------
-// The two small steps of the sampled select, one workgroup per head.
-//   k_select_range   after MODE 3: the bins of the first digit that hold the sample's ranks within four
-//                    standard deviations of its median rank (a binomial count: sqrt(n)/2 ranks each): for
-//                    rows drawn from one distribution the full data's median falls outside them about once
-//                    in 16000 heads
-//   k_select_decide  after MODE 0: the median's bin from the full histogram, and whether the kept keys
-//                    cover it (inside the predicted bins, list not overflowed)
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelectThreads) void k_select_range(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+// The histogram of the first digit (fine_bin).  grid = (kParts, H, tensors).
+template <bool kFull>
+__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    __shared__ uint32_t scratch[kSelectThreads + 2];
-    const int h = blockIdx.x;
-    const uint32_t n_s = (uint32_t)((uint64_t)g.B * ((g.T + kSampleStride - 1) / kSampleStride) * g.n_c);
-    const uint32_t mid = (n_s - 1) / 2;
-    const uint32_t margin = (uint32_t)(2.0f * sqrtf((float)n_s)) + 2u;
-    uint32_t lo, hi, before;
-    pick_bin<kBins0, kSelectThreads>(ws.hist_s + (size_t)h * kBins0, mid > margin ? mid - margin : 0u, scratch, lo, before);
-    pick_bin<kBins0, kSelectThreads>(ws.hist_s + (size_t)h * kBins0, min(n_s - 1, mid + margin), scratch, hi, before);
-    lo = max(lo, 1u);                      // only bins that are one 17-bit prefix each hold candidates
-    hi = min(hi, (uint32_t)kBins0 - 2u);
-    if (threadIdx.x == 0) {
-        ws.plan[h].lo = lo <= hi ? lo : (uint32_t)kBins0;
-        ws.plan[h].span = lo <= hi ? hi - lo : 0u;
-    }
-}
-
-__global__ __launch_bounds__(kSelectThreads) void k_select_decide(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
-{
-    const EncodeTensor &tn = batch.t[blockIdx.z];
-    const Workspace ws = carve_workspace(tn.ws, wo);
-    __shared__ uint32_t scratch[kSelectThreads + 2];
-    const int h = blockIdx.x;
-    const uint32_t rank0 = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
-    uint32_t bin0, before0;
-    pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank0, scratch, bin0, before0);
-    if (threadIdx.x == 0) {
-        const bool covered = bin0 - ws.plan[h].lo <= ws.plan[h].span && ws.cand_count[h] <= (uint32_t)g.cand_cap;
-        ws.plan[h].bin0 = bin0;
-        ws.plan[h].before0 = before0;
-        ws.plan[h].need = fine_bin_is_prefix(bin0) && !covered ? 1u : 0u;
-    }
+    __shared__ uint32_t hist[kBins0];
+    const int h = blockIdx.y;
+    uint32_t bucket, rank_in, n, first, last;
+    if (find_kept(g, ws, h, Buckets(g, ws, h), (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n))
+        return;
+    for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
+        hist[i] = 0;
+    __syncthreads();
+    part_of_rows(g, first, last);
+    each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) { atomicAdd(&hist[fine_bin(key)], 1u); });
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
+        if (hist[i])
+            atomicAdd(&ws.hist0[(size_t)h * kBins0 + i], hist[i]);
 }
 
 // ---------------------------------------------------------------------------------------
-// finish: one workgroup per head.  Locates the first digit again; a head whose candidate list is
-// complete has its median among the list's keys (they share the digit's 17-bit prefix): radix select on
-// their low 46 bits.  After an overflow the second digit is located too and the select runs on the low
-// 36 bits of the keys MODE 2 collected, or, if even those were too many (many equal norms: a constant or
-// coarsely quantised tensor), over the head's raw rows: slow, exact, and only for such inputs.
-// Writes thr[h] = fl(fl(C*C) * median).
+// finish: one workgroup of a head selects from the list that holds the wanted rank.  If there is none, all of the
+// head's workgroups collect the keys of the first digit's bin that holds it, and the last of them to end selects among
+// these, or, if they were too many (a coarsely quantised tensor), among the head's raw rows: slow, exact, and only for such
+// inputs.  5.5 us for 8 heads of 2^20 chunks; a head that was missed costs 90 us more.
+// Writes thr[h] = fl(fl(C*C) * median).  grid = (kParts, H, tensors).
 // ---------------------------------------------------------------------------------------
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
@@ -345,91 +674,93 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    const _Float16 *__restrict__ x = tn.x;
-    __shared__ uint32_t lh[kBins1];
-    __shared__ uint32_t scratch[kSelectThreads + 2];
-    const int h = blockIdx.x;
+    __shared__ uint32_t bins[kRankBins];
+    __shared__ RankScratch sc;
+    __shared__ uint32_t arrived;
+    const int h = blockIdx.y, tid = threadIdx.x;
     uint32_t rank = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
-    uint32_t bin0, before0;
-    pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank, scratch, bin0, before0);
-    rank -= before0;
-
-    unsigned long long median_bits;
-    if (bin0 == 0u) {
-        median_bits = 0ull;  // fp16 data: the bin holds zeros only
-    } else if (!fine_bin_is_prefix(bin0)) {
-        median_bits = 0x7ff0000000000000ull;  // not reached by finite fp16 data: nothing is flagged
+    unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
+    const bool selects = (blockIdx.x + blockIdx.y) % kParts == 0;  // not the same part of every head, whose workgroups one XCD gets
+    unsigned long long median;
+    const Buckets range(g, ws, h);
+    uint32_t bucket, rank_in, n;
+    if (find_kept(g, ws, h, range, rank, bucket, rank_in, n)) {  // uniform
+        if (!selects)
+            return;
+        const unsigned long long *list = cand + bucket * bucket_capacity(g);
+        constexpr int kHeld = 8;  // keys per thread that stay in registers
+        if (range.span == 0ull) {
+            median = range.lo;
+        } else if (n <= kHeld * kSelectThreads) {
+            unsigned long long key[kHeld];
+#pragma unroll
+            for (int u = 0; u < kHeld; ++u)
+                key[u] = u * kSelectThreads + tid < n ? list[u * kSelectThreads + tid] : ~0ull;  // outside every range of keys
+            median = select_rank(
+                [&](auto f) {
+#pragma unroll
+                    for (int u = 0; u < kHeld; ++u)
+                        if (u * kSelectThreads < n)  // uniform
+                            f(key[u]);
+                },
+                range.lo, range.lo + range.span, rank_in, bins, sc);
+        } else {
+            median = select_rank(
+                [&](auto f) {
+                    for (uint32_t i = tid; i < n; i += kSelectThreads)
+                        f(list[i]);
+                },
+                range.lo, range.lo + range.span, rank_in, bins, sc);
+        }
     } else {
-        unsigned long long prefix = (unsigned long long)(bin0 + kFineBase);  // key bits fixed so far, right aligned
-        int low_bits = kFineShift;
-        // sampled select whose kept keys cover the bin: the list also holds keys of the neighbouring bins,
-        // which the comparisons against the prefix below pass over
-        const bool kept = g.select_sampled && !ws.plan[h].need;
-        uint32_t n_cand = kept ? ws.cand_count[h] : *bin_list_counter(g, ws, h);
-        if (n_cand > (uint32_t)g.cand_cap) {
-            uint32_t bin1, before1;
-            pick_bin<kBins1, kSelectThreads>(ws.hist1 + (size_t)h * kBins1, rank, scratch, bin1, before1);
-            rank -= before1;
-            prefix = (prefix << kBits1) | bin1;
-            low_bits = kSecShift;
-            n_cand = ws.cand_count[g.H + h];
-        }
-        const bool from_list = n_cand <= (uint32_t)g.cand_cap;
-        const unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
-
-        unsigned long long low = 0;  // low-part digits fixed so far, right aligned
-        int remaining = low_bits;    // low-part bits still open
-        while (remaining > 0) {
-            const int d = remaining < 10 ? remaining : 10;
-            const int shift = remaining - d;
-            const uint32_t dmask = (1u << d) - 1u;
-            for (int i = threadIdx.x; i < kBins1; i += kSelectThreads)
-                lh[i] = 0;
-            __syncthreads();
-            const unsigned long long want = (prefix << (low_bits - remaining)) | low;  // compare key >> remaining
-            if (from_list) {
-                // four keys requested before the first is used; a slot past the list reads as a key with
-                // bit 63 set, which no prefix matches
-                for (uint32_t i0 = 0; i0 < n_cand; i0 += 4 * kSelectThreads) {
-                    unsigned long long key[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t i = i0 + u * kSelectThreads + threadIdx.x;
-                        key[u] = i < n_cand ? cand[i] : ~0ull;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if ((key[u] >> remaining) == want)
-                            atomicAdd(&lh[(uint32_t)(key[u] >> shift) & dmask], 1u);
+        uint32_t bin, before;
+        pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank, sc.pick, bin, before);
+        rank -= before;
+        if (!fine_bin_is_prefix(bin)) {
+            if (!selects)
+                return;
+            median = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; beyond finite fp16 data (not reached)
+        } else {
+            uint32_t *const n_cand = ws.cand_count + h, *const n_done = ws.cand_count + g.H + h;
+            const unsigned long long lo = (unsigned long long)(bin + kFineBase) << kFineShift;
+            const unsigned long long hi = lo | ((1ull << kFineShift) - 1ull);
+            uint32_t first, last;
+            part_of_rows(g, first, last);
+            each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) {
+                if (fine_bin(key) == bin) {  // one update of the counter per wave
+                    const unsigned long long same = __ballot(1);
+                    const int lane = tid & 63, leader = __ffsll((long long)same) - 1;
+                    uint32_t at = 0;
+                    if (lane == leader)
+                        at = atomicAdd(n_cand, (uint32_t)__popcll(same));
+                    at = (uint32_t)__shfl((int)at, leader, 64) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+                    if (at < (uint32_t)g.cand_cap)
+                        cand[at] = key;
                 }
-            } else {
-                // rare path: sweep the head's rows (every batch entry), one lane per chunk
-                const int c = threadIdx.x & 31, sub = threadIdx.x >> 5;
-                for (int b = 0; b < g.B; ++b) {
-                    const _Float16 *base = x + (int64_t)b * g.sb + (int64_t)h * g.sh;
-                    for (int t = sub; t < g.T; t += kSelectThreads / 32) {
-                        const unsigned long long key =
-                            key_of(chunk_norm2(load_row_chunk<kFull>(base + (int64_t)t * g.st, c, g))) & kKeyMask;
-                        if ((kFull || c < g.n_c) && (key >> remaining) == want)
-                            atomicAdd(&lh[(uint32_t)(key >> shift) & dmask], 1u);
-                    }
-                }
-            }
+            });
+            __threadfence();  // the list before the arrival
             __syncthreads();
-            uint32_t bin, before;
-            pick_bin<kBins1, kSelectThreads>(lh, rank, scratch, bin, before);
-            rank -= before;
-            low = (low << d) | bin;
-            remaining -= d;
+            if (tid == 0)
+                arrived = atomicAdd(n_done, 1u);
+            __syncthreads();
+            if (arrived != (uint32_t)kParts - 1u)
+                return;
+            __threadfence();
+            n = __hip_atomic_load(n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (n <= (uint32_t)g.cand_cap)
+                median = select_rank(
+                    [&](auto f) {
+                        for (uint32_t i = tid; i < n; i += kSelectThreads)
+                            f(cand[i]);
+                    },
+                    lo, hi, rank, bins, sc);
+            else
+                median = select_rank([&](auto f) { each_key<kFull>(g, tn.x, h, 0u, (uint32_t)g.B * (uint32_t)g.T, f); }, lo, hi, rank,
+                                     bins, sc);
         }
-        median_bits = (prefix << low_bits) | low;
     }
-    if (threadIdx.x == 0) {
-        // threshold on squares: fl(fl(C*C) * median), C widened from fp32
-        const double c = (double)C;
-        const double c2 = c * c;
-        ws.thr[h] = c2 * __longlong_as_double((long long)median_bits);
-    }
+    if (tid == 0)
+        ws.thr[h] = threshold_of(median, C);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -639,7 +970,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_shard_pick(Geometry g, Works
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    __shared__ uint32_t scratch[kSelectThreads + 2];
+    __shared__ uint32_t scratch[kPickScratch];
     const int h = blockIdx.x;
     unsigned long long prefix = 0;
     uint32_t rank = (uint32_t)((total_per_head - 1) / 2);
@@ -664,9 +995,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_shard_pick(Geometry g, Works
         ws.state[h].prefix = prefix;
         ws.state[h].rank = rank;
         if (pass == 6) {
-            const double c = (double)C;
-            const double c2 = c * c;
-            ws.thr[h] = c2 * __longlong_as_double((long long)prefix);  // all 63 bits fixed: the median itself
+            ws.thr[h] = threshold_of(prefix, C);  // all 63 bits fixed: the median itself
         }
     }
 }
@@ -726,45 +1055,38 @@ hipError_t launch_shard_median_pass(const Geometry &g, const WorkspaceOffsets &w
 // host-side launch sequences
 // ---------------------------------------------------------------------------------------
 template <bool kFull>
-static void select_sweeps_for(Geometry g, const WorkspaceOffsets &wo, const EncodeBatch &batch, unsigned n, float C,
+static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, unsigned n, float C,
                               hipStream_t stream)
 {
-    const dim3 grid((g.T + kSelectRows - 1) / kSelectRows, g.B * g.H, n), heads(g.H, 1, n), block(kSelectThreads);
-    g.select_sampled = (uint64_t)g.B * g.T * g.n_c >= (uint64_t)kSampleMinChunks ? 1 : 0;
-    if (g.select_sampled) {
-        const int n_t = (g.T + kSampleStride - 1) / kSampleStride;
-        const dim3 grid_s((n_t + kSelectRows - 1) / kSelectRows, g.B * g.H, n);
-        hipLaunchKernelGGL((k_select_sweep<3, kFull>), grid_s, block, 0, stream, g, wo, batch);
-        hipLaunchKernelGGL(k_select_range, heads, block, 0, stream, g, wo, batch);
-        hipLaunchKernelGGL((k_select_sweep<0, kFull, true>), grid, block, 0, stream, g, wo, batch);
-        hipLaunchKernelGGL(k_select_decide, heads, block, 0, stream, g, wo, batch);
-    } else {
-        hipLaunchKernelGGL((k_select_sweep<0, kFull>), grid, block, 0, stream, g, wo, batch);
+    const dim3 heads(g.H, 1, n), samples(g.H, predict_parts(g), n), parts(kParts, g.H, n), block(kSelectThreads);
+    const uint64_t head_rows = (uint64_t)g.B * g.T;
+    if (head_rows <= 256) {
+        hipLaunchKernelGGL((k_select_head<8, kFull>), heads, block, 0, stream, g, wo, batch, C);
+        return;
     }
-    const int rows_late = g.select_sampled ? kSelectRows * kFallbackSpan : kSelectRows;
-    const dim3 grid_late((g.T + rows_late - 1) / rows_late, g.B * g.H, n);
-    hipLaunchKernelGGL((k_select_sweep<1, kFull>), grid_late, block, 0, stream, g, wo, batch);
-    hipLaunchKernelGGL((k_select_sweep<2, kFull>), grid_late, block, 0, stream, g, wo, batch);
-    hipLaunchKernelGGL(k_select_finish<kFull>, heads, block, 0, stream, g, wo, batch, C);
-}
-static void select_sweeps(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, unsigned n, float C,
-                          bool full, hipStream_t stream)
-{
-    if (full)
-        select_sweeps_for<true>(g, wo, batch, n, C, stream);
-    else
-        select_sweeps_for<false>(g, wo, batch, n, C, stream);
+    if (head_rows <= (uint64_t)kHeadRows) {
+        hipLaunchKernelGGL((k_select_head<32, kFull>), heads, block, 0, stream, g, wo, batch, C);
+        return;
+    }
+    hipLaunchKernelGGL(k_select_predict<kFull>, samples, block, 0, stream, g, wo, batch);
+    int rows = kSelectRows;  // down to the 256 of one step while two workgroups per compute unit are not there
+    while (rows > 256 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 512)
+        rows /= 2;
+    hipLaunchKernelGGL(k_select_count<kFull>, dim3((g.T + rows - 1) / rows, g.B * g.H, n), block, 0, stream, g, wo, batch, rows);
+    hipLaunchKernelGGL(k_select_digit<kFull>, parts, block, 0, stream, g, wo, batch);
+    hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }
 
 hipError_t launch_select_median(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                                 float C, bool skip_select, hipStream_t stream)
 {
     const unsigned n = (unsigned)n_tensors;
-    uint32_t n_init = (uint32_t)g.H * kBins0;
-    hipLaunchKernelGGL(k_init, dim3((n_init + kThreads - 1) / kThreads, 1, n), dim3(kThreads), 0, stream, g, wo, batch);
-    if (!skip_select) {
-        select_sweeps(g, wo, batch, n, C, g.D == 4 * kChunksPerRow, stream);
-    }
+    if (skip_select)
+        hipLaunchKernelGGL(k_init, dim3(g.H, 1, n), dim3(kThreads), 0, stream, g, wo, batch);
+    else if (g.D == 4 * kChunksPerRow)
+        launch_select_for<true>(g, wo, batch, n, C, stream);
+    else
+        launch_select_for<false>(g, wo, batch, n, C, stream);
     return hipGetLastError();
 }
 

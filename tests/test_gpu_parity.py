@@ -538,6 +538,57 @@ def test_sampled_select_row_structures(kind, D, B, H, T):
     assert np.array_equal(thr.cpu().numpy().view(np.uint64), ((c * c) * e.m2).view(np.uint64))
 
 
+def _sampled_rows(B, T, D):
+    """The rows of a head that the select's prediction looks at (restated from its kernel's comment): every stride-th,
+    1024 per part, four parts beyond 2^19 chunks."""
+    R = B * T
+    samples = 1024 * (1 if R * ((D + 3) // 4) <= 1 << 19 else 4)
+    return torch.arange(0, R, ((R + samples - 1) // samples) | 1)
+
+
+@pytest.mark.parametrize("kind,D,B,T", [
+    ("plain", 128, 1, 255), ("plain", 45, 2, 128), ("plain", 128, 1, 257), ("plain", 4, 1, 1024), ("plain", 128, 2, 512),
+    ("plain", 128, 1, 1025), ("plain", 45, 3, 683), ("plain", 3, 1, 20000), ("plain", 128, 1, 16384), ("plain", 128, 1, 16385),
+    ("plain", 96, 3, 7300), ("small", 128, 1, 4099), ("large", 100, 2, 1537), ("zero", 128, 1, 16400), ("equal", 128, 1, 16400),
+    ("overflow", 128, 1, 9000), ("overflow", 64, 2, 17000), ("infinite", 128, 1, 1500),
+])
+def test_select_rows_and_predictions(kind, D, B, T):
+    """The select at the edges of its forms (256 and 1024 rows, 2^19 chunks) and where the sampled rows mislead it: smaller
+    or larger than the rest, zero, all equal, or ordinary while the rest is equal and inside the predicted range (no list
+    holds it).  Thresholds bit for bit."""
+    H, S = 2, 1
+    gen = torch.Generator().manual_seed(T + D)
+    x = torch.randn(B, H, T, D, generator=gen) * torch.exp(0.3 * torch.randn(B, H, T, 1, generator=gen))
+    rows = _sampled_rows(B, T, D)
+    b, t = rows // T, rows % T
+    if kind in ("small", "large", "zero"):
+        x[b, 0, t] *= {"small": 0.02, "large": 40.0, "zero": 0.0}[kind]
+    elif kind == "equal":
+        x[b, 0, t] = 0.5
+    elif kind == "overflow":
+        keep = x[b, 0, t].clone()
+        x[:, 0] = 0.91
+        x[b, 0, t] = keep
+    elif kind == "infinite":
+        x[:, 0, ::5] = float("inf")
+    x = x.half()
+    sec_t, sec = _sec(4, H, S)
+    m2 = oracle.encode(_bits(x), sec, rows=np.arange(0, 1)).m2 if kind != "infinite" else None
+    x_dev = x.to(DEV)
+    params = hq.params_for(x_dev, S)
+    ws = hq.alloc_workspace(params, DEV)
+    ws.fill_(0x5A)
+    hq.hqmq_encode(params, x_dev, sec_t.to(DEV), hq.alloc_encoded(params, DEV), ws)
+    thr = hq.hqmq_thresholds(params, ws).cpu().numpy()
+    c = float(np.float32(3.0))
+    if m2 is None:  # a fifth of the keys is infinite: the finite ones' order statistic, found in fp64
+        y = x.double().view(B, H, T, D // 4, 4).pow(2).sum(-1).transpose(0, 1).reshape(H, -1)
+        m2 = y.sort(1).values[:, (y.shape[1] - 1) // 2].numpy()
+        assert np.allclose(thr, (c * c) * m2, rtol=1e-15, atol=0)
+    else:
+        assert np.array_equal(thr.view(np.uint64), ((c * c) * m2).view(np.uint64))
+
+
 def test_exact_tie_structured_input():
     """Chunks like (a, a, 0, 0) sit on the boundary between several codewords when the
     secondary is the identity; whichever the GPU picks must score as the oracle's best."""
