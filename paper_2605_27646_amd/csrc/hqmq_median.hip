@@ -832,34 +832,105 @@ __global__ __launch_bounds__(1024) void k_scan(Geometry g, WorkspaceOffsets wo, 
     }
 }
 
-// grid = (ceil(T / 256), B*H), one thread per row
-template <bool kFull>
-__global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+// kOwnPrefix: no k_scan before it; every workgroup sums the totals of the search workgroups before its rows itself, and the
+// first of a head, and the last of all, write what else k_scan would.  Taken up to kOwnPrefixBlocks, eight loads per thread.
+// 256 rows per workgroup, a thread per row, four of its outliers in flight.  Bound by the latency of its loads: 7.5 us for
+// two [1, 8, 32768, 128] tensors (11.5 with k_scan before it and one outlier at a time), 29 instead of 39 at 5% outliers.
+// grid = (ceil(T / 256), B*H, tensors).
+constexpr uint32_t kOwnPrefixBlocks = 2048;
+// This thread's share of the sum of v[begin .. end), four requested before the first is used.
+__device__ __forceinline__ uint32_t sum_of(const uint32_t *v, uint32_t begin, uint32_t end)
+{
+    uint32_t sum = 0;
+    for (uint32_t i0 = begin + threadIdx.x; i0 < end; i0 += 4 * kThreads) {
+        uint32_t part[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            part[u] = i0 + u * kThreads < end ? v[i0 + u * kThreads] : 0u;
+        sum += part[0] + part[1] + part[2] + part[3];
+    }
+    return sum;
+}
+template <bool kFull, bool kOwnPrefix>
+__global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, uint32_t n_blocks)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
     const uint64_t outlier_capacity = tn.outlier_capacity;
-    const _Float16 *__restrict__ x = tn.x;
+    __shared__ uint32_t sums[2];
+    const int tid = threadIdx.x, lane = tid & 63;
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
-    const int t = blockIdx.x * kThreads + threadIdx.x;
-    if (t >= g.T)
-        return;
+    const int t = blockIdx.x * kThreads + tid;
     const int64_t R = (int64_t)seg * g.T + t;
-    uint32_t word = enc.flags[R];
-    const uint32_t off = enc.row_off[R] + ws.block_pre[(size_t)seg * g.n_search_blocks_per_seg + t / g.search_rows];
-    enc.row_off[R] = off;
-    if (!word)
-        return;
-    const _Float16 *row = x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st;
+    const bool in = t < g.T;
+    uint32_t word = in ? enc.flags[R] : 0u;
+    uint32_t off = in ? enc.row_off[R] : 0u;
+    const uint32_t per_seg = g.n_search_blocks_per_seg;
+    const uint32_t block = (uint32_t)seg * per_seg + (uint32_t)min(t, g.T - 1) / g.search_rows;
+    if (kOwnPrefix) {
+        // everything that is read is requested before the first use
+        const uint32_t first = (uint32_t)seg * per_seg + blockIdx.x * (uint32_t)kThreads / g.search_rows;
+        const bool last = blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1;
+        uint32_t own[4];  // the totals of the search workgroups of these rows
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+            own[u] = first + u < n_blocks ? ws.block_sum[first + u] : 0u;
+        uint32_t before = sum_of(ws.block_sum, 0, first);
+        uint32_t of_head = 0;
+        const bool counts = blockIdx.x == 0 && b == 0;  // uniform
+        if (counts)
+            for (int bb = 0; bb < g.B; ++bb)
+                of_head += sum_of(ws.block_sum, ((uint32_t)bb * g.H + h) * per_seg, ((uint32_t)bb * g.H + h + 1) * per_seg);
+        if (tid == 0)
+            sums[0] = sums[1] = 0;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            before += __shfl_xor(before, d, 64);
+            of_head += __shfl_xor(of_head, d, 64);
+        }
+        __syncthreads();
+        if (lane == 0) {
+            atomicAdd(&sums[0], before);
+            atomicAdd(&sums[1], of_head);
+        }
+        __syncthreads();
+        off += sums[0];
+#pragma unroll
+        for (uint32_t u = 0; u < 3; ++u)
+            off += first + u < block ? own[u] : 0u;
+        if (tid == 0) {
+            if (counts)
+                enc.n_outliers[h] = sums[1];
+            if (last) {
+                const uint32_t total = sums[0] + own[0] + own[1] + own[2] + own[3];
+                enc.n_outliers[g.H] = total;
+                enc.row_off[R - t + g.T] = total;
+                if ((uint64_t)total > outlier_capacity)
+                    atomicOr(enc.status, HQMQ_STATUS_OUTLIER_OVERFLOW);  // next to what the search may have reported
+            }
+        }
+    } else {
+        off += ws.block_pre[block];
+    }
+    if (in)
+        enc.row_off[R] = off;
+    const _Float16 *row = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st;
     uint64_t pos = off;
     while (word) {
-        const int c = __ffs((int)word) - 1;
-        word &= word - 1;
-        if (pos < outlier_capacity)
-            *reinterpret_cast<uint2 *>(enc.outliers + 4 * pos) =
-                __builtin_bit_cast(uint2, load_row_chunk<kFull>(row, c, g));
-        ++pos;
+        half4_t v[4];
+        const int n = min(__popc(word), 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u < n)
+                v[u] = load_row_chunk<kFull>(row, __ffs((int)word) - 1, g);
+            word &= word - 1;  // 0 stays 0
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < n && pos + u < outlier_capacity)
+                *reinterpret_cast<uint2 *>(enc.outliers + 4 * (pos + u)) = __builtin_bit_cast(uint2, v[u]);
+        pos += n;
     }
 }
 
@@ -1107,12 +1178,20 @@ hipError_t launch_outlier_list(const Geometry &g, const WorkspaceOffsets &wo, co
     const unsigned n = (unsigned)n_tensors;
     const uint32_t n_blocks = (uint32_t)g.B * g.H * g.n_search_blocks_per_seg;
     const uint64_t n_rows = (uint64_t)g.B * g.H * g.T;
+    const bool full = g.D == 4 * kChunksPerRow;
+    const dim3 grid((g.T + kThreads - 1) / kThreads, g.B * g.H, n);
+    if (n_blocks <= kOwnPrefixBlocks) {
+        if (full)
+            hipLaunchKernelGGL((k_gather<true, true>), grid, dim3(kThreads), 0, stream, g, wo, batch, n_blocks);
+        else
+            hipLaunchKernelGGL((k_gather<false, true>), grid, dim3(kThreads), 0, stream, g, wo, batch, n_blocks);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_scan, dim3(1, 1, n), dim3(1024), 0, stream, g, wo, batch, n_blocks, n_rows);
-    dim3 grid((g.T + kThreads - 1) / kThreads, g.B * g.H, n);
-    if (g.D == 4 * kChunksPerRow)
-        hipLaunchKernelGGL(k_gather<true>, grid, dim3(kThreads), 0, stream, g, wo, batch);
+    if (full)
+        hipLaunchKernelGGL((k_gather<true, false>), grid, dim3(kThreads), 0, stream, g, wo, batch, n_blocks);
     else
-        hipLaunchKernelGGL(k_gather<false>, grid, dim3(kThreads), 0, stream, g, wo, batch);
+        hipLaunchKernelGGL((k_gather<false, false>), grid, dim3(kThreads), 0, stream, g, wo, batch, n_blocks);
     return hipGetLastError();
 }
 

@@ -741,6 +741,15 @@ def test_outlier_overflow_reports_true_counts():
     assert exact.status == 0 and np.array_equal(exact.outliers, e.outliers)
 
 
+@pytest.mark.parametrize("B,H,T,D,Cmul", [
+    (16, 64, 65, 8, 1.2), (41, 25, 65, 8, 1.2), (1, 3, 2300, 128, 1.05), (2, 2, 4097, 45, 1.05), (1, 2, 1025, 4, 3.0),
+])
+def test_outlier_list_of_many_outliers_and_workgroups(B, H, T, D, Cmul):
+    """The outlier list with and without a scan of the search workgroups' totals before it (2048 and 2050 of them), with up to
+    32 outliers in a row, copied four at a time, and with rows left over in its last workgroup."""
+    _roundtrip(_lognormal_tensor(B, H, T, seed=T + D, sigma_g=0.8, D=D), S=1, Cmul=Cmul)
+
+
 def test_strided_input_and_output():
     """A cache stored [B, T, H, D] passes unchanged through the strides."""
     B, H, T = 2, 3, 50
