@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(1024) void k_list_small(Geometry g, WorkspaceOffset
 //   k_shard_pick   one workgroup per head: (pass > 0) locates the wanted rank in the summed histogram
 //                  of the previous pass and extends the prefix; clears the histogram of this pass;
 //                  (finish) writes the threshold fl(fl(C C) median)
-//   k_shard_hist   sweep of this shard's rows, as k_select_sweep
+//   k_shard_hist   sweep of this shard's rows
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ int shard_digit_bits(int pass) { return pass == 0 ? kBits0 : kBits1; }
 __device__ __forceinline__ int shard_digit_shift(int pass) { return pass == 0 ? kShift0 : kShift1 - 10 * (pass - 1); }
