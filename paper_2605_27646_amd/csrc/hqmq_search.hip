@@ -947,8 +947,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 // A chunk then costs the fold, a look-up of its box and 3 FMA and 5 more operations per listed codeword instead of
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32, so the outcome is the one of the exhaustive fp32 search.
-// Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 73 us, index
-// included; two tensors in a call: 1017 -> 144 us + 28 us for the index.  Bound by VALU issue (300 instructions per
+// Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 68 us + 8 us for the
+// index; two tensors in a call: 1017 -> 143 us + 27 us for the index.  Bound by VALU issue (300 instructions per
 // 64 chunks, 115 of them in the list loop: the longest of 64 lists has 3.4 groups of four on average), LDS busy
 // half of the time; 16 % of the HBM peak.
 // ---------------------------------------------------------------------------------------------------------------
