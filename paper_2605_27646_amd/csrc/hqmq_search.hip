@@ -965,7 +965,8 @@ constexpr int kCellMax = 64;           // codewords of a box before the pairwise
 constexpr float kCellBand = 2.0e-6f;
 constexpr float kCellEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
                                        // kCellBand times the ratio of two scores of a box plus the rounding of the test
-constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box number of y = 1 below n
+constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the
+                                               // cube by 5.4e-7 (fold 3.6e-7, reciprocal and product 1.8e-7), in 0 .. n - 1
 constexpr uint32_t kCellPad = 0x7fffu; // list entry without a codeword; bit 15 marks the last group of a list
 
 // The search numbers the element P_0 that it folds with by what it has at hand (fold_primary), and needs the index of
@@ -1099,7 +1100,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     const int i0 = 4 * b0 + 2 * s0 + ((cell >> 2) & 1), i1 = 4 * b1 + 2 * s1 + ((cell >> 1) & 1), i2 = 4 * b2 + 2 * s2 + (cell & 1);
     const int cell_id = (i0 * n + i1) * n + i2;
     const float hf = 1.0f / (float)n;
-    const float margin = 1.2e-5f;  // y and the box number are rounded, the latter by kCellShrink as well
+    const float margin = 1.2e-5f;  // y and the box number are rounded (7e-7), the latter shrunk by 4e-6 as well
     const float y1 = (float)(2 * i0 + 1) * hf - 1.f, y2 = (float)(2 * i1 + 1) * hf - 1.f, y3 = (float)(2 * i2 + 1) * hf - 1.f;
     const float m1 = (float)(8 * b0 + 4) * hf - 1.f, m2 = (float)(8 * b1 + 4) * hf - 1.f, m3 = (float)(8 * b2 + 4) * hf - 1.f;
     if (blockIdx.x == 0 && tid == 0)
@@ -1410,12 +1411,11 @@ __device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellT
     const float w3 = fmaf(-p3, x0, fmaf(p2, x1, fmaf(-p1, x2, p0 * x3)));
     const float inv = __builtin_amdgcn_rcpf(w0);
     const float y1 = w1 * inv, y2 = w2 * inv, y3 = w3 * inv;
-    // ---- the box.  The scale keeps y = 1 below n; the last clamp is for inputs that break the contract (a zero chunk's
-    // 0 / 0 converts to 0, a corner box without a list) ---------------------------------------------------------------------
-    const float hn = 0.5f * (float)g.cell_n * kCellShrink;
-    const float n = (float)g.cell_n;
-    const float i0 = floorf(fmaf(y1, hn, hn)), i1 = floorf(fmaf(y2, hn, hn)), i2 = floorf(fmaf(y3, hn, hn));
-    const uint32_t box = min((uint32_t)fmaf(fmaf(i0, n, i1), n, i2), (uint32_t)(g.cell_n * g.cell_n * g.cell_n) - 1u);
+    // ---- the box.  Shrunk about the centre, y stays inside the cube at either end; the last clamp is for inputs that break
+    // the contract (a zero chunk's 0 / 0 becomes 0, a corner box without a list) ----------------------------------------------
+    const float n = (float)g.cell_n, middle = 0.5f * n, hn = middle * kCellShrink;
+    const float i0 = floorf(fmaf(y1, hn, middle)), i1 = floorf(fmaf(y2, hn, middle)), i2 = floorf(fmaf(y3, hn, middle));
+    const uint32_t box = (uint32_t)__builtin_amdgcn_fmed3f(fmaf(fmaf(i0, n, i1), n, i2), 0.f, fmaf(n * n, n, -1.f));
     uint32_t group = lds_at<uint16_t>(ct.head + 2u * box);
     // ---- best and runner-up of the list ----------------------------------------------------------------------------------
     float best = 0.f, second = 0.f;

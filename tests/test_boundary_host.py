@@ -300,3 +300,22 @@ def test_division_by_the_biased_reciprocal_is_exact():
     for S in range(1, hq.HQMQ_MAX_S + 1):
         inv = np.float32(np.float32(1.0) / np.float32(S)) * np.float32(1.0 + 2.0 ** -18)
         assert np.array_equal((kf * np.float32(inv)).astype(np.uint32), k // S), S
+
+
+@pytest.mark.parametrize("n", [8, 12, 16, 20])
+def test_box_numbers_of_the_search_index_stay_in_the_grid(n):
+    """The search numbers the box of a coordinate y in [-1, 1] as floor(fma(y, hn, n / 2)), hn = fl((n / 2) (1 - 4e-6)).
+    Rounding can leave y up to 9 * 2^-24 outside the interval (three additions each in the numerator and in the denominator,
+    a reciprocal good to 2^-23, a product): the number must still be one of 0 .. n - 1, and the box, widened by the 1.2e-5
+    that its list allows for, must hold y."""
+    middle = np.float32(0.5 * n)
+    hn = np.float32(middle * np.float32(1.0 - 4.0e-6))
+    steps = np.arange(-200, 10) * 2.0 ** -24
+    edges = (2.0 * np.arange(n + 1) / n - 1.0)[:, None] + np.arange(-300, 301) * 2.0 ** -24
+    y = np.concatenate([1.0 + steps, -(1.0 + steps), edges[1:-1].reshape(-1), np.linspace(-1.0, 1.0, 100001)])
+    y = y.astype(np.float32)
+    # the product has 48 significant bits and the sum with n / 2 at most a few more: exact enough in fp64 to round once
+    box = np.floor((y.astype(np.float64) * np.float64(hn) + np.float64(middle)).astype(np.float32))
+    assert box.min() == 0 and box.max() == n - 1
+    centre = (2.0 * box.astype(np.float64) + 1.0) / n - 1.0
+    assert (np.abs(y.astype(np.float64) - centre) <= 1.0 / n + 1.2e-5).all()

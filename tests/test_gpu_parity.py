@@ -686,6 +686,42 @@ def test_box_index_search(S, D, kind):
     print(compare_encode(g, e, bits, sec), flush=True)
 
 
+@pytest.mark.parametrize("S,D", [(8, 128), (24, 128), (64, 128), (256, 128), (256, 126), (96, 50)])
+def test_box_index_at_the_corners_of_the_fold(S, D):
+    """Chunks (+-a, +-a, 0, 0) in every order fold onto a corner of the octahedron that the search's box index covers, where
+    a rounding either way must stay inside the outermost box: all 1024 fp16 significands, exactly equal magnitudes, a unit
+    of the last place apart, and with a far smaller third component, over the exponents of fp16.  Every such row is compared."""
+    n_c = (D + 3) // 4
+    rng = np.random.default_rng(7)
+    pairs = np.array([(i, j) for i in range(4) for j in range(i)])
+    m, p, sg = (v.reshape(-1) for v in np.meshgrid(np.arange(1024), np.arange(6), np.arange(4), indexing="ij"))
+    chunks = np.zeros((3, m.size, 4), np.uint16)
+    one = np.arange(m.size)
+    for kind in range(3):
+        a = ((rng.integers(2, 30, m.size) << 10) | m).astype(np.uint16)
+        b = a + np.uint16(kind == 1)
+        chunks[kind, one, pairs[p, 0]] = a | ((sg & 1) << 15).astype(np.uint16)
+        chunks[kind, one, pairs[p, 1]] = b | ((sg >> 1) << 15).astype(np.uint16)
+        if kind == 2:
+            rest = np.array([[k for k in range(4) if k not in q] for q in pairs.tolist()])  # the components outside the pair
+            third = rest[p, rng.integers(0, 2, m.size)]
+            chunks[kind, one, third] = np.maximum(a.astype(np.int32) - (13 << 10), 1).astype(np.uint16)
+    flat = chunks.reshape(-1, 4)
+    rows = -(-flat.shape[0] // n_c)
+    T = max(rows, -(-(3 << 21) // ((S + 32) * n_c))) + 7
+    x = rng.standard_normal((1, 2, T, 4 * n_c)).astype(np.float16)
+    x.reshape(2, -1, 4)[:, : flat.shape[0]] = flat.view(np.float16)
+    x = np.ascontiguousarray(x[..., :D])  # a last partial chunk keeps its first components
+    sec_t, sec = _sec(12, 2, S)
+    compared = np.zeros((2, T), bool)
+    compared[:, :rows] = True
+    bits = x.view(np.uint16)
+    e = oracle.encode(bits, sec, b_r=6, Cmul=1e9, rows=compared.reshape(-1))  # nothing is an outlier
+    assert not e.flags.any()
+    g = gpu_encode(torch.from_numpy(x).to(DEV), sec_t.to(DEV), 6, 1e9)
+    print(compare_encode(g, e, bits, sec), flush=True)
+
+
 def test_direction_component_on_a_half_precision_midpoint():
     """Regression: the matrix pass splits every direction component into two fp16 parts; both must be
     taken from the same fp32 value.  Row 630 of this tensor holds a chunk whose fourth component, scaled, is
