@@ -959,10 +959,15 @@ constexpr int kCellThreads = 256;      // workgroup of the index build: 4 lanes 
 constexpr int kCoarseCap = 1024;       // codewords of a block of 4^3 boxes
 constexpr int kMidCap = 384;           // codewords of a sub-block of 2^3 boxes
 constexpr int kCellMax = 64;           // codewords of a box before the pairwise test
-// Two codewords whose scores lie closer than this fraction of the best are not told apart by the lists' arithmetic.  The
-// error of a difference of two scores is at most 7.6e-7 |c_a - c_b| (y: fold, reciprocal) + 5e-7 (functions, 3 FMA), the
-// best is at least 0.7: below 1.6e-6 of it for codewords that can be next to one another (3.4e-7 measured on 800,000).
-constexpr float kCellBand = 2.0e-6f;
+// Two codewords whose scores lie closer than this fraction of the best are not told apart by the lists' arithmetic: more
+// than its largest possible error, so that a clear winner has the best score in exact arithmetic too.  In units of 2^-24,
+// for two unit codewords a and b that tie near the best (both within 45 degrees of the chunk: |a - b| <= sqrt(2)):
+//   y          11.2 |a - b|: a common factor of 5 (three additions in w_0, the reciprocal), 3 sqrt(3) + 1 across it
+//   functions  3 each: three additions of 1/2 per component, times 1 + |y_1| + |y_2| + |y_3| <= 2
+//   values     3 each: three FMA of at most sqrt(2)
+// 27.9 in all, of a best that is at least 1/sqrt(2): 2.35e-6 (3.4e-7 measured on 800,000 chunks).  Secondaries of other
+// norms scale both sides by the largest.
+constexpr float kCellBand = 2.5e-6f;
 constexpr float kCellEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
                                        // kCellBand times the ratio of two scores of a box plus the rounding of the test
 constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the

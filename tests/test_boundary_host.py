@@ -319,3 +319,18 @@ def test_box_numbers_of_the_search_index_stay_in_the_grid(n):
     assert box.min() == 0 and box.max() == n - 1
     centre = (2.0 * box.astype(np.float64) + 1.0) / n - 1.0
     assert (np.abs(y.astype(np.float64) - centre) <= 1.0 / n + 1.2e-5).all()
+
+
+def test_band_of_the_search_index_covers_its_rounding():
+    """A chunk whose two best scores differ by more than the band is decided by the index alone: the band must exceed the
+    largest error that the fold, the functions and their values can have (derived beside the constant), relative to the best
+    score; and the lists must keep what comes within the band."""
+    u = 2.0 ** -24
+    fold = (5.0 + (3.0 * 3.0 ** 0.5 + 1.0)) * u * 2.0 ** 0.5     # common factor and the rest, |a - b| <= sqrt(2)
+    functions = 2 * 3 * 0.5 * 2.0 * u                            # two functions, three additions below 1, 1 + sum |y| <= 2
+    values = 2 * 3 * u                                           # two functions, three FMA below 2
+    worst = (fold + functions + values) / 2.0 ** -0.5
+    source = open(os.path.join(ROOT, "paper_2605_27646_amd", "csrc", "hqmq_search.hip")).read()
+    band = float(re.search(r"kCellBand = ([0-9.e-]+)f;", source).group(1))
+    eps = float(re.search(r"kCellEps = ([0-9.e-]+)f;", source).group(1))
+    assert 2.3e-6 < worst < band < eps / 2
