@@ -153,6 +153,20 @@ static bool use_cells(const Geometry &g)
     return g.A16 > 0 && chunks * (uint64_t)(g.S + 32) >= (3ull << 21);
 }
 
+// Rows per workgroup of the matrix screen: 64, or 256 where rows are short and workgroups plenty, so that copying the
+// operands does not outweigh a workgroup's few chunks.  Search of n tensors with 8 heads, 256 / 64 rows in us: D = 4,
+// S = 16, T = 32768: 19 / 29 (n = 1), 191 / 499 (n = 32); D = 16, T = 32759: 28 / 34 (n = 1); D = 32, T = 16375: 513 / 568
+// (n = 32); but D = 16, S = 64, T = 16375 (512 workgroups): 30 / 28; D = 96, S = 16, T = 4096 (n = 1): 96 / 66, T = 2100
+// (n = 32, 2304 workgroups): 219 / 193; D = 128, T = 4087 (n = 32, 4096 workgroups): 472 / 472.
+static int screen_rows(const Geometry &g, int n)
+{
+    const int64_t blocks = (int64_t)n * g.B * g.H * ((g.T + kSearchRowsLarge - 1) / kSearchRowsLarge);
+    const int64_t enough = 192 * g.n_c > 512 ? 192 * g.n_c : 512;
+    const bool large = g.n_c < kChunksPerRow && g.search_rows == kSearchRowsLarge && blocks >= enough &&
+                       search_waves_for(g.S16, g.A16, g.D, g.row_words, kSearchRowsLarge) == 4;
+    return large ? kSearchRowsLarge : kSearchRowsSmall;
+}
+
 struct WorkspaceLayout {
     uint64_t state, thr, hist0, hist1, plan, cand_count, cand, block_sum, block_pre, aop, total;
 };
@@ -389,20 +403,19 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             const auto blocks = [&](int rows) { return (int64_t)n * g.B * g.H * ((g.T + rows - 1) / rows); };
             gs.search_rows = blocks(kSearchRowsHuge) >= 512 ? kSearchRowsHuge : blocks(kSearchRowsLarge) >= 512 ? kSearchRowsLarge : kSearchRowsSmall;
         } else {
-            gs.search_rows = kSearchRowsSmall;  // 256 at S = 16, T = 4096, one tensor with 8 heads of 96 elements: 96 us, 64: 66
+            gs.search_rows = screen_rows(g, n);
         }
         gs.n_search_blocks_per_seg = (uint32_t)((g.T + gs.search_rows - 1) / gs.search_rows);
         if (gs.search_rows < g.search_rows) {
-            // more workgroups than the arrays of their totals were sized for: the totals take the histograms' memory, which
-            // the select is done with, where they fit it (8 bytes per workgroup and 32 KiB per head)
+            // more workgroups than the arrays of their totals were sized for (256 or 512 rows each): the totals take the
+            // histograms' memory, which the select is done with (8 bytes per workgroup, 32 KiB per head).  They fit: fewer
+            // rows are taken only while a launch has under 512 workgroups of 256 rows (index), or under 3 << 21 chunks per
+            // head times S + 32 (screen).
             const uint64_t bytes = align_up((uint64_t)g.B * g.H * gs.n_search_blocks_per_seg * 4, 256);
-            if (2 * bytes <= (uint64_t)g.H * kBins0 * sizeof(uint32_t)) {
-                wos.block_sum = wo.hist0;
-                wos.block_pre = wo.hist0 + (uint32_t)bytes;
-            } else {
-                gs.search_rows = g.search_rows;
-                gs.n_search_blocks_per_seg = g.n_search_blocks_per_seg;
-            }
+            if (2 * bytes > (uint64_t)g.H * kBins0 * sizeof(uint32_t))
+                return HQMQ_ERR_UNSUPPORTED;
+            wos.block_sum = wo.hist0;
+            wos.block_pre = wo.hist0 + (uint32_t)bytes;
         }
         err = launch_select_median(gs, wo, batch, n, params->C, no_outliers || thr_given != nullptr, st);
         if (err == hipSuccess)

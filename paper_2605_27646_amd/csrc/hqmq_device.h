@@ -10,9 +10,9 @@
 namespace hqmq {
 
 constexpr int kChunksPerRow = 32;    // chunks of a row of D = 128 elements, and the most a row may have
-constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64; the search with
-constexpr int kSearchRowsLarge = 256;  // the box index takes 256 or 512 where that leaves 512 workgroups (1024 rows: no
-constexpr int kSearchRowsHuge = 512;   // faster)
+constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64; the matrix screen
+constexpr int kSearchRowsLarge = 256;  // takes 256 for many short rows, the search with the box index 256 or 512 where that
+constexpr int kSearchRowsHuge = 512;   // leaves 512 workgroups (1024 rows: no faster)
 constexpr int kSearchRowsSwitch = 2048;
 constexpr int kSearchRowsSwitchHuge = 4096;
 constexpr int kThreads = 256;        // default workgroup: 4 wave64
@@ -69,7 +69,7 @@ struct Geometry {
     int32_t cell_groups;  // list groups it may have, group 0 included
     int32_t cell_used;    // codewords its lists may name
     int32_t cell_words;   // 32-bit words of a bit per codeword
-    int32_t search_rows;               // rows per search workgroup (kSearchRowsSmall or kSearchRowsLarge)
+    int32_t search_rows;               // rows per search workgroup (kSearchRowsSmall, Large or Huge)
     uint32_t n_search_blocks_per_seg;  // ceil(T / search_rows)
 };
 
@@ -107,8 +107,8 @@ inline CellShape cell_shape_for(int S)
 static_assert(((13 * kScreenMaxS) / 5 + 99 + 1) * 16 + 5120 * 8 < 65536, "16-bit LDS addresses");
 __host__ __device__ inline size_t cell_head_bytes(int n) { return ((size_t)n * n * n * 2 + 15) / 16 * 16; }
 
-// Waves of a search workgroup of the matrix screen, which has 64 rows: 4 when two workgroups fit a CU's LDS, else one
-// workgroup of 8, which keeps two waves on every SIMD.  (The answers for more rows only size workspaces.)
+// Waves of a search workgroup of the matrix screen: 4 when two workgroups fit a CU's LDS, else one workgroup of 8, which
+// keeps two waves on every SIMD.  (16, for rows that do not leave room for four workgroups, only sizes workspaces.)
 inline int search_waves_for(int S16, int A16, int D, int row_words, int rows)
 {
     if (A16 == 0)

@@ -1717,6 +1717,7 @@ hipError_t prepare_search_kernels()
                               reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall>),
                               reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall>),
                               reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall>),
+                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsLarge>),
                               reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, false, false>),
                               reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, false, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
@@ -1804,7 +1805,10 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
     if (g.A16 > 0)
         hipLaunchKernelGGL(k_prepare_operands, dim3((g.A16 * kATiles * 64 + kThreads - 1) / kThreads, g.H, (unsigned)n_tensors),
                            dim3(kThreads), 0, stream, g, wo, batch);
-    // 64 rows per workgroup (the caller sees to it)
+    // a kernel for these rows per workgroup: 64 always, 256 for the flat form on 4 waves
+    const bool large = g.search_rows == kSearchRowsLarge;
+    if (large ? full || g.A16 == 0 || waves != 4 : g.search_rows != kSearchRowsSmall)
+        return hipErrorInvalidConfiguration;
 #define HQMQ_LAUNCH(KERNEL, W) hipLaunchKernelGGL((KERNEL<W, kSearchRowsSmall>), grid, dim3(64 * W), lds, stream, g, wo, batch)
     if (g.A16 == 0) {
         // more secondaries than the matrix-core screen holds: 64 rows on 4 waves, every chunk scored in fp32
@@ -1818,7 +1822,9 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
         else
             HQMQ_LAUNCH(k_search, 4);
     } else {
-        if (waves == 8)
+        if (large)
+            hipLaunchKernelGGL((k_search_flat<4, kSearchRowsLarge>), grid, dim3(256), lds, stream, g, wo, batch);
+        else if (waves == 8)
             HQMQ_LAUNCH(k_search_flat, 8);
         else
             HQMQ_LAUNCH(k_search_flat, 4);

@@ -786,6 +786,13 @@ def test_outlier_list_of_many_outliers_and_workgroups(B, H, T, D, Cmul):
     _roundtrip(_lognormal_tensor(B, H, T, seed=T + D, sigma_g=0.8, D=D), S=1, Cmul=Cmul)
 
 
+@pytest.mark.parametrize("B,H,T,D,S", [(1, 64, 2049, 4, 16), (1, 64, 2048, 3, 1), (2, 32, 2300, 8, 48), (1, 120, 2305, 14, 16)])
+def test_screen_of_many_short_rows(B, H, T, D, S):
+    """Rows of few chunks in many workgroups: the matrix screen with 256 rows per workgroup, whole and with rows left over,
+    decoded as well."""
+    _roundtrip(_lognormal_tensor(B, H, T, seed=T + D, sigma_g=0.8, D=D), S=S)
+
+
 def test_strided_input_and_output():
     """A cache stored [B, T, H, D] passes unchanged through the strides."""
     B, H, T = 2, 3, 50
