@@ -833,20 +833,24 @@ __global__ __launch_bounds__(1024) void k_scan(Geometry g, WorkspaceOffsets wo, 
 }
 
 // kOwnPrefix: no k_scan before it; every workgroup sums the totals of the search workgroups before its rows itself, and the
-// first of a head, and the last of all, write what else k_scan would.  Taken up to kOwnPrefixBlocks, eight loads per thread.
+// first of a head, and the last of all, write what else k_scan would.  Taken up to kOwnPrefixBlocks, eight loads per thread,
+// and while all workgroups together sum at most kOwnPrefixSums totals: own prefix / scan in us, 8 heads each: 16 tensors of
+// 32768 rows (2^23) 112 / 123, 2 of 256 batch entries of 32 rows (2^23) 11 / 34, 32 of 32768 rows of 4 elements (2^25) 43 / 29.
 // 256 rows per workgroup, a thread per row, four of its outliers in flight.  Bound by the latency of its loads: 7.5 us for
 // two [1, 8, 32768, 128] tensors (11.5 with k_scan before it and one outlier at a time), 29 instead of 39 at 5% outliers.
 // grid = (ceil(T / 256), B*H, tensors).
 constexpr uint32_t kOwnPrefixBlocks = 2048;
-// This thread's share of the sum of v[begin .. end), four requested before the first is used.
-__device__ __forceinline__ uint32_t sum_of(const uint32_t *v, uint32_t begin, uint32_t end)
+constexpr uint64_t kOwnPrefixSums = 1ull << 24;
+// This thread's share of the sum of the n totals v[at(0)], v[at(1)], ..., four requested before the first is used.
+template <typename At>
+__device__ __forceinline__ uint32_t sum_of(const uint32_t *v, uint32_t n, At at)
 {
     uint32_t sum = 0;
-    for (uint32_t i0 = begin + threadIdx.x; i0 < end; i0 += 4 * kThreads) {
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * kThreads) {
         uint32_t part[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            part[u] = i0 + u * kThreads < end ? v[i0 + u * kThreads] : 0u;
+            part[u] = i0 + u * kThreads < n ? v[at(i0 + u * kThreads)] : 0u;
         sum += part[0] + part[1] + part[2] + part[3];
     }
     return sum;
@@ -876,12 +880,14 @@ __global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffset
 #pragma unroll
         for (uint32_t u = 0; u < 4; ++u)
             own[u] = first + u < n_blocks ? ws.block_sum[first + u] : 0u;
-        uint32_t before = sum_of(ws.block_sum, 0, first);
+        uint32_t before = sum_of(ws.block_sum, first, [](uint32_t i) { return i; });
         uint32_t of_head = 0;
         const bool counts = blockIdx.x == 0 && b == 0;  // uniform
-        if (counts)
-            for (int bb = 0; bb < g.B; ++bb)
-                of_head += sum_of(ws.block_sum, ((uint32_t)bb * g.H + h) * per_seg, ((uint32_t)bb * g.H + h + 1) * per_seg);
+        if (counts)  // of all batch entries: H per_seg apart
+            of_head = sum_of(ws.block_sum, (uint32_t)g.B * per_seg, [&](uint32_t i) {
+                const uint32_t bb = i / per_seg;
+                return (bb * ((uint32_t)g.H - 1u) + (uint32_t)h) * per_seg + i;
+            });
         if (tid == 0)
             sums[0] = sums[1] = 0;
 #pragma unroll
@@ -1180,7 +1186,7 @@ hipError_t launch_outlier_list(const Geometry &g, const WorkspaceOffsets &wo, co
     const uint64_t n_rows = (uint64_t)g.B * g.H * g.T;
     const bool full = g.D == 4 * kChunksPerRow;
     const dim3 grid((g.T + kThreads - 1) / kThreads, g.B * g.H, n);
-    if (n_blocks <= kOwnPrefixBlocks) {
+    if (n_blocks <= kOwnPrefixBlocks && (uint64_t)n * grid.x * grid.y * n_blocks <= kOwnPrefixSums) {
         if (full)
             hipLaunchKernelGGL((k_gather<true, true>), grid, dim3(kThreads), 0, stream, g, wo, batch, n_blocks);
         else

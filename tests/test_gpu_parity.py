@@ -778,7 +778,7 @@ def test_outlier_overflow_reports_true_counts():
 
 
 @pytest.mark.parametrize("B,H,T,D,Cmul", [
-    (16, 64, 65, 8, 1.2), (41, 25, 65, 8, 1.2), (1, 3, 2300, 128, 1.05), (2, 2, 4097, 45, 1.05), (1, 2, 1025, 4, 3.0),
+    (16, 64, 65, 8, 1.2), (41, 25, 65, 8, 1.2), (300, 3, 9, 8, 1.2), (5, 2, 1100, 20, 1.2), (1, 3, 2300, 128, 1.05), (2, 2, 4097, 45, 1.05), (1, 2, 1025, 4, 3.0),
 ])
 def test_outlier_list_of_many_outliers_and_workgroups(B, H, T, D, Cmul):
     """The outlier list with and without a scan of the search workgroups' totals before it (2048 and 2050 of them), with up to
