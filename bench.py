@@ -192,7 +192,8 @@ def main() -> int:
     status = max(int(e.status.item()) for e in encs)
 
     import statistics
-    cells = wl.S <= 512 and chunks_per_tensor // wl.H * (wl.S + 32) >= 3 << 21  # the library's rule
+    work_per_segment = wl.T * ((wl.D + 3) // 4) * (wl.S + 32)  # the library's rule
+    cells = wl.S <= 512 and work_per_segment >= 1 << 17 and wl.B * work_per_segment >= 3 << 21
     search_kernel = "k_search_cells" if cells else "k_search" if wl.D == 128 else "k_search_flat"
     decode_kernel = "k_decode" if wl.D in (64, 96, 128) else "k_decode_rows"
     prof = profile_figures(wl.name)

@@ -147,10 +147,14 @@ static Geometry make_geometry(const hqmq_params *p)
 // encodes of 4 tensors with 8 heads of 128 elements, screen / index in us: S = 256: 92 / 90 at T = 512, 118 / 102 at
 // 1024, 355 / 199 at 4096; S = 64: 87 / 94 at 1536, 116 / 110 at 3072, 209 / 183 at 4096; S = 16: 90 / 94 at 3072,
 // 176 / 168 at 4096, 272 / 203 at 16384.  With 64 heads the two meet at the same lengths within a fifth, with 8 earlier.
+// A workgroup copies the whole index for rows of one (batch entry, head) only, so their chunks x (S + 32) have to reach 2^17:
+// search of 2 tensors with 8 heads and many batch entries, screen / index in us: S = 256: 194 / 334 at B = 1024, T = 4, 143 /
+// 190 at 512 x 8, 278 / 200 at 512 x 16; S = 64: 115 / 277 at 1024 x 8, 195 / 296 at 1024 x 16, 179 / 181 at 512 x 32, 176 /
+// 123 at 256 x 64; S = 16: 64 / 95 at 256 x 32, 62 / 68 at 128 x 64, 62 / 56 at 64 x 128.
 static bool use_cells(const Geometry &g)
 {
-    const uint64_t chunks = (uint64_t)g.B * g.T * g.n_c;
-    return g.A16 > 0 && chunks * (uint64_t)(g.S + 32) >= (3ull << 21);
+    const uint64_t work = (uint64_t)g.T * g.n_c * (uint64_t)(g.S + 32);
+    return g.A16 > 0 && work >= (1ull << 17) && g.B * work >= (3ull << 21);
 }
 
 // Rows per workgroup of the matrix screen: 64, or 256 where rows are short and workgroups plenty, so that copying the
@@ -409,8 +413,9 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
         if (gs.search_rows < g.search_rows) {
             // more workgroups than the arrays of their totals were sized for (256 or 512 rows each): the totals take the
             // histograms' memory, which the select is done with (8 bytes per workgroup, 32 KiB per head).  They fit: fewer
-            // rows are taken only while a launch has under 512 workgroups of 256 rows (index), or under 3 << 21 chunks per
-            // head times S + 32 (screen).
+            // rows are taken only while a launch has under 512 workgroups of 256 rows (index; screen of rows of one chunk),
+            // or under 3 << 21 chunks per head times S + 32 (screen of others: such workspaces start at 2048 rows, and the
+            // rows of one segment then reach the index rule's 2^17).
             const uint64_t bytes = align_up((uint64_t)g.B * g.H * gs.n_search_blocks_per_seg * 4, 256);
             if (2 * bytes > (uint64_t)g.H * kBins0 * sizeof(uint32_t))
                 return HQMQ_ERR_UNSUPPORTED;

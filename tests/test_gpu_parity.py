@@ -686,6 +686,13 @@ def test_box_index_search(S, D, kind):
     print(compare_encode(g, e, bits, sec), flush=True)
 
 
+@pytest.mark.parametrize("B,T,D,S", [(60, 42, 128, 64), (60, 43, 128, 64), (400, 16, 126, 240), (700, 3, 128, 256)])
+def test_search_of_many_batch_entries(B, T, D, S):
+    """Many short segments on either side of the line from which one of them is worth a copy of the box index: rows of a
+    segment x chunks x (S + 32) = 2^17."""
+    _roundtrip(_lognormal_tensor(B, 2, T, seed=T + S, sigma_g=0.8, D=D), S=S)
+
+
 @pytest.mark.parametrize("S,D", [(8, 128), (24, 128), (64, 128), (256, 128), (256, 126), (96, 50)])
 def test_box_index_at_the_corners_of_the_fold(S, D):
     """Chunks (+-a, +-a, 0, 0) in every order fold onto a corner of the octahedron that the search's box index covers, where
