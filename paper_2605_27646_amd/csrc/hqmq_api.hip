@@ -131,7 +131,8 @@ static Geometry make_geometry(const hqmq_params *p)
     g.check_finite = (p->flags & HQMQ_FLAG_CHECK_FINITE) ? 1 : 0;
     g.fused_by_head = 0;
     {
-        // the select of a long head keeps the keys of a narrow range around the median: about 2 % of a head's chunks
+        // the select of a long head keeps the keys of a narrow range around the median: 4.7 % of a head's chunks up to 2^19
+        // of them (6.2 % there fit), 2.6 % beyond (3.1 %)
         const uint64_t n_h = (uint64_t)p->B * p->T * g.n_c;
         const uint64_t want = (n_h / 32 + 1023) / 1024 * 1024;
         g.cand_cap = (int32_t)(want > (uint64_t)kCandCap ? want : (uint64_t)kCandCap);
@@ -172,7 +173,7 @@ static int screen_rows(const Geometry &g, int n)
 }
 
 struct WorkspaceLayout {
-    uint64_t state, thr, hist0, hist1, plan, cand_count, cand, block_sum, block_pre, aop, total;
+    uint64_t state, thr, hist0, hist1, plan, cand, block_sum, block_pre, aop, total;
 };
 
 static WorkspaceLayout workspace_layout(const Geometry &g)
@@ -190,7 +191,6 @@ static WorkspaceLayout workspace_layout(const Geometry &g)
     l.hist0 = take((uint64_t)g.H * kBins0 * sizeof(uint32_t));
     l.hist1 = take((uint64_t)g.H * kBins1 * sizeof(uint32_t));
     l.plan = take((uint64_t)g.H * sizeof(SelectPlan));
-    l.cand_count = take((uint64_t)g.H * 3 * sizeof(uint32_t));
     l.cand = take((uint64_t)g.H * g.cand_cap * sizeof(unsigned long long));
     l.block_sum = take(n_blocks * sizeof(uint32_t));
     l.block_pre = take(n_blocks * sizeof(uint32_t));
@@ -291,7 +291,6 @@ static WorkspaceOffsets workspace_offsets(const WorkspaceLayout &l)
     o.hist0 = (uint32_t)l.hist0;
     o.hist1 = (uint32_t)l.hist1;
     o.plan = (uint32_t)l.plan;
-    o.cand_count = (uint32_t)l.cand_count;
     o.cand = (uint32_t)l.cand;
     o.block_sum = (uint32_t)l.block_sum;
     o.block_pre = (uint32_t)l.block_pre;

@@ -39,10 +39,13 @@ struct SelectState {
     uint32_t pad;
 };
 
-// Per-head state of the select's sweep.
+// Per-head state of the select's sweeps.
 struct SelectPlan {
-    uint32_t below;  // keys below the predicted range
-    uint32_t pad[7];
+    uint32_t below;              // keys below the predicted range
+    uint32_t n_cand, n_done;     // where the kept keys did not answer: keys sent to the candidate list (they may exceed
+                                 // cand_cap) and workgroups done with it,
+    uint32_t pad;
+    unsigned long long least, most;  // and the smallest and largest of these keys
 };
 
 // Shape and addressing of one tensor, passed by value to every kernel.
@@ -155,8 +158,6 @@ struct Workspace {
     uint32_t *hist0;               // [H][kBins0]
     uint32_t *hist1;               // [H][kBins1]
     SelectPlan *plan;              // [H] (the predicted range and the lists' counters are in hist1's memory)
-    uint32_t *cand_count;          // [3][H] where the prediction missed: keys sent to the candidate list (they may exceed
-                                   // cand_cap) and workgroups done with it; the third row is not used
     unsigned long long *cand;      // [H][cand_cap]
     uint32_t *block_sum;           // [B*H*n_search_blocks_per_seg] outliers per search workgroup
     uint32_t *block_pre;           // same shape, exclusive prefix
@@ -177,7 +178,7 @@ struct EncodedPtrs {
 
 // Byte offsets of the workspace parts inside one tensor's slice (same for every tensor of a shape).
 struct WorkspaceOffsets {
-    uint32_t state, thr, hist0, hist1, plan, cand_count, cand, block_sum, block_pre, aop;
+    uint32_t state, thr, hist0, hist1, plan, cand, block_sum, block_pre, aop;
 };
 
 // One tensor of an encode batch and the batch itself (passed by value as kernel arguments; every
@@ -203,7 +204,6 @@ __device__ __forceinline__ Workspace carve_workspace(char *base, const Workspace
     ws.hist0 = reinterpret_cast<uint32_t *>(base + o.hist0);
     ws.hist1 = reinterpret_cast<uint32_t *>(base + o.hist1);
     ws.plan = reinterpret_cast<SelectPlan *>(base + o.plan);
-    ws.cand_count = reinterpret_cast<uint32_t *>(base + o.cand_count);
     ws.cand = reinterpret_cast<unsigned long long *>(base + o.cand);
     ws.block_sum = reinterpret_cast<uint32_t *>(base + o.block_sum);
     ws.block_pre = reinterpret_cast<uint32_t *>(base + o.block_pre);

@@ -13,10 +13,10 @@
 //   heads of at most 1024 rows   one workgroup selects from its registers (k_select_head)
 //   longer heads                 k_select_predict (a workgroup per head), k_select_count (the sweep, HBM-bound),
 //                                k_select_digit (only where the prediction missed), k_select_finish
-// For a head whose prediction missed, or whose list overflowed, k_select_digit makes a histogram of a first digit and
-// k_select_finish collects the keys of the bin that holds the median; every other head's workgroups leave at once.  The
-// first digit is made of the exponent and 6 mantissa bits (the squares of fp16 data span 83 binades, which at 64 bins each
-// fit the 8192 bins of a workgroup's LDS).
+// For a head whose prediction missed, or whose list overflowed, k_select_digit makes a histogram of 8192 equal parts of the
+// predicted range, or of a first digit of all keys, and k_select_finish collects the keys of the bin that holds the median;
+// every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
+// fp16 data span 83 binades, which at 64 bins each fit the 8192 bins of a workgroup's LDS).
 // The sequence-sharded median further down is a plain most-significant-digit radix select on the 63 value bits.
 #include "hqmq_device.h"
 
@@ -380,10 +380,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
             ws.hist0[(size_t)h * kBins0 + i] = 0;
         if (tid < kBuckets)
             bucket_counts(ws, h)[tid * kBucketPitch] = 0;
-        if (tid < 3)
-            ws.cand_count[tid * g.H + h] = 0;
         if (tid == 0)
-            ws.plan[h].below = 0;
+            ws.plan[h] = SelectPlan{0u, 0u, 0u, 0u, ~0ull, 0ull};
     }
     for (int i = tid; i < kPredictBins / 4; i += kSelectThreads)
         reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -502,10 +500,10 @@ struct Buckets {
     }
 };
 
-// Where the key of the given rank is among the kept ones: its list and its rank there.  False: not at all (it lies outside
-// the predicted range), or its list overflowed (a range of one value needs none).
+// Where the key of the given rank is among the kept ones: its list and its rank there.  False: not at all, because it lies
+// outside the predicted range, or inside but its list overflowed (a range of one value needs none).
 __device__ __forceinline__ bool find_kept(const Geometry &g, const Workspace &ws, int h, const Buckets &range, uint32_t rank,
-                                          uint32_t &bucket, uint32_t &rank_in, uint32_t &n)
+                                          uint32_t &bucket, uint32_t &rank_in, uint32_t &n, bool &inside)
 {
     const uint32_t below = ws.plan[h].below;
     const int lane = threadIdx.x & 63;  // every wave for itself: a lane per list
@@ -518,7 +516,8 @@ __device__ __forceinline__ bool find_kept(const Geometry &g, const Workspace &ws
             inc += o;
     }
     const unsigned long long past = __ballot(lane < kBuckets && rank >= below && rank - below < inc);
-    if (past == 0ull)
+    inside = past != 0ull;
+    if (!inside)
         return false;
     bucket = (uint32_t)__ffsll((long long)past) - 1u;
     n = (uint32_t)__shfl((int)mine, (int)bucket, 64);
@@ -526,17 +525,53 @@ __device__ __forceinline__ bool find_kept(const Geometry &g, const Workspace &ws
     return n <= bucket_capacity(g) || range.span == 0ull;
 }
 
+// What the histogram of a head whose kept keys do not answer is made of: equal parts of the predicted range's bit patterns
+// where the wanted key lies in it, else, and where the range starts at zero (whose pattern is far from all others), the
+// first digit of every key.
+struct SecondLook {
+    unsigned long long lo, span;
+    int shift;
+    bool linear;
+    __device__ __forceinline__ SecondLook(const Buckets &range, bool inside)
+        : lo(range.lo), span(range.span), linear(inside && range.lo != 0ull)
+    {
+        const int width = 64 - __clzll((long long)(span | 1ull));
+        shift = width > kBits0 ? width - kBits0 : 0;
+    }
+    __device__ __forceinline__ bool counts(unsigned long long key) const { return !linear || key - lo <= span; }
+    __device__ __forceinline__ uint32_t bin_of(unsigned long long key) const
+    {
+        return linear ? (uint32_t)((key - lo) >> shift) : fine_bin(key);
+    }
+    __device__ __forceinline__ uint32_t rank_of(uint32_t rank, uint32_t below) const { return linear ? rank - below : rank; }
+    // Whether the bin's keys have to be looked at; else the key is `known`.
+    __device__ __forceinline__ bool bounds(uint32_t bin, unsigned long long &first, unsigned long long &last,
+                                           unsigned long long &known) const
+    {
+        if (linear) {
+            first = lo + ((unsigned long long)bin << shift);
+            last = first + ((1ull << shift) - 1ull);
+            return true;
+        }
+        known = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; beyond finite fp16 data (not reached)
+        first = (unsigned long long)(bin + kFineBase) << kFineShift;
+        last = first | ((1ull << kFineShift) - 1ull);
+        return fine_bin_is_prefix(bin);
+    }
+};
+
 // The sweep: keys below the predicted range are counted, those in it kept, staged in LDS so that a workgroup updates each
 // list's counter once.  HBM-bound: two [1, 8, 32768, 128] tensors in 31 us, 4.4 TB/s; one of 131072 rows in 56, 4.8.
 // `rows` of one (b, h) segment per workgroup, grid = (ceil(T / rows), B * H, tensors).
-constexpr int kStageKeys = 128;  // keys a workgroup stages per list
+constexpr int kStageKeys = 512;  // keys a workgroup stages per list (2 workgroups of 64 KiB fit a compute unit)
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     __shared__ unsigned long long staged[kBuckets][kStageKeys];
-    __shared__ uint32_t n_staged[kBuckets], n_below;
+    __shared__ uint32_t n_staged[kBuckets], n_below;  // n_staged: all keys of the list, also those past the stage
+    __shared__ uint32_t n_direct[kBuckets], full[kBuckets];  // those of them that the list's counter has; the list is full
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
     const int c = threadIdx.x & 31, sub = threadIdx.x >> 5;
     const int t0 = blockIdx.x * rows, t1 = min(g.T, t0 + rows);
@@ -546,10 +581,32 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
     unsigned long long *lists = ws.cand + (size_t)h * g.cand_cap;
     uint32_t *count = bucket_counts(ws, h);
     if (threadIdx.x < kBuckets)
-        n_staged[threadIdx.x] = 0;
+        n_staged[threadIdx.x] = n_direct[threadIdx.x] = full[threadIdx.x] = 0;
     if (threadIdx.x == 0)
         n_below = 0;
     __syncthreads();
+    // Keys past the stage go straight to their list: one update of its counter for all of a wave's, and none once the list is
+    // full (a tensor that repeats a value a hundred thousand times would queue up at one counter: 28 ns each).
+    auto append = [&](uint32_t k, unsigned long long key) {
+        const int lane = threadIdx.x & 63;
+        for (unsigned long long left = __ballot(1); left;) {  // uniform over the lanes that are here
+            const int leader = __ffsll((long long)left) - 1;
+            const uint32_t k0 = (uint32_t)__shfl((int)k, leader, 64);
+            const unsigned long long same = __ballot(k == k0);
+            left &= ~same;
+            const uint32_t n = (uint32_t)__popcll(same);
+            uint32_t at = 0;
+            if (lane == leader) {
+                at = atomicAdd(&count[k0 * kBucketPitch], n);
+                atomicAdd(&n_direct[k0], n);
+                if (at + n > cap)
+                    full[k0] = 1u;
+            }
+            at = (uint32_t)__shfl((int)at, leader, 64) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            if (k == k0 && at < cap)
+                lists[k * cap + at] = key;
+        }
+    };
     uint32_t below = 0, equal = 0;
     for (int tb = t0 + sub; tb < t1; tb += 256) {
         half4_t v[8];
@@ -569,13 +626,10 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
                     ++equal;
                 } else {
                     const uint32_t k = range.of(key), pos = atomicAdd(&n_staged[k], 1u);
-                    if (pos < (uint32_t)kStageKeys) {
+                    if (pos < (uint32_t)kStageKeys)
                         staged[k][pos] = key;
-                    } else {  // more than the stage holds: straight to the list
-                        const uint32_t at = atomicAdd(&count[k * kBucketPitch], 1u);
-                        if (at < cap)
-                            lists[k * cap + at] = key;
-                    }
+                    else if (!*(volatile uint32_t *)&full[k])
+                        append(k, key);
                 }
             }
         }
@@ -596,8 +650,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
     } else {
         const uint32_t n = min(n_staged[k], (uint32_t)kStageKeys);
         uint32_t at = 0;
-        if ((threadIdx.x & 63) == 0 && n)
-            at = atomicAdd(&count[k * kBucketPitch], n);
+        if ((threadIdx.x & 63) == 0 && n)  // with those that a full list made nobody append
+            at = atomicAdd(&count[k * kBucketPitch], n_staged[k] - n_direct[k]);
         at = (uint32_t)__shfl((int)at, 0, 64);
         for (uint32_t i = threadIdx.x & 63; i < n; i += 64)
             if (at + i < cap)
@@ -608,16 +662,29 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
 }
 
 // ---------------------------------------------------------------------------------------
-// For a head whose kept keys do not answer: kParts workgroups share its rows (of all batch entries one after the other).
-// Every other head's workgroups return at once.
+// For a head whose kept keys do not answer: gridDim.x workgroups share its rows (of all batch entries one after the other).
+// Every other head's workgroups return at once, but their launch takes time too: 512 workgroups in all, at least 4 for a long
+// head and at most one per 256 rows.  (16 per head: the two launches took 42 us instead of 14 for 512 heads of 1400 rows, and
+// 287 instead of 77 where 8 heads of 131072 were missed, on half the chip.)
 // ---------------------------------------------------------------------------------------
-constexpr int kParts = 16;
-// f of the key of every chunk of the rows [first, last) of head h, a lane per chunk, 128 rows per step in flight.
-template <bool kFull, typename F>
-__device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, int h, uint32_t first, uint32_t last, F f)
+static int missed_parts(const Geometry &g, unsigned n_tensors)
+{
+    const uint64_t heads = (uint64_t)g.H * n_tensors, rows = (uint64_t)g.B * g.T;
+    uint64_t parts = (512 + heads - 1) / heads;
+    if (rows >= 8192 && parts < 4)
+        parts = 4;
+    const uint64_t most = rows / 256 < 64 ? rows / 256 : 64;  // 4 and more: these heads have over 1024 rows
+    return (int)(parts < most ? parts : most);
+}
+// f of the key of every chunk of the rows [first, last) of head h, a lane per chunk, 128 rows per step in flight; after each
+// step, then() by the whole workgroup.
+constexpr int kStepRows = 128;
+template <bool kFull, typename F, typename Then>
+__device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, int h, uint32_t first, uint32_t last, F f, Then then)
 {
     const int c = threadIdx.x & 31;
-    for (uint32_t r0 = first + (threadIdx.x >> 5); r0 < last; r0 += 128) {
+    for (uint32_t at = first; at < last; at += kStepRows) {  // uniform
+        const uint32_t r0 = at + (threadIdx.x >> 5);
         half4_t v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -630,16 +697,22 @@ __device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, i
         for (int u = 0; u < 4; ++u)
             if ((kFull || c < g.n_c) && r0 + 32u * u < last)
                 f(key_of(chunk_norm2(v[u])) & kKeyMask);
+        then();
     }
+}
+template <bool kFull, typename F>
+__device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, int h, uint32_t first, uint32_t last, F f)
+{
+    each_key<kFull>(g, x, h, first, last, f, [] {});
 }
 __device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t &first, uint32_t &last)
 {
     const uint64_t R = (uint64_t)g.B * g.T;
-    first = (uint32_t)(R * blockIdx.x / kParts);
-    last = (uint32_t)(R * (blockIdx.x + 1) / kParts);
+    first = (uint32_t)(R * blockIdx.x / gridDim.x);
+    last = (uint32_t)(R * (blockIdx.x + 1) / gridDim.x);
 }
 
-// The histogram of the first digit (fine_bin).  grid = (kParts, H, tensors).
+// The histogram.  grid = (missed_parts(), H, tensors).
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
@@ -648,13 +721,19 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     __shared__ uint32_t hist[kBins0];
     const int h = blockIdx.y;
     uint32_t bucket, rank_in, n, first, last;
-    if (find_kept(g, ws, h, Buckets(g, ws, h), (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n))
+    bool inside;
+    const Buckets range(g, ws, h);
+    if (find_kept(g, ws, h, range, (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n, inside))
         return;
+    const SecondLook look(range, inside);
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
         hist[i] = 0;
     __syncthreads();
     part_of_rows(g, first, last);
-    each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) { atomicAdd(&hist[fine_bin(key)], 1u); });
+    each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) {
+        if (look.counts(key))
+            atomicAdd(&hist[look.bin_of(key)], 1u);
+    });
     __syncthreads();
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
         if (hist[i])
@@ -663,28 +742,37 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
 
 // ---------------------------------------------------------------------------------------
 // finish: one workgroup of a head selects from the list that holds the wanted rank.  If there is none, all of the
-// head's workgroups collect the keys of the first digit's bin that holds it, and the last of them to end selects among
-// these, or, if they were too many (a coarsely quantised tensor), among the head's raw rows: slow, exact, and only for such
-// inputs.  5.5 us for 8 heads of 2^20 chunks; a head that was missed costs 90 us more.
-// Writes thr[h] = fl(fl(C*C) * median).  grid = (kParts, H, tensors).
+// head's workgroups collect the keys of the histogram's bin that holds it, and the last of them to end selects among
+// these.  If they were too many, the bin mostly holds a single value (a coarsely quantised tensor), which is the median;
+// else the last workgroup selects among the head's raw rows: slow, exact, and only for such inputs.
+// 5.5 us for 8 heads of 2^20 chunks.  A call with heads that were missed (16 heads of 2^20 chunks, 8 of 2^22): 30 and 60 us
+// more, with a list that overflowed 75 and 120, with half the keys of one value 165 and 290.
+// Writes thr[h] = fl(fl(C*C) * median).  grid = (missed_parts(), H, tensors).
 // ---------------------------------------------------------------------------------------
+constexpr int kVmcnt0 = 0x0f70;  // s_waitcnt vmcnt(0), the other counters at their largest
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
                                                                   float C)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    __shared__ uint32_t bins[kRankBins];
+    // the keys staged for the candidate list, which takes them when there are more than kStaged after a step
+    constexpr int kStaged = 4096;
+    __shared__ unsigned long long staged[kStaged + kStepRows * kChunksPerRow];
+    uint32_t *const bins = reinterpret_cast<uint32_t *>(staged);
+    static_assert(kRankBins * sizeof(uint32_t) <= sizeof(staged), "the histograms share their memory");
     __shared__ RankScratch sc;
-    __shared__ uint32_t arrived;
+    __shared__ unsigned long long least, most;
+    __shared__ uint32_t n_staged, list_at, arrived;
     const int h = blockIdx.y, tid = threadIdx.x;
     uint32_t rank = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
     unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
-    const bool selects = (blockIdx.x + blockIdx.y) % kParts == 0;  // not the same part of every head, whose workgroups one XCD gets
+    const bool selects = (blockIdx.x + blockIdx.y) % gridDim.x == 0;  // not the same part of every head, whose workgroups one XCD gets
     unsigned long long median;
     const Buckets range(g, ws, h);
     uint32_t bucket, rank_in, n;
-    if (find_kept(g, ws, h, range, rank, bucket, rank_in, n)) {  // uniform
+    bool inside;
+    if (find_kept(g, ws, h, range, rank, bucket, rank_in, n, inside)) {  // uniform
         if (!selects)
             return;
         const unsigned long long *list = cand + bucket * bucket_capacity(g);
@@ -713,40 +801,80 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
                 range.lo, range.lo + range.span, rank_in, bins, sc);
         }
     } else {
+        SelectPlan &plan = ws.plan[h];
+        const SecondLook look(range, inside);
         uint32_t bin, before;
+        unsigned long long lo, hi;
+        rank = look.rank_of(rank, plan.below);
         pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank, sc.pick, bin, before);
         rank -= before;
-        if (!fine_bin_is_prefix(bin)) {
+        if (!look.bounds(bin, lo, hi, median)) {
             if (!selects)
                 return;
-            median = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; beyond finite fp16 data (not reached)
         } else {
-            uint32_t *const n_cand = ws.cand_count + h, *const n_done = ws.cand_count + g.H + h;
-            const unsigned long long lo = (unsigned long long)(bin + kFineBase) << kFineShift;
-            const unsigned long long hi = lo | ((1ull << kFineShift) - 1ull);
+            if (tid == 0) {
+                least = ~0ull;
+                most = 0ull;
+                n_staged = 0u;
+            }
+            __syncthreads();
             uint32_t first, last;
             part_of_rows(g, first, last);
-            each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) {
-                if (fine_bin(key) == bin) {  // one update of the counter per wave
-                    const unsigned long long same = __ballot(1);
-                    const int lane = tid & 63, leader = __ffsll((long long)same) - 1;
-                    uint32_t at = 0;
-                    if (lane == leader)
-                        at = atomicAdd(n_cand, (uint32_t)__popcll(same));
-                    at = (uint32_t)__shfl((int)at, leader, 64) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-                    if (at < (uint32_t)g.cand_cap)
-                        cand[at] = key;
-                }
-            });
-            __threadfence();  // the list before the arrival
+            unsigned long long my_least = ~0ull, my_most = 0ull;
+            auto flush = [&] {  // by the whole workgroup
+                __syncthreads();
+                if (tid == 0)
+                    list_at = atomicAdd(&plan.n_cand, n_staged);
+                __syncthreads();
+                for (uint32_t i = tid; i < n_staged; i += kSelectThreads)
+                    if (list_at + i < (uint32_t)g.cand_cap)
+                        cand[list_at + i] = staged[i];
+                __syncthreads();
+                if (tid == 0)
+                    n_staged = 0u;
+                __syncthreads();
+            };
+            each_key<kFull>(
+                g, tn.x, h, first, last,
+                [&](unsigned long long key) {
+                    if (look.counts(key) && look.bin_of(key) == bin) {
+                        my_least = key < my_least ? key : my_least;
+                        my_most = key > my_most ? key : my_most;
+                        staged[atomicAdd(&n_staged, 1u)] = key;
+                    }
+                },
+                [&] {
+                    __syncthreads();
+                    if (n_staged > (uint32_t)kStaged)  // uniform: nobody adds before flush's barrier or the next
+                        flush();
+                    else
+                        __syncthreads();
+                });
+            flush();
+            if (my_least <= my_most) {
+                atomicMin(&least, my_least);
+                atomicMax(&most, my_most);
+            }
             __syncthreads();
-            if (tid == 0)
-                arrived = atomicAdd(n_done, 1u);
+            if (tid == 0 && least <= most) {
+                atomicMin(&plan.least, least);
+                atomicMax(&plan.most, most);
+            }
+            // The list and its ends before the arrival: every wave waits for its own stores, then one thread makes the whole
+            // workgroup's visible (a fence by each of the 16 waves writes the L2 back 16 times: 200 us for 512 workgroups).
+            __builtin_amdgcn_s_waitcnt(kVmcnt0);
             __syncthreads();
-            if (arrived != (uint32_t)kParts - 1u)
+            if (tid == 0) {
+                __threadfence();
+                arrived = atomicAdd(&plan.n_done, 1u);
+            }
+            __syncthreads();
+            if (arrived != gridDim.x - 1u)
                 return;
-            __threadfence();
-            n = __hip_atomic_load(n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            n = __hip_atomic_load(&plan.n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lo = __hip_atomic_load(&plan.least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            hi = __hip_atomic_load(&plan.most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (n <= (uint32_t)g.cand_cap)
                 median = select_rank(
                     [&](auto f) {
@@ -754,7 +882,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
                             f(cand[i]);
                     },
                     lo, hi, rank, bins, sc);
-            else
+            else  // at once where lo == hi
                 median = select_rank([&](auto f) { each_key<kFull>(g, tn.x, h, 0u, (uint32_t)g.B * (uint32_t)g.T, f); }, lo, hi, rank,
                                      bins, sc);
         }
@@ -1135,7 +1263,7 @@ template <bool kFull>
 static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, unsigned n, float C,
                               hipStream_t stream)
 {
-    const dim3 heads(g.H, 1, n), samples(g.H, predict_parts(g), n), parts(kParts, g.H, n), block(kSelectThreads);
+    const dim3 heads(g.H, 1, n), samples(g.H, predict_parts(g), n), block(kSelectThreads);
     const uint64_t head_rows = (uint64_t)g.B * g.T;
     if (head_rows <= 256) {
         hipLaunchKernelGGL((k_select_head<8, kFull>), heads, block, 0, stream, g, wo, batch, C);
@@ -1145,6 +1273,7 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
         hipLaunchKernelGGL((k_select_head<32, kFull>), heads, block, 0, stream, g, wo, batch, C);
         return;
     }
+    const dim3 parts(missed_parts(g, n), g.H, n);
     hipLaunchKernelGGL(k_select_predict<kFull>, samples, block, 0, stream, g, wo, batch);
     int rows = kSelectRows;  // down to the 256 of one step while two workgroups per compute unit are not there
     while (rows > 256 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 512)
