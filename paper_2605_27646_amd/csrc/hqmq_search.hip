@@ -1456,13 +1456,30 @@ __device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellT
     const uint32_t fold = axis ? 2u * slot + ((signs >> slot) & 1u) : 8u + signs;
     uint32_t p = lds_at<uint8_t>(ct.mul + 32u * fold + (id >> 16));
     uint32_t s = id & 0xffffu;
-    // ---- the others, one at a time, over all secondaries in fp32 (as in search_codeword) ---------------------------------
+    // ---- the others over all secondaries in fp32 (as in search_codeword), one at a time (75 + 0.42 S instructions each) or,
+    // where they are many (secondaries that repeat, lists that do not fit), every lane its own (26 S): two tensors with 8 heads
+    // of 16384 rows in us, one at a time / every lane / matrix screen of short tensors: 16 secondaries twice 8 1033 / 154 / 117,
+    // 64 within a cap of 0.05 712 / 343 / 205, 256 803 / 883 / 521, 256 twice 128 2312 / 1180 / 2666, 512 within 0.3 2440 / 1540
+    // / 877 (a screen in this place, or behind it for what it leaves over, costs every other call 1 to 5 % or 4 us) ------------
     const bool unclear = live && !clear;
     unsigned long long todo = __ballot(unclear);
     if (todo) {
         const float *secl = lds_ptr<float>(ct.sec);
         const Direction u = unit_direction(xv, r2, r_f);
         const float u0 = opaque(u.u0), u1 = opaque(u.u1), u2 = opaque(u.u2), u3 = opaque(u.u3);
+        if (__builtin_expect_with_probability(__popcll(todo) > min(4 + g.S / 10, 30), false, 0.9999)) {
+            todo = 0ull;
+            float most = -1.f;
+            uint32_t first = 0;
+#pragma unroll 1
+            for (int j = 0; j < g.S; ++j) {
+                float v0, v1, v2, v3;
+                const float sc = score_secondary(secl + 4 * j, u0, u1, u2, u3, v0, v1, v2, v3);
+                first = sc > most ? (uint32_t)j : first;
+                most = fmaxf(most, sc);
+            }
+            s = unclear ? first : s;
+        }
         while (todo) {  // wave-uniform
             const int src = __ffsll((long long)todo) - 1;
             todo &= todo - 1ull;

@@ -647,7 +647,8 @@ def _encode_ms(x, sec):
 @pytest.mark.parametrize("kind", ["zeros", "two", "grid"])
 def test_time_of_repeating_norms(kind):
     """What the select does with values that its lists cannot hold costs two more sweeps, not an order of magnitude: at most
-    six times the encode of Gaussian data (1.3 to 2 measured; 58 and 72 times with one update of a list per key of zeros and of two values)."""
+    six times the encode of Gaussian data (1.3 to 2 measured; 58 and 72 with one update of a list per key of zeros and of
+    two values)."""
     B, H, T, D, S = 1, 8, 32768, 128, 16
     gen = torch.Generator().manual_seed(1)
     sec = _sec(4, H, S)[0].to(DEV)
@@ -752,6 +753,35 @@ def test_box_index_search(S, D, kind):
     e = oracle.encode(bits, sec, b_r=6, Cmul=3.0, rows=rows)
     g = gpu_encode(torch.from_numpy(x).to(DEV), torch.from_numpy(sec).to(DEV), 6, 3.0)
     print(compare_encode(g, e, bits, sec), flush=True)
+
+
+@pytest.mark.parametrize("S,D,kind", [(16, 128, "twice"), (70, 96, "equal"), (64, 20, "twice"), (512, 126, "cap")])
+def test_box_index_of_codebooks_that_tie_or_overflow(S, D, kind):
+    """Codebooks that leave most chunks of a wave to the search over all secondaries, where every lane scores its own: the
+    lowest of equal secondaries, some 3000 rows compared."""
+    H = 2
+    T = -(-(3 << 21) // ((S + 32) * ((D + 3) // 4))) + 9
+    x = np.random.default_rng(S).standard_normal((1, H, T, D)).astype(np.float16)
+    sec = _index_codebook(kind, S, H)
+    bits = x.view(np.uint16)
+    rows = np.arange(0, H * T, max(1, H * T // 3000))
+    e = oracle.encode(bits, sec, b_r=6, Cmul=3.0, rows=rows)
+    g = gpu_encode(torch.from_numpy(x).to(DEV), torch.from_numpy(sec).to(DEV), 6, 3.0)
+    stats = compare_encode(g, e, bits, sec)
+    print(stats, flush=True)
+    if kind != "cap":
+        assert stats["index_mismatch_in_near_ties"] == 0
+
+
+def test_time_of_repeating_secondaries():
+    """Every chunk ties: at most six times the encode with a random codebook (2.8 measured, 7.7 with the chunks searched one at
+    a time)."""
+    H, T, S = 8, 16384, 64
+    x = torch.randn(1, H, T, 128, generator=torch.Generator().manual_seed(2)).half().to(DEV)
+    plain = _encode_ms(x, _sec(5, H, S)[0].to(DEV))
+    twice = _encode_ms(x, torch.from_numpy(_index_codebook("twice", S, H)).to(DEV))
+    print(f"twice: {1e3 * twice:.0f} us, random {1e3 * plain:.0f} us", flush=True)
+    assert twice < 6.0 * plain
 
 
 @pytest.mark.parametrize("B,T,D,S", [(60, 42, 128, 64), (60, 43, 128, 64), (400, 16, 126, 240), (700, 3, 128, 256)])
