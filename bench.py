@@ -121,7 +121,11 @@ def main() -> int:
 
     elems_per_step = wl.elems_per_tensor * n_t
     chunks_per_tensor = wl.B * wl.H * wl.T * ((wl.D + 3) // 4)
-    select_reads = 1.0 + 1.0 / 16.0 if chunks_per_tensor // wl.H >= 2 ** 17 else 2.0
+    # the select reads every chunk once; of heads of more than 1024 rows it reads a sample before that, 8192 chunks (four
+    # times as many beyond 2^19 chunks)
+    chunks_per_head = chunks_per_tensor // wl.H
+    sampled = 0 if wl.B * wl.T <= 1024 else 8192 * (1 if chunks_per_head <= 1 << 19 else 4)
+    select_reads = 1.0 + min(1.0, sampled / chunks_per_head)
 
     def new_events(n):
         evs = [torch.cuda.Event(enable_timing=True) for _ in range(n)]
@@ -242,7 +246,6 @@ def main() -> int:
         "encode_phase_ms_per_tensor": {"median_select": t_sel / launches / tensors_per_enc_launch,
                                        "search_quantise_pack": search_ms / tensors_per_enc_launch,
                                        "outlier_scan_gather": t_list / launches / tensors_per_enc_launch},
-        # the select reads every row once and every 16th row before that (heads of at least 2^17 chunks), else twice
         "median_select_reads": select_reads,
         "median_select_GBs": select_reads * 8.0 * chunks_per_tensor * tensors_per_enc_launch / (t_sel / launches * 1e-3) / 1e9,
         "codeword_scores_per_s": 24.0 * wl.S * chunks_per_tensor * tensors_per_enc_launch / (search_ms * 1e-3),
