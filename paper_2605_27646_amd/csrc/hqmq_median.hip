@@ -892,11 +892,11 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
 }
 
 // ---------------------------------------------------------------------------------------
-// outlier bookkeeping after the search kernel has written the flag words, the per-row offsets
-// local to its 64-row workgroup and the workgroup totals:
-//   k_scan    exclusive scan of the workgroup totals (linear row order), per-head totals, status
-//   k_gather  adds the workgroup prefix to every row offset and copies the flagged chunks into
-//             the outlier list in ascending linear chunk order
+// outlier bookkeeping after the search kernel has written the flag words, the per-row offsets local to its workgroup (of
+// search_rows rows) and the workgroup totals:
+//   k_gather  adds the totals of the workgroups before a row's to its offset and copies the flagged chunks into the outlier
+//             list in ascending linear chunk order; per-head totals, grand total and status on the way
+//   k_scan    before it where workgroups are many: exclusive scan of the totals (linear row order), per-head totals, status
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_scan(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
                                                uint32_t n_blocks, uint64_t n_rows)

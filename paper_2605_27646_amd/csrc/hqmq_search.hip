@@ -27,7 +27,7 @@
 // winning group is not ahead of every other group by 6e-6 of its score is searched again over all S secondaries with
 // plain fp32 arithmetic.  Either way the choice between secondaries is made on fp32 closed-form scores.
 //
-// Work split: a workgroup (4 or 8 wave64) owns 64 rows of one (b, h) segment, so the A
+// Work split: a workgroup (4 or 8 wave64) owns 64 rows of one (b, h) segment (256 where rows are short and many), so the A
 // matrices of the head sit in LDS once per workgroup.  A wave takes 64 chunks, one per lane, at a
 // time and runs them as two 32-chunk MFMA column groups: two whole rows of 128 elements in
 // k_search, 64 consecutive chunks of the workgroup's flattened rows in k_search_flat (any other
@@ -946,11 +946,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 // the norms of the secondaries.  About 6 of the 24 S codewords stay (S = 256, n = 20).
 // A chunk then costs the fold, a look-up of its box and 3 FMA and 5 more operations per listed codeword instead of
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
-// is searched again over all S secondaries in fp32, so the outcome is the one of the exhaustive fp32 search.
+// is searched again over all S secondaries in fp32.  Either way the codeword is the best one, or the fp32 search's choice
+// between codewords whose scores differ by no more than its own rounding.
 // Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 68 us + 8 us for the
 // index; two tensors in a call: 1017 -> 143 us + 27 us for the index.  Bound by VALU issue (300 instructions per
 // 64 chunks, 115 of them in the list loop: the longest of 64 lists has 3.4 groups of four on average), LDS busy
 // half of the time; 16 % of the HBM peak.
+// What a codebook costs whose lists do not fit (secondaries close together or equal) stands at the fall-back in cell_codeword.
 // ---------------------------------------------------------------------------------------------------------------
 
 namespace {

@@ -425,8 +425,8 @@ def test_all_zero_and_constant_tensors():
 
 
 def test_median_with_many_equal_norms():
-    """More equal chunk norms than the select kernel's candidate list holds (16384 per head):
-    the exact median must still come out (slow path that re-reads the head's rows)."""
+    """Heads of one value (the select's predicted range is that value: no list is needed) and of two, half each, with a few
+    others: the exact median."""
     x = torch.ones(1, 2, 1100, 128, dtype=torch.float16)             # 35200 chunks of norm 2 per head
     x[0, 0, :300] = 3.0                                               # head 0: 9600 larger ...
     x[0, 0, 300:320, :64] = 40.0                                      # ... and a few outliers
@@ -438,10 +438,9 @@ def test_median_with_many_equal_norms():
 
 @pytest.mark.parametrize("spread", [0.004, 0.03, 0.2])
 def test_median_of_concentrated_norms(spread):
-    """Norms packed into a narrow band: the bin of the select's first digit that holds the median then
-    holds from a few per cent to most of a head's chunks, more than a workgroup stages (0.03) and more
-    than the candidate list keeps (0.004: the third sweep has to narrow it down).  Thresholds bit for
-    bit, and with them every flag word."""
+    """Norms packed into a narrow band: from a few per cent to most of a head's chunks share the exponent and the first
+    mantissa bits of the median, so that the select's sample has to be cut finer than one digit to predict a range.
+    Thresholds bit for bit, and with them every flag word."""
     B, H, T, S = 1, 2, 4096, 1
     gen = torch.Generator().manual_seed(int(spread * 1e4))
     mag = 1.0 + spread * (2.0 * torch.rand(B, H, T, 128, generator=gen) - 1.0)
@@ -467,11 +466,9 @@ def test_median_of_concentrated_norms(spread):
 
 
 def test_sampled_select_and_its_fallbacks():
-    """Heads of at least 2^17 chunks: the select predicts the median's bin from every 16th row.  One head
-    whose sample is representative, one whose sampled rows are eight times smaller than the rest (the
-    prediction misses and the bin is collected by a sweep of its own), one of equal norms (every list
-    overflows: the slow exact path), one of zeros, and one whose sampled rows alone are zero.
-    Thresholds bit for bit."""
+    """Heads of 2^18 chunks: ordinary rows, rows with a period of 16 of which one is eight times smaller or zero (the select
+    samples rows at an odd stride; test_select_rows_and_predictions changes the very rows that it does sample), equal norms
+    and zeros.  Thresholds bit for bit."""
     B, H, T, S = 1, 5, 8192, 1
     gen = torch.Generator().manual_seed(77)
     x = torch.randn(B, H, T, 128, generator=gen) * torch.exp(0.5 * torch.randn(B, H, T, 1, generator=gen))
@@ -503,8 +500,8 @@ def test_sampled_select_and_its_fallbacks():
     ("coarse values", 64, 2, 2, 7000),
 ])
 def test_sampled_select_row_structures(kind, D, B, H, T):
-    """Heads of 2^17 chunks and more whose rows are not drawn from one distribution, in ways that mislead the
-    every-16th-row sample or overflow the candidate list: thresholds bit for bit, encode on sampled rows."""
+    """Heads of 2^17 chunks and more whose rows are not drawn from one distribution: a ramp, a period of 16, a narrow band,
+    zeros, coarse values: thresholds bit for bit, encode on some rows."""
     gen = torch.Generator().manual_seed(len(kind) * 1000 + T)
     x = torch.randn(B, H, T, D, generator=gen) * torch.exp(0.6 * torch.randn(B, H, T, 1, generator=gen))
     t = torch.arange(T).view(1, 1, T, 1)
@@ -918,7 +915,7 @@ def test_strided_input_and_output():
 
 @pytest.mark.parametrize("D", [128, 96])
 def test_strided_input_long_enough_for_the_sampled_select(D):
-    """[B, T, H, D] memory order with heads of more than 2^17 chunks (the select reads every 16th row first)
+    """[B, T, H, D] memory order with heads of more than 2^17 chunks (the select samples pieces of rows first)
     and a pitch above D: thresholds bit for bit, encode on sampled rows."""
     B, H, T, S = 2, 2, 3000 if D == 128 else 4000, 8
     x = _lognormal_tensor(B, H, T, seed=31, D=D)
