@@ -662,7 +662,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
 }
 
 // ---------------------------------------------------------------------------------------
-// For a head whose kept keys do not answer: gridDim.x workgroups share its rows (of all batch entries one after the other).
+// For a head whose kept keys do not answer: gridDim.z workgroups share its rows (of all batch entries one after the other).
 // Every other head's workgroups return at once, but their launch takes time too: 512 workgroups in all, at least 4 for a long
 // head and at most one per 256 rows.  (16 per head: the two launches took 42 us instead of 14 for 512 heads of 1400 rows, and
 // 287 instead of 77 where 8 heads of 131072 were missed, on half the chip.)
@@ -705,21 +705,28 @@ __device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, i
 {
     each_key<kFull>(g, x, h, first, last, f, [] {});
 }
+// The head of a workgroup.  Workgroups go to the eight XCDs in turn and there to the 32 compute units in turn: the next head
+// for the next part, and one more after every 256 workgroups, so that neither the first parts of all heads nor the parts of
+// one head share an XCD or a compute unit (64 parts of one head: 187 us for the call's select on half the compute units, 140).
+__device__ __forceinline__ int missed_head(const Geometry &g)
+{
+    return (int)((blockIdx.x + blockIdx.z + gridDim.x * gridDim.y * blockIdx.z / 256u) % (uint32_t)g.H);
+}
 __device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t &first, uint32_t &last)
 {
     const uint64_t R = (uint64_t)g.B * g.T;
-    first = (uint32_t)(R * blockIdx.x / gridDim.x);
-    last = (uint32_t)(R * (blockIdx.x + 1) / gridDim.x);
+    first = (uint32_t)(R * blockIdx.z / gridDim.z);
+    last = (uint32_t)(R * (blockIdx.z + 1) / gridDim.z);
 }
 
-// The histogram.  grid = (missed_parts(), H, tensors).
+// The histogram.  grid = (H, tensors, missed_parts()).
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
-    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const EncodeTensor &tn = batch.t[blockIdx.y];
     const Workspace ws = carve_workspace(tn.ws, wo);
     __shared__ uint32_t hist[kBins0];
-    const int h = blockIdx.y;
+    const int h = missed_head(g);
     uint32_t bucket, rank_in, n, first, last;
     bool inside;
     const Buckets range(g, ws, h);
@@ -747,14 +754,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
 // else the last workgroup selects among the head's raw rows: slow, exact, and only for such inputs.
 // 5.5 us for 8 heads of 2^20 chunks.  A call with heads that were missed (16 heads of 2^20 chunks, 8 of 2^22): 30 and 60 us
 // more, with a list that overflowed 75 and 120, with half the keys of one value 165 and 290.
-// Writes thr[h] = fl(fl(C*C) * median).  grid = (missed_parts(), H, tensors).
+// Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, missed_parts()).
 // ---------------------------------------------------------------------------------------
 constexpr int kVmcnt0 = 0x0f70;  // s_waitcnt vmcnt(0), the other counters at their largest
 template <bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
                                                                   float C)
 {
-    const EncodeTensor &tn = batch.t[blockIdx.z];
+    const EncodeTensor &tn = batch.t[blockIdx.y];
     const Workspace ws = carve_workspace(tn.ws, wo);
     // the keys staged for the candidate list, which takes them when there are more than kStaged after a step
     constexpr int kStaged = 4096;
@@ -764,10 +771,10 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
     __shared__ RankScratch sc;
     __shared__ unsigned long long least, most;
     __shared__ uint32_t n_staged, list_at, arrived;
-    const int h = blockIdx.y, tid = threadIdx.x;
+    const int h = missed_head(g), tid = threadIdx.x;
     uint32_t rank = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
     unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
-    const bool selects = (blockIdx.x + blockIdx.y) % gridDim.x == 0;  // not the same part of every head, whose workgroups one XCD gets
+    const bool selects = blockIdx.z == 0;  // the workgroups that start first
     unsigned long long median;
     const Buckets range(g, ws, h);
     uint32_t bucket, rank_in, n;
@@ -869,7 +876,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
                 arrived = atomicAdd(&plan.n_done, 1u);
             }
             __syncthreads();
-            if (arrived != gridDim.x - 1u)
+            if (arrived != gridDim.z - 1u)
                 return;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             n = __hip_atomic_load(&plan.n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1273,7 +1280,7 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
         hipLaunchKernelGGL((k_select_head<32, kFull>), heads, block, 0, stream, g, wo, batch, C);
         return;
     }
-    const dim3 parts(missed_parts(g, n), g.H, n);
+    const dim3 parts(g.H, n, missed_parts(g, n));
     hipLaunchKernelGGL(k_select_predict<kFull>, samples, block, 0, stream, g, wo, batch);
     int rows = kSelectRows;  // down to the 256 of one step while two workgroups per compute unit are not there
     while (rows > 256 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 512)
