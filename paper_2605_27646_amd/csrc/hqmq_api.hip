@@ -131,11 +131,13 @@ static Geometry make_geometry(const hqmq_params *p)
     g.check_finite = (p->flags & HQMQ_FLAG_CHECK_FINITE) ? 1 : 0;
     g.fused_by_head = 0;
     {
-        // the select of a long head keeps the keys of a narrow range around the median: 4.7 % of a head's chunks up to 2^19
-        // of them (6.2 % there fit), 2.6 % beyond (3.1 %)
+        // the select of a long head keeps the keys of a narrow range around the median: 4.7 % of a head's chunks up to 2^18
+        // of them, 2.6 % up to 2^19, 1.85 % beyond; with the box index behind them there is room for twice, 1.9 and 1.3
+        // times as many at least
         const uint64_t n_h = (uint64_t)p->B * p->T * g.n_c;
         const uint64_t want = (n_h / 32 + 1023) / 1024 * 1024;
         g.cand_cap = (int32_t)(want > (uint64_t)kCandCap ? want : (uint64_t)kCandCap);
+        g.cand_room = g.cand_cap;
     }
     g.cell_n = g.cell_groups = g.cell_used = g.cell_words = 0;
     g.search_rows = search_rows_for(p->T, g.S16, g.A16, g.D, g.row_words);
@@ -402,6 +404,7 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             gs.cell_groups = c.groups;
             gs.cell_used = c.used;
             gs.cell_words = (24 * g.S + 31) / 32;
+            gs.cand_room = g.cand_cap - cell_index_keys(c);
             // the most rows per workgroup (its copy of the index is made once) that leave 512 workgroups
             const auto blocks = [&](int rows) { return (int64_t)n * g.B * g.H * ((g.T + rows - 1) / rows); };
             gs.search_rows = blocks(kSearchRowsHuge) >= 512 ? kSearchRowsHuge : blocks(kSearchRowsLarge) >= 512 ? kSearchRowsLarge : kSearchRowsSmall;
@@ -421,12 +424,13 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             wos.block_sum = wo.hist0;
             wos.block_pre = wo.hist0 + (uint32_t)bytes;
         }
-        err = launch_select_median(gs, wo, batch, n, params->C, no_outliers || thr_given != nullptr, st);
+        const bool skip_select = no_outliers || thr_given != nullptr;
+        err = launch_select_median(gs, wo, batch, n, params->C, skip_select, st);
         if (err == hipSuccess)
             err = mark(1);
         if (err != hipSuccess)
             return hip_failed(err);
-        err = launch_search(gs, wos, batch, n, st);
+        err = launch_search(gs, wos, batch, n, cells_beside_select(gs, skip_select), st);
         if (err == hipSuccess)
             err = mark(2);
         if (err != hipSuccess)

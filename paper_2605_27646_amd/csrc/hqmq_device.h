@@ -66,7 +66,8 @@ struct Geometry {
     int32_t log2_S;       // log2(S) when S is a power of two, else -1
     float inv_S;          // (1/S)(1 + 2^-18): uint(float(k) * inv_S) == k / S for every k < 2^16, S <= 2730
     int32_t check_finite;  // HQMQ_FLAG_CHECK_FINITE: the search reports chunks holding an infinity or a NaN in the status word
-    int32_t cand_cap;     // candidate keys kept per head: kCandCap, or 1/32 of the head's chunks if that is more
+    int32_t cand_cap;     // candidate keys per head: kCandCap, or 1/32 of the head's chunks if that is more
+    int32_t cand_room;    // of these, what the select may use: the search's box index lies behind them
     int32_t fused_by_head;  // fused search only: one workgroup per head takes the rows of all batch entries (B T <= 64)
     int32_t cell_n;       // boxes per axis of the search's index (0: no index, see hqmq_search.hip)
     int32_t cell_groups;  // list groups it may have, group 0 included
@@ -109,6 +110,8 @@ inline CellShape cell_shape_for(int S)
 // functions and lists lie in the first 64 KiB of LDS: their addresses fit 16 bits
 static_assert(((13 * kScreenMaxS) / 5 + 99 + 1) * 16 + 5120 * 8 < 65536, "16-bit LDS addresses");
 __host__ __device__ inline size_t cell_head_bytes(int n) { return ((size_t)n * n * n * 2 + 15) / 16 * 16; }
+// A head's index in candidate keys: at most 7120 (S = 512) of 32768 and more.
+inline int cell_index_keys(const CellShape &c) { return (int)((cell_head_bytes(c.n) + 15) / 16 * 2) + c.groups; }
 
 // Waves of a search workgroup of the matrix screen: 4 when two workgroups fit a CU's LDS, else one workgroup of 8, which
 // keeps two waves on every SIMD.  (16, for rows that do not leave room for four workgroups, only sizes workspaces.)
@@ -162,7 +165,7 @@ struct Workspace {
     uint32_t *block_sum;           // [B*H*n_search_blocks_per_seg] outliers per search workgroup
     uint32_t *block_pre;           // same shape, exclusive prefix
     uint32_t *cell_state;          // [H][1 + cell_words] counter and used bits of the search's box index; the boxes and
-                                   // lists themselves take the candidate list's memory, which the select is done with
+                                   // lists themselves take the end of the candidate list's memory (cand_room)
     uint4 *aop;                    // [H][kATiles * S16][64] MFMA A operands of the search, built once per call
 };
 
@@ -332,11 +335,18 @@ __device__ __forceinline__ unsigned long long key_of(double r2)
 // Launchers implemented in the kernel translation units (host side).
 hipError_t launch_select_median(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                                 float C, bool skip_select, hipStream_t stream);
+// Heads of at most this many rows are selected by one workgroup; longer ones take a sweep, which builds the box index on
+// the side where the search has one.
+constexpr int kHeadRows = 1024;
+inline bool cells_beside_select(const Geometry &g, bool skip_select)
+{
+    return !skip_select && g.cell_n > 0 && (uint64_t)g.B * g.T > (uint64_t)kHeadRows;
+}
 hipError_t launch_shard_median_pass(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int pass,
                                     unsigned long long total_per_head, float C, hipStream_t stream);
 hipError_t prepare_search_kernels();  // once per device, before the first launch_search on it
 hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
-                         hipStream_t stream);
+                         bool cells_built, hipStream_t stream);
 bool search_fused_available(const Geometry &g);  // launch_search_fused has a kernel for this shape
 hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                                hipStream_t stream);

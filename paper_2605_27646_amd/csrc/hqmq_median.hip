@@ -18,7 +18,7 @@
 // every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
 // fp16 data span 83 binades, which at 64 bins each fit the 8192 bins of a workgroup's LDS).
 // The sequence-sharded median further down is a plain most-significant-digit radix select on the 63 value bits.
-#include "hqmq_device.h"
+#include "hqmq_cells.h"
 
 namespace hqmq {
 
@@ -252,7 +252,6 @@ __device__ __forceinline__ double threshold_of(unsigned long long median_bits, f
 // the sweeps over several workgroups, their histograms in memory, took 40 in five launches.
 // grid = (H, 1, tensors), 1024 threads.
 // ---------------------------------------------------------------------------------------
-constexpr int kHeadRows = 1024;
 template <int kSteps, bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, float C)
 {
@@ -312,8 +311,9 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
 }
 
 // ---------------------------------------------------------------------------------------
-// Longer heads, prediction (and reset): one workgroup per head or, beyond 2^19 chunks, four, bound by their compute
-// unit's instructions and latency (8 us with 8 chunks per thread, 18 with 32: hence four).
+// Longer heads, prediction (and reset): one workgroup per head, beyond 2^18 chunks four and beyond 2^19 eight, bound by their
+// compute unit's instructions and latency (8 us with 8 chunks per thread, 18 with 32: hence several).  The narrower range of
+// more parts leaves the end of the candidate list to the box index.
 // A workgroup's sample: pieces of 8 chunks (64 bytes) of 128 rows per step, so that chunks of one row, which are alike
 // where the rows differ in scale, are few among it; every row's piece follows the one before, turned once more per round,
 // at an odd stride of rows, so that structures of a power-of-two period in either direction do not alias with the sample.
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
 // 16000 heads of independent chunks.
 // In fp32, which only a prediction may be: exponent and 8 mantissa bits (a bin holds about 0.2% of smooth data), the range
 // widened by the rounding of the sum; 10 bits more where those two bins hold more than 1/64 of the sample.
-// A head in one part keeps 4.7% of smooth data, its lists hold at least 6.2%; in four parts 2.6% and 3.1%.
+// A head in one part keeps 4.7% of smooth data, in four 2.6%, in eight 1.85%; the lists hold at least 9.7, 4.8 and 2.4%.
 // grid = (H, parts, tensors).
 // ---------------------------------------------------------------------------------------
 constexpr int kPredictBits = 8, kPredictShift = 23 - kPredictBits;
@@ -330,9 +330,11 @@ constexpr uint32_t kPredictBase = (79u << kPredictBits) - 1u;  // fp32 exponents
 constexpr int kPredictBins = 84 << kPredictBits;
 constexpr int kBuckets = 16;
 constexpr int kBucketPitch = kBins1 / kBuckets;  // words between the counters: atomics to one line wait for each other
+constexpr int kMaxParts = 8;
 __host__ __device__ __forceinline__ int predict_parts(const Geometry &g)
 {
-    return (uint64_t)g.B * g.T * g.n_c <= 1u << 19 ? 1 : 4;
+    const uint64_t n_h = (uint64_t)g.B * g.T * g.n_c;
+    return n_h <= 1u << 18 ? 1 : n_h <= 1u << 19 ? 4 : kMaxParts;
 }
 __device__ __forceinline__ uint32_t *bucket_counts(const Workspace &ws, int h) { return ws.hist1 + (size_t)h * kBins1; }
 __device__ __forceinline__ float2 *predicted_ends(const Workspace &ws, int h)  // between the first two counters
@@ -356,16 +358,16 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
     {
         const uint32_t samples = kPieceRows * kSteps * parts, stride = (R + samples - 1) / samples | 1u;
         const uint32_t pieces = (uint32_t)(g.n_c + kPieceChunks - 1) / kPieceChunks;
-        uint32_t i = tid / kPieceChunks * parts + part, r = i * stride, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
+        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {
-            const uint32_t round = i / pieces, c = (i + round) % pieces * kPieceChunks + tid % kPieceChunks;
+            const uint32_t c = (j + part + j / pieces) % pieces * kPieceChunks + tid % kPieceChunks;
             v[u] = half4_t{0, 0, 0, 0};
             if (r < R && c < (uint32_t)g.n_c) {
                 v[u] = load_row_chunk<kFull>(tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, (int)c, g);
                 loaded |= 1u << u;
             }
-            i += kPieceRows * parts;
+            j += kPieceRows;
             r += kPieceRows * parts * stride;
             t += kPieceRows * parts * stride;
             while (t >= (uint32_t)g.T && r < R) {
@@ -472,19 +474,23 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
 
 // The kept keys' lists: 16 equal parts of the range of values (of bit patterns, the parts above a power of two would hold
 // twice what those below it do).
-__device__ __forceinline__ uint32_t bucket_capacity(const Geometry &g) { return (uint32_t)g.cand_cap / kBuckets; }
+__device__ __forceinline__ uint32_t bucket_capacity(const Geometry &g) { return (uint32_t)g.cand_room / kBuckets; }
 struct Buckets {
     unsigned long long lo, span;  // keys
     float scale;
     __device__ __forceinline__ Buckets(const Geometry &g, const Workspace &ws, int h)
     {
-        const float2 *parts = predicted_ends(ws, h);
-        const int n = predict_parts(g);
-        float first = 0.0f, last = 0.0f;
-        for (int i = 0; i < n; ++i) {
-            first += parts[i].x;
-            last += parts[i].y;
+        // sums over the parts in pairs, so that equal ends sum up exactly
+        const int n = predict_parts(g), lane = threadIdx.x & 63;
+        const float2 own = lane < n ? predicted_ends(ws, h)[lane] : make_float2(0.0f, 0.0f);
+        float first = own.x, last = own.y;
+#pragma unroll
+        for (int d = 1; d < kMaxParts; d <<= 1) {
+            first += __shfl_xor(first, d, 64);
+            last += __shfl_xor(last, d, 64);
         }
+        first = __shfl(first, 0, 64);
+        last = __shfl(last, 0, 64);
         // exact, if the parts agree on a single value; else their ends are 4 units of the last place wide
         first *= 1.0f / (float)n;
         last *= 1.0f / (float)n;
@@ -561,34 +567,74 @@ struct SecondLook {
 };
 
 // The sweep: keys below the predicted range are counted, those in it kept, staged in LDS so that a workgroup updates each
-// list's counter once.  HBM-bound: two [1, 8, 32768, 128] tensors in 31 us, 4.4 TB/s; one of 131072 rows in 56, 4.8.
-// `rows` of one (b, h) segment per workgroup, grid = (ceil(T / rows), B * H, tensors).
-constexpr int kStageKeys = 512;  // keys a workgroup stages per list (2 workgroups of 64 KiB fit a compute unit)
-template <bool kFull>
-__global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows)
+// list's counter once.  HBM-bound: two [1, 8, 32768, 128] tensors in 29 us, 4.6 TB/s; one of 131072 rows in 57, 4.7.
+// A thread has eight loads of 16 bytes (rows of 128 elements) or of a chunk in flight, next to one another over the rows.
+// kCells: workgroups in between build the search's box index, which needs the secondaries only, while the others wait for
+// their rows; a quarter of the sweep's alternates with them, eight by eight (one for each XCD), the rest follows (half, three
+// quarters, all: within 1 %).  The two launches one after the other / together, in us: 16 heads of 32768 rows, S = 256, 51 /
+// 43; 8 heads of 131072, 76 / 58; 64 heads of 8192 rows of 96 elements, S = 192, 81 / 80 (bound by VALU issue); 4 heads of
+// 3074 rows of 100, S = 96, 23 / 14.
+// `rows` of one (b, h) segment per workgroup; grid: cell_blocks() * H * n_tensors, rounded up to 8, and ceil(T / rows) * B * H *
+// n_tensors, likewise.
+constexpr int kCountThreads = kCellThreads;
+constexpr int kCountRows = 512;  // of a workgroup, at most
+constexpr int kStageKeys = 192;  // keys a workgroup stages per list
+struct CountStage {              // LDS
+    unsigned long long staged[kBuckets][kStageKeys];
+    uint32_t n_staged[kBuckets], n_below;            // n_staged: all keys of the list, also those past the stage
+    uint32_t n_direct[kBuckets], full[kBuckets];     // those of them that the list's counter has; the list is full
+};
+template <bool kFull, bool kCells>
+__global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows,
+                                                                uint32_t n_tensors)
 {
-    const EncodeTensor &tn = batch.t[blockIdx.z];
+    constexpr size_t kLds = kCells && sizeof(CellBuild) > sizeof(CountStage) ? sizeof(CellBuild) : sizeof(CountStage);
+    __shared__ __align__(16) unsigned char lds[kLds];
+    uint32_t block = blockIdx.x, tensor;
+    if (kCells) {
+        const uint32_t per_head = (uint32_t)cell_blocks(g), n_cells = n_tensors * (uint32_t)g.H * per_head;
+        const uint32_t cells8 = (n_cells + 7u) / 8u, rows8 = (gridDim.x - 8u * cells8) / 8u;
+        const uint32_t beside = rows8 / 4u, mixed = cells8 + beside;  // the sweep's that alternate with the build's
+        const uint32_t i = block / 8u;
+        const uint32_t rows_before = i < mixed ? (uint32_t)((uint64_t)i * beside / mixed) : i - cells8;
+        if (i < mixed && (uint32_t)((uint64_t)(i + 1u) * beside / mixed) == rows_before) {
+            block = 8u * (i - rows_before) + (block & 7u);
+            if (block >= n_cells)
+                return;
+            const uint32_t head = block / per_head;
+            tensor = head / (uint32_t)g.H;
+            const EncodeTensor &tn = batch.t[tensor];
+            build_cells(g, carve_workspace(tn.ws, wo), tn.sec, (int)(head - tensor * (uint32_t)g.H), (int)(block - head * per_head),
+                        *reinterpret_cast<CellBuild *>(lds));
+            return;
+        }
+        block = 8u * rows_before + (block & 7u);
+    }
+    const uint32_t per_seg = (uint32_t)(g.T + rows - 1) / (uint32_t)rows, per_tensor = per_seg * (uint32_t)(g.B * g.H);
+    tensor = block / per_tensor;
+    if (kCells && tensor >= n_tensors)
+        return;
+    block -= tensor * per_tensor;
+    const EncodeTensor &tn = batch.t[tensor];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    __shared__ unsigned long long staged[kBuckets][kStageKeys];
-    __shared__ uint32_t n_staged[kBuckets], n_below;  // n_staged: all keys of the list, also those past the stage
-    __shared__ uint32_t n_direct[kBuckets], full[kBuckets];  // those of them that the list's counter has; the list is full
-    const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
-    const int c = threadIdx.x & 31, sub = threadIdx.x >> 5;
-    const int t0 = blockIdx.x * rows, t1 = min(g.T, t0 + rows);
-    const _Float16 *base = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh;
+    CountStage &st = *reinterpret_cast<CountStage *>(lds);
+    const int seg = (int)(block / per_seg), b = seg / g.H, h = seg % g.H;
+    const int t0 = (int)(block - (uint32_t)seg * per_seg) * rows, n_rows = min(rows, g.T - t0);
+    const _Float16 *base = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t0 * g.st;
     const Buckets range(g, ws, h);
     const uint32_t cap = bucket_capacity(g);
     unsigned long long *lists = ws.cand + (size_t)h * g.cand_cap;
     uint32_t *count = bucket_counts(ws, h);
-    if (threadIdx.x < kBuckets)
-        n_staged[threadIdx.x] = n_direct[threadIdx.x] = full[threadIdx.x] = 0;
-    if (threadIdx.x == 0)
-        n_below = 0;
+    const int tid = threadIdx.x;
+    if (tid < kBuckets)
+        st.n_staged[tid] = st.n_direct[tid] = st.full[tid] = 0;
+    if (tid == 0)
+        st.n_below = 0;
     __syncthreads();
     // Keys past the stage go straight to their list: one update of its counter for all of a wave's, and none once the list is
     // full (a tensor that repeats a value a hundred thousand times would queue up at one counter: 28 ns each).
     auto append = [&](uint32_t k, unsigned long long key) {
-        const int lane = threadIdx.x & 63;
+        const int lane = tid & 63;
         for (unsigned long long left = __ballot(1); left;) {  // uniform over the lanes that are here
             const int leader = __ffsll((long long)left) - 1;
             const uint32_t k0 = (uint32_t)__shfl((int)k, leader, 64);
@@ -598,9 +644,9 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
             uint32_t at = 0;
             if (lane == leader) {
                 at = atomicAdd(&count[k0 * kBucketPitch], n);
-                atomicAdd(&n_direct[k0], n);
+                atomicAdd(&st.n_direct[k0], n);
                 if (at + n > cap)
-                    full[k0] = 1u;
+                    st.full[k0] = 1u;
             }
             at = (uint32_t)__shfl((int)at, leader, 64) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
             if (k == k0 && at < cap)
@@ -608,57 +654,84 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_count(Geometry g, Wor
         }
     };
     uint32_t below = 0, equal = 0;
-    for (int tb = t0 + sub; tb < t1; tb += 256) {
-        half4_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            v[u] = half4_t{0, 0, 0, 0};
-            if (tb + 32 * u < t1)
-                v[u] = load_row_chunk<kFull>(base + (int64_t)(tb + 32 * u) * g.st, c, g);
+    auto take = [&](const half4_t v, bool in) {
+        const unsigned long long key = key_of(chunk_norm2(v)) & kKeyMask;
+        below += in && key < range.lo ? 1u : 0u;
+        if (in && range.holds(key)) {
+            if (range.span == 0ull) {
+                ++equal;
+            } else {
+                const uint32_t k = range.of(key), pos = atomicAdd(&st.n_staged[k], 1u);
+                if (pos < (uint32_t)kStageKeys)
+                    st.staged[k][pos] = key;
+                else if (!*(volatile uint32_t *)&st.full[k])
+                    append(k, key);
+            }
         }
+    };
+    constexpr int kLoads = 8;
+    if (kFull) {
+        typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+        constexpr int kPieces = kChunksPerRow / 2, kStep = kCountThreads / kPieces;  // 16-byte pieces of a row, rows per load
+        const _Float16 *at = base + (int64_t)(tid / kPieces) * g.st + 8 * (tid % kPieces);
+        for (int r = tid / kPieces; r - tid / kPieces < n_rows; r += kLoads * kStep, at += (int64_t)(kLoads * kStep) * g.st) {
+            half8_t v[kLoads];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const bool in = (kFull || c < g.n_c) && tb + 32 * u < t1;
-            const unsigned long long key = key_of(chunk_norm2(v[u])) & kKeyMask;
-            below += in && key < range.lo ? 1u : 0u;
-            if (in && range.holds(key)) {
-                if (range.span == 0ull) {
-                    ++equal;
-                } else {
-                    const uint32_t k = range.of(key), pos = atomicAdd(&n_staged[k], 1u);
-                    if (pos < (uint32_t)kStageKeys)
-                        staged[k][pos] = key;
-                    else if (!*(volatile uint32_t *)&full[k])
-                        append(k, key);
+            for (int u = 0; u < kLoads; ++u) {
+                v[u] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                if (r + kStep * u < n_rows)
+                    v[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
+            }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const bool in = r + kStep * u < n_rows;
+                take(half4_t{v[u][0], v[u][1], v[u][2], v[u][3]}, in);
+                take(half4_t{v[u][4], v[u][5], v[u][6], v[u][7]}, in);
+            }
+        }
+    } else {
+        const int n_chunks = n_rows * g.n_c;
+        for (int q0 = 0; q0 < n_chunks; q0 += kLoads * kCountThreads) {  // uniform
+            half4_t v[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int q = q0 + u * kCountThreads + tid;
+                v[u] = half4_t{0, 0, 0, 0};
+                if (q < n_chunks) {
+                    const int r = row_of_chunk(q, g);
+                    v[u] = load_row_chunk<false>(base + (int64_t)r * g.st, q - r * g.n_c, g);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u)
+                take(v[u], q0 + u * kCountThreads + tid < n_chunks);
         }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1)
         below += __shfl_xor(below, d, 64);
-    if ((threadIdx.x & 63) == 0)
-        atomicAdd(&n_below, below);
+    if ((tid & 63) == 0)
+        atomicAdd(&st.n_below, below);
     if (equal)
-        atomicAdd(&n_staged[0], equal);
+        atomicAdd(&st.n_staged[0], equal);
     __syncthreads();
-    const int k = threadIdx.x / 64;  // a wave per list
-    static_assert(kBuckets * 64 == kSelectThreads, "a wave per list");
     if (range.span == 0ull) {
-        if (threadIdx.x == 0 && n_staged[0])
-            atomicAdd(&count[0], n_staged[0]);
+        if (tid == 0 && st.n_staged[0])
+            atomicAdd(&count[0], st.n_staged[0]);
     } else {
-        const uint32_t n = min(n_staged[k], (uint32_t)kStageKeys);
-        uint32_t at = 0;
-        if ((threadIdx.x & 63) == 0 && n)  // with those that a full list made nobody append
-            at = atomicAdd(&count[k * kBucketPitch], n_staged[k] - n_direct[k]);
-        at = (uint32_t)__shfl((int)at, 0, 64);
-        for (uint32_t i = threadIdx.x & 63; i < n; i += 64)
-            if (at + i < cap)
-                lists[k * cap + at + i] = staged[k][i];
+        // a thread per list takes the places (with those that a full list made nobody append), a wave at a time fills them
+        if (tid < kBuckets && st.n_staged[tid])
+            st.full[tid] = atomicAdd(&count[tid * kBucketPitch], st.n_staged[tid] - st.n_direct[tid]);
+        __syncthreads();
+        for (int k = tid / 64; k < kBuckets; k += kCountThreads / 64) {
+            const uint32_t n = min(st.n_staged[k], (uint32_t)kStageKeys), at = st.full[k];
+            for (uint32_t i = tid & 63; i < n; i += 64)
+                if (at + i < cap)
+                    lists[k * cap + at + i] = st.staged[k][i];
+        }
     }
-    if (threadIdx.x == 0 && n_below)
-        atomicAdd(&ws.plan[h].below, n_below);
+    if (tid == 0 && st.n_below)
+        atomicAdd(&ws.plan[h].below, st.n_below);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -834,7 +907,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
                     list_at = atomicAdd(&plan.n_cand, n_staged);
                 __syncthreads();
                 for (uint32_t i = tid; i < n_staged; i += kSelectThreads)
-                    if (list_at + i < (uint32_t)g.cand_cap)
+                    if (list_at + i < (uint32_t)g.cand_room)
                         cand[list_at + i] = staged[i];
                 __syncthreads();
                 if (tid == 0)
@@ -882,7 +955,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
             n = __hip_atomic_load(&plan.n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             lo = __hip_atomic_load(&plan.least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             hi = __hip_atomic_load(&plan.most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (n <= (uint32_t)g.cand_cap)
+            if (n <= (uint32_t)g.cand_room)
                 median = select_rank(
                     [&](auto f) {
                         for (uint32_t i = tid; i < n; i += kSelectThreads)
@@ -1282,10 +1355,17 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
     }
     const dim3 parts(g.H, n, missed_parts(g, n));
     hipLaunchKernelGGL(k_select_predict<kFull>, samples, block, 0, stream, g, wo, batch);
-    int rows = kSelectRows;  // down to the 256 of one step while two workgroups per compute unit are not there
-    while (rows > 256 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 512)
+    int rows = kCountRows;  // down to the 128 of one step while four workgroups per compute unit are not there
+    while (rows > 128 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 1024)
         rows /= 2;
-    hipLaunchKernelGGL(k_select_count<kFull>, dim3((g.T + rows - 1) / rows, g.B * g.H, n), block, 0, stream, g, wo, batch, rows);
+    const uint32_t n_count = (uint32_t)((g.T + rows - 1) / rows) * (uint32_t)(g.B * g.H) * n;
+    if (g.cell_n > 0) {
+        const uint32_t n_cells = (uint32_t)(cell_blocks(g) * g.H) * n;
+        hipLaunchKernelGGL((k_select_count<kFull, true>), dim3((n_cells + 7) / 8 * 8 + (n_count + 7) / 8 * 8), dim3(kCountThreads), 0,
+                           stream, g, wo, batch, rows, n);
+    } else {
+        hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(n_count), dim3(kCountThreads), 0, stream, g, wo, batch, rows, n);
+    }
     hipLaunchKernelGGL(k_select_digit<kFull>, parts, block, 0, stream, g, wo, batch);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }

@@ -35,20 +35,11 @@
 //
 // That is the search of short tensors.  Long ones locate a chunk's direction in a box index over the codewords
 // (k_cells, k_search_cells below), which replaces the scan over all S secondaries.
-#include "hqmq_device.h"
+#include "hqmq_cells.h"
 
 namespace hqmq {
 
 namespace {
-
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // LDS serves the instructions of one wave in order; this only stops the compiler from moving
-    // LDS accesses of other lanes' data across the point.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ __forceinline__ uint16_t double_to_half_rne_sat(double v)
 {
@@ -85,14 +76,6 @@ __device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi)
 }
 
 template <int kCtrl>
-__device__ __forceinline__ unsigned long long dpp_move64(unsigned long long v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, 0xf, 0xf, true);
-    return ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo;
-}
-
-template <int kCtrl>
 __device__ __forceinline__ double dpp_move_f64(double v)
 {
     return __longlong_as_double((long long)dpp_move64<kCtrl>((unsigned long long)__double_as_longlong(v)));
@@ -103,11 +86,6 @@ __device__ __forceinline__ double dpp_move(double v)
 {
     return dpp_move_f64<kCtrl>(v);
 }
-template <int kCtrl>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
-}
 
 // Maximum with the lane 16 away (lane ^ 16).
 __device__ __forceinline__ float max_across_16(float v)
@@ -117,37 +95,10 @@ __device__ __forceinline__ float max_across_16(float v)
 }
 __device__ __forceinline__ double max_across_16(double v) { return fmax(v, __shfl_xor(v, 16, 64)); }
 
-__device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b)
-{
-    return a > b ? a : b;
-}
-
 __device__ __forceinline__ double half_bits_to_double(uint16_t h)
 {
     return (double)(float)__builtin_bit_cast(_Float16, h);
 }
-
-// Nearest 24-cell vertex to v in the order of the primary table: p = 0..7 are +1, -1, +i, -i,
-// +j, -j, +k, -k, p = 8 + 8 b0 + 4 b1 + 2 b2 + b3 is ((-1)^b0, (-1)^b1, (-1)^b2, (-1)^b3)/2.
-// Exact ties go to the lowest p.
-__device__ __forceinline__ int nearest_primary(float v0, float v1, float v2, float v3, float &score)
-{
-    float a0 = fabsf(v0), a1 = fabsf(v1), a2 = fabsf(v2), a3 = fabsf(v3);
-    float ax = a0;
-    int pi = (v0 < 0.f) ? 1 : 0;
-    if (a1 > ax) { ax = a1; pi = 2 + ((v1 < 0.f) ? 1 : 0); }
-    if (a2 > ax) { ax = a2; pi = 4 + ((v2 < 0.f) ? 1 : 0); }
-    if (a3 > ax) { ax = a3; pi = 6 + ((v3 < 0.f) ? 1 : 0); }
-    float hs = 0.5f * (((a0 + a1) + a2) + a3);
-    int ph = 8 + ((v0 < 0.f) ? 8 : 0) + ((v1 < 0.f) ? 4 : 0) + ((v2 < 0.f) ? 2 : 0) + ((v3 < 0.f) ? 1 : 0);
-    if (ax >= hs) {
-        score = ax;
-        return pi;
-    }
-    score = hs;
-    return ph;
-}
-
 
 // sigma = fp16(sqrt(rmax)), round to nearest even, saturating.  The fp32 square root is within
 // 2 ulp(fp32) of the exact one, so it rounds to the same fp16 value unless it lies within a few
@@ -245,31 +196,6 @@ __device__ __forceinline__ Parts2 split2(float x)
     p.h = (_Float16)x;
     p.l = (_Float16)(x - (float)p.h);
     return p;
-}
-
-// v = u conj(q) in fp32 and its closed-form score max_p <v, P_p>
-__device__ __forceinline__ float score_secondary(const float *q, float u0, float u1, float u2, float u3, float &v0,
-                                                 float &v1, float &v2, float &v3)
-{
-    const float a = q[0], bq = q[1], cq = q[2], d = q[3];
-    v0 = fmaf(d, u3, fmaf(cq, u2, fmaf(bq, u1, a * u0)));
-    v1 = fmaf(cq, u3, fmaf(-d, u2, fmaf(a, u1, -bq * u0)));
-    v2 = fmaf(-bq, u3, fmaf(a, u2, fmaf(d, u1, -cq * u0)));
-    v3 = fmaf(a, u3, fmaf(bq, u2, fmaf(-cq, u1, -d * u0)));
-    const float a0 = fabsf(v0), a1 = fabsf(v1), a2 = fabsf(v2), a3 = fabsf(v3);
-    return fmaxf(fmaxf(fmaxf(fmaxf(a0, a1), a2), a3), 0.5f * (((a0 + a1) + a2) + a3));  // two v_max3
-}
-
-// Maximum of a 64-bit key over the wave (every lane gets it).
-__device__ __forceinline__ unsigned long long wave_umax64(unsigned long long k)
-{
-    k = umax64(k, dpp_move64<0xB1>(k));   // quad_perm [1, 0, 3, 2]
-    k = umax64(k, dpp_move64<0x4E>(k));   // quad_perm [2, 3, 0, 1]
-    k = umax64(k, dpp_move64<0x141>(k));  // row_half_mirror
-    k = umax64(k, dpp_move64<0x140>(k));  // row_mirror
-    k = umax64(k, (unsigned long long)__shfl_xor((long long)k, 16, 64));
-    k = umax64(k, (unsigned long long)__shfl_xor((long long)k, 32, 64));
-    return k;
 }
 
 // Two groups of secondaries whose screened maxima lie closer than this fraction of the larger one are
@@ -957,10 +883,6 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 
 namespace {
 
-constexpr int kCellThreads = 256;      // workgroup of the index build: 4 lanes per box
-constexpr int kCoarseCap = 1024;       // codewords of a block of 4^3 boxes
-constexpr int kMidCap = 384;           // codewords of a sub-block of 2^3 boxes
-constexpr int kCellMax = 64;           // codewords of a box before the pairwise test
 // Two codewords whose scores lie closer than this fraction of the best are not told apart by the lists' arithmetic: more
 // than its largest possible error, so that a clear winner has the best score in exact arithmetic too.  In units of 2^-24,
 // for two unit codewords a and b that tie near the best (both within 45 degrees of the chunk: |a - b| <= sqrt(2)):
@@ -970,12 +892,8 @@ constexpr int kCellMax = 64;           // codewords of a box before the pairwise
 // 27.9 in all, of a best that is at least 1/sqrt(2): 2.35e-6 (3.4e-7 measured on 800,000 chunks).  Secondaries of other
 // norms scale both sides by the largest.
 constexpr float kCellBand = 2.5e-6f;
-constexpr float kCellEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
-                                       // kCellBand times the ratio of two scores of a box plus the rounding of the test
 constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the
                                                // cube by 5.4e-7 (fold 3.6e-7, reciprocal and product 1.8e-7), in 0 .. n - 1
-constexpr uint32_t kCellPad = 0x7fffu; // list entry without a codeword; bit 15 marks the last group of a list
-
 // The search numbers the element P_0 that it folds with by what it has at hand (fold_primary), and needs the index of
 // P_0 P_p' in the order of the primaries: [fold][p'], rows of 32 bytes.
 struct FoldTable {
@@ -1016,348 +934,15 @@ constexpr FoldTable make_fold_table()
 }
 __constant__ const FoldTable kFoldTable = make_fold_table();
 
-// Component i of primary p.
-__device__ __forceinline__ float primary_component(int p, int i)
-{
-    if (p < 8)
-        return (p >> 1) == i ? ((p & 1) ? -1.f : 1.f) : 0.f;
-    return (((p - 8) >> (3 - i)) & 1) ? -0.5f : 0.5f;
-}
-
-// P_p q as (c_1, c_2, c_3, c_0): the linear function of a box point.
-__device__ __forceinline__ float4_t codeword_function(int p, const float4_t q)
-{
-    const float a = primary_component(p, 0), b = primary_component(p, 1), c = primary_component(p, 2),
-                d = primary_component(p, 3);
-    float4_t f;
-    f[3] = fmaf(-d, q[3], fmaf(-c, q[2], fmaf(-b, q[1], a * q[0])));
-    f[0] = fmaf(-d, q[2], fmaf(c, q[3], fmaf(b, q[0], a * q[1])));
-    f[1] = fmaf(d, q[1], fmaf(c, q[0], fmaf(-b, q[3], a * q[2])));
-    f[2] = fmaf(d, q[0], fmaf(-c, q[1], fmaf(b, q[2], a * q[3])));
-    return f;
-}
-
-__device__ __forceinline__ float value_at(const float4_t f, float m1, float m2, float m3)
-{
-    return fmaf(f[0], m1, fmaf(f[1], m2, fmaf(f[2], m3, f[3])));
-}
-
-// b (value vb at the centre) ahead of c (value vc) by more than eps all over the box of half width h
-__device__ __forceinline__ bool ahead_in_box(const float4_t b, float vb, const float4_t c, float vc, float h, float eps)
-{
-    const float spread = (fabsf(b[0] - c[0]) + fabsf(b[1] - c[1])) + fabsf(b[2] - c[2]);
-    return vb - vc > fmaf(h, spread, eps);
-}
-
-// Box of half width h around m meets the octahedron (with room for the rounding of y).
-__device__ __forceinline__ bool meets_octahedron(float m1, float m2, float m3, float h)
-{
-    return (fmaxf(fabsf(m1) - h, 0.f) + fmaxf(fabsf(m2) - h, 0.f)) + fmaxf(fabsf(m3) - h, 0.f) <= 1.0001f;
-}
-
-struct CellIndex {        // parts of one head's index in the workspace
-    uint16_t *head;       // [n^3] first group of the box's list; 0 = no list
-    uint2 *list;          // [cell_groups] groups of four 16-bit entries k = p S + s; group 0 belongs to no list
-    uint32_t *n_groups;   // groups handed out beyond group 0
-    uint32_t *used;       // [cell_words] bit k: codeword k is in some list
-};
-__device__ __forceinline__ CellIndex cell_index_of(const Geometry &g, const Workspace &ws, int h)
-{
-    CellIndex ix;
-    char *base = reinterpret_cast<char *>(ws.cand + (size_t)h * g.cand_cap);
-    ix.head = reinterpret_cast<uint16_t *>(base);
-    ix.list = reinterpret_cast<uint2 *>(base + cell_head_bytes(g.cell_n));
-    ix.n_groups = ws.cell_state + (size_t)h * (1 + g.cell_words);
-    ix.used = ix.n_groups + 1;
-    return ix;
-}
-
 }  // namespace
 
-// Index build: workgroup (block, head, tensor) does the 4^3 boxes of one block of the grid.
-//   1  the best codeword at the block's centre, and the codewords that it is not ahead of all over the block
-//   2  the same for its 2^3 sub-blocks of 2^3 boxes against that list (32 lanes each)
-//   3  the same for every box against its sub-block's list (4 lanes each), then the survivors against eight strong ones,
-//      the best two of each lane's share (every pair: 2 % fewer entries for three times the work)
-//   4  the lists, four entries to a group, in space handed out by one counter per head
-// A box whose list does not fit any of the arrays gets none; its chunks take the search over all S secondaries.
-// grid = ((n / 4)^3, H, tensors), block = 256.
+// The index build as a launch of its own, where no sweep over the rows goes before the search.
+// grid = (cell_blocks(), H, tensors).
 __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
+    __shared__ CellBuild lds;
     const EncodeTensor &tn = batch.t[blockIdx.z];
-    const Workspace ws = carve_workspace(tn.ws, wo);
-    const int h = blockIdx.y, S = g.S, n = g.cell_n, nb = n / 4;
-    const float *sec_h = tn.sec + (size_t)h * S * 4;
-    const CellIndex ix = cell_index_of(g, ws, h);
-
-    __shared__ float4_t cf[kCoarseCap];
-    __shared__ uint16_t ck[kCoarseCap];
-    __shared__ uint32_t cused[kCoarseCap / 32];
-    __shared__ uint16_t mid[8][kMidCap];
-    __shared__ uint16_t kept[64][kCellMax];
-    __shared__ uint32_t first_group[64];
-    __shared__ unsigned long long wave_key[kCellThreads / 64];
-    __shared__ uint32_t n_coarse, list_base;
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int b0 = blockIdx.x / (nb * nb), b1 = (blockIdx.x / nb) % nb, b2 = blockIdx.x % nb;
-    // box of this lane's quad: sub-block tid / 32, box of it (tid / 4) % 8
-    const int cell = tid >> 2, sub = tid & 3, sb = tid >> 5;
-    const int s0 = sb >> 2, s1 = (sb >> 1) & 1, s2 = sb & 1;
-    const int i0 = 4 * b0 + 2 * s0 + ((cell >> 2) & 1), i1 = 4 * b1 + 2 * s1 + ((cell >> 1) & 1), i2 = 4 * b2 + 2 * s2 + (cell & 1);
-    const int cell_id = (i0 * n + i1) * n + i2;
-    const float hf = 1.0f / (float)n;
-    const float margin = 1.2e-5f;  // y and the box number are rounded (7e-7), the latter shrunk by 4e-6 as well
-    const float y1 = (float)(2 * i0 + 1) * hf - 1.f, y2 = (float)(2 * i1 + 1) * hf - 1.f, y3 = (float)(2 * i2 + 1) * hf - 1.f;
-    const float m1 = (float)(8 * b0 + 4) * hf - 1.f, m2 = (float)(8 * b1 + 4) * hf - 1.f, m3 = (float)(8 * b2 + 4) * hf - 1.f;
-    if (blockIdx.x == 0 && tid == 0)
-        ix.list[0] = make_uint2(kCellPad | 0x8000u | (kCellPad << 16), kCellPad | (kCellPad << 16));
-    if (!meets_octahedron(m1, m2, m3, 4.f * hf)) {  // uniform
-        if (sub == 0)
-            ix.head[cell_id] = 0;
-        return;
-    }
-    if (tid == 0)
-        n_coarse = 0;
-    if (tid < kCoarseCap / 32)
-        cused[tid] = 0;
-
-    // ---- 1: the block ------------------------------------------------------------------------------------------------
-    unsigned long long key = 0ull;
-    for (int s = tid; s < S; s += kCellThreads) {
-        float v0, v1, v2, v3;
-        const float sc = score_secondary(sec_h + 4 * s, 1.f, m1, m2, m3, v0, v1, v2, v3);
-        key = umax64(key, ((unsigned long long)__float_as_uint(sc) << 32) | (0xffffffffu - (uint32_t)s));
-    }
-    key = wave_umax64(key);
-    if (lane == 0)
-        wave_key[tid >> 6] = key;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kCellThreads / 64; ++w)
-        key = umax64(key, wave_key[w]);
-    const int s_best = (int)min(0xffffffffu - (uint32_t)key, (uint32_t)S - 1u);
-    float4_t best;
-    float v_best;
-    {
-        float v0, v1, v2, v3, sc;
-        (void)score_secondary(sec_h + 4 * s_best, 1.f, m1, m2, m3, v0, v1, v2, v3);
-        const int p = nearest_primary(v0, v1, v2, v3, sc);
-        best = codeword_function(p, *reinterpret_cast<const float4_t *>(sec_h + 4 * s_best));
-        v_best = value_at(best, m1, m2, m3);
-    }
-    {
-        const float hb = 4.f * hf + margin, eps = kCellEps * fabsf(v_best);
-        for (int s0 = 0; s0 < S; s0 += kCellThreads) {  // uniform
-            const int s = s0 + tid;
-            float4_t q = {0.f, 0.f, 0.f, 0.f};
-            if (s < S)
-                q = *reinterpret_cast<const float4_t *>(sec_h + 4 * s);
-            // c: P_p q as (c_1, c_2, c_3, c_0), v its value at the centre; its negative is tested along with it
-            uint32_t left = 0;
-            auto test = [&](const float4_t c, float v, int p, int p_neg) {
-                left |= ahead_in_box(best, v_best, c, v, hb, eps) ? 0u : 1u << p;
-                left |= ahead_in_box(best, v_best, -c, -v, hb, eps) ? 0u : 1u << p_neg;
-            };
-            const float4_t e0 = {q[1], q[2], q[3], q[0]}, e1 = {q[0], -q[3], q[2], -q[1]};  // q, i q
-            const float4_t e2 = {q[3], q[0], -q[1], -q[2]}, e3 = {-q[2], q[1], q[0], -q[3]};  // j q, k q
-            const float v0 = value_at(e0, m1, m2, m3), v1 = value_at(e1, m1, m2, m3);
-            const float v2 = value_at(e2, m1, m2, m3), v3 = value_at(e3, m1, m2, m3);
-            test(e0, v0, 0, 1);
-            test(e1, v1, 2, 3);
-            test(e2, v2, 4, 5);
-            test(e3, v3, 6, 7);
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const float4_t ea = a ? e0 - e1 : e0 + e1;
-                const float va = a ? v0 - v1 : v0 + v1;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const float4_t eb = (b & 2 ? -e2 : e2) + (b & 1 ? -e3 : e3);
-                    const float vb = (b & 2 ? -v2 : v2) + (b & 1 ? -v3 : v3);
-                    const int p = 8 + 4 * a + b;
-                    test(0.5f * (ea + eb), 0.5f * (va + vb), p, 31 - p);
-                }
-            }
-            if (s >= S)
-                left = 0;
-            // the wave's survivors take consecutive places
-            const uint32_t count = __popc(left);
-            uint32_t inc = count;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t o = __shfl_up(inc, d, 64);
-                if (lane >= d)
-                    inc += o;
-            }
-            uint32_t base = 0;
-            if (lane == 63)
-                base = atomicAdd(&n_coarse, inc);
-            uint32_t at = __shfl(base, 63, 64) + inc - count;
-            for (; left; left &= left - 1u, ++at) {
-                const int p = __ffs((int)left) - 1;
-                if (at < (uint32_t)kCoarseCap) {
-                    cf[at] = codeword_function(p, q);
-                    ck[at] = (uint16_t)(p * S + s);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const int nc = n_coarse <= (uint32_t)kCoarseCap ? (int)n_coarse : 0;  // 0: no lists in this block
-
-    // The strongest of `count` entries `entry(j)` at (z1, z2, z3), over `lanes` neighbouring lanes of which this one is number l.
-    auto strongest = [&](auto entry, int count, int l, int lanes, float z1, float z2, float z3, float &v) {
-        float vb = -3.4e38f;
-        int jb = 0;
-        for (int j = l; j < count; j += lanes) {
-            const int i = entry(j);
-            const float w = value_at(cf[i], z1, z2, z3);
-            jb = w > vb ? i : jb;
-            vb = fmaxf(vb, w);
-        }
-        for (int d = 1; d < lanes; d <<= 1) {
-            const float vo = __shfl_xor(vb, d, 64);
-            const int jo = __shfl_xor(jb, d, 64);
-            const bool take = vo > vb || (vo == vb && jo < jb);
-            vb = take ? vo : vb;
-            jb = take ? jo : jb;
-        }
-        v = vb;
-        return jb;
-    };
-
-    // ---- 2: the sub-block ----------------------------------------------------------------------------------------------
-    int nm = 0;
-    if (nc > 0) {
-        const float z1 = (float)(8 * b0 + 4 * s0 + 2) * hf - 1.f, z2 = (float)(8 * b1 + 4 * s1 + 2) * hf - 1.f,
-                    z3 = (float)(8 * b2 + 4 * s2 + 2) * hf - 1.f;
-        if (meets_octahedron(z1, z2, z3, 2.f * hf)) {
-            float vb;
-            const int jb = strongest([](int j) { return j; }, nc, tid & 31, 32, z1, z2, z3, vb);
-            const float4_t bf = cf[jb];
-            const float eps = kCellEps * fabsf(vb), hm = 2.f * hf + margin;
-            for (int j0 = 0; j0 < nc; j0 += 32) {  // uniform over the half-wave
-                const int j = j0 + (tid & 31);
-                bool stays = false;
-                if (j < nc) {
-                    const float4_t c = cf[j];
-                    stays = !ahead_in_box(bf, vb, c, value_at(c, z1, z2, z3), hm, eps);
-                }
-                const uint32_t votes = (uint32_t)(__ballot(stays) >> (lane & 32));
-                const int at = nm + __popc(votes & ((1u << (lane & 31)) - 1u));
-                if (stays && at < kMidCap)
-                    mid[sb][at] = (uint16_t)j;
-                nm += __popc(votes);
-            }
-        }
-    }
-    wave_lds_sync();  // the lanes of a sub-block, and of a box, belong to one wave
-    if (nm > kMidCap)
-        nm = 0;
-
-    // ---- 3: the box ------------------------------------------------------------------------------------------------------
-    uint32_t keep = 0;  // bit i: entry sub + 4 i of kept[cell] is in the list
-    if (nm > 0 && meets_octahedron(y1, y2, y3, hf)) {
-        const float hc = hf + margin;
-        const uint16_t *list = mid[sb];
-        float vb;
-        const int jb = strongest([&](int j) { return (int)list[j]; }, nm, sub, 4, y1, y2, y3, vb);
-        const float4_t bf = cf[jb];
-        const float eps = kCellEps * fabsf(vb);
-        float v_own[2] = {-3.4e38f, -3.4e38f};  // the two strongest survivors of this lane's share
-        int j_own[2] = {jb, jb}, m = 0;
-        for (int j0 = 0; j0 < nm; j0 += 4) {  // uniform over the quad
-            const int j = j0 + sub;
-            bool stays = false;
-            int i = 0;
-            if (j < nm) {
-                i = list[j];
-                const float4_t c = cf[i];
-                const float v = value_at(c, y1, y2, y3);
-                stays = !ahead_in_box(bf, vb, c, v, hc, eps);
-                if (stays) {
-                    j_own[1] = v > v_own[0] ? j_own[0] : v > v_own[1] ? i : j_own[1];
-                    v_own[1] = __builtin_amdgcn_fmed3f(v, v_own[0], v_own[1]);
-                    j_own[0] = v > v_own[0] ? i : j_own[0];
-                    v_own[0] = fmaxf(v_own[0], v);
-                }
-            }
-            const uint32_t votes = (uint32_t)(__ballot(stays) >> (lane & ~3)) & 15u;
-            const int at = m + __popc(votes & ((1u << sub) - 1u));
-            if (stays && at < kCellMax)
-                kept[cell][at] = (uint16_t)i;
-            m += __popc(votes);
-        }
-        if (m > kCellMax)
-            m = 0;
-        float4_t strong[8];
-        float v_strong[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            strong[k] = cf[__shfl(j_own[k & 1], (lane & ~3) + (k >> 1), 64)];
-            v_strong[k] = value_at(strong[k], y1, y2, y3);
-        }
-        wave_lds_sync();
-        for (int i = sub; i < m; i += 4) {
-            const float4_t c = cf[kept[cell][i]];
-            const float v = value_at(c, y1, y2, y3);
-            bool out = false;
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                out |= ahead_in_box(strong[k], v_strong[k], c, v, hc, eps);
-            keep |= out ? 0u : 1u << (i >> 2);
-        }
-    }
-    // ---- 4: space for the lists, entries -----------------------------------------------------------------------------------
-    const uint32_t mine = __popc(keep);
-    uint32_t before = 0, total = 0;  // entries of the quad's lanes in front of this one, and of all four
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t o = __shfl(mine, (lane & ~3) + d, 64);
-        before += d < sub ? o : 0u;
-        total += o;
-    }
-    const uint32_t groups = (total + 3) >> 2;
-    if (sub == 0)
-        first_group[cell] = groups;
-    __syncthreads();
-    if (tid < 64) {
-        const uint32_t v = first_group[tid];
-        uint32_t inc = v;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = __shfl_up(inc, d, 64);
-            if (lane >= d)
-                inc += o;
-        }
-        const uint32_t all = __shfl(inc, 63, 64);
-        if (tid == 0)
-            list_base = 1u + (all ? atomicAdd(ix.n_groups, all) : 0u);
-        first_group[tid] = inc - v;
-    }
-    __syncthreads();
-    const uint32_t first = list_base + first_group[cell];
-    const bool fits = groups > 0 && first + groups <= (uint32_t)g.cell_groups;
-    if (sub == 0)
-        ix.head[cell_id] = fits ? (uint16_t)first : (uint16_t)0;
-    if (fits) {
-        uint16_t *dst = reinterpret_cast<uint16_t *>(ix.list + first);
-        uint32_t at = before;
-        for (uint32_t left = keep; left; left &= left - 1u) {
-            const int j = kept[cell][sub + 4 * (__ffs((int)left) - 1)];
-            atomicOr(&cused[j >> 5], 1u << (j & 31));
-            dst[at] = (uint16_t)(ck[j] | (at == 4 * (groups - 1) ? 0x8000u : 0u));
-            ++at;
-        }
-        if (sub == 3)  // the last lane's entries end the list
-            for (at = total; at < 4 * groups; ++at)
-                dst[at] = (uint16_t)kCellPad;
-    }
-    __syncthreads();
-    for (int j = tid; j < nc; j += kCellThreads)
-        if ((cused[j >> 5] >> (j & 31)) & 1u)
-            atomicOr(&ix.used[ck[j] >> 5], 1u << (ck[j] & 31));
+    build_cells(g, carve_workspace(tn.ws, wo), tn.sec, blockIdx.y, blockIdx.x, lds);
 }
 
 namespace {
@@ -1791,13 +1376,13 @@ hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, co
 }
 
 hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
-                         hipStream_t stream)
+                         bool cells_built, hipStream_t stream)
 {
     dim3 grid((g.T + g.search_rows - 1) / g.search_rows, g.B * g.H, (unsigned)n_tensors);
     const bool full = g.D == 4 * kChunksPerRow;
     if (g.cell_n > 0) {
-        const int nb = g.cell_n / 4;
-        hipLaunchKernelGGL(k_cells, dim3(nb * nb * nb, g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
+        if (!cells_built)
+            hipLaunchKernelGGL(k_cells, dim3(cell_blocks(g), g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
         const size_t lds_cells = cell_lds_bytes(g);
 #define HQMQ_LAUNCH_CELLS(R)                                                                                             \
     do {                                                                                                             \

@@ -788,6 +788,42 @@ def test_search_of_many_batch_entries(B, T, D, S):
     _roundtrip(_lognormal_tensor(B, 2, T, seed=T + S, sigma_g=0.8, D=D), S=S)
 
 
+@pytest.mark.parametrize("kind,D,B,T,S", [
+    ("columns", 128, 1, 1025, 250), ("columns", 128, 3, 8193, 16), ("columns", 100, 2, 10486, 9), ("columns", 128, 1, 16511, 129),
+    ("small", 128, 1, 9000, 64), ("small", 96, 1, 22000, 33), ("grid", 128, 2, 8200, 16), ("two", 128, 1, 16400, 512),
+])
+def test_box_index_built_beside_the_select(kind, D, B, T, S):
+    """The sweep of the select builds the search's index, which lies behind the select's lists: rows on and off the sweep's
+    steps of 128, one, four and eight parts of the prediction, chunks whose scale is a matter of their column (the prediction
+    takes eight columns of a row), and heads whose prediction misses or whose lists are filled to the last key, which have to
+    leave the index alone.  Thresholds bit for bit, encode on some rows."""
+    H = 2
+    gen = torch.Generator().manual_seed(T + D)
+    if kind in ("grid", "two"):
+        x = _repeating_tensor(kind, B, H, T, D, gen)
+    else:
+        x = torch.randn(B, H, T, D, generator=gen)
+        x *= torch.exp(1.5 * torch.randn(1, H, 1, (D + 3) // 4, generator=gen)).repeat_interleave(4, 3)[..., :D]
+        if kind == "small":
+            R, n_h = B * T, B * T * ((D + 3) // 4)
+            samples = 1024 * (1 if n_h <= 1 << 18 else 4 if n_h <= 1 << 19 else 8)
+            rows = torch.arange(0, R, ((R + samples - 1) // samples) | 1)
+            x[rows // T, 0, rows % T] *= 0.02
+        x = x.half()
+    sec_t, sec = _sec(4, H, S)
+    xb = _bits(x)
+    e = oracle.encode(xb, sec, rows=np.arange(0, B * H * T, 53))
+    x_dev, sec_dev = x.to(DEV), sec_t.to(DEV)
+    print(compare_encode(gpu_encode(x_dev, sec_dev), e, xb, sec), flush=True)
+    params = hq.params_for(x_dev, S)
+    ws = hq.alloc_workspace(params, DEV)
+    hq.hqmq_encode(params, x_dev, sec_dev, hq.alloc_encoded(params, DEV), ws)
+    thr = hq.hqmq_thresholds(params, ws)
+    torch.cuda.synchronize()
+    c = float(np.float32(3.0))
+    assert np.array_equal(thr.cpu().numpy().view(np.uint64), ((c * c) * e.m2).view(np.uint64))
+
+
 @pytest.mark.parametrize("S,D", [(8, 128), (24, 128), (64, 128), (256, 128), (256, 126), (96, 50)])
 def test_box_index_at_the_corners_of_the_fold(S, D):
     """Chunks (+-a, +-a, 0, 0) in every order fold onto a corner of the octahedron that the search's box index covers, where
