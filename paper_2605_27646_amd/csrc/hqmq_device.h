@@ -148,9 +148,9 @@ inline int search_rows_for(int T, int S16, int A16, int D, int row_words)
 inline size_t cell_lds_bytes(const Geometry &g)
 {
     const size_t tables = ((size_t)g.cell_used + 1) * 16 + (size_t)g.S * 16 + cell_head_bytes(g.cell_n) +
-                          (size_t)g.cell_groups * 8 + (size_t)g.cell_used * 4 + 24 * 32;
+                          (size_t)g.cell_groups * 8 + (size_t)g.cell_used * 4 + 33 * 32;
     const size_t scratch = (size_t)g.cell_words * 8 + 4;
-    const size_t rows = (16 * 64 + (size_t)g.search_rows) * 4;
+    const size_t rows = 16 * 64 * 4 + (size_t)g.search_rows * 8;
     return tables + (rows > scratch ? rows : scratch);
 }
 
@@ -326,6 +326,11 @@ __device__ __forceinline__ int row_of_chunk(int q, const Geometry &g)
 {
     return g.n_c == 1 ? q : (int)__umulhi((uint32_t)q, g.n_c_magic);
 }
+
+// The lanes for which p holds (__ballot takes an integer, which costs two vector instructions).
+__device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// This lane's bit of a mask of the wave.
+__device__ __forceinline__ bool of_mask(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 __device__ __forceinline__ unsigned long long key_of(double r2)
 {

@@ -118,11 +118,12 @@ __device__ __forceinline__ uint16_t sigma_of_row_max(double rmax)
     return sigma16;
 }
 
-// Whether sigma_of_row_max has to take the fp64 recipe: rmax its argument (rounded to fp32), sf the fp32 square root.
-__device__ __forceinline__ bool scale_unsure(float rmax, float sf)
+// Whether sigma_of_row_max has to take the fp64 recipe: sf the fp32 square root, at most 65504.  It is within 4 units of the
+// last place: 1 of the instruction, 3 / 2 roundings of 2^-24 of an fp32 argument.
+__device__ __forceinline__ bool scale_unsure(float sf)
 {
-    const int dist = (int)(__float_as_uint(sf) & 0x1fffu) - 0x1000;
-    return rmax != 0.f && sf < 65504.f && (sf < 0x1.0p-14f || (dist >= -8 && dist <= 8));
+    const uint32_t bits = __float_as_uint(sf);
+    return ((bits - (0x1000u - 8u)) & 0x1fffu) <= 16u || bits - 1u < 0x387fffffu;  // next to a midpoint; below 2^-14, not zero
 }
 
 __device__ __forceinline__ int radius_code_exact(double r2, uint16_t sigma16, double Lq)
@@ -421,23 +422,16 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
 // scan / gather kernels that follow.  Called by one wave.
 template <int kRows>
 __device__ __forceinline__ void write_row_offsets(const Geometry &g, const Workspace &ws, const EncodedPtrs &enc, int lane,
-                                                  int seg, int t0, const uint32_t *rcnt)
+                                                  int seg, int t0, const uint2 *state)
 {
     uint32_t carry = 0;
 #pragma unroll
     for (int part = 0; part < kRows / 64; ++part) {
         const int r = 64 * part + lane;
-        const uint32_t cnt = t0 + r < g.T ? rcnt[r] : 0u;
-        uint32_t inc = cnt;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            uint32_t o = __shfl_up(inc, d, 64);
-            if (lane >= d)
-                inc += o;
-        }
+        const uint32_t cnt = t0 + r < g.T ? __popc(state[r].x) : 0u, inc = wave_scan(cnt);
         if (t0 + r < g.T)
             enc.row_off[(int64_t)seg * g.T + t0 + r] = carry + inc - cnt;
-        carry += __shfl(inc, 63, 64);
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     }
     if (lane == 0)
         ws.block_sum[(size_t)seg * g.n_search_blocks_per_seg + blockIdx.x] = carry;
@@ -874,10 +868,10 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32.  Either way the codeword is the best one, or the fp32 search's choice
 // between codewords whose scores differ by no more than its own rounding.
-// Measured, [1, 8, 32768, 128], S = 256, per tensor of a 32-tensor launch: 448 us (matrix screen) -> 68 us + 8 us for the
-// index; two tensors in a call: 1017 -> 143 us + 27 us for the index.  Bound by VALU issue (300 instructions per
-// 64 chunks, 115 of them in the list loop: the longest of 64 lists has 3.4 groups of four on average), LDS busy
-// half of the time; 16 % of the HBM peak.
+// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 127 by the index (and 14 beside the
+// select's sweep).  Bound by VALU issue (282 instructions per 64 chunks, 115 of them in the list loop: the longest of
+// 64 lists has 3.4 groups of four on average), LDS busy half of the time.  145 us and 327 instructions with fp64 norms of
+// every chunk, ballots of integers, the fold by all sixteen products and the rows' state stored row by row.
 // What a codebook costs whose lists do not fit (secondaries close together or equal) stands at the fall-back in cell_codeword.
 // ---------------------------------------------------------------------------------------------------------------
 
@@ -894,24 +888,13 @@ namespace {
 constexpr float kCellBand = 2.5e-6f;
 constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the
                                                // cube by 5.4e-7 (fold 3.6e-7, reciprocal and product 1.8e-7), in 0 .. n - 1
-// The search numbers the element P_0 that it folds with by what it has at hand (fold_primary), and needs the index of
-// P_0 P_p' in the order of the primaries: [fold][p'], rows of 32 bytes.
+// The search numbers the element P_0 that it folds with by 4 f + 16 for f = p_0 / 4 + p_1 / 2 + p_2 + 2 p_3 in twice its
+// components: odd from 1 to 31 for the half-integer elements, even for the axis elements.  It needs the index of P_0 P_p' in
+// the order of the primaries: [fold][p'], rows of 32 bytes.
+constexpr int kFolds = 33;
 struct FoldTable {
-    alignas(16) uint8_t at[24 * 32];
+    alignas(16) uint8_t at[kFolds * 32];
 };
-// fold < 8: axis element 2 slot + sign; else half-integer element with the sign bits fold - 8.  The bits (slots) 0..3
-// belong to components 2, 0, 3, 1: where the packed sign bits of the four halves end up.
-constexpr int fold_primary(int fold)
-{
-    const int comp[4] = {2, 0, 3, 1};
-    if (fold < 8)
-        return 2 * comp[fold >> 1] + (fold & 1);
-    int p = 8;
-    for (int slot = 0; slot < 4; ++slot)
-        if (((fold - 8) >> slot) & 1)
-            p += 8 >> comp[slot];
-    return p;
-}
 constexpr FoldTable make_fold_table()
 {
     FoldTable t{};
@@ -921,14 +904,14 @@ constexpr FoldTable make_fold_table()
             el[p][i] = p < 8 ? ((p >> 1) == i ? ((p & 1) ? -2 : 2) : 0) : ((((p - 8) >> (3 - i)) & 1) ? -1 : 1);
     for (int a = 0; a < 24; ++a)
         for (int b = 0; b < 24; ++b) {
-            const int *x = el[fold_primary(a)], *y = el[b];
+            const int *x = el[a], *y = el[b], fold = x[0] + 2 * x[1] + 4 * x[2] + 8 * x[3] + 16;
             const int c[4] = {x[0] * y[0] - x[1] * y[1] - x[2] * y[2] - x[3] * y[3],
                               x[0] * y[1] + x[1] * y[0] + x[2] * y[3] - x[3] * y[2],
                               x[0] * y[2] - x[1] * y[3] + x[2] * y[0] + x[3] * y[1],
                               x[0] * y[3] + x[1] * y[2] - x[2] * y[1] + x[3] * y[0]};
             for (int p = 0; p < 24; ++p)
                 if (c[0] == 2 * el[p][0] && c[1] == 2 * el[p][1] && c[2] == 2 * el[p][2] && c[3] == 2 * el[p][3])
-                    t.at[32 * a + b] = (uint8_t)p;
+                    t.at[32 * fold + b] = (uint8_t)p;
         }
     return t;
 }
@@ -951,10 +934,10 @@ namespace {
 // LDS addresses, so that neither takes arithmetic (the first two arrays end below 2^16, checked by the host).
 struct CellTables {
     uint32_t base;    // address of the codeword functions (c_1, c_2, c_3, c_0) [cell_used + 1]; the last never wins
-    uint32_t list;    // [cell_groups] groups of four addresses of functions; bit 0 of the first: last group of its list
+    uint32_t list;    // [cell_groups] groups of four addresses of functions, the first two ascending in the last group of a list
     uint32_t head;    // [n^3] u16 address of the box's first group
     uint32_t id;      // [cell_used] p' << 16 | s of the codeword
-    uint32_t mul;     // [24][32] u8: FoldTable
+    uint32_t mul;     // [kFolds][32] u8: FoldTable
     uint32_t sec;     // [S][4] the head's secondaries
     uint32_t end;
 };
@@ -966,7 +949,7 @@ __host__ __device__ inline CellTables cell_tables(const Geometry &g, uint32_t ba
     t.head = t.list + (uint32_t)g.cell_groups * 8u;
     t.id = t.head + (uint32_t)cell_head_bytes(g.cell_n);
     t.mul = t.id + (uint32_t)g.cell_used * 4u;
-    t.sec = t.mul + 24u * 32u;
+    t.sec = t.mul + (uint32_t)kFolds * 32u;
     t.end = t.sec + (uint32_t)g.S * 16u;
     return t;
 }
@@ -983,77 +966,82 @@ __device__ __forceinline__ T *lds_ptr(uint32_t address)
 
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 
-// Code word of the lane's chunk, as search_codeword returns it (called by all 64 lanes); live: the chunk is neither
-// flagged nor zero nor past the end.
-__device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellTables &ct, int lane, const half4_t xv,
-                                                  double r2, float r_f, bool live, int rq)
+// Code word of the lane's chunk x, as search_codeword returns it (called by all 64 lanes);
+// live: the wave's chunks that are neither flagged nor zero nor past the end.
+struct Chunk4 {
+    float x0, x1, x2, x3;
+};
+__device__ __forceinline__ double chunk_norm2(const Chunk4 &x)  // as of the fp16 values
 {
-    const float x0 = (float)xv[0], x1 = (float)xv[1], x2 = (float)xv[2], x3 = (float)xv[3];
-    // ---- fold: P_0 nearest to x.  An axis element when twice the largest |x_i| exceeds the sum (never for two at once) ----
-    const float a0 = fabsf(x0), a1 = fabsf(x1), a2 = fabsf(x2), a3 = fabsf(x3);
-    const float big = fmaxf(fmaxf(fmaxf(a0, a1), a2), a3);
-    const bool axis = 2.f * big > ((a0 + a1) + a2) + a3;
-    const float bound = axis ? big : 0.f, mag = axis ? 1.f : 0.5f;
-    const bool h0 = a0 >= bound, h1 = a1 >= bound, h2 = a2 >= bound, h3 = a3 >= bound;
-    const float p0 = h0 ? copysignf(mag, x0) : 0.f, p1 = h1 ? copysignf(mag, x1) : 0.f;
-    const float p2 = h2 ? copysignf(mag, x2) : 0.f, p3 = h3 ? copysignf(mag, x3) : 0.f;
-    const float w0 = fmaf(p3, x3, fmaf(p2, x2, fmaf(p1, x1, p0 * x0)));
-    const float w1 = fmaf(p3, x2, fmaf(-p2, x3, fmaf(-p1, x0, p0 * x1)));
-    const float w2 = fmaf(-p3, x1, fmaf(-p2, x0, fmaf(p1, x3, p0 * x2)));
-    const float w3 = fmaf(-p3, x0, fmaf(p2, x1, fmaf(-p1, x2, p0 * x3)));
-    const float inv = __builtin_amdgcn_rcpf(w0);
+    // opaque: rare branches use it, and what they have in common would be kept in registers for all of them
+    const double x0 = (double)opaque(x.x0), x1 = (double)opaque(x.x1), x2 = (double)opaque(x.x2), x3 = (double)opaque(x.x3);
+    return fma(x3, x3, fma(x2, x2, fma(x1, x1, x0 * x0)));
+}
+__device__ __forceinline__ bool chunk_nonfinite(const Chunk4 &x)
+{
+    auto field = [](float v) { return __float_as_uint(v) & 0x7f800000u; };
+    return max(max(field(x.x0), field(x.x1)), max(field(x.x2), field(x.x3))) == 0x7f800000u;
+}
+__device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellTables &ct, int lane, const Chunk4 x,
+                                                  unsigned long long live, int rq)
+{
+    // ---- fold: P_0 nearest to x, in twice its components.  An axis element when twice the largest |x_i| exceeds the sum
+    // (never for two at once); either way w_0 is the larger of the two ------------------------------------------------------
+    const float a0 = fabsf(x.x0), a1 = fabsf(x.x1), a2 = fabsf(x.x2), a3 = fabsf(x.x3);
+    const float big = fmaxf(fmaxf(fmaxf(a0, a1), a2), a3), sum = ((a0 + a1) + a2) + a3;
+    const bool axis = big + big > sum;
+    const float bound = axis ? big : 0.f, mag = axis ? 2.f : 1.f;
+    auto component = [&](float v) { return fabsf(v) >= bound ? copysignf(mag, v) : 0.f; };
+    const float p0 = component(x.x0), p1 = component(x.x1), p2 = component(x.x2), p3 = component(x.x3);
+    const float inv = __builtin_amdgcn_rcpf(fmaxf(big + big, sum));
+    const float w1 = fmaf(p3, x.x2, fmaf(-p2, x.x3, fmaf(-p1, x.x0, p0 * x.x1)));
+    const float w2 = fmaf(-p3, x.x1, fmaf(-p2, x.x0, fmaf(p1, x.x3, p0 * x.x2)));
+    const float w3 = fmaf(-p3, x.x0, fmaf(p2, x.x1, fmaf(-p1, x.x2, p0 * x.x3)));
     const float y1 = w1 * inv, y2 = w2 * inv, y3 = w3 * inv;
-    // ---- the box.  Shrunk about the centre, y stays inside the cube at either end; the last clamp is for inputs that break
+    const float f = fmaf(p3, 2.f, fmaf(p1, 0.5f, p2) + 0.25f * p0);  // exact
+    const uint32_t fold_row = (uint32_t)fmaf(f, 128.f, (float)(512u + ct.mul));
+    // ---- the box.  Shrunk about the centre, y stays inside the cube at either end; the last bound is for inputs that break
     // the contract (a zero chunk's 0 / 0 becomes 0, a corner box without a list) ----------------------------------------------
-    const float n = (float)g.cell_n, middle = 0.5f * n, hn = middle * kCellShrink;
-    const float i0 = floorf(fmaf(y1, hn, middle)), i1 = floorf(fmaf(y2, hn, middle)), i2 = floorf(fmaf(y3, hn, middle));
-    const uint32_t box = (uint32_t)__builtin_amdgcn_fmed3f(fmaf(fmaf(i0, n, i1), n, i2), 0.f, fmaf(n * n, n, -1.f));
+    const uint32_t n = (uint32_t)g.cell_n;
+    const float middle = 0.5f * (float)n, hn = middle * kCellShrink;
+    const uint32_t i0 = (uint32_t)fmaf(y1, hn, middle), i1 = (uint32_t)fmaf(y2, hn, middle), i2 = (uint32_t)fmaf(y3, hn, middle);
+    const uint32_t box = min(__umul24(i0, n * n) + __umul24(i1, n) + i2, n * n * n - 1u);
     uint32_t group = lds_at<uint16_t>(ct.head + 2u * box);
     // ---- best and runner-up of the list ----------------------------------------------------------------------------------
     float best = 0.f, second = 0.f;
     uint32_t at = ct.base;
-    uint2v e = lds_at<uint2v>(group);
-    for (;;) {
-        const bool last = (e.x & 1u) != 0u;
-        const uint32_t o[4] = {e.x & 0xfff0u, e.x >> 16, e.y & 0xffffu, e.y >> 16};
-        group += 8u;
-        e = lds_at<uint2v>(group);  // one past the last list is still inside the tables
-        float4_t f[4];
+    for (bool last = false; !last; group += 8u) {
+        const uint2v e = lds_at<uint2v>(group);
+        const uint32_t o[4] = {e.x & 0xffffu, e.x >> 16, e.y & 0xffffu, e.y >> 16};
+        last = o[0] <= o[1];
+        float4_t fn[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            f[i] = lds_at<float4_t>(o[i]);
+            fn[i] = lds_at<float4_t>(o[i]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float v = value_at(f[i], y1, y2, y3);
+            const float v = value_at(fn[i], y1, y2, y3);
             second = __builtin_amdgcn_fmed3f(v, best, second);  // second <= best
             if (v > best)
                 at = o[i];
             best = fmaxf(best, v);
         }
-        if (last)
-            break;
     }
-    const bool clear = best - second > kCellBand * best;  // false without a list
-    const uint32_t id = lds_at<uint32_t>(ct.id + ((at - ct.base) >> 2));
-    // packed signs of components 2, 0, 3, 1 in bits 0..3
-    const uint2 raw = __builtin_bit_cast(uint2, xv);
-    const uint32_t t = (raw.x & 0x80008000u) | ((raw.y >> 1) & 0x40004000u);
-    const uint32_t signs = ((t >> 14) & 3u) | (t >> 28);
-    const uint32_t slot = h3 ? 2u : h1 ? 3u : h0 ? 1u : 0u;
-    const uint32_t fold = axis ? 2u * slot + ((signs >> slot) & 1u) : 8u + signs;
-    uint32_t p = lds_at<uint8_t>(ct.mul + 32u * fold + (id >> 16));
+    unsigned long long todo = live & ballot(!(best * (1.f - kCellBand) > second));  // true without a list
+    const uint32_t id = lds_at<uint32_t>((at >> 2) + (ct.id - (ct.base >> 2)));
+    uint32_t p = lds_at<uint8_t>(fold_row + (id >> 16));
     uint32_t s = id & 0xffffu;
     // ---- the others over all secondaries in fp32 (as in search_codeword), one at a time (75 + 0.42 S instructions each) or,
     // where they are many (secondaries that repeat, lists that do not fit), every lane its own (26 S): two tensors with 8 heads
     // of 16384 rows in us, one at a time / every lane / matrix screen of short tensors: 16 secondaries twice 8 1033 / 154 / 117,
     // 64 within a cap of 0.05 712 / 343 / 205, 256 803 / 883 / 521, 256 twice 128 2312 / 1180 / 2666, 512 within 0.3 2440 / 1540
     // / 877 (a screen in this place, or behind it for what it leaves over, costs every other call 1 to 5 % or 4 us) ------------
-    const bool unclear = live && !clear;
-    unsigned long long todo = __ballot(unclear);
     if (todo) {
+        const bool unclear = of_mask(todo);
         const float *secl = lds_ptr<float>(ct.sec);
-        const Direction u = unit_direction(xv, r2, r_f);
-        const float u0 = opaque(u.u0), u1 = opaque(u.u1), u2 = opaque(u.u2), u3 = opaque(u.u3);
+        // as unit_direction, from the fp64 norm: ties fall the same way in every search
+        const float scale = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf((float)chunk_norm2(x))) * kOperandScale;
+        const float u0 = opaque(x.x0 * scale), u1 = opaque(x.x1 * scale), u2 = opaque(x.x2 * scale), u3 = opaque(x.x3 * scale);
         if (__builtin_expect_with_probability(__popcll(todo) > min(4 + g.S / 10, 30), false, 0.9999)) {
             todo = 0ull;
             float most = -1.f;
@@ -1089,7 +1077,7 @@ __device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellT
         const uint32_t pu = (uint32_t)nearest_primary(v0, v1, v2, v3, sc);
         p = unclear ? pu : p;
     }
-    return live ? ((uint32_t)rq << g.w_idx) | (__umul24(p, (uint32_t)g.S) + s) : 0u;
+    return of_mask(live) ? ((uint32_t)rq << g.w_idx) | (__umul24(p, (uint32_t)g.S) + s) : 0u;
 }
 
 // A head's index from the workspace into LDS: lists (entries k become addresses), boxes, and the functions of the
@@ -1107,7 +1095,7 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
     uint32_t *head = lds_ptr<uint32_t>(ct.head), *id = lds_ptr<uint32_t>(ct.id);
     for (int s = tid; s < g.S; s += kThreadsS)
         secl[s] = reinterpret_cast<const float4_t *>(sec_h)[s];
-    for (int i = tid; i < 24 * 32 / 4; i += kThreadsS)
+    for (int i = tid; i < kFolds * 32 / 4; i += kThreadsS)
         lds_ptr<uint32_t>(ct.mul)[i] = reinterpret_cast<const uint32_t *>(kFoldTable.at)[i];
     if (tid < 64) {  // exclusive prefix of the used bits, nw <= 6 * 64 words
         uint32_t w[6], sum = 0;
@@ -1169,7 +1157,9 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
     };
     for (int i = tid; i < n_groups; i += kThreadsS) {
         const uint2 raw = ix.list[i];
-        list[i] = make_uint2(address_of(raw.x & 0x7fffu) | ((raw.x >> 15) & 1u) | (address_of(raw.x >> 16) << 16),
+        const uint32_t a = address_of(raw.x & 0x7fffu), b = address_of(raw.x >> 16);
+        const uint32_t low = min(a, b), high = max(a, b);  // equal: pads
+        list[i] = make_uint2(raw.x & 0x8000u ? low | (high << 16) : high | (low << 16),
                              address_of(raw.y & 0xffffu) | (address_of(raw.y >> 16) << 16));
     }
     __syncthreads();
@@ -1202,16 +1192,18 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
     const EncodedPtrs enc = tn.enc;
     extern __shared__ float4_t cell_smem[];
     const CellTables ct = cell_tables(g, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float4_t *)cell_smem);
-    uint32_t *pack = lds_ptr<uint32_t>(ct.end);
-    uint32_t *rcnt = pack + kWaves * 64;  // pack: also the scratch of load_cells
+    uint2 *state = lds_ptr<uint2>(ct.end);                           // of a row: flag word, scale
+    uint32_t *pack = reinterpret_cast<uint32_t *>(state + kRows);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
     const int t0 = blockIdx.x * kRows;
-    load_cells<64 * kWaves>(g, ws, h, tn.sec + (size_t)h * g.S * 4, ct, pack);
+    load_cells<64 * kWaves>(g, ws, h, tn.sec + (size_t)h * g.S * 4, ct, reinterpret_cast<uint32_t *>(state));  // scratch
 
     const double thr = ws.thr[h];
+    // a squared norm in fp32 differs from the fp64 one by at most 3 * 2^-24 of it: outside these it decides
+    const float thr_sure = (float)thr * (1.f + 0x1p-21f), thr_perhaps = (float)thr * (1.f - 0x1p-21f);
     const double Lq = (double)((1 << g.b_r) - 1);
     const int n_c = kFull ? kChunksPerRow : g.n_c, row_words = kFull ? g.w : g.row_words;
     const int slot = kSlot ? kSlot : n_c;
@@ -1219,30 +1211,36 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
     const int rl = lane / slot, c = lane - rl * slot;  // the lane's row of the pass and chunk of the row
     const int n_rows = min(kRows, g.T - t0);         // >= 1 by the grid's size
     uint32_t *my_pack = pack + wv * 64;              // rows_pass * row_words <= 64 words: w <= 22 as S <= kScreenMaxS
-    const _Float16 *row = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * rows_pass + rl) * g.st;
+    const _Float16 *rows = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * rows_pass) * g.st;
     const int64_t row_step = (int64_t)(kWaves * rows_pass) * g.st;
+    const uint32_t own_chunk = 2u * (uint32_t)rl * (uint32_t)g.st + 8u * (uint32_t)c;  // kFull: bytes, below 2^32 (launch_search)
     const int64_t row0 = (int64_t)seg * g.T + t0;
     const float Lf = (float)Lq;
-    for (int r0 = wv * rows_pass; r0 < n_rows; r0 += kWaves * rows_pass, row += row_step) {  // wave-uniform
+    for (int r0 = wv * rows_pass; r0 < n_rows; r0 += kWaves * rows_pass, rows += row_step) {  // wave-uniform
         const int r = r0 + rl;
         const bool valid = (kFull || (rl < rows_pass && c < n_c)) && r < n_rows;
         half4_t xv = {0, 0, 0, 0};
-        if (valid)
-            xv = load_row_chunk<kFull>(row, c, g);
-        const double r2 = chunk_norm2(xv);
-        const bool flagged = valid && (r2 > thr);
-        const unsigned long long ballot = __ballot(flagged);
-        const uint32_t word = (uint32_t)(ballot >> ((unsigned)(rl * slot) & 63u)) &
-                              (kFull ? 0xffffffffu : (uint32_t)((1ull << n_c) - 1ull));
+        if (kFull)  // the second row past the end: the first once more
+            xv = load_chunk(reinterpret_cast<const _Float16 *>(reinterpret_cast<const char *>(rows) + (r0 + 1 < n_rows ? own_chunk : 8u * (uint32_t)c)));
+        else if (valid)
+            xv = load_row_chunk<false>(rows + (int64_t)rl * g.st, c, g);
+        const Chunk4 x = {opaque((float)xv[0]), opaque((float)xv[1]), opaque((float)xv[2]), opaque((float)xv[3])};
+        const float r2f = fmaf(x.x3, x.x3, fmaf(x.x2, x.x2, fmaf(x.x1, x.x1, x.x0 * x.x0)));  // squares are exact: three roundings
+        // Predicates of the whole wave are kept as masks: combined on the scalar unit, they cost no vector instruction.
+        unsigned long long flags = ballot(r2f > thr_sure);
+        if (flags != ballot(r2f > thr_perhaps))  // a ten-millionth of the chunks
+            flags = ballot(chunk_norm2(x) > thr);
+        if (!kFull)
+            flags &= ballot(valid);
+        const bool flagged = of_mask(flags);
         if (g.check_finite) {  // uniform
-            const bool bad = valid && chunk_nonfinite(xv);
-            if (__ballot(bad) != 0ull && lane == 0)
+            const bool bad = valid && chunk_nonfinite(x);
+            if (ballot(bad) != 0ull && lane == 0)
                 atomicOr(enc.status, HQMQ_STATUS_NONFINITE);
         }
-        // The row's scale, sigma_of_row_max of the largest r^2: rounding to fp32 is monotone, so the fp32 maximum decides
+        // The row's scale, sigma_of_row_max of the largest r^2: the fp32 maximum is within 3 * 2^-24 of the fp64 one and decides
         // unless its square root lies next to a rounding boundary; then the fp64 maximum is taken as well.
         // r^2 is 0 or at least 2^-48: the fp32 value is zero for a zero chunk only.
-        const float r2f = (float)r2;
         auto row_max = [&](auto v) {
             if (kSlot) {  // after each step the running maxima are uniform over a block twice as large, so the mirrors pair the right blocks
                 v = fmax(v, dpp_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
@@ -1257,31 +1255,32 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
             }
             return __shfl(v, lane - c, 64);
         };
-        const float rmax = row_max(flagged ? 0.f : r2f);
-        const float sf = __builtin_amdgcn_sqrtf(rmax);  // 1 ulp
-        uint16_t sigma16 = sf >= 65504.f ? (uint16_t)0x7bff : __builtin_bit_cast(uint16_t, (_Float16)sf);
-        if (__any(scale_unsure(rmax, sf))) {
-            const double exact = row_max(flagged ? 0.0 : r2);
-            if (scale_unsure(rmax, sf))
+        const float sf = fminf(__builtin_amdgcn_sqrtf(row_max(flagged ? 0.f : r2f)), 65504.f);  // 1 ulp
+        uint16_t sigma16 = __builtin_bit_cast(uint16_t, (_Float16)sf);
+        const bool unsure_scale = scale_unsure(sf);
+        if (ballot(unsure_scale)) {
+            const double exact = row_max(flagged ? 0.0 : chunk_norm2(x));
+            if (unsure_scale)
                 sigma16 = double_to_half_rne_sat(sqrt(exact));
         }
         const float r_f = __builtin_amdgcn_sqrtf(r2f);
-        const bool live = r2f != 0.f && valid && !flagged;
+        unsigned long long live = ballot(r2f != 0.f) & ~flags;
+        if (!kFull)
+            live &= ballot(valid);
         // radius_code
         int rq = 0;
         {
             const float q = fminf(r_f * Lf * __builtin_amdgcn_rcpf((float)__builtin_bit_cast(_Float16, sigma16)), Lf);
             const float whole = rintf(q);
-            const bool round = live && sigma16 != 0;
-            const bool unsure = round && fabsf(q - whole) > 0.5f - (6e-7f * Lf + 1e-6f);
-            rq = round ? (int)whole : 0;
-            if (__any(unsure)) {
-                if (unsure)
-                    rq = radius_code_exact(r2, sigma16, Lq);
+            rq = sigma16 != 0 ? (int)whole : 0;
+            const unsigned long long unsure = live & ballot(sigma16 != 0) & ballot(fabsf(q - whole) > 0.5f - (6e-7f * Lf + 1e-6f));
+            if (unsure) {
+                if (of_mask(unsure))
+                    rq = radius_code_exact(chunk_norm2(x), sigma16, Lq);
             }
         }
         my_pack[lane] = 0;  // after the previous pass's reads of it: LDS serves a wave in order
-        const uint32_t code = cell_codeword(g, ct, lane, xv, r2, r_f, live, rq);
+        const uint32_t code = cell_codeword(g, ct, lane, x, live, rq);
         wave_lds_sync();
         if (code) {
             const uint32_t bitpos = (uint32_t)c * g.w;
@@ -1293,17 +1292,25 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
         }
         wave_lds_sync();
         // the pass's rows are neighbours, and so are their code words
+        uint32_t *codes = enc.codes + (row0 + r0) * row_words;
         if (lane < min(rows_pass, n_rows - r0) * row_words)
-            enc.codes[(row0 + r0) * row_words + lane] = my_pack[lane];
-        if (valid && c == 0) {
-            enc.sigma[row0 + r] = sigma16;
-            enc.flags[row0 + r] = word;
-            rcnt[r] = __popc(word);
+            codes[(uint32_t)lane] = my_pack[lane];
+        if (kFull) {
+            const uint32_t word = of_mask(~0ull << 32) ? (uint32_t)(flags >> 32) : (uint32_t)flags;
+            if (of_mask(r0 + 1 < n_rows ? 1ull | 1ull << 32 : 1ull))
+                state[r] = make_uint2(word, sigma16);
+        } else if (valid && c == 0) {
+            state[r] = make_uint2((uint32_t)(flags >> ((unsigned)(rl * slot) & 63u)) & (uint32_t)((1ull << n_c) - 1ull), sigma16);
         }
     }
     __syncthreads();
+    for (int r = tid; r < n_rows; r += 64 * kWaves) {
+        const uint2 of = state[r];
+        enc.flags[row0 + r] = of.x;
+        enc.sigma[row0 + r] = (uint16_t)of.y;
+    }
     if (wv == 0)
-        write_row_offsets<kRows>(g, ws, enc, lane, seg, t0, rcnt);
+        write_row_offsets<kRows>(g, ws, enc, lane, seg, t0, state);
 }
 
 // The search kernels' dynamic LDS may exceed the 64 KiB a kernel gets by default: raises the limit
@@ -1381,12 +1388,13 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
     dim3 grid((g.T + g.search_rows - 1) / g.search_rows, g.B * g.H, (unsigned)n_tensors);
     const bool full = g.D == 4 * kChunksPerRow;
     if (g.cell_n > 0) {
+        const bool full_rows = full && g.st < (1ll << 29);  // 32-bit offsets inside a pass
         if (!cells_built)
             hipLaunchKernelGGL(k_cells, dim3(cell_blocks(g), g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
         const size_t lds_cells = cell_lds_bytes(g);
 #define HQMQ_LAUNCH_CELLS(R)                                                                                             \
     do {                                                                                                             \
-        if (full)                                                                                                    \
+        if (full_rows)                                                                                               \
             hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch);    \
         else if (g.n_c > 21)                                                                                         \
             hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);   \
