@@ -326,19 +326,20 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(Geometry g, DecodeBatch 
     }
 }
 
-// Decode for head dimensions other than 128 (rows of n_c = ceil(D / 4) <= 32 chunks, ceil(n_c w / 32)
-// code words each): the plain mapping, one lane per chunk slot, a 32-lane slot per row, the lanes
-// past the row's chunks idle.  Same arithmetic as k_decode; the elements of a last partial chunk that
-// lie past D are not written (the truncation of the paper's App. "Padding wrapper for d_h not
-// divisible by 4").
-// grid = (ceil(T / 64), B*H, tensors), block = 256: 8 rows per pass, 8 passes.
+// Decode for any head dimension and strides (rows of n_c = ceil(D / 4) <= 32 chunks, ceil(n_c w / 32) code words each): a
+// workgroup owns 64 rows of one (b, h) and takes their chunks as one flat list, one per lane.  Same arithmetic as k_decode;
+// the elements of a last partial chunk that lie past D are not written (the truncation of the paper's App. "Padding wrapper
+// for d_h not divisible by 4").  Bound by the latency of its loads: kGeneralBatch chunks of a lane are requested before the
+// first is used, then their outliers.  Two tensors with 8 heads of 32768 rows, in us, one row per half-wave and pass / now: D = 100
+// 54 / 40, D = 45 68 / 33, D = 126 76 / 50, D = 101 75 / 49 (batches of 2: 42, 32, 50, 51; of 8: 45, 38, 52, 53).
+// grid = (ceil(T / 64), B*H, tensors), block = 256.
 // dynamic LDS: prim [48][4] f32 | secl [S][4] f32
+constexpr int kGeneralBatch = 4;
 template <bool kPow2>
 __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeBatch batch)
 {
     const DecodeTensor &dt = batch.t[blockIdx.z];
     const uint64_t outlier_capacity = dt.outlier_capacity;
-    _Float16 *__restrict__ out = dt.out;
 
     extern __shared__ float lds[];
     float *prim = lds;
@@ -346,6 +347,37 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
 
     const int tid = threadIdx.x;
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
+    const int t0 = blockIdx.x * kGeneralRows;
+    const int n_chunks = min(kGeneralRows, g.T - t0) * g.n_c;  // >= 1 by the grid's size
+    const int64_t R0 = (int64_t)seg * g.T + t0;
+    const uint32_t *codes = dt.codes + R0 * g.row_words, *flags = dt.flags + R0, *row_off = dt.row_off + R0;
+    const uint16_t *sigmas = dt.sigma + R0;
+    _Float16 *out = dt.out + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t0 * g.st;
+    const bool pairs_ok = ((g.D | (int)g.sb | (int)g.sh | (int)g.st) & 1) == 0;
+    const uint32_t w = g.w, w_idx = g.w_idx;
+    const uint32_t code_mask = (1u << w) - 1u, idx_mask = (1u << w_idx) - 1u;
+    struct Fetched {
+        uint32_t d0, d1, word, off, c;
+        int r;
+        uint16_t sigma;
+    };
+    auto fetch = [&](int q) {
+        Fetched f;
+        q = min(q, n_chunks - 1);  // lanes past the end repeat the last chunk and store nothing
+        f.r = row_of_chunk(q, g);
+        f.c = (uint32_t)(q - f.r * g.n_c);
+        const uint32_t i0 = f.c * w >> 5, *words = codes + (uint32_t)f.r * (uint32_t)g.row_words;
+        f.d0 = words[i0];
+        f.d1 = words[min(i0 + 1u, (uint32_t)g.row_words - 1u)];  // a code that ends in the row's last word needs no other
+        f.word = flags[f.r];
+        f.off = row_off[f.r];
+        f.sigma = sigmas[f.r];
+        return f;
+    };
+    Fetched f[kGeneralBatch];
+#pragma unroll
+    for (int u = 0; u < kGeneralBatch; ++u)
+        f[u] = fetch(tid + u * kDecThreads);
     const float *sec_h = dt.sec + (size_t)h * g.S * 4;
     for (int s = tid; s < g.S; s += kDecThreads)
         *reinterpret_cast<float4_t *>(secl + 4 * s) = *reinterpret_cast<const float4_t *>(sec_h + 4 * s);
@@ -360,31 +392,19 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
     }
     __syncthreads();
 
-    const int c = tid & 31, rsub = tid >> 5;
-    if (c >= g.n_c)
-        return;
-    const uint32_t w = g.w, w_idx = g.w_idx;
-    const uint32_t bitpos = (uint32_t)c * w, i0 = bitpos >> 5, sh = bitpos & 31;
-    const uint32_t code_mask = (1u << w) - 1u, idx_mask = (1u << w_idx) - 1u;
-    for (int pass = 0; pass < kGeneralRows / 8; ++pass) {
-        const int t = blockIdx.x * kGeneralRows + pass * 8 + rsub;
-        if (t >= g.T)
-            break;  // later passes lie further past the end
-        const int64_t R = (int64_t)seg * g.T + t;
-        const uint32_t *words = dt.codes + R * g.row_words;
-        const uint32_t d0 = words[i0];
-        const uint32_t d1 = (i0 + 1 < (uint32_t)g.row_words) ? words[i0 + 1] : 0u;
-        const uint32_t code = __builtin_amdgcn_alignbit(d1, d0, sh) & code_mask;
-        const uint32_t word = dt.flags[R];
-        half4_t hv;
-        if ((word >> c) & 1u) {
-            const uint64_t pos = (uint64_t)dt.row_off[R] + __popc(word & ((1u << c) - 1u));
-            uint2 v = make_uint2(0u, 0u);
-            if (pos < outlier_capacity)
-                v = *reinterpret_cast<const uint2 *>(dt.outliers + 4 * pos);
-            hv = __builtin_bit_cast(half4_t, v);
-        } else {
-            const float sigma = (float)__builtin_bit_cast(_Float16, dt.sigma[R]);
+    for (int q0 = tid;;) {
+        uint2 pay[kGeneralBatch];
+#pragma unroll
+        for (int u = 0; u < kGeneralBatch; ++u) {
+            pay[u] = make_uint2(0u, 0u);
+            const uint64_t pos = (uint64_t)f[u].off + __popc(f[u].word & ((1u << f[u].c) - 1u));
+            if (((f[u].word >> f[u].c) & 1u) && pos < outlier_capacity)
+                pay[u] = *reinterpret_cast<const uint2 *>(dt.outliers + 4 * pos);
+        }
+#pragma unroll
+        for (int u = 0; u < kGeneralBatch; ++u) {
+            const uint32_t code = __builtin_amdgcn_alignbit(f[u].d1, f[u].d0, f[u].c * w & 31u) & code_mask;
+            const float sigma = (float)__builtin_bit_cast(_Float16, f[u].sigma);
             const uint32_t rq = code >> w_idx;
             uint32_t p, sidx;
             if (kPow2) {
@@ -409,19 +429,36 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
                 for (int i = 0; i < 4; ++i)
                     y[i] = __builtin_amdgcn_fmed3f(y[i], -65504.f, 65504.f);
             }
+            half4_t hv;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 hv[i] = (_Float16)y[i];
-        }
-        _Float16 *dst = out + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st + 4 * c;
-        if (g.vec_ok) {
-            *reinterpret_cast<uint2 *>(dst) = __builtin_bit_cast(uint2, hv);
-        } else {
+            if ((f[u].word >> f[u].c) & 1u)
+                hv = __builtin_bit_cast(half4_t, pay[u]);
+            if (q0 + u * kDecThreads < n_chunks) {
+                _Float16 *dst = out + (int64_t)f[u].r * g.st + 4 * f[u].c;
+                const int left = g.D - 4 * (int)f[u].c;  // elements of the row from this chunk on
+                if (g.vec_ok) {
+                    *reinterpret_cast<uint2 *>(dst) = __builtin_bit_cast(uint2, hv);
+                } else if (pairs_ok) {
+                    const uint2 v = __builtin_bit_cast(uint2, hv);
+                    reinterpret_cast<uint32_t *>(dst)[0] = v.x;
+                    if (left > 2)
+                        reinterpret_cast<uint32_t *>(dst)[1] = v.y;
+                } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (4 * c + e < g.D)
-                    dst[e] = hv[e];
+                    for (int e = 0; e < 4; ++e)
+                        if (e < left)
+                            dst[e] = hv[e];
+                }
+            }
         }
+        q0 += kGeneralBatch * kDecThreads;
+        if (q0 - tid >= n_chunks)  // uniform
+            break;
+#pragma unroll
+        for (int u = 0; u < kGeneralBatch; ++u)
+            f[u] = fetch(q0 + u * kDecThreads);
     }
 }
 

@@ -253,6 +253,32 @@ def test_other_head_dimensions_small(D, B, H, T, S, b_r):
     assert stats["outliers"] > 0
 
 
+@pytest.mark.parametrize("D,pitch,B,H,T,S", [
+    (2, 2, 1, 2, 513, 16), (6, 6, 2, 1, 65, 24), (6, 7, 1, 1, 64, 24), (80, 80, 1, 2, 65, 48), (100, 108, 1, 1, 1, 96), (126, 126, 1, 2, 63, 64),
+    (127, 128, 1, 1, 130, 33)])
+def test_decode_of_any_row_with_a_truncated_list(D, pitch, B, H, T, S):
+    """The decode that takes chunks of any row length one after the other: last lanes, rows and workgroups, elements stored by
+    chunks, pairs (even dimension and strides) or one by one, a third of the chunks flagged and the list cut in half (zeros
+    beyond it), nothing written past a row."""
+    x = torch.zeros(B, H, T, pitch, dtype=torch.float16)
+    x[..., :D] = _lognormal_tensor(B, H, T, seed=D + T, sigma_g=1.0, D=D)
+    sec_t, sec = _sec(4, H, S)
+    e = oracle.encode(_bits(x[..., :D].contiguous()), sec, b_r=5, Cmul=1.1)
+    keep = e.outliers.reshape(-1, 4).shape[0] // 2
+    bufs = upload_encoded(e, DEV)
+    bufs = hq.EncodedBuffers(codes=bufs.codes, sigma=bufs.sigma, flags=bufs.flags, row_off=bufs.row_off,
+                             outliers=bufs.outliers[:keep].contiguous(), n_outliers=bufs.n_outliers, status=bufs.status)
+    cut = e.outliers.reshape(-1, 4).copy()
+    cut[keep:] = 0
+    want, r_hat = oracle.decode(e.codes, e.sigma, e.flags, e.row_off, cut, sec, B, H, T, 5, True, D=D)
+    out = torch.full((B, H, T, pitch), 7.0, dtype=torch.float16, device=DEV)
+    hq.hqmq_decode(hq.params_for(out[..., :D], S, 5), bufs, sec_t.to(DEV), out[..., :D])
+    torch.cuda.synchronize()
+    got = out.cpu()
+    assert (got[..., D:] == 7.0).all()
+    compare_decode(_bits(got[..., :D].contiguous()).reshape(want.shape), want, r_hat, e.flag)
+
+
 @pytest.mark.parametrize("D,pitch", [(45, 53), (96, 104), (64, 64 + 8), (3, 4)])
 def test_other_head_dimensions_touch_nothing_past_the_row(D, pitch):
     """Rows stored with a pitch larger than D: encode must not read, and decode must not write, the
