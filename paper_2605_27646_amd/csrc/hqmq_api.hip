@@ -174,6 +174,15 @@ static int screen_rows(const Geometry &g, int n)
     return large ? kSearchRowsLarge : kSearchRowsSmall;
 }
 
+// Rows of a generation step with thresholds known beforehand that one launch encodes and lists (k_append): up to 4 of up to
+// 64 (batch entry, head) segments.  Two launches per 32 tensors / one per 64, in us, S = 256: 64 tensors of 64 rows (8 batch
+// entries of 8 heads) 38 / 31, of 32 rows 36 / 19, 16 of 64 rows 20 / 17; but of 128 rows, whose scores fill the chip and
+// which every workgroup would count, 16 tensors 21 / 23, 64 tensors 61 / 64.
+static bool append_applies(const Geometry &g)
+{
+    return g.A16 > 0 && g.T <= 4 && (int64_t)g.B * g.H * g.T <= kAppendRows;
+}
+
 struct WorkspaceLayout {
     uint64_t state, thr, hist0, hist1, plan, cand, block_sum, block_pre, aop, total;
 };
@@ -354,6 +363,50 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             return hipEventRecord(static_cast<hipEvent_t>(phase_events[i]), st);
         return hipSuccess;
     };
+    // the pointers of tensor i, as the launch of a generation step's rows takes them: 48 bits each
+    auto append_parts = [&](int32_t i, uint64_t (&at)[kAppParts]) {
+        const void *const parts[kAppParts] = {x_dev[i],     sec_dev[i],       thr_given ? thr_given[i] : nullptr, enc[i].codes,
+                                              enc[i].sigma, enc[i].flags,     enc[i].row_off,
+                                              enc[i].outliers, enc[i].n_outliers, enc[i].status};
+        uint64_t all = 0;
+        for (int p = 0; p < kAppParts; ++p)
+            all |= at[p] = reinterpret_cast<uintptr_t>(parts[p]);
+        return all >> 48 == 0;
+    };
+    bool append = (no_outliers || thr_given != nullptr) && append_applies(g);
+    for (int32_t i = 0; i < n_tensors && append; ++i) {
+        uint64_t at[kAppParts];
+        append = append_parts(i, at);
+    }
+    if (append) {
+        AppendShape shape = {g.B, g.H, g.T, g.D, g.n_c, g.n_c_magic, g.row_words, g.vec_ok, g.S, g.b_r, g.w_idx, g.w, g.check_finite,
+                             0, 0, g.sb, g.sh, g.st, static_cast<char *>(workspace_dev) + l.thr, l.total};
+        hipError_t err = mark(0);
+        if (err == hipSuccess)
+            err = mark(1);
+        for (int32_t first = 0; first < n_tensors && err == hipSuccess; first += kMaxAppendBatch) {
+            shape.n_tensors = n_tensors - first < kMaxAppendBatch ? n_tensors - first : kMaxAppendBatch;
+            AppendBatch batch;
+            for (int i = 0; i < shape.n_tensors; ++i) {
+                uint64_t at[kAppParts];
+                append_parts(first + i, at);
+                for (int p = 0; p < kAppParts; ++p) {
+                    batch.low[p][i] = (uint32_t)at[p];
+                    batch.high[p][i] = (uint16_t)(at[p] >> 32);
+                }
+                batch.capacity[i] = (uint16_t)(outlier_capacity[first + i] < (uint64_t)kAppendChunks ? outlier_capacity[first + i] : kAppendChunks);
+            }
+            // a workgroup per head for all batch entries where these fill the chip: 64 tensors of 8 batch entries and 8 heads,
+            // S = 64, in 19 us instead of 41
+            shape.by_head = g.B > 1 && (int64_t)shape.n_tensors * g.H >= 256;
+            err = launch_append(shape, batch, st);
+        }
+        if (err == hipSuccess)
+            err = mark(2);
+        if (err == hipSuccess)
+            err = mark(3);
+        return err == hipSuccess ? HQMQ_OK : hip_failed(err);
+    }
     for (int32_t first = 0; first < n_tensors; first += kMaxEncodeBatch) {
         const int n = (n_tensors - first < kMaxEncodeBatch) ? n_tensors - first : kMaxEncodeBatch;
         EncodeBatch batch;

@@ -199,6 +199,28 @@ struct EncodeBatch {
     EncodeTensor t[kMaxEncodeBatch];
 };
 
+// The rows of one generation step, thresholds known: up to 64 tensors (32 layers' K and V) in one launch.  Their pointers are
+// kept as 48 bits each, so that they fit the 4 KiB of kernel arguments, and the shape as what such a launch needs of it.
+constexpr int kMaxAppendBatch = 64;
+constexpr int kAppendRows = 64;      // of a tensor, at most
+constexpr int kAppendChunks = kAppendRows * kChunksPerRow;
+enum AppendPart { kAppX, kAppSec, kAppThr, kAppCodes, kAppSigma, kAppFlags, kAppRowOff, kAppOutliers, kAppCounts, kAppStatus, kAppParts };
+struct AppendShape {
+    int32_t B, H, T, D, n_c;
+    uint32_t n_c_magic;
+    int32_t row_words, vec_ok, S, b_r, w_idx, w, check_finite;
+    int32_t n_tensors, by_head;
+    int64_t sb, sh, st;
+    char *thr_out;        // where hqmq_thresholds finds the first tensor's thresholds,
+    uint64_t thr_stride;  // those of tensor i + 1 this far behind those of i; of the last kMaxEncodeBatch tensors, slice i mod that
+};
+struct AppendBatch {
+    uint32_t low[kAppParts][kMaxAppendBatch];
+    uint16_t high[kAppParts][kMaxAppendBatch];
+    uint16_t capacity[kMaxAppendBatch];  // of the outlier list, at most kAppendChunks
+};
+static_assert(sizeof(AppendShape) + sizeof(AppendBatch) <= 4096, "kernel arguments");
+
 __device__ __forceinline__ Workspace carve_workspace(char *base, const WorkspaceOffsets &o)
 {
     Workspace ws;
@@ -302,8 +324,8 @@ __device__ __forceinline__ half4_t load_chunk(const _Float16 *p)
 // every chunk 8-byte aligned) is the plain vector load.  Otherwise lanes past the row's chunks, and
 // the elements past D inside the last chunk, read as +0: the zero padding of a head whose dimension
 // is not a multiple of 4 (paper App. "Padding wrapper for d_h not divisible by 4").
-template <bool kFull>
-__device__ __forceinline__ half4_t load_row_chunk(const _Float16 *row, int c, const Geometry &g)
+template <bool kFull, typename Shape>
+__device__ __forceinline__ half4_t load_row_chunk(const _Float16 *row, int c, const Shape &g)
 {
     if (kFull)
         return load_chunk(row + 4 * c);
@@ -322,7 +344,8 @@ __device__ __forceinline__ half4_t load_row_chunk(const _Float16 *row, int c, co
 }
 
 // q / n_c for a flat chunk index q < 2^27 (one chunk per row: the multiplier would not fit 32 bits).
-__device__ __forceinline__ int row_of_chunk(int q, const Geometry &g)
+template <typename Shape>
+__device__ __forceinline__ int row_of_chunk(int q, const Shape &g)
 {
     return g.n_c == 1 ? q : (int)__umulhi((uint32_t)q, g.n_c_magic);
 }
@@ -355,6 +378,7 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
 bool search_fused_available(const Geometry &g);  // launch_search_fused has a kernel for this shape
 hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                                hipStream_t stream);
+hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStream_t stream);
 hipError_t launch_outlier_list_small(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch,
                                      int n_tensors, hipStream_t stream);
 hipError_t launch_outlier_list(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,

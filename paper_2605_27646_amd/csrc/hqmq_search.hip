@@ -853,6 +853,229 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
 }
 
 // ---------------------------------------------------------------------------------------------------------------
+// The rows that a generation step appends, thresholds known beforehand (or none): everything in one launch.
+// Workgroup (segment, tensor) encodes the T rows of one (batch entry, head), or of a head in all batch entries, two at a time: all waves hold the same 64 chunks
+// (a single row: its 32 chunks twice) and score a share of the secondaries each in fp32, which for so few rows is less work
+// than the operand tables of a matrix screen (3840 vector instructions a row at S = 256, one operand table: 1920 and the
+// screen).  The best of the shares, the lowest secondary on exact ties, is what the other searches find.
+// The outlier list needs the outliers of the rows before a workgroup's, of other heads and batch entries: every workgroup
+// counts those of the whole tensor itself (at most kAppendChunks chunks, four loads a thread in flight), so that no
+// second launch and no order among workgroups is needed.
+// Measured with 64 tensors of 8 heads, S = 256, in us, four launches (operand tables, screen and a list kernel for 32 tensors
+// each) / now: one row per head 27 / 9, four rows 36 / 19, four batch entries 35 / 19, eight 38 / 31; two tensors 14.7 / 8.4.
+// Bound by VALU issue from some thousand rows on and by the call's latency below.
+// grid = (B * H, or H by head, tensors), block = 512.
+// ---------------------------------------------------------------------------------------------------------------
+constexpr int kAppendWaves = 8, kAppendThreads = 64 * kAppendWaves;
+template <bool kFull>
+__global__ __launch_bounds__(kAppendThreads) void k_append(AppendShape g, AppendBatch batch)
+{
+    const int tensor = blockIdx.y;
+    auto part = [&](AppendPart p) { return ((uintptr_t)batch.high[p][tensor] << 32) | batch.low[p][tensor]; };
+    const _Float16 *x = reinterpret_cast<const _Float16 *>(part(kAppX));
+    const double *thr_given = reinterpret_cast<const double *>(part(kAppThr));
+    const double never = __longlong_as_double(0x7ff0000000000000LL);
+
+    __shared__ float4_t secl[kScreenMaxS];
+    __shared__ uint32_t count[kAppendRows], any_bad;
+    __shared__ float best_of[kAppendWaves][64];
+    __shared__ int s_of[kAppendWaves][64];
+    __shared__ uint32_t pack[64];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = g.by_head ? 0 : blockIdx.x / g.H, h = blockIdx.x - b * g.H;
+    const int n_here = g.by_head ? g.B * g.T : g.T;  // rows of this workgroup: of all batch entries, or of one
+    const int c = lane & 31, half = lane >> 5;
+    const int n_rows = g.B * g.H * g.T, n_chunks = n_rows * g.n_c;
+    const bool in_row = kFull || c < g.n_c;
+    auto load_own = [&](int v, int &R) {  // chunk c of the workgroup's row v, and its linear row
+        const int bb = g.by_head ? v / g.T : b, t = g.by_head ? v - bb * g.T : v;
+        R = (bb * g.H + h) * g.T + t;
+        half4_t xv = {0, 0, 0, 0};
+        if (in_row)
+            xv = load_row_chunk<kFull>(x + (int64_t)bb * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, c, g);
+        return xv;
+    };
+
+    // ---- requested first: the first rows, the secondaries, the tensor's chunks for the count ---------------------------
+    int R;
+    half4_t xv = load_own(min(half, n_here - 1), R);
+    float4_t q_own = {0.f, 0.f, 0.f, 0.f};
+    if (tid < g.S)
+        q_own = reinterpret_cast<const float4_t *>(part(kAppSec))[(size_t)h * g.S + tid];
+    const double thr = thr_given ? thr_given[h] : never;
+    const bool counts = thr_given != nullptr || g.check_finite != 0;  // uniform
+    constexpr int kLoads = kAppendChunks / kAppendThreads;
+    half4_t v[kLoads];
+    double thr_of[kLoads];
+    int row_of[kLoads];
+    if (counts) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int q = tid + u * kAppendThreads;
+            v[u] = half4_t{0, 0, 0, 0};
+            thr_of[u] = never;
+            row_of[u] = 0;
+            if (u * kAppendThreads < n_chunks && q < n_chunks) {
+                const int r = row_of_chunk(q, g), sg = r / g.T, bb = sg / g.H, hh = sg - bb * g.H;
+                row_of[u] = r;
+                v[u] = load_row_chunk<kFull>(x + (int64_t)bb * g.sb + (int64_t)hh * g.sh + (int64_t)(r - sg * g.T) * g.st,
+                                             q - r * g.n_c, g);
+                if (thr_given)
+                    thr_of[u] = thr_given[hh];
+            }
+        }
+    }
+    if (tid < kAppendRows)
+        count[tid] = 0;
+    if (tid == 0)
+        any_bad = 0;
+    if (tid < g.S)
+        secl[tid] = q_own;
+    __syncthreads();
+    if (counts) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            if (u * kAppendThreads < n_chunks) {  // uniform; past the end: zeros that nothing flags
+                if (chunk_norm2(v[u]) > thr_of[u])
+                    atomicAdd(&count[row_of[u]], 1u);
+                if (g.check_finite && chunk_nonfinite(v[u]))
+                    any_bad = 1u;
+            }
+        }
+    }
+    __syncthreads();
+    // ---- wave 0: where each row's outliers start in the list, over the counts; totals -------------------------------------
+    if (wv == 0) {
+        static_assert(kAppendRows == 64, "a lane per row");
+        const uint32_t mine = count[lane], inc = wave_scan(mine), total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        uint32_t *n_outliers = reinterpret_cast<uint32_t *>(part(kAppCounts));
+        if (b == 0) {
+            uint32_t of_head = 0;
+            for (int i = lane; i < g.B * g.T; i += 64) {
+                const int bb = i / g.T;
+                of_head += count[(bb * g.H + h) * g.T + i - bb * g.T];
+            }
+            of_head = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(of_head), 63);
+            if (lane == 0) {
+                n_outliers[h] = of_head;
+                if (tensor + kMaxEncodeBatch >= g.n_tensors)
+                    reinterpret_cast<double *>(g.thr_out + (uint64_t)(tensor % kMaxEncodeBatch) * g.thr_stride)[h] = thr;
+            }
+        }
+        if (blockIdx.x == 0 && lane == 0) {
+            n_outliers[g.H] = total;
+            reinterpret_cast<uint32_t *>(part(kAppRowOff))[n_rows] = total;
+            *reinterpret_cast<uint32_t *>(part(kAppStatus)) = (total > (uint32_t)batch.capacity[tensor] ? HQMQ_STATUS_OUTLIER_OVERFLOW : 0u) |
+                                                              (any_bad ? HQMQ_STATUS_NONFINITE : 0u);
+        }
+        wave_lds_sync();
+        count[lane] = inc - mine;
+        wave_lds_sync();
+    }
+
+    const double Lq = (double)((1 << g.b_r) - 1);
+    for (int v0 = 0; v0 < n_here; v0 += 2) {
+        const bool single = v0 + 1 == n_here;  // uniform: both halves hold the same row
+        if (v0 > 0)
+            xv = load_own(min(v0 + half, n_here - 1), R);
+        const double r2 = chunk_norm2(xv);
+        const float r_f = __builtin_amdgcn_sqrtf((float)r2);
+        const Direction u = unit_direction(xv, r2, r_f);
+        const float u0 = opaque(u.u0), u1 = opaque(u.u1), u2 = opaque(u.u2), u3 = opaque(u.u3);
+        // this lane's share of the secondaries
+        const int share = single ? 2 * wv + half : wv, shares = single ? 2 * kAppendWaves : kAppendWaves;
+        const int per = (g.S + shares - 1) / shares, s0 = share * per;
+        float best = -1.f;
+        int s_best = 0;
+#pragma unroll 4
+        for (int j = 0; j < per; ++j) {
+            const int s = min(s0 + j, g.S - 1);
+            float v0, v1, v2, v3;
+            const float sc = score_secondary(reinterpret_cast<const float *>(secl + s), u0, u1, u2, u3, v0, v1, v2, v3);
+            s_best = sc > best ? s : s_best;
+            best = fmaxf(best, sc);
+        }
+        if (v0 > 0)
+            __syncthreads();  // wave 0 has read the shares of the rows before
+        best_of[wv][lane] = best;
+        s_of[wv][lane] = s_best;
+        __syncthreads();
+        if (wv != 0)
+            continue;
+        // ---- wave 0: the best of the shares (ascending secondaries), and all that is written ------------------------------
+        best = -1.f;
+#pragma unroll
+        for (int k = 0; k < kAppendWaves; ++k) {
+            const int l = single ? c : lane;
+            float sc = best_of[k][l];
+            int s = s_of[k][l];
+            s_best = sc > best ? s : s_best;
+            best = fmaxf(best, sc);
+            if (single) {
+                sc = best_of[k][32 + c];
+                s = s_of[k][32 + c];
+                s_best = sc > best ? s : s_best;
+                best = fmaxf(best, sc);
+            }
+        }
+        const bool valid = in_row && (!single || half == 0);
+        const bool flagged = valid && r2 > thr;
+        const unsigned long long flags = ballot(flagged);
+        const uint32_t word = half ? (uint32_t)(flags >> 32) : (uint32_t)flags;
+        double rmax = flagged ? 0.0 : r2;
+        rmax = fmax(rmax, dpp_move_f64<0xB1>(rmax));   // quad_perm [1, 0, 3, 2]
+        rmax = fmax(rmax, dpp_move_f64<0x4E>(rmax));   // quad_perm [2, 3, 0, 1]
+        rmax = fmax(rmax, dpp_move_f64<0x141>(rmax));  // row_half_mirror
+        rmax = fmax(rmax, dpp_move_f64<0x140>(rmax));  // row_mirror
+        rmax = fmax(rmax, __shfl_xor(rmax, 16, 64));
+        const uint16_t sigma16 = sigma_of_row_max(rmax);
+        const int rq = radius_code(r2, r_f, sigma16, Lq);
+        uint32_t code = 0;
+        if (valid && !flagged && r2 != 0.0) {
+            float v0, v1, v2, v3, sc;
+            const int s = min(s_best, g.S - 1);
+            (void)score_secondary(reinterpret_cast<const float *>(secl + s), u0, u1, u2, u3, v0, v1, v2, v3);
+            code = ((uint32_t)rq << g.w_idx) | (uint32_t)(nearest_primary(v0, v1, v2, v3, sc) * g.S + s);
+        }
+        pack[lane] = 0;
+        wave_lds_sync();
+        if (code) {
+            const uint32_t bitpos = (uint32_t)c * g.w, sh = bitpos & 31;
+            uint32_t *d0 = pack + 32 * half + (bitpos >> 5);
+            atomicOr(d0, code << sh);
+            if (sh + g.w > 32)
+                atomicOr(d0 + 1, code >> (32 - sh));
+        }
+        wave_lds_sync();
+        const uint32_t off = count[R];
+        if (!single || half == 0) {
+            if (c < g.row_words)
+                reinterpret_cast<uint32_t *>(part(kAppCodes))[R * g.row_words + c] = pack[lane];
+            if (c == 0) {
+                reinterpret_cast<uint16_t *>(part(kAppSigma))[R] = sigma16;
+                reinterpret_cast<uint32_t *>(part(kAppFlags))[R] = word;
+                reinterpret_cast<uint32_t *>(part(kAppRowOff))[R] = off;
+            }
+            const uint32_t pos = off + (uint32_t)__popc(word & ((1u << c) - 1u));
+            if (flagged && pos < (uint32_t)batch.capacity[tensor])
+                reinterpret_cast<uint2 *>(part(kAppOutliers))[pos] = __builtin_bit_cast(uint2, xv);
+        }
+    }
+}
+
+hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(g.by_head ? g.H : g.B * g.H), (unsigned)g.n_tensors);
+    if (g.D == 4 * kChunksPerRow)
+        hipLaunchKernelGGL(k_append<true>, grid, dim3(kAppendThreads), 0, stream, g, batch);
+    else
+        hipLaunchKernelGGL(k_append<false>, grid, dim3(kAppendThreads), 0, stream, g, batch);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------------------------
 // The search of long tensors: point location instead of a scan over the secondaries.
 //
 // Folding.  The score of codeword P_p q_s is <u, P_p q_s> = <conj(P_0) u, P_p' q_s> with P_p = P_0 P_p' for any P_0 of

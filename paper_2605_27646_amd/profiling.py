@@ -68,8 +68,7 @@ def main(raw: str, wl: str) -> None:
 A step is {groups} hqmq_encode_batch call(s) and one hqmq_decode_batch call; every kernel launch covers {per_launch:g} tensors
 (blockIdx.z = tensor).""" + ("""  After the timed steps bench.py runs its fused-attention extra (6 passes of one
 hqmq_attend per layer, 4 query heads per kv head).""" if has_att else "") + ("""  Then its appended-token extra: 53 encodes of the
-one-token tensors of a generation step with supplied thresholds (the fused search kernel `k_search<.., true, ..>` or
-`k_search_flat<.., true, ..>` and `k_list_small`, two launches of 32 tensors each per encode).""" if "append" in d else "") + f"""
+one-token tensors of a generation step with supplied thresholds (`k_append`, one launch of 64 tensors per encode).""" if "append" in d else "") + f"""
 
 command (run from /tmp with TMPDIR=/tmp):
   rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o trace -- python3 bench.py --workload {wl} --steps 3 --warmup 1 --no-cpu-baseline
@@ -101,7 +100,7 @@ bench.py line of the same build (python bench.py --workload {wl}; {d['warmup']} 
     if "append" in d:
         apd = d["append"]
         out.append(f"  appended-token extra: {apd['us_per_step']:.1f} us for the {apd['tensors']} tensors {apd['shape']} of one generation step "
-                   f"(hqmq_encode_batch with supplied thresholds: the fused search kernel and k_list_small, one launch each per 32 tensors)")
+                   f"(hqmq_encode_batch with supplied thresholds: k_append, one launch per 64 tensors)")
     if "cpu_baseline" in d:
         cb = d["cpu_baseline"]
         out.append(f"  cpu_baseline (the oracle, {cb['cores']} threads, {cb['sample']}): {cb['value']:.3e} elems/s; "

@@ -1218,6 +1218,76 @@ def test_batched_incremental_encode_equals_single_calls():
         assert torch.equal(a.outliers[:total].view(torch.int16), b.outliers[:total].view(torch.int16))
 
 
+@pytest.mark.parametrize("n,B,H,T,D,S,b_r", [
+    (65, 1, 8, 1, 128, 256, 6),   # a second launch, for one tensor; one row per workgroup
+    (33, 8, 8, 1, 128, 16, 6),    # a workgroup per head for eight batch entries; 64 rows
+    (64, 3, 4, 3, 100, 33, 4),    # ... an odd number of rows; 25 chunks per row
+    (2, 16, 1, 4, 45, 5, 3),      # a partial last chunk, fewer secondaries than shares
+    (1, 1, 64, 1, 64, 512, 8),    # the most heads and secondaries
+    (3, 1, 16, 4, 3, 1, 6),       # one partial chunk per row
+    (2, 5, 13, 1, 128, 40, 6),    # 65 rows: two launches
+    (2, 8, 9, 1, 128, 24, 6),     # 72 rows: two launches, a workgroup per head
+])
+def test_rows_of_a_generation_step(n, B, H, T, D, S, b_r):
+    """Up to 64 rows per tensor with thresholds known beforehand, up to 64 tensors in one launch: against the oracle for some
+    tensors, with lists too short for their outliers, thresholds read back from every slice of the workspace, extraction off,
+    and a non-finite value in the tensor's last row reported."""
+    nc = -(-D // 4)
+    cb = hq.hqmq_build_codebooks(9, n, H, S)
+    xs, secs, thrs, es = [], [], [], {}
+    for i in range(n):
+        x = _lognormal_tensor(B, H, 8, seed=900 + i, sigma_g=0.9, D=D)[:, :, :T].contiguous()
+        r2 = oracle.encode(_bits(x), cb[i, 0].contiguous().numpy(), b_r=b_r, use_outliers=False).r2 if i == 0 else r2
+        thr = np.array([np.quantile(r2.reshape(B, H, T * nc)[:, h], 0.7) for h in range(H)]) * (1.0 + 0.01 * i)
+        if i in (0, 31, n - 1):
+            es[i] = oracle.encode(_bits(x), cb[i, 0].contiguous().numpy(), b_r=b_r, thresholds=thr)
+        xs.append(x.to(DEV)), secs.append(cb[i, 0].contiguous().to(DEV)), thrs.append(torch.from_numpy(thr).to(DEV))
+    params = hq.params_for(xs[0], S, b_r)
+    full = B * H * T * nc
+
+    def run(flags, caps, thresholds):
+        p = hq.params_for(xs[0], S, b_r, flags=flags)
+        encs = [hq.alloc_encoded(p, DEV, outlier_capacity=c) for c in caps]
+        ws = hq.alloc_batch_workspace(p, n, DEV)
+        ws.fill_(0x5A)
+        for b in encs:
+            for t in (b.codes, b.flags, b.row_off, b.n_outliers, b.status):
+                t.fill_(-1)
+            b.outliers.fill_(7.0)
+        batch = hq.EncodeBatch(p, xs, secs, encs, ws)
+        if thresholds:
+            hq.hqmq_encode_batch_given_thresholds(batch, thrs)
+        else:
+            hq.hqmq_encode_batch(batch)
+        torch.cuda.synchronize()
+        return encs, ws
+
+    encs, ws = run(hq.HQMQ_FLAG_CHECK_FINITE, [full if i % 2 == 0 else 1 for i in range(n)], True)
+    from gpu_util import GpuEncoded
+    for i, e in es.items():
+        b = encs[i]
+        n_out = b.n_outliers.cpu().numpy().view(np.uint32)
+        kept = min(int(n_out[-1]), b.outliers.shape[0])
+        assert np.array_equal(n_out, e.n_out) and int(b.status.item()) == (hq.HQMQ_STATUS_OUTLIER_OVERFLOW if int(n_out[-1]) > kept else 0)
+        whole = e.outliers.reshape(-1, 4)
+        assert np.array_equal(b.outliers[:kept].cpu().numpy().view(np.uint16), whole[:kept])
+        g = GpuEncoded(params, b, b.codes.cpu().numpy().view(np.uint32), b.sigma.cpu().numpy().view(np.uint16),
+                       b.flags.cpu().numpy().view(np.uint32), b.row_off.cpu().numpy().view(np.uint32), n_out, whole, 0)
+        compare_encode(g, e, _bits(xs[i].cpu()), secs[i].cpu().numpy())
+    for i in range(n):
+        if i + 32 >= n:
+            assert torch.equal(hq.hqmq_thresholds(params, ws, i % 32), thrs[i])
+    plain, _ = run(hq.HQMQ_FLAG_NO_OUTLIERS, [0] * n, False)
+    want = oracle.encode(_bits(xs[-1].cpu()), secs[-1].cpu().numpy(), b_r=b_r, use_outliers=False)
+    assert np.array_equal(plain[-1].sigma.cpu().numpy().view(np.uint16), want.sigma)
+    assert int(plain[-1].n_outliers.abs().sum()) == 0 and int(plain[-1].row_off.abs().sum()) == 0 and int(plain[-1].status.item()) == 0
+    xs[-1][-1, -1, -1, -1] = float("nan")
+    for flags, thresholds in ((hq.HQMQ_FLAG_CHECK_FINITE, True), (hq.HQMQ_FLAG_CHECK_FINITE | hq.HQMQ_FLAG_NO_OUTLIERS, False)):
+        encs, _ = run(flags, [full] * n, thresholds)
+        assert int(encs[-1].status.item()) == hq.HQMQ_STATUS_NONFINITE
+        assert n == 1 or int(encs[0].status.item()) == 0
+
+
 @pytest.mark.parametrize("D", [128, 96])
 def test_check_finite_flag_reports_infinities_and_nans(D):
     """The paper does not define the encode of a non-finite value; the library's contract is a status bit
