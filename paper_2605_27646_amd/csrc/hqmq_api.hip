@@ -171,7 +171,21 @@ static int screen_rows(const Geometry &g, int n)
     const int64_t enough = 192 * g.n_c > 512 ? 192 * g.n_c : 512;
     const bool large = g.n_c < kChunksPerRow && g.search_rows == kSearchRowsLarge && blocks >= enough &&
                        search_waves_for(g.S16, g.A16, g.D, g.row_words, kSearchRowsLarge) == 4;
-    return large ? kSearchRowsLarge : kSearchRowsSmall;
+    if (large)
+        return kSearchRowsLarge;
+    // Few workgroups: down to 8 rows each, while a launch then has at most 2048 and two waves still get a pass of 64 chunks.
+    // Whole encodes with 64 / 32 / 16 / 8 rows in us, 8 heads of 128 elements: S = 16, T = 1024 38 / 31 / 28 / 28, T = 2500
+    // 49 / 45 / 43 / 47 (2504 workgroups); S = 256, T = 256 64 / 42 / 31 / 25; S = 64, 8 tensors, T = 1000 71 / 68 / 68 / 69;
+    // D = 45, S = 48, 2 tensors, T = 900 43 / 42 / 40 / 45 (96 chunks in the last).
+    int rows = kSearchRowsSmall;
+    for (int half = rows / 2; half >= 8; half /= 2) {
+        const int64_t wgs = (int64_t)n * g.B * g.H * ((g.T + half - 1) / half);
+        const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, half);
+        if (wgs > 2048 || half * g.n_c < 128 || half < 2 * waves)
+            break;
+        rows = half;
+    }
+    return rows;
 }
 
 // Rows of a generation step with thresholds known beforehand that one launch encodes and lists (k_append): up to 4 of up to
@@ -470,7 +484,7 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             // histograms' memory, which the select is done with (8 bytes per workgroup, 32 KiB per head).  They fit: fewer
             // rows are taken only while a launch has under 512 workgroups of 256 rows (index; screen of rows of one chunk),
             // or under 3 << 21 chunks per head times S + 32 (screen of others: such workspaces start at 2048 rows, and the
-            // rows of one segment then reach the index rule's 2^17).
+            // rows of one segment then reach the index rule's 2^17), or at most 2048 workgroups (screen of under 64 rows).
             const uint64_t bytes = align_up((uint64_t)g.B * g.H * gs.n_search_blocks_per_seg * 4, 256);
             if (2 * bytes > (uint64_t)g.H * kBins0 * sizeof(uint32_t))
                 return HQMQ_ERR_UNSUPPORTED;

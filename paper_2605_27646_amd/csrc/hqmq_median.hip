@@ -18,7 +18,7 @@
 // every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
 // fp16 data span 83 binades, which at 64 bins each fit the 8192 bins of a workgroup's LDS).
 // The sequence-sharded median further down is a plain most-significant-digit radix select on the 63 value bits.
-#include "hqmq_cells.h"
+#include "hqmq_tables.h"
 
 namespace hqmq {
 
@@ -210,11 +210,15 @@ __device__ __forceinline__ uint32_t fine_bin(unsigned long long key)
 __device__ __forceinline__ bool fine_bin_is_prefix(uint32_t bin) { return bin >= 1u && bin <= (uint32_t)kBins0 - 2u; }
 
 // ---------------------------------------------------------------------------------------
-// reset of the per-call state of head h: what the search's index counts in, and the caller's counters
+// reset of the per-call state of head h: what the search's index counts in, or the operands of its matrix screen, and the
+// caller's counters
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void reset_head(const Geometry &g, const Workspace &ws, const EncodedPtrs &enc, int h, int tid, int threads)
+__device__ __forceinline__ void reset_head(const Geometry &g, const Workspace &ws, const EncodeTensor &tn, int h, int tid, int threads)
 {
-    if (g.cell_n > 0)
+    const EncodedPtrs &enc = tn.enc;
+    if (g.cell_n == 0)
+        build_operands(g, ws, tn.sec, h, tid, threads);
+    else
         for (int i = tid; i < 1 + g.cell_words; i += threads)
             ws.cell_state[(size_t)h * (1 + g.cell_words) + i] = 0;
     if (tid == 0) {
@@ -227,12 +231,12 @@ __device__ __forceinline__ void reset_head(const Geometry &g, const Workspace &w
 }
 
 // Without a select: thresholds from the caller, or +infinity (nothing is flagged).  grid = (H, 1, tensors).
-__global__ __launch_bounds__(kThreads) void k_init(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+__global__ __launch_bounds__(kSelectThreads) void k_init(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const int h = blockIdx.x;
-    reset_head(g, ws, tn.enc, h, threadIdx.x, kThreads);
+    reset_head(g, ws, tn, h, threadIdx.x, kSelectThreads);
     if (threadIdx.x == 0)
         ws.thr[h] = tn.thr_given ? tn.thr_given[h] : __longlong_as_double(0x7ff0000000000000LL);
 }
@@ -261,7 +265,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
     __shared__ uint32_t hist[kBins0];
     __shared__ RankScratch sc;
     static_assert(kRankBins <= kBins0, "the histograms share their memory");
-    reset_head(g, ws, tn.enc, h, tid, kSelectThreads);
+    reset_head(g, ws, tn, h, tid, kSelectThreads);
     const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
     const bool active = kFull || c < g.n_c;
     half4_t v[kSteps];
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
         }
     }
     if (part == 0) {
-        reset_head(g, ws, tn.enc, h, tid, kSelectThreads);
+        reset_head(g, ws, tn, h, tid, kSelectThreads);
         for (int i = tid; i < kBins0; i += kSelectThreads)
             ws.hist0[(size_t)h * kBins0 + i] = 0;
         if (tid < kBuckets)
@@ -1070,7 +1074,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffset
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
     const uint64_t outlier_capacity = tn.outlier_capacity;
-    __shared__ uint32_t sums[2];
+    __shared__ uint32_t sums[2], starts[64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
     const int t = blockIdx.x * kThreads + tid;
@@ -1084,10 +1088,9 @@ __global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffset
         // everything that is read is requested before the first use
         const uint32_t first = (uint32_t)seg * per_seg + blockIdx.x * (uint32_t)kThreads / g.search_rows;
         const bool last = blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1;
-        uint32_t own[4];  // the totals of the search workgroups of these rows
-#pragma unroll
-        for (uint32_t u = 0; u < 4; ++u)
-            own[u] = first + u < n_blocks ? ws.block_sum[first + u] : 0u;
+        // the totals of the search workgroups of these rows: one of 256 rows and more, up to 32 of 8
+        const uint32_t n_own = g.search_rows >= kThreads ? 1u : (uint32_t)kThreads / g.search_rows;
+        const uint32_t own = (uint32_t)tid < n_own && first + tid < n_blocks ? ws.block_sum[first + tid] : 0u;
         uint32_t before = sum_of(ws.block_sum, first, [](uint32_t i) { return i; });
         uint32_t of_head = 0;
         const bool counts = blockIdx.x == 0 && b == 0;  // uniform
@@ -1103,21 +1106,20 @@ __global__ __launch_bounds__(kThreads) void k_gather(Geometry g, WorkspaceOffset
             before += __shfl_xor(before, d, 64);
             of_head += __shfl_xor(of_head, d, 64);
         }
+        if (tid < 64)  // one wave: where each search workgroup's outliers start behind those before `first`; own is 0 past n_own
+            starts[tid] = wave_scan(own);
         __syncthreads();
         if (lane == 0) {
             atomicAdd(&sums[0], before);
             atomicAdd(&sums[1], of_head);
         }
         __syncthreads();
-        off += sums[0];
-#pragma unroll
-        for (uint32_t u = 0; u < 3; ++u)
-            off += first + u < block ? own[u] : 0u;
+        off += sums[0] + (block > first ? starts[block - first - 1] : 0u);
         if (tid == 0) {
             if (counts)
                 enc.n_outliers[h] = sums[1];
             if (last) {
-                const uint32_t total = sums[0] + own[0] + own[1] + own[2] + own[3];
+                const uint32_t total = sums[0] + starts[63];
                 enc.n_outliers[g.H] = total;
                 enc.row_off[R - t + g.T] = total;
                 if ((uint64_t)total > outlier_capacity)
@@ -1375,7 +1377,7 @@ hipError_t launch_select_median(const Geometry &g, const WorkspaceOffsets &wo, c
 {
     const unsigned n = (unsigned)n_tensors;
     if (skip_select)
-        hipLaunchKernelGGL(k_init, dim3(g.H, 1, n), dim3(kThreads), 0, stream, g, wo, batch);
+        hipLaunchKernelGGL(k_init, dim3(g.H, 1, n), dim3(kSelectThreads), 0, stream, g, wo, batch);
     else if (g.D == 4 * kChunksPerRow)
         launch_select_for<true>(g, wo, batch, n, C, stream);
     else

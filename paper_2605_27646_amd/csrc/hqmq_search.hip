@@ -35,7 +35,7 @@
 //
 // That is the search of short tensors.  Long ones locate a chunk's direction in a box index over the codewords
 // (k_cells, k_search_cells below), which replaces the scan over all S secondaries.
-#include "hqmq_cells.h"
+#include "hqmq_tables.h"
 
 namespace hqmq {
 
@@ -63,16 +63,6 @@ __device__ __forceinline__ uint16_t double_to_half_rne_sat(double v)
         ++q;
     uint32_t out = ((uint32_t)(E + 14) << 10) + (uint32_t)q;
     return out > 0x7bff ? (uint16_t)0x7bff : (uint16_t)out;
-}
-
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-constexpr float kOperandScale = 1024.f;
-
-__device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi)
-{
-    typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-    const half2_t v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, v);
 }
 
 template <int kCtrl>
@@ -175,29 +165,6 @@ __device__ __forceinline__ Direction unit_direction(const half4_t xv, double r2,
 }
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
-
-// x = h + l to 24 bits (|x - h - l| <= 2^-24 |x|), each part an fp16
-struct Parts2 {
-    _Float16 h, l;
-};
-// Hides how an fp32 value was computed.  split2 needs it: left to itself the compiler folds the
-// multiplication that produced x into one of the two conversions (v_fma_mixlo_f16 rounds the exact product
-// once) and converts the rounded x for the other (rounded twice); where x sits on the midpoint between two
-// fp16 values the two disagree by one fp16 step and h + l misses x by 2^-11 |x|.  Seen once in 786,432
-// chunks; harmless only when the product is exact (a scaling by a power of two).
-__device__ __forceinline__ float opaque(float x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
-}
-// x: a value that went through opaque(), or an exact scaling of one.
-__device__ __forceinline__ Parts2 split2(float x)
-{
-    Parts2 p;
-    p.h = (_Float16)x;
-    p.l = (_Float16)(x - (float)p.h);
-    return p;
-}
 
 // Two groups of secondaries whose screened maxima lie closer than this fraction of the larger one are
 // not told apart by the screen.  Its error is below 7e-7 |q_s| per score (operands carried to 2^-24 each,
@@ -454,50 +421,6 @@ __device__ __forceinline__ void write_row_offsets(const Geometry &g, const Works
 //   secl  [16*S16][4] f32      the head's secondaries (zero padded to a multiple of 16)
 //   pack  [kWaves][2][32] u32 row code words being assembled
 //   rcnt  [search_rows] u32    outliers per row of the workgroup
-// The search's MFMA A operands of every head, built once per call into the workspace (the workgroups
-// of the search then only copy their head's table into LDS).  grid = (ceil(4 S16 64 / 256), H, tensors).
-// Entry idx of a head's operand table: tile idx / 64 of 8 secondaries, lane l = idx % 64 holding row
-// l % 32 = 4 (secondary in tile) + i and the factors k = 2 (l / 32), 2 (l / 32) + 1 of that row, each in the
-// slots [h h l l].
-__device__ __forceinline__ uint4 operand_entry(const float *sec_h, int S, int idx)
-{
-    const int tile = idx >> 6, l = idx & 63;
-    const int row = l & 31, kh = l >> 5;
-    const int i = row & 3;
-    const int sidx = 8 * tile + (row >> 2);
-    float a = 0.f, bq = 0.f, c = 0.f, d = 0.f;  // zero rows pad S up to a multiple of 16
-    if (sidx < S) {
-        const float *q = sec_h + 4 * sidx;
-        a = q[0], bq = q[1], c = q[2], d = q[3];
-    }
-    // v = u (x) conj(q):  v0 =  a u0 + b u1 + c u2 + d u3
-    //                     v1 = -b u0 + a u1 - d u2 + c u3
-    //                     v2 = -c u0 + d u1 + a u2 - b u3
-    //                     v3 = -d u0 - c u1 + b u2 + a u3
-    auto entry = [&](int k) -> float {  // A[i][k]
-        if (i == 0)
-            return (k == 0) ? a : (k == 1) ? bq : (k == 2) ? c : d;
-        if (i == 1)
-            return (k == 0) ? -bq : (k == 1) ? a : (k == 2) ? -d : c;
-        if (i == 2)
-            return (k == 0) ? -c : (k == 1) ? d : (k == 2) ? a : -bq;
-        return (k == 0) ? -d : (k == 1) ? -c : (k == 2) ? bq : a;
-    };
-    const float va = entry(2 * kh), vb = entry(2 * kh + 1);
-    const Parts2 pa = split2(opaque(va) * kOperandScale), pb = split2(opaque(vb) * kOperandScale);
-    return make_uint4(pack2(pa.h, pa.h), pack2(pa.l, pa.l), pack2(pb.h, pb.h), pack2(pb.l, pb.l));
-}
-
-__global__ __launch_bounds__(kThreads) void k_prepare_operands(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
-{
-    const EncodeTensor &tn = batch.t[blockIdx.z];
-    const Workspace ws = carve_workspace(tn.ws, wo);
-    const int h = blockIdx.y;
-    const int idx = blockIdx.x * kThreads + threadIdx.x;
-    if (idx < g.A16 * kATiles * 64)
-        ws.aop[(size_t)h * g.A16 * kATiles * 64 + idx] = operand_entry(tn.sec + (size_t)h * g.S * 4, g.S, idx);
-}
-
 // kWaves: 4, or 8 when tables and row state are so large that only one workgroup fits a CU: twice the waves then
 // share the tables and keep two waves on every SIMD.
 // This kernel is for rows of 128 elements (32 chunks: two rows per wave); k_search_flat below takes
@@ -506,7 +429,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_operands(Geometry g, Works
 // supplied thresholds, extraction switched off): no kernel runs before this one, so it takes its thresholds
 // from the caller's array (+infinity without one), builds the head's operand table itself, and reports a
 // non-finite input through bit 31 of its workgroup total, which the list kernel turns into the status word.
-template <int kWaves, int kRows, bool kFused = false, bool kScreen = true>
+template <int kWaves, bool kFused = false, bool kScreen = true>
 __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
     constexpr int kThreadsS = 64 * kWaves;
@@ -527,7 +450,8 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     // batch entries, so that the head's tables are built once; its rows are the pairs (b, t), b-major
     const bool by_head = kFused && g.fused_by_head != 0;
     const int seg = blockIdx.y, b = by_head ? 0 : seg / g.H, h = by_head ? seg : seg % g.H;
-    const int t0 = blockIdx.x * kRows;
+    const int rows = g.search_rows;  // of a workgroup: 2 kWaves to 64
+    const int t0 = blockIdx.x * rows;
     const int n_here = by_head ? g.B * g.T : g.T;  // rows this workgroup column addresses
     const float *sec_h = sec + (size_t)h * g.S * 4;
     // row v of the column: its batch entry and token, the address of its chunk c, its linear row index
@@ -566,7 +490,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
         for (int idx = tid; idx < (kScreen ? g.S16 : 0) * kATiles * 64; idx += kThreadsS)
             amat[idx] = operand_entry(sec_h, g.S, idx);
         if (coop)  // the one pass writes the counters of rows 0 and 1 only
-            for (int r = tid; r < kRows; r += kThreadsS)
+            for (int r = tid; r < rows; r += kThreadsS)
                 rcnt[r] = 0;
     } else {
         const uint4 *src = ws.aop + (size_t)h * (kScreen ? g.S16 : 0) * kATiles * 64;
@@ -584,7 +508,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     const int c = lane & 31, half_id = lane >> 5;
     uint32_t *my_pack = pack + wv * 64;
 
-    const int n_it = coop ? 1 : kRows / (2 * kWaves);
+    const int n_it = coop ? 1 : rows / (2 * kWaves);
     for (int it = 0; it < n_it; ++it) {
         const int r_in_block = coop ? half_id : it * 2 * kWaves + wv * 2 + half_id;
         const int t = t0 + r_in_block;
@@ -664,33 +588,22 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     // scan / gather kernels that follow --------------------------------------------------------------
     const uint32_t bad_any = kFused ? (uint32_t)__syncthreads_or((int)bad_seen) : (__syncthreads(), 0u);
     if (wv == 0) {
-        uint32_t carry = 0;
-#pragma unroll
-        for (int part = 0; part < kRows / 64; ++part) {
-            const int r = 64 * part + lane;
-            const uint32_t cnt = rcnt[r];
-            uint32_t inc = cnt;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                uint32_t o = __shfl_up(inc, d, 64);
-                if (lane >= d)
-                    inc += o;
+        const int r = lane;  // a lane per row
+        const uint32_t cnt = r < rows ? rcnt[r] : 0u, inc = wave_scan(cnt);
+        if (by_head) {
+            // every batch entry's rows are a run of their own in the list's order: offsets restart at each run, and each run
+            // reports its total as a workgroup would
+            const int run = r / g.T, start = run * g.T;
+            const uint32_t before_run = __shfl(inc - cnt, min(start, 63), 64);
+            if (r < n_here) {
+                enc.row_off[row_at(r, 0).R] = inc - cnt - before_run;
+                if (r - start == g.T - 1)
+                    ws.block_sum[(size_t)run * g.H + h] = (inc - before_run) | (bad_any ? 0x80000000u : 0u);
             }
-            if (by_head) {
-                // (64 rows at most, one part) every batch entry's rows are a run of their own in the list's
-                // order: offsets restart at each run, and each run reports its total as a workgroup would
-                const int run = r / g.T, start = run * g.T;
-                const uint32_t before_run = __shfl(inc - cnt, min(start, 63), 64);
-                if (r < n_here) {
-                    enc.row_off[row_at(r, 0).R] = inc - cnt - before_run;
-                    if (r - start == g.T - 1)
-                        ws.block_sum[(size_t)run * g.H + h] = (inc - before_run) | (bad_any ? 0x80000000u : 0u);
-                }
-            } else if (t0 + r < g.T) {
-                enc.row_off[row_at(t0 + r, 0).R] = carry + inc - cnt;
-            }
-            carry += __shfl(inc, 63, 64);
+        } else if (r < rows && t0 + r < g.T) {
+            enc.row_off[row_at(t0 + r, 0).R] = inc - cnt;
         }
+        const uint32_t carry = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         if (lane == 0 && !by_head)  // a workgroup holds at most 512 x 32 outliers: bit 31 is free for the flag
             ws.block_sum[(size_t)seg * g.n_search_blocks_per_seg + blockIdx.x] = carry | (bad_any ? 0x80000000u : 0u);
     }
@@ -711,29 +624,29 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
 // Dynamic LDS: amat | secl as in k_search, then rowmax u64 [kRows] | fword u32 [kRows] |
 // sig u32 [kRows] | rcnt u32 [kRows] | pack u32 [kRows * row_words].
 // kFused: as in k_search.
-template <int kWaves, int kRows, bool kFused = false, bool kScreen = true>
+template <int kWaves, bool kFused = false, bool kScreen = true>
 __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
     constexpr int kThreadsS = 64 * kWaves;
-    static_assert(kRows % 64 == 0 && kRows <= kThreadsS, "one thread per row in the scale pass");
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
     const _Float16 *__restrict__ x = tn.x;
+    const int rows_wg = g.search_rows;  // of a workgroup: 8 to 64, or 256 on 4 waves; a thread per row in the scale pass
     extern __shared__ float smem[];
     uint4 *amat = reinterpret_cast<uint4 *>(smem);
     float *secl = reinterpret_cast<float *>(amat + (size_t)(kScreen ? g.S16 : 0) * kATiles * 64);
     unsigned long long *rowmax = reinterpret_cast<unsigned long long *>(secl + (size_t)g.S16 * 16 * 4);
-    uint32_t *fword = reinterpret_cast<uint32_t *>(rowmax + kRows);
-    uint32_t *sig = fword + kRows;
-    uint32_t *rcnt = sig + kRows;
-    uint32_t *pack = rcnt + kRows;
+    uint32_t *fword = reinterpret_cast<uint32_t *>(rowmax + rows_wg);
+    uint32_t *sig = fword + rows_wg;
+    uint32_t *rcnt = sig + rows_wg;
+    uint32_t *pack = rcnt + rows_wg;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
-    const int t0 = blockIdx.x * kRows;
-    const int nrows = min(kRows, g.T - t0);       // >= 1 by the grid's size
+    const int t0 = blockIdx.x * rows_wg;
+    const int nrows = min(rows_wg, g.T - t0);       // >= 1 by the grid's size
     const int nchunks = nrows * g.n_c;
     const int row_words = g.row_words;
     const int64_t row0 = (int64_t)seg * g.T + t0;  // linear index of the workgroup's first row
@@ -754,11 +667,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
         for (int idx = tid; idx < (kScreen ? g.S16 : 0) * kATiles * 64; idx += kThreadsS)
             amat[idx] = src[idx];
     }
-    for (int i = tid; i < kRows; i += kThreadsS) {
+    for (int i = tid; i < rows_wg; i += kThreadsS) {
         rowmax[i] = 0ull;
         fword[i] = 0u;
     }
-    for (int i = tid; i < kRows * row_words; i += kThreadsS)
+    for (int i = tid; i < rows_wg * row_words; i += kThreadsS)
         pack[i] = 0u;
     __syncthreads();
 
@@ -786,7 +699,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
             atomicMax(&rowmax[r], key_of(r2));  // non-negative doubles order like their bit patterns
     }
     const uint32_t bad_any = kFused ? (uint32_t)__syncthreads_or((int)bad_seen) : (__syncthreads(), 0u);
-    if (tid < kRows) {
+    if (tid < rows_wg) {
         uint32_t word = 0;
         if (tid < nrows) {
             word = fword[tid];
@@ -832,20 +745,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
     // ---- outlier offsets local to the workgroup and its total ---------------------------------------
     if (wv == 0) {
         uint32_t carry = 0;
-#pragma unroll
-        for (int part = 0; part < kRows / 64; ++part) {
-            const int r = 64 * part + lane;
-            const uint32_t cnt = rcnt[r];
-            uint32_t inc = cnt;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                uint32_t o = __shfl_up(inc, d, 64);
-                if (lane >= d)
-                    inc += o;
-            }
+        for (int r0 = 0; r0 < rows_wg; r0 += 64) {
+            const int r = r0 + lane;
+            const uint32_t cnt = r < rows_wg ? rcnt[r] : 0u, inc = wave_scan(cnt);
             if (r < nrows)
                 enc.row_off[row0 + r] = carry + inc - cnt;
-            carry += __shfl(inc, 63, 64);
+            carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         }
         if (lane == 0)
             ws.block_sum[(size_t)seg * g.n_search_blocks_per_seg + blockIdx.x] = carry | (bad_any ? 0x80000000u : 0u);
@@ -1543,17 +1448,16 @@ hipError_t prepare_search_kernels()
 {
     // the fused forms also hold static LDS (the workgroup-wide OR, the merge buffer of the cooperative pass: up to
     // 6 KiB), which counts against the same 160 KiB
-    const void *fused[] = {reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, true>),
-                           reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall, true>),
-                           reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, true>),
-                           reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall, true>)};
-    const void *variants[] = {reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall>),
-                              reinterpret_cast<const void *>(k_search<8, kSearchRowsSmall>),
-                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall>),
-                              reinterpret_cast<const void *>(k_search_flat<8, kSearchRowsSmall>),
-                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsLarge>),
-                              reinterpret_cast<const void *>(k_search<4, kSearchRowsSmall, false, false>),
-                              reinterpret_cast<const void *>(k_search_flat<4, kSearchRowsSmall, false, false>),
+    const void *fused[] = {reinterpret_cast<const void *>(k_search<4, true>),
+                           reinterpret_cast<const void *>(k_search<8, true>),
+                           reinterpret_cast<const void *>(k_search_flat<4, true>),
+                           reinterpret_cast<const void *>(k_search_flat<8, true>)};
+    const void *variants[] = {reinterpret_cast<const void *>(k_search<4>),
+                              reinterpret_cast<const void *>(k_search<8>),
+                              reinterpret_cast<const void *>(k_search_flat<4>),
+                              reinterpret_cast<const void *>(k_search_flat<8>),
+                              reinterpret_cast<const void *>(k_search<4, false, false>),
+                              reinterpret_cast<const void *>(k_search_flat<4, false, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
@@ -1593,14 +1497,14 @@ hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, co
     const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows);
     if (g.D == 4 * kChunksPerRow) {
         if (waves == 8)
-            hipLaunchKernelGGL((k_search<8, kSearchRowsSmall, true>), grid, dim3(512), lds, stream, g, wo, batch);
+            hipLaunchKernelGGL((k_search<8, true>), grid, dim3(512), lds, stream, g, wo, batch);
         else
-            hipLaunchKernelGGL((k_search<4, kSearchRowsSmall, true>), grid, dim3(256), lds, stream, g, wo, batch);
+            hipLaunchKernelGGL((k_search<4, true>), grid, dim3(256), lds, stream, g, wo, batch);
     } else {
         if (waves == 8)
-            hipLaunchKernelGGL((k_search_flat<8, kSearchRowsSmall, true>), grid, dim3(512), lds, stream, g, wo, batch);
+            hipLaunchKernelGGL((k_search_flat<8, true>), grid, dim3(512), lds, stream, g, wo, batch);
         else
-            hipLaunchKernelGGL((k_search_flat<4, kSearchRowsSmall, true>), grid, dim3(256), lds, stream, g, wo, batch);
+            hipLaunchKernelGGL((k_search_flat<4, true>), grid, dim3(256), lds, stream, g, wo, batch);
     }
     return hipGetLastError();
 }
@@ -1637,32 +1541,26 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
     }
     const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
     const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows);
-    if (g.A16 > 0)
-        hipLaunchKernelGGL(k_prepare_operands, dim3((g.A16 * kATiles * 64 + kThreads - 1) / kThreads, g.H, (unsigned)n_tensors),
-                           dim3(kThreads), 0, stream, g, wo, batch);
-    // a kernel for these rows per workgroup: 64 always, 256 for the flat form on 4 waves
-    const bool large = g.search_rows == kSearchRowsLarge;
-    if (large ? full || g.A16 == 0 || waves != 4 : g.search_rows != kSearchRowsSmall)
+    // rows per workgroup that the kernels take: two per wave and up to 64, or 256 for the flat form on 4 waves
+    const int rows = g.search_rows;
+    if (full ? rows > kSearchRowsSmall || rows % (2 * waves) : rows > kSearchRowsSmall && (rows != kSearchRowsLarge || waves != 4))
         return hipErrorInvalidConfiguration;
-#define HQMQ_LAUNCH(KERNEL, W) hipLaunchKernelGGL((KERNEL<W, kSearchRowsSmall>), grid, dim3(64 * W), lds, stream, g, wo, batch)
-    if (g.A16 == 0) {
-        // more secondaries than the matrix-core screen holds: 64 rows on 4 waves, every chunk scored in fp32
+#define HQMQ_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * waves), lds, stream, g, wo, batch)
+    if (g.A16 == 0) {  // more secondaries than the matrix-core screen holds: 4 waves, every chunk scored in fp32
         if (full)
-            hipLaunchKernelGGL((k_search<4, kSearchRowsSmall, false, false>), grid, dim3(256), lds, stream, g, wo, batch);
+            HQMQ_LAUNCH(k_search<4, false, false>);
         else
-            hipLaunchKernelGGL((k_search_flat<4, kSearchRowsSmall, false, false>), grid, dim3(256), lds, stream, g, wo, batch);
+            HQMQ_LAUNCH(k_search_flat<4, false, false>);
     } else if (full) {
         if (waves == 8)
-            HQMQ_LAUNCH(k_search, 8);
+            HQMQ_LAUNCH(k_search<8>);
         else
-            HQMQ_LAUNCH(k_search, 4);
+            HQMQ_LAUNCH(k_search<4>);
     } else {
-        if (large)
-            hipLaunchKernelGGL((k_search_flat<4, kSearchRowsLarge>), grid, dim3(256), lds, stream, g, wo, batch);
-        else if (waves == 8)
-            HQMQ_LAUNCH(k_search_flat, 8);
+        if (waves == 8)
+            HQMQ_LAUNCH(k_search_flat<8>);
         else
-            HQMQ_LAUNCH(k_search_flat, 4);
+            HQMQ_LAUNCH(k_search_flat<4>);
     }
 #undef HQMQ_LAUNCH
     return hipGetLastError();

@@ -1,5 +1,5 @@
-// Building the box index of the search over long tensors (what the index is: hqmq_search.hip).  Included where a kernel
-// builds it: beside the sweep of the median select, or in a launch of its own before the search.
+// The tables of the search that are built before it (what they are: hqmq_search.hip): the operands of the matrix screen, by the
+// call's first kernel, and the box index over the codewords, beside the sweep of the median select or in a launch of its own.
 #pragma once
 
 #include "hqmq_device.h"
@@ -97,6 +97,81 @@ __device__ __forceinline__ unsigned long long wave_umax64(unsigned long long k)
     k = umax64(k, (unsigned long long)__shfl_xor((long long)k, 16, 64));
     k = umax64(k, (unsigned long long)__shfl_xor((long long)k, 32, 64));
     return k;
+}
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+constexpr float kOperandScale = 1024.f;
+
+__device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi)
+{
+    typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+    const half2_t v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// x = h + l to 24 bits (|x - h - l| <= 2^-24 |x|), each part an fp16
+struct Parts2 {
+    _Float16 h, l;
+};
+// Hides how an fp32 value was computed.  split2 needs it: left to itself the compiler folds the
+// multiplication that produced x into one of the two conversions (v_fma_mixlo_f16 rounds the exact product
+// once) and converts the rounded x for the other (rounded twice); where x sits on the midpoint between two
+// fp16 values the two disagree by one fp16 step and h + l misses x by 2^-11 |x|.  Seen once in 786,432
+// chunks; harmless only when the product is exact (a scaling by a power of two).
+__device__ __forceinline__ float opaque(float x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+// x: a value that went through opaque(), or an exact scaling of one.
+__device__ __forceinline__ Parts2 split2(float x)
+{
+    Parts2 p;
+    p.h = (_Float16)x;
+    p.l = (_Float16)(x - (float)p.h);
+    return p;
+}
+
+// The search's MFMA A operands (how they are used: hqmq_search.hip).
+// Entry idx of a head's operand table: tile idx / 64 of 8 secondaries, lane l = idx % 64 holding row
+// l % 32 = 4 (secondary in tile) + i and the factors k = 2 (l / 32), 2 (l / 32) + 1 of that row, each in the
+// slots [h h l l].
+__device__ __forceinline__ uint4 operand_entry(const float *sec_h, int S, int idx)
+{
+    const int tile = idx >> 6, l = idx & 63;
+    const int row = l & 31, kh = l >> 5;
+    const int i = row & 3;
+    const int sidx = 8 * tile + (row >> 2);
+    float a = 0.f, bq = 0.f, c = 0.f, d = 0.f;  // zero rows pad S up to a multiple of 16
+    if (sidx < S) {
+        const float *q = sec_h + 4 * sidx;
+        a = q[0], bq = q[1], c = q[2], d = q[3];
+    }
+    // v = u (x) conj(q):  v0 =  a u0 + b u1 + c u2 + d u3
+    //                     v1 = -b u0 + a u1 - d u2 + c u3
+    //                     v2 = -c u0 + d u1 + a u2 - b u3
+    //                     v3 = -d u0 - c u1 + b u2 + a u3
+    auto entry = [&](int k) -> float {  // A[i][k]
+        if (i == 0)
+            return (k == 0) ? a : (k == 1) ? bq : (k == 2) ? c : d;
+        if (i == 1)
+            return (k == 0) ? -bq : (k == 1) ? a : (k == 2) ? -d : c;
+        if (i == 2)
+            return (k == 0) ? -c : (k == 1) ? d : (k == 2) ? a : -bq;
+        return (k == 0) ? -d : (k == 1) ? -c : (k == 2) ? bq : a;
+    };
+    const float va = entry(2 * kh), vb = entry(2 * kh + 1);
+    const Parts2 pa = split2(opaque(va) * kOperandScale), pb = split2(opaque(vb) * kOperandScale);
+    return make_uint4(pack2(pa.h, pa.h), pack2(pa.l, pa.l), pack2(pb.h, pb.h), pack2(pb.l, pb.l));
+}
+
+// Head h's operands into the workspace, once per call: the workgroups of the search then only copy them into LDS.  Done by
+// the call's first kernel, a workgroup per head (a launch of their own took 4 us).
+__device__ __forceinline__ void build_operands(const Geometry &g, const Workspace &ws, const float *sec, int h, int tid, int threads)
+{
+    const int n = g.A16 * kATiles * 64;
+    for (int idx = tid; idx < n; idx += threads)
+        ws.aop[(size_t)h * n + idx] = operand_entry(sec + (size_t)h * g.S * 4, g.S, idx);
 }
 
 constexpr int kCellThreads = 256;      // workgroup of the index build: 4 lanes per box

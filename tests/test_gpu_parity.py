@@ -957,6 +957,15 @@ def test_screen_of_many_short_rows(B, H, T, D, S):
     _roundtrip(_lognormal_tensor(B, H, T, seed=T + D, sigma_g=0.8, D=D), S=S)
 
 
+@pytest.mark.parametrize("B,H,T,D,S", [
+    (1, 8, 1023, 128, 16), (1, 8, 2501, 128, 5), (2, 3, 517, 128, 64), (1, 2, 13, 128, 256), (1, 1, 70, 128, 512),  # 8, 16, 16, 8, 8 rows
+    (1, 3, 259, 100, 40), (3, 2, 301, 64, 24), (1, 2, 300, 45, 16), (1, 2, 9, 128, 600)])
+def test_screen_of_few_rows_per_workgroup(B, H, T, D, S):
+    """The matrix screen with 8 to 32 rows per workgroup, last workgroups of one row and more, up to 32 totals for a
+    workgroup of the outlier list, a fifth of the chunks flagged."""
+    _roundtrip(_lognormal_tensor(B, H, T, seed=T + S, sigma_g=0.9, D=D), S=S, Cmul=1.5)
+
+
 def test_strided_input_and_output():
     """A cache stored [B, T, H, D] passes unchanged through the strides."""
     B, H, T = 2, 3, 50
