@@ -652,6 +652,50 @@ def test_select_of_repeating_norms(kind, B, T, D):
         assert (m2 == 0.0).all()
 
 
+def _head_with_cluster(R, D, k, gen):
+    """fp16 [R, D] with k chunks around the median whose squared norms are neighbours on either side of 1, steps of 2e-9
+    apart (up to 30 of them share an fp32 value); of the others one half is smaller, one larger."""
+    n = R * (D // 4)
+    y = torch.zeros(n, 4, dtype=torch.float16)
+    y[: (n - k) // 2, 0] = 0.5
+    y[(n - k) // 2 + k:, 0] = 2.0
+    mid = y[(n - k) // 2: (n - k) // 2 + k]
+    mid[:, 0], mid[:, 1] = 1.0 - 2.0 ** -11, (1.0 - 2.0 ** -10) / 32
+    rest = 1.0 - (mid[:1].double() ** 2).sum()
+    first = int(np.sqrt(float(rest)).astype(np.float16).view(np.uint16)) - k // 2
+    mid[:, 2] = torch.from_numpy(np.arange(first, first + k).astype(np.uint16).view(np.float16))
+    return y[torch.randperm(n, generator=gen)].view(R, D)
+
+
+@pytest.mark.parametrize("R,D", [(1, 128), (7, 20), (256, 128), (257, 44), (1024, 128), (1023, 96)])
+@pytest.mark.parametrize("kind", ["zeros", "two", "grid", "adjacent", 1, 63, 64, 65, 200])
+def test_select_of_short_heads(kind, R, D):
+    """Heads of one workgroup: squared norms that repeat, and as many as one wave ranks (64), fewer or more, of which fp32 does
+    not tell the order and the bin's lower end parts them.  In several batch entries too.  Thresholds bit for bit."""
+    H, S = 2, 1
+    gen = torch.Generator().manual_seed(R + D)
+    if isinstance(kind, int):
+        if kind > R * (D // 4):
+            kind = R * (D // 4)
+        x = torch.stack([_head_with_cluster(R, D, kind, gen) for _ in range(H)]).unsqueeze(0)
+    else:
+        x = _repeating_tensor(kind, 1, H, R, D, gen)
+    sec_t, sec = _sec(4, H, S)
+    for B in (1, 3):
+        if R % B:
+            continue
+        xb = x.view(H, B, R // B, D).transpose(0, 1).contiguous()
+        m2 = oracle.encode(_bits(xb), sec, rows=np.arange(0, 1)).m2
+        x_dev = xb.to(DEV)
+        params = hq.params_for(x_dev, S)
+        ws = hq.alloc_workspace(params, DEV)
+        ws.fill_(0x5A)
+        hq.hqmq_encode(params, x_dev, sec_t.to(DEV), hq.alloc_encoded(params, DEV), ws)
+        thr = hq.hqmq_thresholds(params, ws).cpu().numpy()
+        c = float(np.float32(3.0))
+        assert np.array_equal(thr.view(np.uint64), ((c * c) * m2).view(np.uint64))
+
+
 def _encode_ms(x, sec):
     """Shortest of several encodes of a device tensor, in ms."""
     params = hq.params_for(x, sec.shape[1])
