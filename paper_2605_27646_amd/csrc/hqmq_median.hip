@@ -44,14 +44,8 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t rank, ui
         local[i] = hist[tid * kPer + i];
         sum += local[i];
     }
-    // inclusive scan over the block: shuffle scan inside each wave, then wave totals through LDS
-    uint32_t inc = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t o = __shfl_up(inc, d, 64);
-        if (lane >= d)
-            inc += o;
-    }
+    // inclusive scan over the block: inside each wave, then wave totals through LDS
+    const uint32_t inc = wave_scan(sum);
     if (lane == 63)
         scratch[wv] = inc;
     __syncthreads();
@@ -93,13 +87,7 @@ __device__ __forceinline__ void pick_two(const uint32_t *hist, Ranks ranks, uint
         local[i] = hist[tid * kPer + i];
         sum += local[i];
     }
-    uint32_t inc = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(inc, d, 64);
-        if (lane >= d)
-            inc += o;
-    }
+    const uint32_t inc = wave_scan(sum);
     if (lane == 63)
         scratch[wv] = inc;
     __syncthreads();
@@ -250,65 +238,155 @@ __device__ __forceinline__ double threshold_of(unsigned long long median_bits, f
 }
 
 // ---------------------------------------------------------------------------------------
-// A head of at most 1024 rows (of all batch entries one after the other) in one workgroup, its keys in registers: a lane
-// per chunk and 32 rows per step, all requested before the first is used; the first digit's histogram, then select_rank
-// within the digit that holds the rank.  Bound by that compute unit's instructions and latency: 17 us for 1024 rows, where
-// the sweeps over several workgroups, their histograms in memory, took 40 in five launches.
+// A head of at most 1024 rows (of all batch entries one after the other) in one workgroup, its chunks in registers: a lane
+// per chunk and 32 rows per step, all requested before the first is used.  A histogram of the squared norms in fp32 (exact
+// squares, three rounded additions: within 3 * 2^-24 of the fp64 sum), exponent and 9 mantissa bits; the fp64 median lies in
+// the bin that holds the rank, or within that error of its ends, and what is below the bin by more than twice the error is
+// below the median: only the chunks in and 8 units around the bin (some 25 of 32768 smooth ones) get an fp64 norm, and one
+// wave ranks them by counting.  More of them (values that repeat): select_rank among them.
+// Bound by that compute unit's loads and latency: 12 us for 1024 rows, 6.4 for 256 and fewer; with every norm in fp64, a
+// second histogram, addresses multiplied out per step and scans through LDS 17 and 8.7.
 // grid = (H, 1, tensors), 1024 threads.
 // ---------------------------------------------------------------------------------------
+constexpr int kHeadBits = 9, kHeadShift = 23 - kHeadBits;
+constexpr uint32_t kHeadBase = (79u << kHeadBits) - 1u;  // fp32 exponents 79 (2^-48) to 162; bin 0: zero, the last: not finite
+constexpr int kHeadBins = 84 << kHeadBits, kHeadWords = kHeadBins / 2;
+constexpr uint32_t kHeadSlack = 8u;  // twice the error of a norm in fp32, in units of the last place
+static_assert(kHeadRows * kChunksPerRow < 1 << 16, "two counters share a word");
+
 template <int kSteps, bool kFull>
 __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, float C)
 {
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
-    const int h = blockIdx.x, tid = threadIdx.x, c = tid & 31;
-    __shared__ uint32_t hist[kBins0];
+    const int h = blockIdx.x, tid = threadIdx.x, c = tid & 31, lane = tid & 63, wv = tid >> 6;
+    constexpr int kPer = kHeadWords / kSelectThreads, kW = kSelectThreads / 64;
+    static_assert(kHeadWords % kSelectThreads == 0 && kRankBins <= kHeadWords, "bins tile the block; the histograms share memory");
+    __shared__ __align__(16) uint32_t hist[kHeadWords];
     __shared__ RankScratch sc;
-    static_assert(kRankBins <= kBins0, "the histograms share their memory");
-    reset_head(g, ws, tn, h, tid, kSelectThreads);
     const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
     const bool active = kFull || c < g.n_c;
     half4_t v[kSteps];
     {
-        uint32_t r = tid >> 5, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
+        uint32_t r = tid >> 5, t = r;
+        const _Float16 *row = tn.x + (int64_t)h * g.sh + (int64_t)t * g.st;
+        const int64_t step = 32 * g.st, wrap = g.sb - (int64_t)g.T * g.st;
+        auto into_entry = [&] {  // t past its batch entry's rows: the entries that follow
+            while (t >= (uint32_t)g.T && r < R) {
+                t -= (uint32_t)g.T;
+                row += wrap;
+            }
+        };
+        into_entry();
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {
             v[u] = half4_t{0, 0, 0, 0};
             if (active && r < R)
-                v[u] = load_row_chunk<kFull>(tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, c, g);
+                v[u] = load_row_chunk<kFull>(row, c, g);
             r += 32;
-            t += 32;
-            while (t >= (uint32_t)g.T && r < R) {
-                t -= (uint32_t)g.T;
-                ++b;
+            row += step;
+            if (g.B > 1) {
+                t += 32;
+                into_entry();
             }
         }
     }
-    for (int i = tid; i < kBins0; i += kSelectThreads)
-        hist[i] = 0;
+    for (int i = tid; i < kHeadWords / 4; i += kSelectThreads)
+        reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0)
+        sc.n_few = sc.result = 0;
+    reset_head(g, ws, tn, h, tid, kSelectThreads);
     __syncthreads();
-    unsigned long long key[kSteps];
+    uint32_t key[kSteps];
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
         const bool in = active && (uint32_t)(tid >> 5) + 32u * u < R;
-        key[u] = in ? key_of(chunk_norm2(v[u])) & kKeyMask : ~0ull;
-        if (in)
-            atomicAdd(&hist[fine_bin(key[u])], 1u);
+        const float x0 = (float)v[u][0], x1 = (float)v[u][1], x2 = (float)v[u][2], x3 = (float)v[u][3];
+        key[u] = in ? __float_as_uint(fmaf(x3, x3, fmaf(x2, x2, fmaf(x1, x1, x0 * x0)))) & 0x7fffffffu : ~0u;
+        if (in) {
+            const uint32_t bin = min(max(key[u] >> kHeadShift, kHeadBase) - kHeadBase, (uint32_t)kHeadBins - 1u);
+            atomicAdd(&hist[bin >> 1], 1u << (16u * (bin & 1u)));
+        }
     }
     __syncthreads();
     const uint32_t rank = (R * (uint32_t)g.n_c - 1u) / 2u;
-    uint32_t bin, before;
-    pick_bin<kBins0, kSelectThreads>(hist, rank, sc.pick, bin, before);
-    unsigned long long median = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; beyond finite fp16 data (not reached)
-    if (fine_bin_is_prefix(bin)) {
-        const unsigned long long lo = (unsigned long long)(bin + kFineBase) << kFineShift;
-        median = select_rank(
-            [&](auto f) {
+    uint32_t bin, below_bin;
+    {
+        uint32_t sum = 0;
 #pragma unroll
-                for (int u = 0; u < kSteps; ++u)
-                    f(key[u]);
-            },
-            lo, lo | ((1ull << kFineShift) - 1ull), rank - before, hist, sc);
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t two = hist[tid * kPer + i];
+            sum += (two & 0xffffu) + (two >> 16);
+        }
+        uint32_t before = wave_scan(sum);
+        if (lane == 63)
+            sc.pick[wv] = before;
+        __syncthreads();
+        before -= sum;
+#pragma unroll
+        for (int k = 0; k < kW; ++k)
+            before += k < wv ? sc.pick[k] : 0u;
+        if (rank - before < sum) {
+            sc.pick[kW] = tid;
+            sc.pick[kW + 1] = before;
+        }
+        __syncthreads();
+        // every wave: a lane per bin of the thread whose bins hold the rank
+        static_assert(2 * kPer <= 64, "a lane per bin");
+        const int owner = (int)sc.pick[kW];
+        const uint32_t two = hist[owner * kPer + min(lane >> 1, kPer - 1)];
+        const uint32_t n = lane < 2 * kPer ? two >> (16 * (lane & 1)) & 0xffffu : 0u;
+        const uint32_t first = sc.pick[kW + 1] + wave_scan(n) - n;
+        const int at = __ffsll((unsigned long long)ballot(rank - first < n)) - 1;
+        bin = (uint32_t)(2 * owner * kPer + at);
+        below_bin = (uint32_t)__builtin_amdgcn_readlane((int)first, at);
+    }
+    unsigned long long median = bin == 0u ? 0ull : 0x7ff0000000000000ull;  // zeros; not finite
+    if (bin != 0u && bin != (uint32_t)kHeadBins - 1u) {
+        const uint32_t first = (bin + kHeadBase) << kHeadShift, f_lo = first - kHeadSlack;
+        const uint32_t f_span = (1u << kHeadShift) - 1u + 2u * kHeadSlack;
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const bool near = key[u] - f_lo <= f_span;
+            const unsigned long long mask = ballot(near);
+            if (mask != 0ull) {  // one count per wave: a value may repeat in every chunk
+                const uint32_t n = (uint32_t)__popcll(mask) | (uint32_t)__popcll(ballot(near && key[u] < first)) << 16;
+                uint32_t at = 0;
+                if (lane == 0)
+                    at = atomicAdd(&sc.n_few, n);
+                at = (__builtin_amdgcn_readfirstlane((int)at) & 0xffffu) +
+                     __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (near && at < (uint32_t)kFew)
+                    sc.few[at] = key_of(chunk_norm2(v[u]));
+            }
+        }
+        __syncthreads();
+        const uint32_t count = sc.n_few & 0xffffu, left = rank - (below_bin - (sc.n_few >> 16));
+        if (count <= (uint32_t)kFew) {
+            if ((uint32_t)tid < count) {
+                const unsigned long long mine = sc.few[tid];
+                uint32_t less = 0;
+                for (uint32_t j = 0; j < count; ++j) {
+                    const unsigned long long other = sc.few[j];
+                    less += other < mine || (other == mine && j < (uint32_t)tid) ? 1u : 0u;
+                }
+                if (less == left)
+                    sc.result = mine;
+            }
+            __syncthreads();
+            median = sc.result;
+        } else {
+            __syncthreads();  // select_rank clears the count that every thread has to read before
+            median = select_rank(
+                [&](auto f) {
+#pragma unroll
+                    for (int u = 0; u < kSteps; ++u)
+                        if (key[u] - f_lo <= f_span)
+                            f(key_of(chunk_norm2(v[u])));
+                },
+                key_of((double)__uint_as_float(f_lo - kHeadSlack)), key_of((double)__uint_as_float(f_lo + f_span + kHeadSlack)),
+                left, hist, sc);
+        }
     }
     if (tid == 0)
         ws.thr[h] = threshold_of(median, C);
@@ -362,21 +440,33 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
     {
         const uint32_t samples = kPieceRows * kSteps * parts, stride = (R + samples - 1) / samples | 1u;
         const uint32_t pieces = (uint32_t)(g.n_c + kPieceChunks - 1) / kPieceChunks;
-        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride, b = r / (uint32_t)g.T, t = r - b * (uint32_t)g.T;
+        const uint32_t inverse = ((1u << 20) + pieces - 1u) / pieces;  // i / pieces = i * inverse >> 20 for i below 2^12
+        static_assert(kPieceRows * kSteps * 2 + kMaxParts < 1 << 12, "j + part + j / pieces");
+        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride, t = r;
+        const _Float16 *row = tn.x + (int64_t)h * g.sh;
+        if (r < R) {
+            const uint32_t b = r / (uint32_t)g.T;
+            t = r - b * (uint32_t)g.T;
+            row += (int64_t)b * g.sb + (int64_t)t * g.st;
+        }
+        const uint32_t more = kPieceRows * parts * stride;
+        const int64_t step = (int64_t)more * g.st, wrap = g.sb - (int64_t)g.T * g.st;
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {
-            const uint32_t c = (j + part + j / pieces) % pieces * kPieceChunks + tid % kPieceChunks;
+            const uint32_t i = j + part + (j * inverse >> 20);
+            const uint32_t c = (i - (i * inverse >> 20) * pieces) * kPieceChunks + tid % kPieceChunks;
             v[u] = half4_t{0, 0, 0, 0};
             if (r < R && c < (uint32_t)g.n_c) {
-                v[u] = load_row_chunk<kFull>(tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)t * g.st, (int)c, g);
+                v[u] = load_row_chunk<kFull>(row, (int)c, g);
                 loaded |= 1u << u;
             }
             j += kPieceRows;
-            r += kPieceRows * parts * stride;
-            t += kPieceRows * parts * stride;
+            r += more;
+            t += more;
+            row += step;
             while (t >= (uint32_t)g.T && r < R) {
                 t -= (uint32_t)g.T;
-                ++b;
+                row += wrap;
             }
         }
     }
