@@ -577,14 +577,14 @@ struct Buckets {
         // sums over the parts in pairs, so that equal ends sum up exactly
         const int n = predict_parts(g), lane = threadIdx.x & 63;
         const float2 own = lane < n ? predicted_ends(ws, h)[lane] : make_float2(0.0f, 0.0f);
-        float first = own.x, last = own.y;
-#pragma unroll
-        for (int d = 1; d < kMaxParts; d <<= 1) {
-            first += __shfl_xor(first, d, 64);
-            last += __shfl_xor(last, d, 64);
-        }
-        first = __shfl(first, 0, 64);
-        last = __shfl(last, 0, 64);
+        auto sum8 = [](float v) {  // of the first eight lanes
+            v += dpp_move<0xb1>(v);   // neighbours
+            v += dpp_move<0x4e>(v);   // pairs
+            v += dpp_move<0x141>(v);  // fours: the half row mirrored
+            return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+        };
+        static_assert(kMaxParts == 8, "a part per lane of the sum");
+        float first = sum8(own.x), last = sum8(own.y);
         // exact, if the parts agree on a single value; else their ends are 4 units of the last place wide
         first *= 1.0f / (float)n;
         last *= 1.0f / (float)n;
@@ -600,28 +600,30 @@ struct Buckets {
     }
 };
 
+// What the sweep counted for a head, a list per lane: requested together with the range, not after it.
+struct KeptCounts {
+    uint32_t below, mine;
+    __device__ __forceinline__ KeptCounts(const Workspace &ws, int h)
+        : below(ws.plan[h].below), mine((threadIdx.x & 63) < kBuckets ? bucket_counts(ws, h)[(threadIdx.x & 63) * kBucketPitch] : 0u)
+    {
+    }
+};
+
 // Where the key of the given rank is among the kept ones: its list and its rank there.  False: not at all, because it lies
 // outside the predicted range, or inside but its list overflowed (a range of one value needs none).
-__device__ __forceinline__ bool find_kept(const Geometry &g, const Workspace &ws, int h, const Buckets &range, uint32_t rank,
+__device__ __forceinline__ bool find_kept(const Geometry &g, const KeptCounts &kept, const Buckets &range, uint32_t rank,
                                           uint32_t &bucket, uint32_t &rank_in, uint32_t &n, bool &inside)
 {
-    const uint32_t below = ws.plan[h].below;
-    const int lane = threadIdx.x & 63;  // every wave for itself: a lane per list
-    const uint32_t mine = lane < kBuckets ? bucket_counts(ws, h)[lane * kBucketPitch] : 0u;
-    uint32_t inc = mine;
-#pragma unroll
-    for (int d = 1; d < kBuckets; d <<= 1) {
-        const uint32_t o = __shfl_up(inc, d, 64);
-        if (lane >= d)
-            inc += o;
-    }
-    const unsigned long long past = __ballot(lane < kBuckets && rank >= below && rank - below < inc);
+    const uint32_t below = kept.below, mine = kept.mine;
+    const int lane = threadIdx.x & 63;  // every wave for itself
+    const uint32_t inc = wave_scan(mine);
+    const unsigned long long past = ballot(lane < kBuckets && rank >= below && rank - below < inc);
     inside = past != 0ull;
     if (!inside)
         return false;
     bucket = (uint32_t)__ffsll((long long)past) - 1u;
-    n = (uint32_t)__shfl((int)mine, (int)bucket, 64);
-    rank_in = rank - below - ((uint32_t)__shfl((int)inc, (int)bucket, 64) - n);
+    n = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)bucket);
+    rank_in = rank - below - ((uint32_t)__builtin_amdgcn_readlane((int)inc, (int)bucket) - n);
     return n <= bucket_capacity(g) || range.span == 0ull;
 }
 
@@ -896,8 +898,9 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     const int h = missed_head(g);
     uint32_t bucket, rank_in, n, first, last;
     bool inside;
+    const KeptCounts kept(ws, h);
     const Buckets range(g, ws, h);
-    if (find_kept(g, ws, h, range, (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n, inside))
+    if (find_kept(g, kept, range, (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n, inside))
         return;
     const SecondLook look(range, inside);
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
@@ -943,10 +946,11 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
     unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
     const bool selects = blockIdx.z == 0;  // the workgroups that start first
     unsigned long long median;
+    const KeptCounts kept(ws, h);
     const Buckets range(g, ws, h);
     uint32_t bucket, rank_in, n;
     bool inside;
-    if (find_kept(g, ws, h, range, rank, bucket, rank_in, n, inside)) {  // uniform
+    if (find_kept(g, kept, range, rank, bucket, rank_in, n, inside)) {  // uniform
         if (!selects)
             return;
         const unsigned long long *list = cand + bucket * bucket_capacity(g);
