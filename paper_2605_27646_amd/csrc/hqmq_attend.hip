@@ -39,8 +39,7 @@ constexpr int kStageRows = 16;                      // rows per wave and tile
 constexpr int kMaxW = 24;                           // w = w_idx + b_r <= 16 + 8
 constexpr int kStageWords = kStageRows * kMaxW + 4; // + padding: a 2-word window may start at the last word
 constexpr int kPaySlots = 128;                      // outlier payloads of a wave's 16 rows kept in LDS
-constexpr int kSideWords = kStageWords + 3 * kStageRows + 2 * kPaySlots;  // one side (K or V) of one wave
-constexpr int kLoadsPerLane = (kStageRows * kMaxW + 63) / 64;
+constexpr int kSideWords = kStageWords + 3 * kStageRows + 2 * kPaySlots + 4;  // one side (K or V) of one wave
 constexpr float kNegBig = -1.0e30f;                 // "no row seen yet" (finite, so differences stay finite)
 constexpr int kRedStride = 2 + 128;                 // one partial state: maximum, sum, 128 weighted values
 constexpr int kAttendTargetBlocks = 512;            // two resident workgroups per compute unit
@@ -61,48 +60,57 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One tile's encoded rows of one side on their way from memory to LDS.
+// One tile's encoded rows of one side on their way from memory to LDS.  Every lane loads, past the tile's end its last
+// word again: no lane mask per load, and the bases stay scalar.  Rows that are not there get a scale of zero and no flags:
+// whatever their code words say, they decode to zeros.
+template <int kNc>
 struct TileRegs {
-    uint32_t cw[kLoadsPerLane];
+    static constexpr int kLoads = (kStageRows * (kNc * kMaxW / 32) + 63) / 64;  // of the code words, at the largest w
+    uint32_t cw[kLoads];
     uint32_t fw, sg, ro;
 };
 
-__device__ __forceinline__ void load_tile(TileRegs &t, const AttendSide &s, int64_t R0, int nrows,
-                                          uint32_t row_words, int lane)
+template <int kNc>
+__device__ __forceinline__ void load_tile(TileRegs<kNc> &t, const AttendSide &s, int64_t R0, int nrows,
+                                          uint32_t row_words, uint32_t lane)
 {
-#pragma unroll
-    for (int j = 0; j < kLoadsPerLane; ++j)
-        t.cw[j] = 0;
-    t.fw = t.sg = t.ro = 0;
     if (nrows > 0) {
         const uint32_t *cw = s.codes + R0 * row_words;
-        const int ncw = nrows * (int)row_words;
+        const uint32_t last = (uint32_t)nrows * row_words - 1u;
 #pragma unroll
-        for (int j = 0; j < kLoadsPerLane; ++j)
-            if (lane + 64 * j < ncw)
-                t.cw[j] = cw[lane + 64 * j];
-        if (lane < nrows) {
-            t.fw = s.flags[R0 + lane];
-            t.sg = s.sigma[R0 + lane];
-            t.ro = s.row_off[R0 + lane];
-        }
+        for (uint32_t j = 0; j < TileRegs<kNc>::kLoads; ++j)  // all of them: a branch per load costs more, and its wait is not exact
+            t.cw[j] = cw[min(lane + 64u * j, last)];
+        const uint32_t row = min(lane, (uint32_t)nrows - 1u);
+        t.fw = (s.flags + R0)[row];
+        t.sg = (s.sigma + R0)[row];
+        t.ro = (s.row_off + R0)[row];
     }
 }
 
-// LDS image of one side: code words [16 rows][row_words] | padding | flag words [16] | scales [16] |
-// offsets [16] | payload window [64] x 8 bytes
-__device__ __forceinline__ void stage_tile(const TileRegs &t, uint32_t *stage, int lane)
+// LDS image of one side: code words [16 rows][row_words] | room for reads past the last | flag words [16] | scales [16] |
+// offsets [16] | payload window [128] x 8 bytes | one slot more, read and not used
+template <int kNc>
+__device__ __forceinline__ void stage_tile(TileRegs<kNc> &t, uint32_t *stage, int nrows, int lane)
 {
 #pragma unroll
-    for (int j = 0; j < kLoadsPerLane; ++j)
+    for (int j = 0; j < TileRegs<kNc>::kLoads; ++j)
         stage[lane + 64 * j] = t.cw[j];
-    if (lane < 4)
-        stage[kStageWords - 4 + lane] = 0;
+    t.fw = lane < nrows ? t.fw : 0u;
+    t.sg = lane < nrows ? t.sg : 0u;
     if (lane < kStageRows) {
         stage[kStageWords + lane] = t.fw;
         stage[kStageWords + kStageRows + lane] = t.sg;
         stage[kStageWords + 2 * kStageRows + lane] = t.ro;
     }
+}
+
+// The larger of a lane's value and those of the three lanes 16, 32 and 48 away.
+__device__ __forceinline__ float max_over_rows(float v)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 __device__ __forceinline__ uint32_t pack_half2(float lo, float hi)
@@ -161,7 +169,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
     uint32_t *stage_v = stage_all + (wv * 2 + 1) * kSideWords;
 
     // ---- first tile on its way while the tables are set up ----------------------------------------------
-    TileRegs tk, tv;
+    TileRegs<kNc> tk = {}, tv = {};
     int nrows = min(kStageRows, row_end - (row_begin + wv * kStageRows));
     {
         const int64_t R0 = (int64_t)seg * g.T + row_begin + wv * kStageRows;
@@ -216,36 +224,42 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
     // the next 64 (rare) are copied when the tile is staged; a still larger window (more than a
     // quarter of the chunks flagged) sends the tile down the careful path, which reads the list.
     struct Window {
-        uint32_t base, n;
-        uint2 mine;  // entry `lane` of the window, on its way to LDS
+        uint32_t base, n, in_list;  // in_list: entries that the list has room for
+        uint2 mine;                 // entry `lane` of the window, on its way to LDS
     };
-    auto open_window = [&](const AttendSide &s, const TileRegs &t, int nr) {
+    auto window_of = [&](const AttendSide &s, const TileRegs<kNc> &t, int nr) {
         Window wd;
-        wd.base = 0;
-        wd.n = 0;
-        wd.mine = make_uint2(0u, 0u);
-        if (nr > 0) {
-            const int last_row = nr - 1;
-            wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
-            const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, last_row);
-            const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, last_row);
-            wd.n = ro_l + __popc(fw_l) - wd.base;
-            // unconditional load (a conditional one would be waited for on the spot): lanes past the
-            // window or the list's capacity re-read a neighbour's entry; a wave without outliers reads
-            // 8 harmless bytes of the offset array
-            const bool has_pay = wd.n > 0 && (uint64_t)wd.base < s.outlier_capacity;
-            const uint64_t last = has_pay ? min((uint64_t)wd.n, s.outlier_capacity - wd.base) - 1u : 0u;
-            const uint2 *src = has_pay ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
-                                       : reinterpret_cast<const uint2 *>(s.row_off);
-            wd.mine = src[min((uint64_t)lane, last)];
-            if (!has_pay || (uint64_t)lane > last)
-                wd.mine = make_uint2(0u, 0u);
-        }
+        wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
+        const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, nr - 1);
+        const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, nr - 1);
+        wd.n = ro_l + __popc(fw_l) - wd.base;
+        wd.in_list = (uint64_t)wd.base < s.outlier_capacity ? (uint32_t)min((uint64_t)wd.n, s.outlier_capacity - wd.base) : 0u;
         return wd;
+    };
+    // unconditional load (a conditional one would be waited for on the spot): lanes past the window or the list's capacity
+    // re-read a neighbour's entry; a wave without outliers reads 8 harmless bytes of the offset array.  Nothing looks at the
+    // entry before it is staged.
+    auto request = [&](const AttendSide &s, Window &wd) {
+        const uint2 *src = wd.in_list ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
+                                      : reinterpret_cast<const uint2 *>(s.row_off);
+        wd.mine = src[min((uint32_t)lane, wd.in_list ? wd.in_list - 1u : 0u)];
+    };
+    // Both sides' bounds before either request: looking at the second side's offsets after the first request would wait for
+    // that too (0.7 us per tile).
+    Window wk = {}, wvw = {};
+    auto open_windows = [&](int nr) {
+        if (nr > 0) {
+            wk = window_of(a.k, tk, nr);
+            wvw = window_of(a.v, tv, nr);
+            request(a.k, wk);
+            request(a.v, wvw);
+        } else {
+            wk.n = wvw.n = wk.in_list = wvw.in_list = 0u;
+        }
     };
     auto stage_window = [&](const AttendSide &s, const Window &wd, uint32_t *stage) {
         uint2 *st_pay = reinterpret_cast<uint2 *>(stage + kStageWords + 3 * kStageRows);
-        st_pay[lane] = wd.mine;
+        st_pay[lane] = (uint32_t)lane < wd.in_list ? wd.mine : make_uint2(0u, 0u);
         if (wd.n > 64u) {  // wave-uniform and rare: more than 64 outliers in 16 rows
             for (uint32_t k = 64u + lane; k < min(wd.n, (uint32_t)kPaySlots); k += 64u) {
                 const uint64_t at = (uint64_t)wd.base + k;
@@ -334,12 +348,12 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
         return out;
     };
 
-    Window wk = open_window(a.k, tk, nrows), wvw = open_window(a.v, tv, nrows);
+    open_windows(nrows);
 
     for (int t0 = row_begin; t0 < row_end; t0 += kAttendTile) {
         // ---- this tile's rows and payload windows into LDS; the next tile's rows requested -----------
-        stage_tile(tk, stage_k, lane);
-        stage_tile(tv, stage_v, lane);
+        stage_tile(tk, stage_k, nrows, lane);
+        stage_tile(tv, stage_v, nrows, lane);
         stage_window(a.k, wk, stage_k);
         stage_window(a.v, wvw, stage_v);
         wave_lds_sync();
@@ -404,8 +418,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
                 s4[i] = seen ? sc[i] * a.qscale : kNegBig;
                 mx = fmaxf(mx, s4[i]);
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = max_over_rows(mx);
             const float mn = fmaxf(m_run, mx);
             if (__any(mn > m_run)) {
                 // some head's maximum rose: rescale.  The accumulators of this lane belong to heads
@@ -451,10 +464,8 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
         }
 
         // ---- the next tile's payload windows (its offsets have arrived by now) ---------------------------
-        if (more) {
-            wk = open_window(a.k, tk, nn);
-            wvw = open_window(a.v, tv, nn);
-        }
+        if (more)
+            open_windows(nn);
 
         // ---- weighted values: lane (n16, j4) supplies chunks n16 and n16 + 16 of rows 4 j4 + i -----------
         if (nrows > 0) {
@@ -574,9 +585,15 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
 // sixteen fused ones.  An entry is the product of the primary and the secondary in the decode's order of
 // operations with the radius left out; scaling it afterwards rounds differently from the decode in the last
 // fp32 bit, which can move an element whose exact value sits on the midpoint of two fp16 values, and nothing
-// else.  One workgroup of 8 waves per compute unit (tiles of 128 rows); everything else as k_attend_partial.
+// else.  One workgroup of 8 waves per compute unit (tiles of 128 rows).  For the scores a lane takes neighbouring chunks
+// (kM j4 .. kM j4 + kM - 1), for the values kU neighbouring ones of four rows: which chunks a lane supplies is free as long
+// as q and the output columns follow, and neighbours share the shifts, the masks and the count of the outliers before them.
+// Bound by instruction issue and LDS latency at two waves per SIMD, and by the wait for rows and payloads: 32 us for
+// 8 heads of 32768 tokens x 128, D = 64, 8 x 8 x 3001 19.4; with the second side's window requested behind a wait for the
+// first's, twice per tile, 38.6 and 23.4.  Parts left out, 8 x 32768 x 128: no loads after the first tile 28, no
+// reconstruction 16, neither 9, of which the set-up 3.4, the tables 0.7 and the partial sums 1.6.
 // grid = (n_splits, B*H), block = 512.
-// dynamic LDS: max(lut [48] u32 | table K [13 S][4] f32 | table V | staging [8 waves][K, V][kSideWords] u32,
+// dynamic LDS: max(lut [48] uint2 | table K [13 S][4] f32 | table V | staging [8 waves][K, V][kSideWords] u32,
 //                  merge buffer [8 waves][G][130] f32)
 // ---------------------------------------------------------------------------------------
 constexpr int kJointWaves = 8;
@@ -612,8 +629,8 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
     constexpr int kU = (kNc + 15) / 16;  // column groups of 16 chunks on the value side
     constexpr int kD = 4 * kNc;
     extern __shared__ float lds[];
-    uint32_t *lut = reinterpret_cast<uint32_t *>(lds);      // [48] byte offset of the primary's rows in a table | sign
-    float *tab_k = lds + 48;                                // [13 S][4]: 12 primaries, then zeros
+    uint2 *lut = reinterpret_cast<uint2 *>(lds);            // [48] byte offset of the primary's rows in a table, sign bit
+    float *tab_k = lds + 2 * 48;                            // [13 S][4]: 12 primaries, then zeros
     float *tab_v = tab_k + table_floats;
     uint32_t *stage_all = reinterpret_cast<uint32_t *>(tab_v + table_floats);
 
@@ -637,21 +654,28 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
     uint32_t *stage_k = stage_all + (wv * 2 + 0) * kSideWords;
     uint32_t *stage_v = stage_all + (wv * 2 + 1) * kSideWords;
 
-    // ---- first tile on its way while the tables are set up ----------------------------------------------
-    TileRegs tk, tv;
+    // ---- the first secondaries and the first tile on their way while the tables are set up --------------
+    // thread i: secondary i of K, then of V
+    const float *sk = a.k.sec + (size_t)h * g.S * 4, *sv = a.v.sec + (size_t)h * g.S * 4;
+    auto secondary = [&](uint32_t i) {
+        const bool is_v = i >= (uint32_t)g.S;
+        return *reinterpret_cast<const float4_t *>((is_v ? sv : sk) + 4 * (is_v ? i - (uint32_t)g.S : i));
+    };
+    float4_t sec = secondary(min((uint32_t)tid, 2u * (uint32_t)g.S - 1u));
+    TileRegs<kNc> tk = {}, tv = {};
     int nrows = min(kStageRows, row_end - (row_begin + wv * kStageRows));
     {
         const int64_t R0 = (int64_t)seg * g.T + row_begin + wv * kStageRows;
         load_tile(tk, a.k, R0, nrows, row_words, lane);
         load_tile(tv, a.v, R0, nrows, row_words, lane);
     }
-    // Q^T as the B operand of the score products: lane (head n16, j4) holds q[head][16 m + 4 j4 + 0..3]
+    // Q^T as the B operand of the score products: lane (head n16, j4) holds q[head][4 (kM j4 + m) + 0..3]
     uint2 qb[kM];
     {
-        const _Float16 *qh = a.q + (((size_t)b * g.H + h) * G + min(n16, G - 1)) * kD + 4 * j4;
+        const _Float16 *qh = a.q + (((size_t)b * g.H + h) * G + min(n16, G - 1)) * kD + 4 * kM * j4;
 #pragma unroll
         for (int m = 0; m < kM; ++m) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(qh + 16 * m);
+            const uint2 v = *reinterpret_cast<const uint2 *>(qh + 4 * m);
             qb[m] = (n16 < G) ? v : make_uint2(0u, 0u);
         }
     }
@@ -659,17 +683,13 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         // Half tables: entry (c, s) = P_c (x) q_s for the 12 primaries with a positive first non-zero component
         // (+1, +i, +j, +k and (+1/2, +-1/2, +-1/2, +-1/2)); primary p is one of them or its negative, which the
         // look-up table records as a sign to be put on the radius.
-        const float *sk = a.k.sec + (size_t)h * g.S * 4, *sv = a.v.sec + (size_t)h * g.S * 4;
-        for (uint32_t i = tid; i < 4u * (uint32_t)g.S; i += kJointThreads) {
-            const uint32_t side_grp = (uint32_t)((float)i * g.inv_S);  // i / S: 0, 1 = K's two groups of six, 2, 3 = V's
-            const uint32_t sidx = i - side_grp * (uint32_t)g.S;
-            const bool is_v = side_grp >= 2;
-            const float4_t q = *reinterpret_cast<const float4_t *>((is_v ? sv : sk) + 4 * sidx);
-            float4_t *dst = reinterpret_cast<float4_t *>(is_v ? tab_v : tab_k) + (size_t)6 * (side_grp & 1u) * g.S + sidx;
-            if (side_grp & 1u)
-                half_table_entries<1>(q, dst, g.S);
-            else
-                half_table_entries<0>(q, dst, g.S);
+        for (uint32_t i = tid; i < 2u * (uint32_t)g.S; i += kJointThreads) {
+            if (i >= (uint32_t)kJointThreads)
+                sec = secondary(i);
+            const bool is_v = i >= (uint32_t)g.S;
+            float4_t *dst = reinterpret_cast<float4_t *>(is_v ? tab_v : tab_k) + (is_v ? i - (uint32_t)g.S : i);
+            half_table_entries<0>(sec, dst, g.S);
+            half_table_entries<1>(sec, dst + (size_t)6 * g.S, g.S);
         }
         for (int sidx = tid; sidx < g.S; sidx += kJointThreads) {  // a thirteenth block of zeros: for an index past the codebook
             *reinterpret_cast<float4_t *>(tab_k + 4 * (12 * g.S + sidx)) = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -686,15 +706,13 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
                 neg = b >> 3;
                 c = 4u + ((neg ? ~b : b) & 7u);
             }
-            lut[p] = (c * (uint32_t)g.S * 16u) | (neg << 31);
+            lut[p] = make_uint2(c * (uint32_t)g.S * 16u, neg << 31);
         }
     }
-    __syncthreads();
-
     // running state of head n16 (m_run is the same in all four j4 groups; l_run holds this lane's
     // rows only and is summed over j4 at the end)
     float m_run = kNegBig, l_run = 0.f;
-    // [upper chunk u][component e]: element i = head 4 j4 + i, output column n16 = dimension 64 u + 4 n16 + e
+    // [chunk u of the lane's][component e]: element i = head 4 j4 + i, output column n16 = dimension 4 (kU n16 + u) + e
     float4_t acc[kU][4];
 #pragma unroll
     for (int u = 0; u < kU; ++u)
@@ -702,8 +720,11 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         for (int e = 0; e < 4; ++e)
             acc[u][e] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    const uint32_t code_mask = (1u << w) - 1u, idx_mask = (1u << w_idx) - 1u;
+    const uint32_t idx_mask = (1u << w_idx) - 1u;
     const float inv_L = g.inv_L;
+    // k / S = k * div_mul >> div_shift for k below 48 S: the multiplier is too large by less than 1 / 48 S of itself
+    const uint32_t div_shift = 32u - (uint32_t)__clz((int)(48u * (uint32_t)g.S * (uint32_t)g.S));
+    const uint32_t div_mul = ((1u << div_shift) + (uint32_t)g.S - 1u) / (uint32_t)g.S;
 
     // Outlier payloads of a wave's 16 rows: one contiguous window of the list, its first 128 entries
     // copied to LDS (zeros for entries beyond the list's capacity).  The first 64 are requested half
@@ -711,36 +732,42 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
     // the next 64 (rare) are copied when the tile is staged; a still larger window (more than a
     // quarter of the chunks flagged) sends the tile down the careful path, which reads the list.
     struct Window {
-        uint32_t base, n;
-        uint2 mine;  // entry `lane` of the window, on its way to LDS
+        uint32_t base, n, in_list;  // in_list: entries that the list has room for
+        uint2 mine;                 // entry `lane` of the window, on its way to LDS
     };
-    auto open_window = [&](const AttendSide &s, const TileRegs &t, int nr) {
+    auto window_of = [&](const AttendSide &s, const TileRegs<kNc> &t, int nr) {
         Window wd;
-        wd.base = 0;
-        wd.n = 0;
-        wd.mine = make_uint2(0u, 0u);
-        if (nr > 0) {
-            const int last_row = nr - 1;
-            wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
-            const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, last_row);
-            const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, last_row);
-            wd.n = ro_l + __popc(fw_l) - wd.base;
-            // unconditional load (a conditional one would be waited for on the spot): lanes past the
-            // window or the list's capacity re-read a neighbour's entry; a wave without outliers reads
-            // 8 harmless bytes of the offset array
-            const bool has_pay = wd.n > 0 && (uint64_t)wd.base < s.outlier_capacity;
-            const uint64_t last = has_pay ? min((uint64_t)wd.n, s.outlier_capacity - wd.base) - 1u : 0u;
-            const uint2 *src = has_pay ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
-                                       : reinterpret_cast<const uint2 *>(s.row_off);
-            wd.mine = src[min((uint64_t)lane, last)];
-            if (!has_pay || (uint64_t)lane > last)
-                wd.mine = make_uint2(0u, 0u);
-        }
+        wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
+        const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, nr - 1);
+        const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, nr - 1);
+        wd.n = ro_l + __popc(fw_l) - wd.base;
+        wd.in_list = (uint64_t)wd.base < s.outlier_capacity ? (uint32_t)min((uint64_t)wd.n, s.outlier_capacity - wd.base) : 0u;
         return wd;
+    };
+    // unconditional load (a conditional one would be waited for on the spot): lanes past the window or the list's capacity
+    // re-read a neighbour's entry; a wave without outliers reads 8 harmless bytes of the offset array.  Nothing looks at the
+    // entry before it is staged.
+    auto request = [&](const AttendSide &s, Window &wd) {
+        const uint2 *src = wd.in_list ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
+                                      : reinterpret_cast<const uint2 *>(s.row_off);
+        wd.mine = src[min((uint32_t)lane, wd.in_list ? wd.in_list - 1u : 0u)];
+    };
+    // Both sides' bounds before either request: looking at the second side's offsets after the first request would wait for
+    // that too (0.7 us per tile).
+    Window wk = {}, wvw = {};
+    auto open_windows = [&](int nr) {
+        if (nr > 0) {
+            wk = window_of(a.k, tk, nr);
+            wvw = window_of(a.v, tv, nr);
+            request(a.k, wk);
+            request(a.v, wvw);
+        } else {
+            wk.n = wvw.n = wk.in_list = wvw.in_list = 0u;
+        }
     };
     auto stage_window = [&](const AttendSide &s, const Window &wd, uint32_t *stage) {
         uint2 *st_pay = reinterpret_cast<uint2 *>(stage + kStageWords + 3 * kStageRows);
-        st_pay[lane] = wd.mine;
+        st_pay[lane] = (uint32_t)lane < wd.in_list ? wd.mine : make_uint2(0u, 0u);
         if (wd.n > 64u) {  // wave-uniform and rare: more than 64 outliers in 16 rows
             for (uint32_t k = 64u + lane; k < min(wd.n, (uint32_t)kPaySlots); k += 64u) {
                 const uint64_t at = (uint64_t)wd.base + k;
@@ -750,63 +777,55 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         }
     };
 
-    // One chunk of `row` as the library's decode returns it (four fp16 values, two dwords), in three
-    // steps so that the LDS round trips of neighbouring chunks overlap: the code, then the table
-    // entries and the payload slot it selects, then the arithmetic.
-    // kFast: the wave's whole payload window sits in LDS and no scale of the tile can push a product
-    // beyond the fp16 range, so there is neither a far load nor a clamp.  The choice is made per
-    // tile and side.
-    auto read_code = [&](const uint32_t *stage, int row, uint32_t c) {
-        const uint32_t bitpos = c * w;
-        const uint32_t *rw = stage + row * row_words + (bitpos >> 5);
-        const uint32_t d0 = rw[0], d1 = rw[1];
-        const uint32_t code = __builtin_amdgcn_alignbit(d1, d0, bitpos & 31u) & code_mask;
-        // a chunk slot past the row's chunks (value side, 24 chunks per row): what was read lies inside
-        // the staged words but means nothing; code 0 decodes to zeros and its flag bit is never set
-        return (kNc % 16 == 0 || c < (uint32_t)kNc) ? code : 0u;
-    };
-    // A chunk is reconstructed in three steps so that the LDS round trips of neighbouring chunks overlap: the
-    // primary's entry of the look-up table and the payload slot (pre), the table entry (fetch), the arithmetic
-    // (finish).
+    // One chunk as the library's decode returns it (four fp16 values, two dwords), in three steps so that the LDS round
+    // trips of neighbouring chunks overlap: the primary's entry of the look-up table and the payload slot (pre), the table
+    // entry (fetch), the arithmetic (finish).  code: the chunk's w bits, with others above them.
+    // slot: byte offset in the window of the payload that the chunk takes if it is flagged, of the next one if not.
+    // flag: all ones for a flagged chunk, else zero; rows that are not there have none.
+    // kFast: the wave's whole payload window sits in LDS and no scale of the tile can push a product beyond the fp16 range,
+    // so there is neither a far load nor a clamp.  The choice is made per tile and side.
     struct Pre {
-        uint32_t lutv, s_off, pos;
-        uint2 pay;
+        uint32_t code, s_idx, slot;
+        uint2 lutv, pay;
     };
     struct Fetched {
         float4_t d;
-        uint32_t lutv, pos;
+        uint32_t code, sign, slot;
         uint2 pay;
     };
-    auto pre = [&](const uint32_t *stage, uint32_t base, uint32_t code, uint32_t c, uint32_t word, uint32_t roff) {
+    auto pre = [&](auto fast_tag, const uint32_t *stage, uint32_t code, uint32_t slot) {
         Pre f;
         uint32_t p;
         if (kPow2) {
-            p = (code >> g.log2_S) & 31u;
-            f.s_off = (code << 4) & (((uint32_t)g.S - 1u) << 4);
+            p = (code >> g.log2_S) & 31u;  // w_idx = log2 S + 5
+            f.s_idx = code & ((uint32_t)g.S - 1u);
         } else {
             const uint32_t kk = code & idx_mask;
-            p = (uint32_t)((float)kk * g.inv_S);  // < 48
-            f.s_off = (kk - __umul24(p, (uint32_t)g.S)) << 4;
+            p = __umul24(kk, div_mul) >> div_shift;  // < 48
+            f.s_idx = kk - __umul24(p, (uint32_t)g.S);
         }
+        f.code = code;
+        f.slot = slot;
         f.lutv = lut[p];
-        f.pos = roff + __popc(word & ((1u << c) - 1u)) - base;
-        const uint2 *st_pay = reinterpret_cast<const uint2 *>(stage + kStageWords + 3 * kStageRows);
-        f.pay = st_pay[min(f.pos, (uint32_t)kPaySlots - 1u)];
+        const char *st_pay = reinterpret_cast<const char *>(stage + kStageWords + 3 * kStageRows);
+        constexpr uint32_t kLastSlot = 8u * (kPaySlots - 1u);
+        f.pay = *reinterpret_cast<const uint2 *>(st_pay + (decltype(fast_tag)::value ? slot : min(slot, kLastSlot)));
         return f;
     };
     auto fetch = [&](const float *tab, const Pre &q) {
         Fetched f;
-        f.d = *reinterpret_cast<const float4_t *>(reinterpret_cast<const char *>(tab) + (q.lutv & 0x7fffffffu) + q.s_off);
-        f.lutv = q.lutv;
-        f.pos = q.pos;
+        f.d = *reinterpret_cast<const float4_t *>(reinterpret_cast<const char *>(tab) + ((q.s_idx << 4) + q.lutv.x));
+        f.sign = q.lutv.y;
+        f.code = q.code;
+        f.slot = q.slot;
         f.pay = q.pay;
         return f;
     };
-    auto finish = [&](auto fast_tag, const AttendSide &s, uint32_t base, const Fetched &f, uint32_t code,
-                      uint32_t c, uint32_t word, float sol, bool row_valid) {
+    auto finish = [&](auto fast_tag, const AttendSide &s, uint32_t base, const Fetched &f, uint32_t flag, float sol) {
         constexpr bool kFast = decltype(fast_tag)::value;
         // the radius with the primary's sign
-        const float rh = __uint_as_float(__float_as_uint((float)(code >> w_idx) * sol) | (f.lutv & 0x80000000u));
+        const uint32_t r = __builtin_amdgcn_ubfe(f.code, w_idx, w - w_idx);
+        const float rh = __uint_as_float(__float_as_uint((float)r * sol) | f.sign);
         float y0 = rh * f.d[0], y1 = rh * f.d[1], y2 = rh * f.d[2], y3 = rh * f.d[3];
         if (!kFast) {
             const float lim = 65504.f;  // the decode saturates instead of overflowing to infinity
@@ -815,30 +834,28 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
             y2 = __builtin_amdgcn_fmed3f(y2, -lim, lim);
             y3 = __builtin_amdgcn_fmed3f(y3, -lim, lim);
         }
-        uint2 out = make_uint2(pack_half2(y0, y1), pack_half2(y2, y3));
-        const bool fl = row_valid && ((word >> c) & 1u);
         uint2 pay = f.pay;
         if (!kFast) {
             const bool any = s.outlier_capacity > 0;
             const uint2 *src = any ? reinterpret_cast<const uint2 *>(s.outliers)
                                    : reinterpret_cast<const uint2 *>(s.row_off);
             const uint64_t last = any ? s.outlier_capacity - 1u : 0u;
-            const uint64_t at = (uint64_t)base + f.pos;
+            const uint64_t at = (uint64_t)base + (f.slot >> 3);
             const uint2 far = src[min(at, last)];
-            if (f.pos >= (uint32_t)kPaySlots)
+            if (f.slot >= 8u * kPaySlots)
                 pay = at < s.outlier_capacity ? far : make_uint2(0u, 0u);
         }
-        out.x = fl ? pay.x : out.x;
-        out.y = fl ? pay.y : out.y;
-        return out;
+        return make_uint2((flag & pay.x) | (~flag & pack_half2(y0, y1)), (flag & pay.y) | (~flag & pack_half2(y2, y3)));
     };
 
-    Window wk = open_window(a.k, tk, nrows), wvw = open_window(a.v, tv, nrows);
+    asm volatile("" : "+v"(vis));  // arrived before the windows are requested: its first use would wait for these too
+    open_windows(nrows);
+    __syncthreads();  // the tables
 
     for (int t0 = row_begin; t0 < row_end; t0 += kJointTile) {
         // ---- this tile's rows and payload windows into LDS; the next tile's rows requested -----------
-        stage_tile(tk, stage_k, lane);
-        stage_tile(tv, stage_v, lane);
+        stage_tile(tk, stage_k, nrows, lane);
+        stage_tile(tv, stage_v, nrows, lane);
         stage_window(a.k, wk, stage_k);
         stage_window(a.v, wvw, stage_v);
         wave_lds_sync();
@@ -872,23 +889,33 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
                     (float)__builtin_bit_cast(_Float16, (uint16_t)stage_k[kStageWords + kStageRows + n16]);
                 const uint32_t roff = stage_k[kStageWords + 2 * kStageRows + n16];
                 const float sol = sigma * inv_L;
-                const bool valid = n16 < nrows;
+                const uint32_t flags = word >> (kM * j4);  // bit m: the lane's chunk m
+                uint32_t slot = (roff - base_k + __popc(word & ((1u << (kM * j4)) - 1u))) << 3;
                 uint32_t code[kM];
 #pragma unroll
-                for (int m = 0; m < kM; ++m)
-                    code[m] = read_code(stage_k, n16, (uint32_t)(4 * m + j4));
-                Pre pb = pre(stage_k, base_k, code[0], (uint32_t)j4, word, roff);
+                for (int m = 0; m < kM; ++m) {
+                    const uint32_t bitpos = (uint32_t)(kM * j4 + m) * w;
+                    const uint32_t *rw = stage_k + n16 * row_words + (bitpos >> 5);
+                    code[m] = __builtin_amdgcn_alignbit(rw[1], rw[0], bitpos & 31u);
+                }
+                auto flag_of = [&](int m) { return (uint32_t)__builtin_amdgcn_sbfe((int)flags, m, 1); };
+                auto next = [&](int m) {
+                    const Pre f = pre(fast_tag, stage_k, code[m], slot);
+                    slot = (uint32_t)(__mul24((int)flag_of(m), -8) + (int)slot);
+                    return f;
+                };
+                Pre pb = next(0);
                 Fetched cur = fetch(tab_k, pb);
                 if (kM > 1)
-                    pb = pre(stage_k, base_k, code[1], (uint32_t)(4 + j4), word, roff);
+                    pb = next(1);
 #pragma unroll
                 for (int m = 0; m < kM; ++m) {
                     Fetched nxt = cur;
                     if (m + 1 < kM)
                         nxt = fetch(tab_k, pb);
                     if (m + 2 < kM)
-                        pb = pre(stage_k, base_k, code[m + 2], (uint32_t)(4 * (m + 2) + j4), word, roff);
-                    const uint2 kh = finish(fast_tag, a.k, base_k, cur, code[m], (uint32_t)(4 * m + j4), word, sol, valid);
+                        pb = next(m + 2);
+                    const uint2 kh = finish(fast_tag, a.k, base_k, cur, flag_of(m), sol);
                     sc = mfma16(kh, qb[m], sc);
                     cur = nxt;
                     __builtin_amdgcn_sched_barrier(0);  // keep the order of the three steps
@@ -902,14 +929,13 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
             // ---- softmax update: lane (head n16, j4) holds the scores of rows 4 j4 + i --------------------
             float s4[4];
             float mx = kNegBig;
+            const int seen = min(nrows, vis - (t0 + wv * kStageRows)) - 4 * j4;  // of the lane's four rows
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const bool seen = 4 * j4 + i < nrows && t0 + wv * kStageRows + 4 * j4 + i < vis;
-                s4[i] = seen ? sc[i] * a.qscale : kNegBig;
+                s4[i] = i < seen ? sc[i] * a.qscale : 3.f * kNegBig;  // its weight is 0 whatever the maximum
                 mx = fmaxf(mx, s4[i]);
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = max_over_rows(mx);
             const float mn = fmaxf(m_run, mx);
             if (__any(mn > m_run)) {
                 // some head's maximum rose: rescale.  The accumulators of this lane belong to heads
@@ -930,9 +956,7 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
             float pw[4], ph[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float e = __builtin_amdgcn_exp2f(s4[i] - m_run);
-                const bool seen = 4 * j4 + i < nrows && t0 + wv * kStageRows + 4 * j4 + i < vis;
-                pw[i] = seen ? e : 0.f;
+                pw[i] = __builtin_amdgcn_exp2f(s4[i] - m_run);
                 l_run += pw[i];
             }
             // P^T as the A operand of the value products, split into an fp16 pair.  The weights (<= 1)
@@ -955,10 +979,8 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         }
 
         // ---- the next tile's payload windows (its offsets have arrived by now) ---------------------------
-        if (more) {
-            wk = open_window(a.k, tk, nn);
-            wvw = open_window(a.v, tv, nn);
-        }
+        if (more)
+            open_windows(nn);
 
         // ---- weighted values: lane (n16, j4) supplies chunks n16 and n16 + 16 of rows 4 j4 + i -----------
         if (nrows > 0) {
@@ -970,31 +992,46 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
                 const uint4v sig4 = *reinterpret_cast<const uint4v *>(stage_v + kStageWords + kStageRows + 4 * j4);
                 const uint4v roff4 =
                     *reinterpret_cast<const uint4v *>(stage_v + kStageWords + 2 * kStageRows + 4 * j4);
-                uint32_t code[4 * kU];
+                uint32_t code[4 * kU], slot[4];
                 float sol[4];
+                const uint32_t c0 = (uint32_t)(kU * n16), bitpos = c0 * w;  // the lane's chunks: c0 .. c0 + kU - 1
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     sol[i] = (float)__builtin_bit_cast(_Float16, (uint16_t)sig4[i]) * inv_L;
-#pragma unroll
-                    for (int u = 0; u < kU; ++u)
-                        code[4 * u + i] = read_code(stage_v, 4 * j4 + i, (uint32_t)(n16 + 16 * u));
+                    slot[i] = (roff4[i] - base_v + __popc(word4[i] & ((1u << c0) - 1u))) << 3;
+                    const uint32_t *rw = stage_v + (4 * j4 + i) * row_words + (bitpos >> 5);
+                    code[kU * i] = __builtin_amdgcn_alignbit(rw[1], rw[0], bitpos & 31u);
+                    if (kU == 2)
+                        code[kU * i + kU - 1] = __builtin_amdgcn_alignbit(__builtin_amdgcn_alignbit(rw[2], rw[1], bitpos & 31u),
+                                                                          code[kU * i], w);
+                    // chunks past the row (24 per row): what was read lies inside the staged words but means nothing; code 0
+                    // decodes to zeros and its flag bit is never set
+                    if (kNc % 16 != 0 && c0 >= (uint32_t)kNc)
+                        code[kU * i] = code[kU * i + kU - 1] = 0u;
                 }
-                Pre pb = pre(stage_v, base_v, code[0], (uint32_t)n16, word4[0], roff4[0]);
+                auto flag_of = [&](int at) { return (uint32_t)__builtin_amdgcn_sbfe((int)word4[at & 3], c0 + (uint32_t)(at >> 2), 1); };
+                auto next = [&](int at) {  // chunk at >> 2 of row at & 3
+                    const int i = at & 3;
+                    const Pre f = pre(fast_tag, stage_v, code[kU * i + (at >> 2)], slot[i]);
+                    if (at + 4 < 4 * kU)
+                        slot[i] = (uint32_t)(__mul24((int)flag_of(at), -8) + (int)slot[i]);
+                    return f;
+                };
+                Pre pb = next(0);
                 Fetched cur = fetch(tab_v, pb);
-                pb = pre(stage_v, base_v, code[1], (uint32_t)n16, word4[1], roff4[1]);
+                pb = next(1);
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     uint2 vh[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int at = 4 * u + i, nx = at + 1, n2 = at + 2;
+                        const int at = 4 * u + i;
                         Fetched nxt = cur;
-                        if (nx < 4 * kU)
+                        if (at + 1 < 4 * kU)
                             nxt = fetch(tab_v, pb);
-                        if (n2 < 4 * kU)
-                            pb = pre(stage_v, base_v, code[n2], (uint32_t)(n16 + 16 * (n2 >> 2)), word4[n2 & 3], roff4[n2 & 3]);
-                        vh[i] = finish(fast_tag, a.v, base_v, cur, code[at], (uint32_t)(n16 + 16 * u), word4[i],
-                                       sol[i], 4 * j4 + i < nrows);
+                        if (at + 2 < 4 * kU)
+                            pb = next(at + 2);
+                        vh[i] = finish(fast_tag, a.v, base_v, cur, flag_of(at), sol[i]);
                         cur = nxt;
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -1039,7 +1076,7 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         if (head < G) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                float *dst = red + (wv * G + head) * kRedStride + 2 + 64 * u + 4 * n16;
+                float *dst = red + (wv * G + head) * kRedStride + 2 + 4 * (kU * n16 + u);
                 *reinterpret_cast<float2 *>(dst) = make_float2(acc[u][0][i], acc[u][1][i]);
                 *reinterpret_cast<float2 *>(dst + 2) = make_float2(acc[u][2][i], acc[u][3][i]);
             }
@@ -1165,7 +1202,7 @@ static size_t joint_lds_bytes(const Geometry &g, int G, int *table_floats)
     const int tf = 13 * g.S * 4;
     if (table_floats)
         *table_floats = tf;
-    const size_t loop = (48 + 2 * (size_t)tf + (size_t)kJointWaves * 2 * kSideWords) * sizeof(float);
+    const size_t loop = (2 * 48 + 2 * (size_t)tf + (size_t)kJointWaves * 2 * kSideWords) * sizeof(float);
     const size_t merge = (size_t)kJointWaves * G * kRedStride * sizeof(float);
     return loop > merge ? loop : merge;
 }
