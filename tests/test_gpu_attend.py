@@ -324,6 +324,50 @@ def test_attend_windows_larger_than_the_lds_slots():
     _check(got, want, Kd, Vd, q, 0.3)
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("D,S,T", [(128, 256, 37), (96, 85, 16), (64, 24, 145)])
+def test_attend_window_sizes(D, S, T, n):
+    """Outlier windows of 16 rows at the edges of what a wave holds (a lane's entry, 64; the slots, 128), among them the last
+    chunks of the window and of a row; other rows of the tile without outliers, the last tile of 5, 16 or 1 rows."""
+    B, H, Hq, b_r = 1, 2, 6, 4
+    gen = torch.Generator().manual_seed(100 * n + D)
+    nc = D // 4
+
+    def tensor(at):
+        x = 0.05 * torch.randn(B, H, T, nc, 4, generator=gen)
+        for h in range(H):
+            flat = torch.randperm(16 * nc, generator=gen)[:n]
+            flat[0] = 16 * nc - 1 if at == 0 else 5 * nc - 1  # the last chunk of all, or of a row
+            flat = torch.unique(flat)  # the chosen one may have been among the others
+            x[0, h, flat // nc, flat % nc] = 3.0 + torch.rand(len(flat), 4, generator=gen)
+        return x.view(B, H, T, D).to(torch.float16)
+
+    k, v = tensor(0), tensor(1)
+    sec_k, sec_v = _secs(40 + n, H, S)
+    # the threshold between the two kinds of chunks, whatever their shares
+    thr = torch.full((H,), 4.0, dtype=torch.float64)
+    enc = []
+    for x, sec in ((k, sec_k), (v, sec_v)):
+        x_dev = x.to(DEV)
+        params = hq.params_for(x_dev, S, b_r)
+        bufs = hq.alloc_encoded(params, DEV, outlier_capacity=H * T * nc)
+        hq.hqmq_encode_given_thresholds(params, x_dev, sec.to(DEV), thr.to(DEV), bufs, hq.alloc_workspace(params, DEV))
+        enc.append((params, bufs))
+    torch.cuda.synchronize()
+
+    class Host:
+        def __init__(self, b):
+            self.codes, self.flags, self.row_off = (t.cpu().numpy().view(np.uint32) for t in (b.codes, b.flags, b.row_off))
+            self.sigma, self.outliers = (t.cpu().numpy().view(np.uint16) for t in (b.sigma, b.outliers))
+    hosts = [Host(b) for _, b in enc]
+    counts = [np.diff(h.row_off.astype(np.int64)).reshape(H, T)[:, :16].sum(1) for h in hosts]
+    assert all((n - 1 <= c).all() and (c <= n).all() for c in counts)
+    q = _query(B, Hq, seed=n, gain=1.0, D=D)
+    want, Kd, Vd = _oracle_attend(hosts, (sec_k.numpy(), sec_v.numpy()), q, 0.1, B, H, T, b_r, D)
+    got = _gpu_attend(enc[0][0], q, 0.1, enc[0][1], sec_k.to(DEV), enc[1][1], sec_v.to(DEV))
+    _check(got, want, Kd, Vd, q, 0.1)
+
+
 def test_attend_with_truncated_outlier_lists():
     """An encode that overflowed its lists: the dropped outliers count as zeros, as in the decode."""
     B, H, T, Hq, S, b_r = 1, 2, 300, 4, 16, 6
