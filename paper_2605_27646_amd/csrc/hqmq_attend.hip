@@ -1108,89 +1108,89 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
     }
 }
 
-// grid = (B * H * G, D / 16): workgroup (head, y) produces 16 of the head's D output dimensions.
-// First the global maximum and the weight 2^(m_s - M) of every split (kept in LDS), then plain
-// weighted sums with independent loads: thread (j, i) adds the splits j, j + 16, ... for dimension i.
-constexpr int kMergeDims = 16;
-constexpr int kMergeWays = kAttThreads / kMergeDims;
-__global__ __launch_bounds__(kAttThreads) void k_attend_merge(AttendArgs a)
+// grid = (B * H * G, ceil(D / 64)): a workgroup produces up to 64 of a head's output dimensions, a lane each; its waves
+// share the splits.  Every wave finds the head's maximum by itself, has a weight 2^(m_s - M) per lane and its first partial
+// sums requested before it waits for anything; one barrier.  Four waves that have all of theirs requested at once up to 32
+// splits, else 16 waves.  Bound by the latency of one load after the launch.  Whole calls with 16 dimensions per workgroup
+// of 256 threads and four barriers / so: 256 heads of 4 splits, D = 64, 20.0 / 19.6 us, 1024 heads of 4, D = 64, 24.6 /
+// 21.8, 2048 heads of 1, D = 96, 41 / 34; 4 heads of
+// 256 splits 16.4 / 15.9 (four waves for these: 18.7).
+constexpr int kMergeDims = 64;
+constexpr int kMergeFew = 32;  // splits
+template <typename F>
+__device__ __forceinline__ float reduce_wave(float v, F f)
 {
-    extern __shared__ float wts[];  // [n_splits] weights, then [kMergeWays][kMergeDims + 1] partial sums
-    __shared__ float red[kAttWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    auto with = [&](auto ctrl) {  // another lane of the row
+        return f(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)));
+    };
+    v = with(std::integral_constant<int, 0xb1>{});   // neighbours
+    v = with(std::integral_constant<int, 0x4e>{});   // pairs
+    v = with(std::integral_constant<int, 0x141>{});  // fours: the half row mirrored
+    v = with(std::integral_constant<int, 0x140>{});  // eights: the row mirrored
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void k_attend_merge(AttendArgs a)
+{
+    constexpr int kEarly = kWaves == 4 ? kMergeFew / 4 : 16;
+    __shared__ float sums[kWaves][kMergeDims], denominators[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t head = blockIdx.x;
-    const int d0 = blockIdx.y * kMergeDims;
+    const int d = blockIdx.y * kMergeDims + lane;
     const int n = a.n_splits;
     const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + head * n;
-    const float *pa = a.part_acc + head * n * 128;
+    const float *pa = a.part_acc + head * n * 128 + d;  // a pitch of 128: dimensions past D are read and not used
+    const int per = (n + kWaves - 1) / kWaves, first = wv * per, end = min(n, first + per);
 
-    // the first four partial sums of this thread's dimension are requested before anything waits on the maxima
-    const int i = tid % kMergeDims, j = tid / kMergeDims;
-    float early[4];
+    float early[kEarly];
+    float2 st = ml[min(first + lane, n - 1)];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int sp = j + u * kMergeWays;
-        early[u] = sp < n ? pa[(size_t)sp * 128 + d0 + i] : 0.f;
-    }
+    for (int u = 0; u < kEarly; ++u)
+        early[u] = pa[(size_t)min(first + u, n - 1) * 128];
     float mx = kNegBig;
-    for (int s = tid; s < n; s += kAttThreads)
+    for (int s = lane; s < n; s += 64)
         mx = fmaxf(mx, ml[s].x);
-#pragma unroll
-    for (int step = 32; step >= 1; step >>= 1)
-        mx = fmaxf(mx, __shfl_xor(mx, step));
-    if (lane == 0)
-        red[wv] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    float lsum = 0.f;
-    for (int s = tid; s < n; s += kAttThreads) {
-        const float2 st = ml[s];
-        const float wgt = __builtin_amdgcn_exp2f(st.x - mx);
-        wts[s] = wgt;
+    mx = reduce_wave(mx, [](float x, float y) { return fmaxf(x, y); });
+    float o = 0.f, lsum = 0.f;
+    for (int s0 = first; s0 < end; s0 += 64) {  // once for up to 64 kWaves splits
+        if (s0 > first)
+            st = ml[min(s0 + lane, n - 1)];
+        const float wgt = s0 + lane < end ? __builtin_amdgcn_exp2f(st.x - mx) : 0.f;
         lsum = fmaf(st.y, wgt, lsum);
-    }
+        const int here = min(end - s0, 64);
+        for (int j0 = 0; j0 < here; j0 += kEarly) {
+            float v[kEarly];
 #pragma unroll
-    for (int step = 32; step >= 1; step >>= 1)
-        lsum += __shfl_xor(lsum, step);
+            for (int u = 0; u < kEarly; ++u)
+                v[u] = s0 + j0 == first ? early[u] : pa[(size_t)min(s0 + j0 + u, n - 1) * 128];
+#pragma unroll
+            for (int u = 0; u < kEarly; ++u)
+                if (j0 + u < here)  // uniform
+                    o = fmaf(v[u], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), j0 + u)), o);
+        }
+    }
+    lsum = reduce_wave(lsum, [](float x, float y) { return x + y; });
+    sums[wv][lane] = o;
     if (lane == 0)
-        red[wv] = lsum;
+        denominators[wv] = lsum;
     __syncthreads();
-    lsum = (red[0] + red[1]) + (red[2] + red[3]);
-
-    float o = 0.f;
+    if (wv != 0)
+        return;
+    float tot = 0.f;
+    lsum = 0.f;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int sp = j + u * kMergeWays;
-        if (sp < n)
-            o = fmaf(early[u], wts[sp], o);
+    for (int k = 0; k < kWaves; ++k) {
+        lsum += denominators[k];
+        tot += sums[k][lane];
     }
-    int s = j + 4 * kMergeWays;
-    for (; s + 3 * kMergeWays < n; s += 4 * kMergeWays) {  // four loads in flight
-        const float v0 = pa[(size_t)s * 128 + d0 + i];
-        const float v1 = pa[(size_t)(s + kMergeWays) * 128 + d0 + i];
-        const float v2 = pa[(size_t)(s + 2 * kMergeWays) * 128 + d0 + i];
-        const float v3 = pa[(size_t)(s + 3 * kMergeWays) * 128 + d0 + i];
-        o = fmaf(v0, wts[s], o);
-        o = fmaf(v1, wts[s + kMergeWays], o);
-        o = fmaf(v2, wts[s + 2 * kMergeWays], o);
-        o = fmaf(v3, wts[s + 3 * kMergeWays], o);
-    }
-    for (; s < n; s += kMergeWays)
-        o = fmaf(pa[(size_t)s * 128 + d0 + i], wts[s], o);
-    float *sums = wts + n;
-    sums[j * (kMergeDims + 1) + i] = o;
-    __syncthreads();
-    if (tid < kMergeDims) {
-        float tot = 0.f;
-#pragma unroll
-        for (int jj = 0; jj < kMergeWays; ++jj)
-            tot += sums[jj * (kMergeDims + 1) + tid];
-        // a head that may see no token at all has an empty softmax: zeros
-        a.out[head * a.D + d0 + tid] = lsum > 0.f ? (_Float16)(tot / lsum) : (_Float16)0.f;
-    }
+    // a head that may see no token at all has an empty softmax: zeros
+    if (d < a.D)
+        a.out[head * a.D + d] = lsum > 0.f ? (_Float16)(tot / lsum) : (_Float16)0.f;
     // log-sum-exp of the head's scores (the running maximum is kept in the log2 domain)
-    if (a.lse && blockIdx.y == 0 && tid == 0)
+    if (a.lse && blockIdx.y == 0 && lane == 0)
         a.lse[head] = lsum > 0.f ? (mx + __builtin_amdgcn_logf(lsum)) * 0.693147180559945309417f
                                  : -__builtin_inff();
 }
@@ -1306,9 +1306,11 @@ hipError_t launch_attend(const Geometry &g, const AttendArgs &a, hipStream_t str
     hipError_t err = hipGetLastError();
     if (err != hipSuccess)
         return err;
-    const size_t merge_lds = ((size_t)a.n_splits + kMergeWays * (kMergeDims + 1)) * sizeof(float);
-    hipLaunchKernelGGL(k_attend_merge, dim3((unsigned)(g.B * g.H * a.G), (unsigned)(g.D / kMergeDims)), dim3(kAttThreads),
-                       merge_lds, stream, a);
+    const dim3 outputs((unsigned)(g.B * g.H * a.G), (unsigned)((g.D + kMergeDims - 1) / kMergeDims));
+    if (a.n_splits <= kMergeFew)
+        hipLaunchKernelGGL(k_attend_merge<4>, outputs, dim3(64 * 4), 0, stream, a);
+    else
+        hipLaunchKernelGGL(k_attend_merge<16>, outputs, dim3(64 * 16), 0, stream, a);
     return hipGetLastError();
 }
 

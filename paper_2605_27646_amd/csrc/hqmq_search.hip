@@ -417,7 +417,7 @@ __device__ __forceinline__ void write_row_offsets(const Geometry &g, const Works
 //
 // Dynamic LDS layout:
 //   amat  [2*S16][64] x 16 B   MFMA A operands, one 64-lane tile per 8 secondaries
-//                              (copied from the table k_prepare_operands built for the head)
+//                              (copied from the table that the call's first kernel built for the head)
 //   secl  [16*S16][4] f32      the head's secondaries (zero padded to a multiple of 16)
 //   pack  [kWaves][2][32] u32 row code words being assembled
 //   rcnt  [search_rows] u32    outliers per row of the workgroup

@@ -368,6 +368,29 @@ def test_attend_window_sizes(D, S, T, n):
     _check(got, want, Kd, Vd, q, 0.1)
 
 
+@pytest.mark.parametrize("D,T", [(128, 64 * 31 + 1), (64, 64 * 33), (96, 64 * 64 + 1), (128, 64 * 65)])
+def test_attend_split_counts(D, T):
+    """One kv head, so that every tile of 64 tokens is a split of its own: 32, 33, 65 and 65 of them, where four waves, with
+    all their partial sums requested at once, give way to 16; with lse."""
+    B, H, Hq, S, b_r = 1, 1, 3, 16, 4
+    k, v = _tensors(B, H, T, seed=T, D=D)
+    sec_k, sec_v = _secs(12, H, S)
+    gk, gv = gpu_encode(k.to(DEV), sec_k.to(DEV), b_r), gpu_encode(v.to(DEV), sec_v.to(DEV), b_r)
+    q = _query(B, Hq, seed=T + 1, gain=2.0, D=D)
+    want, Kd, Vd = _oracle_attend((gk, gv), (sec_k.numpy(), sec_v.numpy()), q, 0.2, B, H, T, b_r, D)
+    q_dev = q.to(DEV)
+    out = torch.full_like(q_dev, float("nan"))
+    lse = torch.full((B, Hq), float("nan"), device=DEV)
+    ws = torch.empty(hq.hqmq_attend_workspace_bytes(gk.params, Hq), dtype=torch.uint8, device=DEV)
+    ws.fill_(0xCD)
+    hq.hqmq_attend_lse(gk.params, q_dev, 0.2, gk.bufs, sec_k.to(DEV), gv.bufs, sec_v.to(DEV), out, lse, ws)
+    torch.cuda.synchronize()
+    s = np.einsum("bhgd,bhtd->bhgt", q.numpy().astype(np.float64).reshape(B, H, Hq // H, D), Kd.hat) * 0.2
+    top = s.max(-1, keepdims=True)
+    lse_want = (top[..., 0] + np.log(np.exp(s - top).sum(-1))).reshape(B, Hq)
+    _check(out.cpu().numpy().astype(np.float64), want, Kd, Vd, q, 0.2, lse=lse.cpu().numpy().astype(np.float64), lse_want=lse_want)
+
+
 def test_attend_with_truncated_outlier_lists():
     """An encode that overflowed its lists: the dropped outliers count as zeros, as in the decode."""
     B, H, T, Hq, S, b_r = 1, 2, 300, 4, 16, 6
