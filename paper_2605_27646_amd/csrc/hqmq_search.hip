@@ -1014,6 +1014,8 @@ namespace {
 // 27.9 in all, of a best that is at least 1/sqrt(2): 2.35e-6 (3.4e-7 measured on 800,000 chunks).  Secondaries of other
 // norms scale both sides by the largest.
 constexpr float kCellBand = 2.5e-6f;
+constexpr float kCellEps = 1.0e-5f;  // the lists keep what comes within this of the best
+static_assert(kCellEps == kListEps && 2.0f * kCellBand < kCellEps, "a list holds the runner-up of every chunk in the band");
 constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the
                                                // cube by 5.4e-7 (fold 3.6e-7, reciprocal and product 1.8e-7), in 0 .. n - 1
 // The search numbers the element P_0 that it folds with by 4 f + 16 for f = p_0 / 4 + p_1 / 2 + p_2 + 2 p_3 in twice its

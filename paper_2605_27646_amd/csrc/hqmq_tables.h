@@ -177,7 +177,7 @@ __device__ __forceinline__ void build_operands(const Geometry &g, const Workspac
 constexpr int kCellThreads = 256;      // workgroup of the index build: 4 lanes per box
 constexpr int kCoarseCap = 1024;       // codewords of a block of 4^3 boxes
 constexpr int kMidCap = 384;           // codewords of a sub-block of 2^3 boxes
-constexpr float kCellEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
+constexpr float kListEps = 1.0e-5f;    // lists keep what comes within this fraction of the centre's best score: more than
                                        // kCellBand times the ratio of two scores of a box plus the rounding of the test
 constexpr uint32_t kCellPad = 0x7fffu; // list entry without a codeword; bit 15 marks the last group of a list
 
@@ -342,7 +342,7 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
         v_best = value_at(best, m1, m2, m3);
     }
     {
-        const float hb = 4.f * hf + margin, eps = kCellEps * fabsf(v_best);
+        const float hb = 4.f * hf + margin, eps = kListEps * fabsf(v_best);
 #pragma unroll
         for (int u = 0; u < kOwn; ++u) {
             if (u * kCellThreads >= S)  // uniform
@@ -416,7 +416,7 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
             vb = fmaxf(vb, __shfl_xor(vb, 16, 64));
             const uint32_t holds = (uint32_t)(__ballot(v == vb) >> (lane & 32));
             const float4_t bf = lds.cf[__shfl(j_best, (lane & 32) + __ffs((int)holds) - 1, 64)];
-            const float eps = kCellEps * fabsf(vb), hm = 2.f * hf + margin;
+            const float eps = kListEps * fabsf(vb), hm = 2.f * hf + margin;
             for (int j0 = 0; j0 < nc; j0 += 32) {  // uniform over the half-wave
                 const int j = j0 + l;
                 const float4_t c = lds.cf[min(j, nc - 1)];
@@ -457,7 +457,7 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
             quad_max(dpp_move<0xB1>(vb), dpp_move<0xB1>(jb));
             quad_max(dpp_move<0x4E>(vb), dpp_move<0x4E>(jb));
             const float4_t bf = lds.cf[jb];
-            const float eps = kCellEps * fabsf(vb);
+            const float eps = kListEps * fabsf(vb);
             float v_own[2] = {-3.4e38f, -3.4e38f};  // the two strongest survivors of this lane's share
             int j_own[2] = {jb, jb};
 #pragma unroll
