@@ -229,6 +229,38 @@ __global__ __launch_bounds__(kSelectThreads) void k_init(Geometry g, WorkspaceOf
         ws.thr[h] = tn.thr_given ? tn.thr_given[h] : __longlong_as_double(0x7ff0000000000000LL);
 }
 
+// Rows r, r + step, r + 2 step, ... of a head, those of all batch entries one after the other: where row r lies and how far it is
+// from each to the next.  A step is so many whole entries and rows, and one entry more when the rows run over its end: the
+// time of a step does not depend on T.  (One entry at a time, [1024, 8, 1, 128] took 49 us more.)
+struct RowWalk {
+    int64_t first, step, wrap;
+    uint32_t t, rows;
+    __device__ __forceinline__ RowWalk(const Geometry &g, uint32_t r, uint32_t by)
+    {
+        t = r;
+        rows = by;
+        first = (int64_t)r * g.st;
+        step = (int64_t)by * g.st;
+        wrap = 0;
+        if (g.B > 1) {  // uniform
+            const uint32_t T = (uint32_t)g.T, b = r / T, entries = by / T;
+            t = r - b * T;
+            rows = by - entries * T;
+            wrap = g.sb - (int64_t)T * g.st;
+            first += (int64_t)b * wrap;
+            step += (int64_t)entries * wrap;
+        }
+    }
+    __device__ __forceinline__ int64_t over_end(const Geometry &g)  // after each step, where there are entries
+    {
+        asm volatile("" : "+v"(t));  // a branch, not 16 more instructions per step for a call without entries (0.8 us of 15)
+        t += rows;
+        const bool over = t >= (uint32_t)g.T;
+        t -= over ? (uint32_t)g.T : 0u;
+        return over ? wrap : 0;
+    }
+};
+
 // threshold on squares: fl(fl(C*C) * median), C widened from fp32
 __device__ __forceinline__ double threshold_of(unsigned long long median_bits, float C)
 {
@@ -268,27 +300,19 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
     const bool active = kFull || c < g.n_c;
     half4_t v[kSteps];
     {
-        uint32_t r = tid >> 5, t = r;
-        const _Float16 *row = tn.x + (int64_t)h * g.sh + (int64_t)t * g.st;
-        const int64_t step = 32 * g.st, wrap = g.sb - (int64_t)g.T * g.st;
-        auto into_entry = [&] {  // t past its batch entry's rows: the entries that follow
-            while (t >= (uint32_t)g.T && r < R) {
-                t -= (uint32_t)g.T;
-                row += wrap;
-            }
-        };
-        into_entry();
+        uint32_t r = tid >> 5;
+        const _Float16 *row = tn.x + (int64_t)h * g.sh;
+        RowWalk walk(g, r, 32u);
+        row += walk.first;
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {
             v[u] = half4_t{0, 0, 0, 0};
             if (active && r < R)
                 v[u] = load_row_chunk<kFull>(row, c, g);
             r += 32;
-            row += step;
-            if (g.B > 1) {
-                t += 32;
-                into_entry();
-            }
+            row += walk.step;
+            if (g.B > 1)
+                row += walk.over_end(g);
         }
     }
     for (int i = tid; i < kHeadWords / 4; i += kSelectThreads)
@@ -442,15 +466,11 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
         const uint32_t pieces = (uint32_t)(g.n_c + kPieceChunks - 1) / kPieceChunks;
         const uint32_t inverse = ((1u << 20) + pieces - 1u) / pieces;  // i / pieces = i * inverse >> 20 for i below 2^12
         static_assert(kPieceRows * kSteps * 2 + kMaxParts < 1 << 12, "j + part + j / pieces");
-        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride, t = r;
-        const _Float16 *row = tn.x + (int64_t)h * g.sh;
-        if (r < R) {
-            const uint32_t b = r / (uint32_t)g.T;
-            t = r - b * (uint32_t)g.T;
-            row += (int64_t)b * g.sb + (int64_t)t * g.st;
-        }
+        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride;
         const uint32_t more = kPieceRows * parts * stride;
-        const int64_t step = (int64_t)more * g.st, wrap = g.sb - (int64_t)g.T * g.st;
+        const _Float16 *row = tn.x + (int64_t)h * g.sh;
+        RowWalk walk(g, r, more);
+        row += walk.first;
 #pragma unroll
         for (int u = 0; u < kSteps; ++u) {
             const uint32_t i = j + part + (j * inverse >> 20);
@@ -462,12 +482,9 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
             }
             j += kPieceRows;
             r += more;
-            t += more;
-            row += step;
-            while (t >= (uint32_t)g.T && r < R) {
-                t -= (uint32_t)g.T;
-                row += wrap;
-            }
+            row += walk.step;
+            if (g.B > 1)
+                row += walk.over_end(g);
         }
     }
     if (part == 0) {
