@@ -563,20 +563,23 @@ def test_sampled_select_row_structures(kind, D, B, H, T):
 
 def _sampled_rows(B, T, D):
     """The rows of a head that the select's prediction looks at (restated from its kernel's comment): every stride-th,
-    1024 per part, four parts beyond 2^19 chunks."""
+    1024 per part, four parts beyond 2^18 chunks and eight beyond 2^19."""
     R = B * T
-    samples = 1024 * (1 if R * ((D + 3) // 4) <= 1 << 19 else 4)
+    chunks = R * ((D + 3) // 4)
+    samples = 1024 * (1 if chunks <= 1 << 18 else 4 if chunks <= 1 << 19 else 8)
     return torch.arange(0, R, ((R + samples - 1) // samples) | 1)
 
 
 @pytest.mark.parametrize("kind,D,B,T", [
     ("plain", 128, 1, 255), ("plain", 45, 2, 128), ("plain", 128, 1, 257), ("plain", 4, 1, 1024), ("plain", 128, 2, 512),
     ("plain", 128, 1, 1025), ("plain", 45, 3, 683), ("plain", 3, 1, 20000), ("plain", 128, 1, 16384), ("plain", 128, 1, 16385),
+    ("plain", 128, 1, 8192), ("plain", 128, 1, 8193),
     ("plain", 96, 3, 7300), ("small", 128, 1, 4099), ("large", 100, 2, 1537), ("zero", 128, 1, 16400), ("equal", 128, 1, 16400),
-    ("overflow", 128, 1, 9000), ("overflow", 64, 2, 17000), ("infinite", 128, 1, 1500),
+    ("zero", 128, 1, 12000), ("overflow", 128, 1, 7000), ("overflow", 128, 1, 9000), ("overflow", 64, 2, 17000),
+    ("infinite", 128, 1, 1500),
 ])
 def test_select_rows_and_predictions(kind, D, B, T):
-    """The select at the edges of its forms (256 and 1024 rows, 2^19 chunks) and where the sampled rows mislead it: smaller
+    """The select at the edges of its forms (256 and 1024 rows, 2^18 and 2^19 chunks) and where the sampled rows mislead it: smaller
     or larger than the rest, zero, all equal, or ordinary while the rest is equal and inside the predicted range (no list
     holds it).  Thresholds bit for bit."""
     H, S = 2, 1
