@@ -334,8 +334,11 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(Geometry g, DecodeBatch 
 // 54 / 40, D = 45 68 / 33, D = 126 76 / 50, D = 101 75 / 49 (batches of 2: 42, 32, 50, 51; of 8: 45, 38, 52, 53).
 // grid = (ceil(T / 64), B*H, tensors), block = 256.
 // dynamic LDS: prim [48][4] f32 | secl [S][4] f32
+// kBatch: 4; 1 or 2 where a segment has no more chunks than so many per lane, as the rest of a batch of 4 decodes its last chunk
+// over again.  In us, one row per half-wave and pass / always 4 / so: 8 tensors of 256 x 8 segments of 100 elements, T = 1 15.0 /
+// 26.5 / 15.2, T = 7 23.3 / 29.4 / 20.8, T = 11 30.6 / 32.3 / 26.5; one of 512 x 8, T = 11 9.3 / 10.6 / 9.0.
 constexpr int kGeneralBatch = 4;
-template <bool kPow2>
+template <bool kPow2, int kBatch>
 __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeBatch batch)
 {
     const DecodeTensor &dt = batch.t[blockIdx.z];
@@ -374,9 +377,9 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
         f.sigma = sigmas[f.r];
         return f;
     };
-    Fetched f[kGeneralBatch];
+    Fetched f[kBatch];
 #pragma unroll
-    for (int u = 0; u < kGeneralBatch; ++u)
+    for (int u = 0; u < kBatch; ++u)
         f[u] = fetch(tid + u * kDecThreads);
     const float *sec_h = dt.sec + (size_t)h * g.S * 4;
     for (int s = tid; s < g.S; s += kDecThreads)
@@ -391,18 +394,20 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
         prim[tid] = v;
     }
     __syncthreads();
+    if (kBatch == 1 && (tid & ~63) >= n_chunks)  // a wave without chunks
+        return;
 
     for (int q0 = tid;;) {
-        uint2 pay[kGeneralBatch];
+        uint2 pay[kBatch];
 #pragma unroll
-        for (int u = 0; u < kGeneralBatch; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
             pay[u] = make_uint2(0u, 0u);
             const uint64_t pos = (uint64_t)f[u].off + __popc(f[u].word & ((1u << f[u].c) - 1u));
             if (((f[u].word >> f[u].c) & 1u) && pos < outlier_capacity)
                 pay[u] = *reinterpret_cast<const uint2 *>(dt.outliers + 4 * pos);
         }
 #pragma unroll
-        for (int u = 0; u < kGeneralBatch; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
             const uint32_t code = __builtin_amdgcn_alignbit(f[u].d1, f[u].d0, f[u].c * w & 31u) & code_mask;
             const float sigma = (float)__builtin_bit_cast(_Float16, f[u].sigma);
             const uint32_t rq = code >> w_idx;
@@ -453,11 +458,11 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_rows(Geometry g, DecodeB
                 }
             }
         }
-        q0 += kGeneralBatch * kDecThreads;
+        q0 += kBatch * kDecThreads;
         if (q0 - tid >= n_chunks)  // uniform
             break;
 #pragma unroll
-        for (int u = 0; u < kGeneralBatch; ++u)
+        for (int u = 0; u < kBatch; ++u)
             f[u] = fetch(q0 + u * kDecThreads);
     }
 }
@@ -487,10 +492,22 @@ hipError_t launch_decode(const Geometry &g, const DecodeBatch &batch, int n_tens
     } else {
         const size_t lds_rows = ((size_t)g.S * 4 + 48 * 4) * sizeof(float);
         dim3 grid((unsigned)((g.T + kGeneralRows - 1) / kGeneralRows), (unsigned)(g.B * g.H), (unsigned)n_tensors);
-        if ((g.S & (g.S - 1)) == 0)
-            hipLaunchKernelGGL(k_decode_rows<true>, grid, dim3(kDecThreads), lds_rows, stream, g, batch);
+        const bool pow2 = (g.S & (g.S - 1)) == 0;
+        const int64_t chunks = (int64_t)g.T * g.n_c;  // of a segment
+#define HQMQ_LAUNCH_ROWS(N)                                                                                                \
+    do {                                                                                                                   \
+        if (pow2)                                                                                                          \
+            hipLaunchKernelGGL((k_decode_rows<true, N>), grid, dim3(kDecThreads), lds_rows, stream, g, batch);             \
+        else                                                                                                               \
+            hipLaunchKernelGGL((k_decode_rows<false, N>), grid, dim3(kDecThreads), lds_rows, stream, g, batch);            \
+    } while (0)
+        if (chunks <= kDecThreads)
+            HQMQ_LAUNCH_ROWS(1);
+        else if (chunks <= 2 * kDecThreads)
+            HQMQ_LAUNCH_ROWS(2);
         else
-            hipLaunchKernelGGL(k_decode_rows<false>, grid, dim3(kDecThreads), lds_rows, stream, g, batch);
+            HQMQ_LAUNCH_ROWS(kGeneralBatch);
+#undef HQMQ_LAUNCH_ROWS
     }
     return hipGetLastError();
 }
