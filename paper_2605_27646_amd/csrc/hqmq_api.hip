@@ -188,13 +188,60 @@ static int screen_rows(const Geometry &g, int n)
     return rows;
 }
 
-// Rows of a generation step with thresholds known beforehand that one launch encodes and lists (k_append): up to 4 of up to
-// 64 (batch entry, head) segments.  Two launches per 32 tensors / one per 64, in us, S = 256: 64 tensors of 64 rows (8 batch
-// entries of 8 heads) 38 / 31, of 32 rows 36 / 19, 16 of 64 rows 20 / 17; but of 128 rows, whose scores fill the chip and
-// which every workgroup would count, 16 tensors 21 / 23, 64 tensors 61 / 64.
-static bool append_applies(const Geometry &g)
+// The fused search of short segments takes the rows of a head in all batch entries on one workgroup, which then builds the head's
+// tables once, while these fill no more than one pass of its waves (rows of 128 elements).
+static bool fused_takes_heads(const Geometry &g)
 {
-    return g.A16 > 0 && g.T <= 4 && (int64_t)g.B * g.H * g.T <= kAppendRows;
+    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
+    return g.B > 1 && (int64_t)g.B * g.T <= 2 * waves && g.D == 4 * kChunksPerRow;
+}
+
+// Rows of a generation step with thresholds known beforehand: one launch for up to 64 tensors (k_append), or two for up to 32
+// (the fused search and its list).  k_append's workgroups, of a segment each or of a head in all batch entries, read the chunks of
+// the whole tensor and score two rows at a time: it loses where segments are many (and dimensions no multiples of 4), or rows per
+// workgroup; it saves a launch and the operand tables.  Which, by the time in ns that each takes: a first round of workgroups,
+// and what every further one adds.  The terms are fitted to the three forms of 6500 shapes (1 to 64 tensors and rows, S = 1 to
+// 512, D = 1 to 128; 6 to 150 us), two launches within 3.4 % rms, k_append 8: of these, 10 are 5 to 10 % slower than by two
+// launches, none more (by k_append for all of them 205 are, up to 70 %).  In us, two launches / k_append by segment / by
+// head, S = 256 unless said: 64 tensors of 8 heads x 1 row 26 / 8.4, of 4 rows 35 / 18, of 8 batch entries 36 / 48 / 28, 32 of
+// these 18 / 27 / 20; 32 of 64 heads x 1 row, D = 127, S = 16 17 / 29; 24 of 8 x 8 segments, S = 8 10 / 17 / 13; 64 of 4 x 4
+// segments x 4 rows, D = 40 34 / 29 / 39; one of 8 heads x 1 row 12.3 / 7.6.
+constexpr int kNoAppend = 0, kAppendSegments = 1, kAppendHeads = 2;
+static double append_ns(const Geometry &g, int n, bool heads)
+{
+    const bool whole_chunks = g.D % 4 == 0;
+    const int passes = ((heads ? g.B * g.T : g.T) + 1) / 2;
+    const double chunks = (double)g.B * g.H * g.T * g.n_c, more = (n * g.H * (heads ? 1 : g.B) + 255) / 256 - 1;
+    return 4000 + passes * (1830 + 8.8 * g.S) + chunks * (whole_chunks ? 0.32 : 1.5) +
+           more * (370 + passes * (290 + 3.7 * g.S) + chunks * (whole_chunks ? 0.63 : 0.97));
+}
+static double fused_ns(const Geometry &g, int n_tensors)
+{
+    const bool full = g.D == 4 * kChunksPerRow, heads = fused_takes_heads(g);
+    const bool coop = full && (heads ? g.B * g.T : g.T) <= 2;  // the waves share a pass's secondaries
+    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
+    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows) + (full ? 3072 : 0);
+    const size_t most = full ? 3 : 4, per_cu = kLdsPerCu / lds < most ? kLdsPerCu / lds : most;
+    double ns = 0;
+    for (int left = n_tensors; left > 0; left -= kMaxEncodeBatch) {
+        const int workgroups = (left < kMaxEncodeBatch ? left : kMaxEncodeBatch) * g.H * (heads ? 1 : g.B);
+        const double rounds = (double)((workgroups + 256 * per_cu - 1) / (256 * per_cu));
+        ns += 8600 + g.S * (coop ? 16 : 27) + 8.0 * g.T * g.n_c + (rounds - 1) * (2700 + g.S * (coop ? 14 : 21)) +
+              workgroups * (1.3 + 0.0067 * g.S) + (g.D % 4 == 0 ? 0.0 : 1070 * rounds);
+    }
+    return ns;
+}
+static int append_route(const Geometry &g, int n_tensors)
+{
+    if (g.A16 == 0 || g.T > 4 || (int64_t)g.B * g.H * g.T > kAppendRows)
+        return kNoAppend;
+    const int n = n_tensors < kMaxAppendBatch ? n_tensors : kMaxAppendBatch;
+    const double segments = append_ns(g, n, false), heads = append_ns(g, n, true);
+    // a head per workgroup where these fill most of the chip: of fewer with many passes each the fit is not sure
+    const bool by_head = g.B > 1 && n * g.H >= 200 && heads < segments;
+    if ((by_head ? heads : segments) > fused_ns(g, n))
+        return kNoAppend;
+    return by_head ? kAppendHeads : kAppendSegments;
 }
 
 struct WorkspaceLayout {
@@ -387,14 +434,15 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             all |= at[p] = reinterpret_cast<uintptr_t>(parts[p]);
         return all >> 48 == 0;
     };
-    bool append = (no_outliers || thr_given != nullptr) && append_applies(g);
+    const int route = no_outliers || thr_given != nullptr ? append_route(g, n_tensors) : kNoAppend;
+    bool append = route != kNoAppend;
     for (int32_t i = 0; i < n_tensors && append; ++i) {
         uint64_t at[kAppParts];
         append = append_parts(i, at);
     }
     if (append) {
         AppendShape shape = {g.B, g.H, g.T, g.D, g.n_c, g.n_c_magic, g.row_words, g.vec_ok, g.S, g.b_r, g.w_idx, g.w, g.check_finite,
-                             0, 0, g.sb, g.sh, g.st, static_cast<char *>(workspace_dev) + l.thr, l.total};
+                             0, route == kAppendHeads, g.sb, g.sh, g.st, static_cast<char *>(workspace_dev) + l.thr, l.total};
         hipError_t err = mark(0);
         if (err == hipSuccess)
             err = mark(1);
@@ -410,9 +458,6 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
                 }
                 batch.capacity[i] = (uint16_t)(outlier_capacity[first + i] < (uint64_t)kAppendChunks ? outlier_capacity[first + i] : kAppendChunks);
             }
-            // a workgroup per head for all batch entries where these fill the chip: 64 tensors of 8 batch entries and 8 heads,
-            // S = 64, in 19 us instead of 41
-            shape.by_head = g.B > 1 && (int64_t)shape.n_tensors * g.H >= 256;
             err = launch_append(shape, batch, st);
         }
         if (err == hipSuccess)
@@ -444,12 +489,8 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
         const bool fused = (no_outliers || thr_given != nullptr) && n_rows_t <= (uint64_t)kSmallListRows &&
                            n_blocks_t <= (uint64_t)kSmallListBlocks && search_fused_available(g);
         if (fused) {
-            // several batch entries whose rows together fill no more than one pass of the workgroup's waves (rows
-            // of 128 elements): a workgroup per head takes them all, and builds the head's tables once instead
-            // of once per batch entry; more rows than that are faster on workgroups of their own
             Geometry gf = g;
-            const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-            gf.fused_by_head = (g.B > 1 && (int64_t)g.B * g.T <= 2 * waves && g.D == 4 * kChunksPerRow) ? 1 : 0;
+            gf.fused_by_head = fused_takes_heads(g) ? 1 : 0;
             err = mark(1);
             if (err == hipSuccess)
                 err = launch_search_fused(gf, wo, batch, n, st);

@@ -1349,7 +1349,10 @@ def test_batched_incremental_encode_equals_single_calls():
 @pytest.mark.parametrize("n,B,H,T,D,S,b_r", [
     (65, 1, 8, 1, 128, 256, 6),   # a second launch, for one tensor; one row per workgroup
     (33, 8, 8, 1, 128, 16, 6),    # a workgroup per head for eight batch entries; 64 rows
-    (64, 3, 4, 3, 100, 33, 4),    # ... an odd number of rows; 25 chunks per row
+    (64, 3, 8, 1, 100, 33, 4),    # ... an odd number of rows; 25 chunks per row
+    (64, 3, 4, 3, 100, 33, 4),    # two passes per segment instead of five per head
+    (32, 1, 64, 1, 127, 16, 6),   # two launches, because every segment's workgroup would read all 64 rows
+    (24, 8, 8, 1, 128, 8, 6),     # ... a workgroup per head for eight batch entries
     (2, 16, 1, 4, 45, 5, 3),      # a partial last chunk, fewer secondaries than shares
     (1, 1, 64, 1, 64, 512, 8),    # the most heads and secondaries
     (3, 1, 16, 4, 3, 1, 6),       # one partial chunk per row
@@ -1357,8 +1360,8 @@ def test_batched_incremental_encode_equals_single_calls():
     (2, 8, 9, 1, 128, 24, 6),     # 72 rows: two launches, a workgroup per head
 ])
 def test_rows_of_a_generation_step(n, B, H, T, D, S, b_r):
-    """Up to 64 rows per tensor with thresholds known beforehand, up to 64 tensors in one launch: against the oracle for some
-    tensors, with lists too short for their outliers, thresholds read back from every slice of the workspace, extraction off,
+    """Up to 64 rows per tensor with thresholds known beforehand, up to 64 tensors in one launch, and what two launches do
+    instead: against the oracle for some tensors, with lists too short for their outliers, thresholds read back from every slice of the workspace, extraction off,
     and a non-finite value in the tensor's last row reported."""
     nc = -(-D // 4)
     cb = hq.hqmq_build_codebooks(9, n, H, S)
@@ -1414,6 +1417,32 @@ def test_rows_of_a_generation_step(n, B, H, T, D, S, b_r):
         encs, _ = run(flags, [full] * n, thresholds)
         assert int(encs[-1].status.item()) == hq.HQMQ_STATUS_NONFINITE
         assert n == 1 or int(encs[0].status.item()) == 0
+
+
+@pytest.mark.parametrize("n,D,S,few,more", [(64, 127, 16, (1, 64), (1, 65)), (24, 128, 8, (8, 8), (8, 9))])
+def test_time_of_a_generation_step_of_many_rows(n, D, S, few, more):
+    """64 rows per tensor take no longer than a row or eight more, which always go by two launches: at most 1.3 times as long
+    (1.0 measured; 1.5 and 1.65 in one launch)."""
+    times = []
+    for B, H in (few, more):
+        xs = [_lognormal_tensor(B, H, 1, seed=i, D=D).to(DEV) for i in range(n)]
+        secs = [_sec(i, H, S)[0].to(DEV) for i in range(n)]
+        params = hq.params_for(xs[0], S)
+        encs = [hq.alloc_encoded(params, DEV, outlier_capacity=B * H * 32) for _ in range(n)]
+        batch = hq.EncodeBatch(params, xs, secs, encs, hq.alloc_batch_workspace(params, n, DEV))
+        thrs = hq.ThresholdBatch(batch, [torch.full((H,), 100.0, dtype=torch.float64, device=DEV)] * n)
+        best = float("inf")
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                hq.hqmq_encode_batch_given_thresholds(batch, thrs)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 20)
+        times.append(best)
+    print(f"{1e3 * times[0]:.1f} us, with more rows {1e3 * times[1]:.1f} us", flush=True)
+    assert times[0] < 1.3 * times[1]
 
 
 @pytest.mark.parametrize("D", [128, 96])
