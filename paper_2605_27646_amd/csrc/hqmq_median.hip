@@ -18,6 +18,8 @@
 // every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
 // fp16 data span 83 binades, which at 64 bins each fit the 8192 bins of a workgroup's LDS).
 // The sequence-sharded median further down is a plain most-significant-digit radix select on the 63 value bits.
+#include <algorithm>
+
 #include "hqmq_tables.h"
 
 namespace hqmq {
@@ -1471,13 +1473,21 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
     int rows = kCountRows;  // down to the 128 of one step while four workgroups per compute unit are not there
     while (rows > 128 && (uint64_t)((g.T + rows - 1) / rows) * g.B * g.H * n < 1024)
         rows /= 2;
-    const uint32_t n_count = (uint32_t)((g.T + rows - 1) / rows) * (uint32_t)(g.B * g.H) * n;
-    if (g.cell_n > 0) {
-        const uint32_t n_cells = (uint32_t)(cell_blocks(g) * g.H) * n;
-        hipLaunchKernelGGL((k_select_count<kFull, true>), dim3((n_cells + 7) / 8 * 8 + (n_count + 7) / 8 * 8), dim3(kCountThreads), 0,
-                           stream, g, wo, batch, rows, n);
-    } else {
-        hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(n_count), dim3(kCountThreads), 0, stream, g, wo, batch, rows, n);
+    // Its workgroups lie along one axis, whose threads have to stay below 2^32: that leaves room for 130,000 heads with an index of
+    // 125 workgroups each, fewer than 32 tensors may have (one tensor's always fit: at most 65535 heads, 2^27 rows).
+    const uint32_t cells = g.cell_n > 0 ? (uint32_t)(cell_blocks(g) * g.H) : 0u;                    // of a tensor
+    const uint32_t sweep = (uint32_t)((g.T + rows - 1) / rows) * (uint32_t)(g.B * g.H);
+    const unsigned most = (0xffffffffu / (unsigned)kCountThreads - 16u) / (cells + sweep);
+    EncodeBatch rest = batch;
+    for (unsigned first = 0; first < n; first += most) {
+        const unsigned m = n - first < most ? n - first : most;
+        if (first > 0)
+            std::copy(batch.t + first, batch.t + first + m, rest.t);
+        if (g.cell_n > 0)
+            hipLaunchKernelGGL((k_select_count<kFull, true>), dim3((cells * m + 7) / 8 * 8 + (sweep * m + 7) / 8 * 8), dim3(kCountThreads),
+                               0, stream, g, wo, rest, rows, m);
+        else
+            hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(sweep * m), dim3(kCountThreads), 0, stream, g, wo, rest, rows, m);
     }
     hipLaunchKernelGGL(k_select_digit<kFull>, parts, block, 0, stream, g, wo, batch);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);

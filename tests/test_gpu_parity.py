@@ -969,6 +969,35 @@ def test_box_index_built_beside_the_select(kind, D, B, T, S):
     assert np.array_equal(thr.cpu().numpy().view(np.uint64), ((c * c) * e.m2).view(np.uint64))
 
 
+def test_box_index_of_more_heads_than_a_launch_holds():
+    """32 tensors of 4100 heads whose index has 125 workgroups each: more threads than one axis of a grid takes.  Every tensor's
+    bytes are those of a call of its own.  (50 GB, most of it workspace; the heads share their rows, the tensors their inputs.)"""
+    n, H, T, S = 32, 4100, 1280, 129
+    x = _lognormal_tensor(1, 1, T, seed=3, sigma_g=0.8).to(DEV).expand(1, H, T, 128)
+    sec = _sec(3, H, S)[0].to(DEV)
+    params = hq.params_for(x, S, 1)
+    ws = hq.alloc_batch_workspace(params, n, DEV)
+    want = hq.alloc_encoded(params, DEV, outlier_capacity=1 << 20)
+    want.outliers.zero_()
+    hq.hqmq_encode(params, x, sec, want, ws[: int(hq.hqmq_sizes(params).workspace_bytes)])
+    thr = hq.hqmq_thresholds(params, ws)
+    encs = [hq.alloc_encoded(params, DEV, outlier_capacity=1 << 20) for _ in range(n)]
+    for b in encs:
+        b.codes.fill_(-1)
+        b.outliers.zero_()
+    hq.hqmq_encode_batch(hq.EncodeBatch(params, [x] * n, [sec] * n, encs, ws))
+    torch.cuda.synchronize()
+    assert torch.isfinite(thr).all() and (thr == thr[0]).all()
+    for i, b in enumerate(encs):
+        assert torch.equal(hq.hqmq_thresholds(params, ws, i), thr), i
+        for part in ("codes", "flags", "row_off", "n_outliers", "status"):
+            assert torch.equal(getattr(b, part), getattr(want, part)), (i, part)
+        assert torch.equal(b.sigma.view(torch.int16), want.sigma.view(torch.int16)), i
+        assert torch.equal(b.outliers.view(torch.int16), want.outliers.view(torch.int16)), i
+    del encs, ws
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("S,D", [(8, 128), (24, 128), (64, 128), (256, 128), (256, 126), (96, 50)])
 def test_box_index_at_the_corners_of_the_fold(S, D):
     """Chunks (+-a, +-a, 0, 0) in every order fold onto a corner of the octahedron that the search's box index covers, where
