@@ -1284,26 +1284,38 @@ def test_incremental_encode_of_appended_tokens(T_new):
 
 
 @pytest.mark.parametrize("D,B,H,T,S,b_r", [
-    (128, 1, 8, 1, 256, 6),     # one appended token of the headline shape: one row per workgroup, all waves on one pass
-    (128, 3, 2, 2, 512, 8),     # two rows per workgroup; 8-wave workgroups (S = 512)
-    (128, 1, 2, 1, 1, 3),       # fewer groups of secondaries than waves
-    (128, 2, 3, 1, 40, 4),      # 3 groups over 4 waves
+    # one launch (up to 4 tokens and 64 rows)
+    (128, 1, 8, 1, 256, 6),     # one appended token of the headline shape: one row per workgroup
+    (128, 3, 2, 2, 512, 8),     # two rows per workgroup, the most secondaries
+    (128, 1, 2, 1, 1, 3),       # fewer secondaries than shares
+    (128, 2, 3, 1, 40, 4),      # shares of three and two secondaries
+    (128, 8, 8, 1, 256, 6),     # a generation step of 8 sequences: 64 rows
+    (128, 4, 2, 2, 64, 6),
+    (128, 3, 3, 3, 24, 4),      # two passes, the second of one row
+    (128, 5, 2, 3, 512, 6),
+    (128, 2, 2, 1, 16, 6),
+    (96, 2, 4, 1, 192, 4),      # other head dimensions
+    (64, 1, 8, 3, 192, 4),
+    # two launches
+    (128, 1, 66, 1, 256, 6),    # one row per workgroup: all waves on one pass
+    (128, 1, 33, 2, 33, 6),     # two rows per workgroup: the same
     (128, 1, 2, 65, 96, 4),     # a full workgroup and one of a single row
     (128, 2, 2, 66, 24, 6),     # ... and one of two rows
     (128, 1, 3, 130, 16, 6),    # three workgroups per segment, the last with two rows
     (128, 4, 8, 128, 64, 6),    # 4096 rows, 64 workgroups: the largest tensor the short form takes
-    (128, 8, 8, 1, 256, 6),     # a generation step of 8 sequences: one workgroup per head takes all batch entries
-    (128, 4, 2, 2, 64, 6),      # ... 8 rows per head: one pass of the four waves exactly
-    (128, 3, 3, 3, 24, 4),      # 9 rows per head: back to one workgroup per (batch entry, head)
-    (128, 5, 2, 3, 512, 6),     # 15 rows per head on 8-wave workgroups
-    (128, 2, 2, 1, 16, 6),      # two batch entries of one row: one cooperative pass for both
-    (96, 2, 4, 1, 192, 4),      # other head dimensions: the flat kernel's short form
-    (64, 1, 8, 3, 192, 4),
+    (128, 2, 33, 1, 256, 6),    # a workgroup per head for all batch entries: one pass of all waves for two of one row
+    (128, 2, 17, 2, 64, 6),     # ... four rows
+    (128, 3, 11, 2, 512, 8),    # ... six
+    (128, 2, 11, 3, 24, 4),     # ... six in runs of three
+    (128, 2, 9, 4, 40, 6),      # ... eight: one pass of the four waves exactly
+    (128, 1, 2, 5, 1, 3),       # one group of secondaries for four waves
+    (128, 3, 9, 3, 24, 4),      # nine rows per head: a workgroup per (batch entry, head) again
+    (96, 2, 17, 2, 192, 4),     # other head dimensions: the flat kernel's short form
     (45, 2, 2, 5, 48, 4),
 ])
 def test_short_tensors_with_known_thresholds(D, B, H, T, S, b_r):
-    """Tensors of a few rows whose thresholds are known beforehand (supplied, or extraction off) take the
-    two-launch form of the encode: parity with the oracle in both modes, and bytes equal to those of the
+    """Tensors of a few rows whose thresholds are known beforehand (supplied, or extraction off) are encoded by
+    one launch or by two: parity with the oracle in both modes, and bytes equal to those of the
     same rows encoded as part of a tensor long enough to take the general form (thresholds supplied)."""
     print(f"case D={D} B={B} H={H} T={T} S={S} b_r={b_r}", flush=True)
     x = _lognormal_tensor(B, H, T, seed=7 * T + S + D, sigma_g=1.0, D=D)
