@@ -1154,23 +1154,18 @@ __global__ __launch_bounds__(64 * kWaves) void k_attend_merge(AttendArgs a)
     for (int s = lane; s < n; s += 64)
         mx = fmaxf(mx, ml[s].x);
     mx = reduce_wave(mx, [](float x, float y) { return fmaxf(x, y); });
-    float o = 0.f, lsum = 0.f;
-    for (int s0 = first; s0 < end; s0 += 64) {  // once for up to 64 kWaves splits
-        if (s0 > first)
-            st = ml[min(s0 + lane, n - 1)];
-        const float wgt = s0 + lane < end ? __builtin_amdgcn_exp2f(st.x - mx) : 0.f;
-        lsum = fmaf(st.y, wgt, lsum);
-        const int here = min(end - s0, 64);
-        for (int j0 = 0; j0 < here; j0 += kEarly) {
-            float v[kEarly];
+    const int here = end - first;  // at most 64 (launch_attend)
+    const float wgt = lane < here ? __builtin_amdgcn_exp2f(st.x - mx) : 0.f;
+    float o = 0.f, lsum = st.y * wgt;
+    for (int j0 = 0; j0 < here; j0 += kEarly) {
+        float v[kEarly];
 #pragma unroll
-            for (int u = 0; u < kEarly; ++u)
-                v[u] = s0 + j0 == first ? early[u] : pa[(size_t)min(s0 + j0 + u, n - 1) * 128];
+        for (int u = 0; u < kEarly; ++u)
+            v[u] = j0 == 0 ? early[u] : pa[(size_t)min(first + j0 + u, n - 1) * 128];
 #pragma unroll
-            for (int u = 0; u < kEarly; ++u)
-                if (j0 + u < here)  // uniform
-                    o = fmaf(v[u], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), j0 + u)), o);
-        }
+        for (int u = 0; u < kEarly; ++u)
+            if (j0 + u < here)  // uniform
+                o = fmaf(v[u], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), j0 + u)), o);
     }
     lsum = reduce_wave(lsum, [](float x, float y) { return x + y; });
     sums[wv][lane] = o;
@@ -1307,6 +1302,7 @@ hipError_t launch_attend(const Geometry &g, const AttendArgs &a, hipStream_t str
     if (err != hipSuccess)
         return err;
     const dim3 outputs((unsigned)(g.B * g.H * a.G), (unsigned)((g.D + kMergeDims - 1) / kMergeDims));
+    static_assert(kAttendTargetBlocks <= 64 * 16 && kJointTargetBlocks <= 64 * 16, "a lane per split of a wave's share");
     if (a.n_splits <= kMergeFew)
         hipLaunchKernelGGL(k_attend_merge<4>, outputs, dim3(64 * 4), 0, stream, a);
     else

@@ -368,11 +368,13 @@ def test_attend_window_sizes(D, S, T, n):
     _check(got, want, Kd, Vd, q, 0.1)
 
 
-@pytest.mark.parametrize("D,T", [(128, 64 * 31 + 1), (64, 64 * 33), (96, 64 * 64 + 1), (128, 64 * 65)])
-def test_attend_split_counts(D, T):
+@pytest.mark.parametrize("D,T,S", [(128, 64 * 31 + 1, 16), (64, 64 * 33, 16), (96, 64 * 64 + 1, 16), (128, 64 * 65, 16),
+                                   (64, 64 * 256, 300), (96, 64 * 256 + 1, 300), (128, 64 * 400, 512), (64, 64 * 512, 300)])
+def test_attend_split_counts(D, T, S):
     """One kv head, so that every tile of 64 tokens is a split of its own: 32, 33, 65 and 65 of them, where four waves, with
-    all their partial sums requested at once, give way to 16; with lse."""
-    B, H, Hq, S, b_r = 1, 1, 3, 16, 4
+    all their partial sums requested at once, give way to 16; 256, 257, 400 and 512, where these request a second time (with
+    tables that do not fit: the form with tables has 256 splits at most); with lse."""
+    B, H, Hq, b_r = 1, 1, 3, 4
     k, v = _tensors(B, H, T, seed=T, D=D)
     sec_k, sec_v = _secs(12, H, S)
     gk, gv = gpu_encode(k.to(DEV), sec_k.to(DEV), b_r), gpu_encode(v.to(DEV), sec_v.to(DEV), b_r)
