@@ -170,7 +170,7 @@ static int screen_rows(const Geometry &g, int n)
     const int64_t blocks = (int64_t)n * g.B * g.H * ((g.T + kSearchRowsLarge - 1) / kSearchRowsLarge);
     const int64_t enough = 192 * g.n_c > 512 ? 192 * g.n_c : 512;
     const bool large = g.n_c < kChunksPerRow && g.search_rows == kSearchRowsLarge && blocks >= enough &&
-                       search_waves_for(g.S16, g.A16, g.D, g.row_words, kSearchRowsLarge) == 4;
+                       4 * search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, kSearchRowsLarge) <= kLdsPerCu;
     if (large)
         return kSearchRowsLarge;
     // Few workgroups: down to 8 rows each, while a launch then has at most 2048 and two waves still get a pass of 64 chunks.
@@ -178,10 +178,9 @@ static int screen_rows(const Geometry &g, int n)
     // 49 / 45 / 43 / 47 (2504 workgroups); S = 256, T = 256 64 / 42 / 31 / 25; S = 64, 8 tensors, T = 1000 71 / 68 / 68 / 69;
     // D = 45, S = 48, 2 tensors, T = 900 43 / 42 / 40 / 45 (96 chunks in the last).
     int rows = kSearchRowsSmall;
-    for (int half = rows / 2; half >= 8; half /= 2) {
+    for (int half = rows / 2; half >= 2 * kSearchWaves; half /= 2) {
         const int64_t wgs = (int64_t)n * g.B * g.H * ((g.T + half - 1) / half);
-        const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, half);
-        if (wgs > 2048 || half * g.n_c < 128 || half < 2 * waves)
+        if (wgs > 2048 || half * g.n_c < 128)
             break;
         rows = half;
     }
@@ -192,8 +191,7 @@ static int screen_rows(const Geometry &g, int n)
 // tables once, while these fill no more than one pass of its waves (rows of 128 elements).
 static bool fused_takes_heads(const Geometry &g)
 {
-    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-    return g.B > 1 && (int64_t)g.B * g.T <= 2 * waves && g.D == 4 * kChunksPerRow;
+    return g.B > 1 && (int64_t)g.B * g.T <= 2 * kSearchWaves && g.D == 4 * kChunksPerRow;
 }
 
 // Rows of a generation step with thresholds known beforehand: one launch for up to 64 tensors (k_append), or two for up to 32
@@ -219,8 +217,7 @@ static double fused_ns(const Geometry &g, int n_tensors)
 {
     const bool full = g.D == 4 * kChunksPerRow, heads = fused_takes_heads(g);
     const bool coop = full && (heads ? g.B * g.T : g.T) <= 2;  // the waves share a pass's secondaries
-    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows) + (full ? 3072 : 0);
+    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, g.search_rows) + (full ? 3072 : 0);
     const size_t most = full ? 3 : 4, per_cu = kLdsPerCu / lds < most ? kLdsPerCu / lds : most;
     double ns = 0;
     for (int left = n_tensors; left > 0; left -= kMaxEncodeBatch) {

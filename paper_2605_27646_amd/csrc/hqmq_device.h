@@ -10,9 +10,9 @@
 namespace hqmq {
 
 constexpr int kChunksPerRow = 32;    // chunks of a row of D = 128 elements, and the most a row may have
-constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64; the matrix screen
-constexpr int kSearchRowsLarge = 256;  // takes 256 for many short rows, the search with the box index 256 or 512 where that
-constexpr int kSearchRowsHuge = 512;   // leaves 512 workgroups (1024 rows: no faster)
+constexpr int kSearchRowsSmall = 64;   // rows per search workgroup = granularity of the outlier scan: 64; the matrix screen takes
+constexpr int kSearchRowsLarge = 256;  // 8, 16 or 32 for few rows and 256 for many short ones, the search with the box index 256
+constexpr int kSearchRowsHuge = 512;   // or 512 where that leaves 512 workgroups (1024 rows: no faster)
 constexpr int kSearchRowsSwitch = 2048;
 constexpr int kSearchRowsSwitchHuge = 4096;
 constexpr int kThreads = 256;        // default workgroup: 4 wave64
@@ -73,22 +73,25 @@ struct Geometry {
     int32_t cell_groups;  // list groups it may have, group 0 included
     int32_t cell_used;    // codewords its lists may name
     int32_t cell_words;   // 32-bit words of a bit per codeword
-    int32_t search_rows;               // rows per search workgroup (kSearchRowsSmall, Large or Huge)
+    int32_t search_rows;               // rows per search workgroup: 8, 16, 32, kSearchRowsSmall, Large or Huge
     uint32_t n_search_blocks_per_seg;  // ceil(T / search_rows)
 };
 
-// Dynamic LDS of one search workgroup (host side; the kernels carve the same layout): the head's
-// MFMA A operands and secondaries, and the per-row state, which for rows of
-// 128 elements is two rows of code words per wave and a counter per row, and for other row lengths a
-// running maximum, flag word, scale, counter and the code words of every row of the workgroup.
-inline size_t search_lds_bytes(int S16, int A16, int D, int row_words, int waves, int rows)
+constexpr int kSearchWaves = 4;       // of a workgroup of the matrix screen
+constexpr size_t kLdsPerCu = 160 * 1024;
+
+// Dynamic LDS of one search workgroup of the matrix screen (host side; the kernels carve the same layout): the head's MFMA A
+// operands and secondaries, and the per-row state, which for rows of 128 elements is two rows of code words per wave and a counter
+// per row, and for other row lengths a running maximum, flag word, scale, counter and the code words of every row of the workgroup.
+constexpr size_t search_lds_bytes(int S16, int A16, int D, int row_words, int waves, int rows)
 {
     const size_t tables = (size_t)A16 * kATiles * 64 * 16 + (size_t)S16 * 16 * 4 * 4;
     if (D == 4 * kChunksPerRow)
         return tables + ((size_t)waves * 2 * 32 + (size_t)rows) * 4;
     return tables + (size_t)rows * (8 + 4 + 4 + 4 + 4 * (size_t)row_words);
 }
-constexpr size_t kLdsPerCu = 160 * 1024;
+// 31 chunks of 22 bits: two workgroups of 64 rows fit a compute unit whatever the shape
+static_assert(2 * search_lds_bytes(kScreenMaxS / 16, kScreenMaxS / 16, 124, 22, kSearchWaves, kSearchRowsSmall) <= kLdsPerCu, "two workgroups");
 
 // Shape of the search's box index for S secondaries: boxes per axis, list groups and codewords (a random codebook of
 // unit quaternions needs 3730 groups and 610 codewords at S = 256, 2210 and 360 at 128, 850 and 115 at 24, with a
@@ -113,33 +116,21 @@ __host__ __device__ inline size_t cell_head_bytes(int n) { return ((size_t)n * n
 // A head's index in candidate keys: at most 7120 (S = 512) of 32768 and more.
 inline int cell_index_keys(const CellShape &c) { return (int)((cell_head_bytes(c.n) + 15) / 16 * 2) + c.groups; }
 
-// Waves of a search workgroup of the matrix screen: 4 when two workgroups fit a CU's LDS, else one workgroup of 8, which
-// keeps two waves on every SIMD.  (16, for rows that do not leave room for four workgroups, only sizes workspaces.)
-inline int search_waves_for(int S16, int A16, int D, int row_words, int rows)
-{
-    if (A16 == 0)
-        return 4;  // the unscreened search has one shape
-    if (rows >= kSearchRowsLarge && kLdsPerCu / search_lds_bytes(S16, A16, D, row_words, 4, rows) < 4 &&
-        search_lds_bytes(S16, A16, D, row_words, 16, rows) <= kLdsPerCu)
-        return 16;
-    return 2 * search_lds_bytes(S16, A16, D, row_words, 4, rows) > kLdsPerCu ? 8 : 4;
-}
-
 // The rows per workgroup that a workspace is sized for (its arrays of workgroup totals): no launch takes fewer without
 // finding its own place for the totals.  A size that callers have allocated for, so it stays.
 inline int search_rows_for(int T, int S16, int A16, int D, int row_words)
 {
     if (A16 == 0)
         return kSearchRowsSmall;  // the unscreened search has one shape
-    const auto four_fit = [&](int rows) { return kLdsPerCu / search_lds_bytes(S16, A16, D, row_words, 4, rows) >= 4; };
+    const auto four_fit = [&](int rows) { return kLdsPerCu / search_lds_bytes(S16, A16, D, row_words, kSearchWaves, rows) >= 4; };
     if (T >= kSearchRowsSwitch && four_fit(kSearchRowsLarge))
         return kSearchRowsLarge;
     if (four_fit(kSearchRowsSmall))
         return kSearchRowsSmall;
-    if (T >= kSearchRowsSwitchHuge && search_waves_for(S16, A16, D, row_words, kSearchRowsHuge) == 16)
+    if (T >= kSearchRowsSwitchHuge && !four_fit(kSearchRowsHuge) && search_lds_bytes(S16, A16, D, row_words, 16, kSearchRowsHuge) <= kLdsPerCu)
         return kSearchRowsHuge;
     if (T >= kSearchRowsSwitch &&
-        (D == 4 * kChunksPerRow || 2 * search_lds_bytes(S16, A16, D, row_words, 4, kSearchRowsLarge) <= kLdsPerCu))
+        (D == 4 * kChunksPerRow || 2 * search_lds_bytes(S16, A16, D, row_words, kSearchWaves, kSearchRowsLarge) <= kLdsPerCu))
         return kSearchRowsLarge;
     return kSearchRowsSmall;
 }

@@ -27,9 +27,9 @@
 // winning group is not ahead of every other group by 6e-6 of its score is searched again over all S secondaries with
 // plain fp32 arithmetic.  Either way the choice between secondaries is made on fp32 closed-form scores.
 //
-// Work split: a workgroup (4 or 8 wave64) owns 64 rows of one (b, h) segment (256 where rows are short and many), so the A
-// matrices of the head sit in LDS once per workgroup.  A wave takes 64 chunks, one per lane, at a
-// time and runs them as two 32-chunk MFMA column groups: two whole rows of 128 elements in
+// Work split: a workgroup of 4 waves owns 64 rows of one (b, h) segment (down to 8 where workgroups are
+// few, 256 where rows are short and many), so the A matrices of the head sit in LDS once per workgroup.
+// A wave takes 64 chunks, one per lane, at a time and runs them as two 32-chunk MFMA column groups: two whole rows of 128 elements in
 // k_search, 64 consecutive chunks of the workgroup's flattened rows in k_search_flat (any other
 // head dimension).  The per-chunk steps (scale, radius code, direction search) are shared.
 //
@@ -189,13 +189,13 @@ constexpr float kScreenBand = 6.0e-6f;
 // of that chunk in fp32, 64 at a time.  The decision between secondaries is therefore always taken
 // on fp32 closed-form scores, the lowest s winning exact ties.
 //
-// kCoop (a workgroup whose rows fill a single pass): all kWaves waves of the workgroup hold the same 64
+// kCoop (a workgroup whose rows fill a single pass): all waves of the workgroup hold the same 64
 // chunks, each screens its share of the groups, the per-chunk results (best lane-group, its score, the
-// runner-up) meet in `merge` [kWaves][64][3], and wave 0 alone decides and returns the code words (the other
+// runner-up) meet in `merge` [kSearchWaves][64][3], and wave 0 alone decides and returns the code words (the other
 // waves return 0).  The merged triple is what one wave screening every group would have found, except when two
 // waves tie for the best score exactly; the runner-up then equals the best and the chunk takes the fp32 search,
 // as any tie between groups does.
-template <bool kCoop = false, int kWaves = 1, bool kScreen = true>
+template <bool kCoop = false, bool kScreen = true>
 __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane, const Direction u, bool flagged,
                                                     double r2, int rq, const uint4 *amat, const float *secl,
                                                     int wv = 0, float *merge = nullptr)
@@ -227,7 +227,7 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
     // groups this wave screens: those held as matrix operands (none beyond kScreenMaxS secondaries: the
     // screen is then skipped and every chunk takes the fp32 search below)
     const int n_grp = kScreen ? g.S16 : 0;
-    const int per_wave = kCoop ? (n_grp + kWaves - 1) / kWaves : n_grp;
+    const int per_wave = kCoop ? (n_grp + kSearchWaves - 1) / kSearchWaves : n_grp;
     const int grp_begin = kCoop ? min(wv * per_wave, n_grp) : 0;
     const int grp_end = kCoop ? min(grp_begin + per_wave, n_grp) : n_grp;
     const uint4 *arow = amat + lane;
@@ -322,7 +322,7 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
         if (wv != 0)
             return 0u;
 #pragma unroll
-        for (int k = 1; k < kWaves; ++k) {  // a wave without groups left its initial -1: never the best
+        for (int k = 1; k < kSearchWaves; ++k) {  // a wave without groups left its initial -1: never the best
             const float *theirs = merge + (k * 64 + lane) * 3;
             const float tb = theirs[0], tr = theirs[1];
             const int tf = __float_as_int(theirs[2]);
@@ -419,20 +419,18 @@ __device__ __forceinline__ void write_row_offsets(const Geometry &g, const Works
 //   amat  [2*S16][64] x 16 B   MFMA A operands, one 64-lane tile per 8 secondaries
 //                              (copied from the table that the call's first kernel built for the head)
 //   secl  [16*S16][4] f32      the head's secondaries (zero padded to a multiple of 16)
-//   pack  [kWaves][2][32] u32 row code words being assembled
+//   pack  [kSearchWaves][2][32] u32 row code words being assembled
 //   rcnt  [search_rows] u32    outliers per row of the workgroup
-// kWaves: 4, or 8 when tables and row state are so large that only one workgroup fits a CU: twice the waves then
-// share the tables and keep two waves on every SIMD.
 // This kernel is for rows of 128 elements (32 chunks: two rows per wave); k_search_flat below takes
 // every other head dimension.
 // kFused: the form for tensors of a few rows whose thresholds are known beforehand (appended tokens with
 // supplied thresholds, extraction switched off): no kernel runs before this one, so it takes its thresholds
 // from the caller's array (+infinity without one), builds the head's operand table itself, and reports a
 // non-finite input through bit 31 of its workgroup total, which the list kernel turns into the status word.
-template <int kWaves, bool kFused = false, bool kScreen = true>
-__global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+template <bool kFused = false, bool kScreen = true>
+__global__ __launch_bounds__(64 * kSearchWaves, kFused ? 1 : 4) void k_search(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
-    constexpr int kThreadsS = 64 * kWaves;
+    constexpr int kThreadsS = 64 * kSearchWaves;
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
@@ -442,7 +440,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     uint4 *amat = reinterpret_cast<uint4 *>(smem);
     float *secl = reinterpret_cast<float *>(amat + (size_t)(kScreen ? g.S16 : 0) * kATiles * 64);
     uint32_t *pack = reinterpret_cast<uint32_t *>(secl + (size_t)g.S16 * 16 * 4);
-    uint32_t *rcnt = pack + kWaves * 2 * 32;
+    uint32_t *rcnt = pack + kSearchWaves * 2 * 32;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, and known to be
@@ -450,7 +448,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     // batch entries, so that the head's tables are built once; its rows are the pairs (b, t), b-major
     const bool by_head = kFused && g.fused_by_head != 0;
     const int seg = blockIdx.y, b = by_head ? 0 : seg / g.H, h = by_head ? seg : seg % g.H;
-    const int rows = g.search_rows;  // of a workgroup: 2 kWaves to 64
+    const int rows = g.search_rows;  // of a workgroup: 2 kSearchWaves to 64
     const int t0 = blockIdx.x * rows;
     const int n_here = by_head ? g.B * g.T : g.T;  // rows this workgroup column addresses
     const float *sec_h = sec + (size_t)h * g.S * 4;
@@ -471,7 +469,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     // runs its single pass on all its waves together (search_codeword's cooperative form), and the first
     // chunk is requested before the tables
     const bool coop = kFused && n_here - t0 <= 2;  // uniform over the workgroup
-    __shared__ float merge[kFused ? kWaves * 64 * 3 : 1];
+    __shared__ float merge[kFused ? kSearchWaves * 64 * 3 : 1];
     half4_t first_chunk = {0, 0, 0, 0};
     if (kFused) {
         const int v = t0 + (coop ? 0 : wv * 2) + (lane >> 5);
@@ -508,12 +506,12 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
     const int c = lane & 31, half_id = lane >> 5;
     uint32_t *my_pack = pack + wv * 64;
 
-    const int n_it = coop ? 1 : rows / (2 * kWaves);
+    const int n_it = coop ? 1 : rows / (2 * kSearchWaves);
     for (int it = 0; it < n_it; ++it) {
-        const int r_in_block = coop ? half_id : it * 2 * kWaves + wv * 2 + half_id;
+        const int r_in_block = coop ? half_id : it * 2 * kSearchWaves + wv * 2 + half_id;
         const int t = t0 + r_in_block;
         const bool valid = t < n_here;
-        if (!coop && t0 + it * 2 * kWaves + wv * 2 >= n_here) {  // wave-uniform: both rows of this iteration lie past the end
+        if (!coop && t0 + it * 2 * kSearchWaves + wv * 2 >= n_here) {  // wave-uniform: both rows of this iteration lie past the end
             if (c == 0)
                 rcnt[r_in_block] = 0;
             continue;
@@ -552,11 +550,11 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
         my_pack[lane] = 0;  // after the previous iteration's reads of it: LDS serves a wave in order
         uint32_t code;
         if (coop) {
-            code = search_codeword<true, kWaves>(g, lane, u, flagged, r2, rq, amat, secl, wv, merge);
+            code = search_codeword<true>(g, lane, u, flagged, r2, rq, amat, secl, wv, merge);
             if (wv != 0)
                 continue;  // wave 0 holds the result and writes the two rows
         } else {
-            code = search_codeword<false, 1, kScreen>(g, lane, u, flagged, r2, rq, amat, secl);
+            code = search_codeword<false, kScreen>(g, lane, u, flagged, r2, rq, amat, secl);
         }
 
         // ---- pack the row: chunk c at bits [c*w, (c+1)*w) -----------------------------------------
@@ -611,7 +609,7 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
 
 
 // The same search for any head dimension: rows of n_c = ceil(D / 4) <= 32 chunks.  A workgroup owns
-// 64 or 256 rows of one (b, h) segment and treats their chunks as one flat list, 64 consecutive
+// 8 to 64, or 256, rows of one (b, h) segment and treats their chunks as one flat list, 64 consecutive
 // chunks per wave and iteration, so that every lane of every matrix product carries a chunk whatever
 // n_c is.  Rows then straddle waves, so what the row-per-half-wave kernel does with cross-lane
 // operations goes through LDS here:
@@ -624,10 +622,10 @@ __global__ __launch_bounds__(64 * kWaves, kFused ? 1 : 4) void k_search(Geometry
 // Dynamic LDS: amat | secl as in k_search, then rowmax u64 [kRows] | fword u32 [kRows] |
 // sig u32 [kRows] | rcnt u32 [kRows] | pack u32 [kRows * row_words].
 // kFused: as in k_search.
-template <int kWaves, bool kFused = false, bool kScreen = true>
-__global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+template <bool kFused = false, bool kScreen = true>
+__global__ __launch_bounds__(64 * kSearchWaves) void k_search_flat(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
 {
-    constexpr int kThreadsS = 64 * kWaves;
+    constexpr int kThreadsS = 64 * kSearchWaves;
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
@@ -724,7 +722,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_search_flat(Geometry g, Workspa
         const float r_f = __builtin_amdgcn_sqrtf((float)r2);
         const int rq = radius_code(r2, r_f, sigma16, Lq);
         const Direction u = unit_direction(xv, r2, r_f);
-        const uint32_t code = search_codeword<false, 1, kScreen>(g, lane, u, flagged || !valid, r2, rq, amat, secl);
+        const uint32_t code = search_codeword<false, kScreen>(g, lane, u, flagged || !valid, r2, rq, amat, secl);
         if (code) {
             const uint32_t bitpos = (uint32_t)c * g.w;
             const uint32_t d0 = bitpos >> 5, sh = bitpos & 31;
@@ -1450,16 +1448,11 @@ hipError_t prepare_search_kernels()
 {
     // the fused forms also hold static LDS (the workgroup-wide OR, the merge buffer of the cooperative pass: up to
     // 6 KiB), which counts against the same 160 KiB
-    const void *fused[] = {reinterpret_cast<const void *>(k_search<4, true>),
-                           reinterpret_cast<const void *>(k_search<8, true>),
-                           reinterpret_cast<const void *>(k_search_flat<4, true>),
-                           reinterpret_cast<const void *>(k_search_flat<8, true>)};
-    const void *variants[] = {reinterpret_cast<const void *>(k_search<4>),
-                              reinterpret_cast<const void *>(k_search<8>),
-                              reinterpret_cast<const void *>(k_search_flat<4>),
-                              reinterpret_cast<const void *>(k_search_flat<8>),
-                              reinterpret_cast<const void *>(k_search<4, false, false>),
-                              reinterpret_cast<const void *>(k_search_flat<4, false, false>),
+    const void *fused[] = {reinterpret_cast<const void *>(k_search<true>), reinterpret_cast<const void *>(k_search_flat<true>)};
+    const void *variants[] = {reinterpret_cast<const void *>(k_search<>),
+                              reinterpret_cast<const void *>(k_search_flat<>),
+                              reinterpret_cast<const void *>(k_search<false, false>),
+                              reinterpret_cast<const void *>(k_search_flat<false, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
@@ -1482,32 +1475,18 @@ hipError_t prepare_search_kernels()
     return err;
 }
 
-// The fused form exists for the workgroup shapes that short segments get: 64 rows, 4 or 8 waves.
-bool search_fused_available(const Geometry &g)
-{
-    if (g.A16 == 0)
-        return false;  // no screen: the general form
-    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-    return g.search_rows == kSearchRowsSmall && (waves == 4 || waves == 8);
-}
+// The fused form exists for the workgroups that short segments get, of 64 rows, and codebooks that are screened.
+bool search_fused_available(const Geometry &g) { return g.A16 > 0 && g.search_rows == kSearchRowsSmall; }
 
 hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                                hipStream_t stream)
 {
     dim3 grid((g.T + g.search_rows - 1) / g.search_rows, g.fused_by_head ? g.H : g.B * g.H, (unsigned)n_tensors);
-    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows);
-    if (g.D == 4 * kChunksPerRow) {
-        if (waves == 8)
-            hipLaunchKernelGGL((k_search<8, true>), grid, dim3(512), lds, stream, g, wo, batch);
-        else
-            hipLaunchKernelGGL((k_search<4, true>), grid, dim3(256), lds, stream, g, wo, batch);
-    } else {
-        if (waves == 8)
-            hipLaunchKernelGGL((k_search_flat<8, true>), grid, dim3(512), lds, stream, g, wo, batch);
-        else
-            hipLaunchKernelGGL((k_search_flat<4, true>), grid, dim3(256), lds, stream, g, wo, batch);
-    }
+    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, g.search_rows);
+    if (g.D == 4 * kChunksPerRow)
+        hipLaunchKernelGGL(k_search<true>, grid, dim3(64 * kSearchWaves), lds, stream, g, wo, batch);
+    else
+        hipLaunchKernelGGL(k_search_flat<true>, grid, dim3(64 * kSearchWaves), lds, stream, g, wo, batch);
     return hipGetLastError();
 }
 
@@ -1541,28 +1520,21 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
 #undef HQMQ_LAUNCH_CELLS
         return hipGetLastError();
     }
-    const int waves = search_waves_for(g.S16, g.A16, g.D, g.row_words, g.search_rows);
-    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, waves, g.search_rows);
-    // rows per workgroup that the kernels take: two per wave and up to 64, or 256 for the flat form on 4 waves
+    const size_t lds = search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, g.search_rows);
+    // rows per workgroup that the kernels take: two per wave and up to 64, or 256 for the flat form
     const int rows = g.search_rows;
-    if (full ? rows > kSearchRowsSmall || rows % (2 * waves) : rows > kSearchRowsSmall && (rows != kSearchRowsLarge || waves != 4))
+    if (full ? rows > kSearchRowsSmall || rows % (2 * kSearchWaves) : rows > kSearchRowsSmall && rows != kSearchRowsLarge)
         return hipErrorInvalidConfiguration;
-#define HQMQ_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * waves), lds, stream, g, wo, batch)
-    if (g.A16 == 0) {  // more secondaries than the matrix-core screen holds: 4 waves, every chunk scored in fp32
+#define HQMQ_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(64 * kSearchWaves), lds, stream, g, wo, batch)
+    if (g.A16 == 0) {  // more secondaries than the matrix-core screen holds: every chunk scored in fp32
         if (full)
-            HQMQ_LAUNCH(k_search<4, false, false>);
+            HQMQ_LAUNCH(k_search<false, false>);
         else
-            HQMQ_LAUNCH(k_search_flat<4, false, false>);
+            HQMQ_LAUNCH(k_search_flat<false, false>);
     } else if (full) {
-        if (waves == 8)
-            HQMQ_LAUNCH(k_search<8>);
-        else
-            HQMQ_LAUNCH(k_search<4>);
+        HQMQ_LAUNCH(k_search<>);
     } else {
-        if (waves == 8)
-            HQMQ_LAUNCH(k_search_flat<8>);
-        else
-            HQMQ_LAUNCH(k_search_flat<4>);
+        HQMQ_LAUNCH(k_search_flat<>);
     }
 #undef HQMQ_LAUNCH
     return hipGetLastError();
