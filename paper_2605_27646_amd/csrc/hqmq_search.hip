@@ -987,7 +987,7 @@ hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStre
 // |y_1| + |y_2| + |y_3| <= 1 (24-cell: its cells are octahedra).  Scores divided by w_0 > 0 are
 // c_0 + c_1 y_1 + c_2 y_2 + c_3 y_3: linear in y.
 // Cells.  The cube [-1, 1]^3 is cut into n^3 boxes; a box has the list of the codewords that are the best, or within
-// kCellEps of the best, somewhere in it.  Codeword c is left out when another one b is ahead of it all over the box:
+// kListEps of the best, somewhere in it.  Codeword c is left out when another one b is ahead of it all over the box:
 // <b - c, (1, m)> > h sum_i |b_i - c_i| + eps at the centre m with half width h: exact for linear functions, whatever
 // the norms of the secondaries.  About 6 of the 24 S codewords stay (S = 256, n = 20).
 // A chunk then costs the fold, a look-up of its box and 3 FMA and 5 more operations per listed codeword instead of
@@ -1012,8 +1012,7 @@ namespace {
 // 27.9 in all, of a best that is at least 1/sqrt(2): 2.35e-6 (3.4e-7 measured on 800,000 chunks).  Secondaries of other
 // norms scale both sides by the largest.
 constexpr float kCellBand = 2.5e-6f;
-constexpr float kCellEps = 1.0e-5f;  // the lists keep what comes within this of the best
-static_assert(kCellEps == kListEps && 2.0f * kCellBand < kCellEps, "a list holds the runner-up of every chunk in the band");
+static_assert(2.0f * kCellBand < kListEps, "a list holds the runner-up of every chunk in the band");
 constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -1 and 1, which rounding can move past the
                                                // cube by 5.4e-7 (fold 3.6e-7, reciprocal and product 1.8e-7), in 0 .. n - 1
 // The search numbers the element P_0 that it folds with by 4 f + 16 for f = p_0 / 4 + p_1 / 2 + p_2 + 2 p_3 in twice its

@@ -330,7 +330,9 @@ def test_band_of_the_search_index_covers_its_rounding():
     functions = 2 * 3 * 0.5 * 2.0 * u                            # two functions, three additions below 1, 1 + sum |y| <= 2
     values = 2 * 3 * u                                           # two functions, three FMA below 2
     worst = (fold + functions + values) / 2.0 ** -0.5
-    source = open(os.path.join(ROOT, "paper_2605_27646_amd", "csrc", "hqmq_search.hip")).read()
-    band = float(re.search(r"kCellBand = ([0-9.e-]+)f;", source).group(1))
-    eps = float(re.search(r"kCellEps = ([0-9.e-]+)f;", source).group(1))
+    def constant(source, name):
+        text = open(os.path.join(ROOT, "paper_2605_27646_amd", "csrc", source)).read()
+        return float(re.search(name + r" = ([0-9.e-]+)f;", text).group(1))
+
+    band, eps = constant("hqmq_search.hip", "kCellBand"), constant("hqmq_tables.h", "kListEps")
     assert 2.3e-6 < worst < band < eps / 2
