@@ -254,8 +254,9 @@ def main() -> int:
         "bits_per_element_stored": (encs[0].nbytes() - encs[0].outliers.numel() * 2 + 8 * n_out / n_t) * 8
         / wl.elems_per_tensor,
         # The search reads every chunk once and writes its code: that is what it cannot do without, so its roofline is
-        # HBM; what it spends the time on is VALU issue ("executed", from the committed rocprofv3 counters; the phase
-        # also holds the launch that builds the box index).  "fp32_equivalent" is the metric's own yardstick, the fp32
+        # HBM; what it spends the time on is VALU issue ("executed", from the committed rocprofv3 counters).  The box index
+        # that it reads is built beside the median select's sweep: its time is in the select's phase, whose GB/s are of the
+        # sweep's bytes alone (for heads of at most 1024 rows it is a launch in the search's phase).  "fp32_equivalent" is the metric's own yardstick, the fp32
         # flops of the exhaustive search in closed form (36 S per chunk) against the 157.3 TFLOP/s fp32 peak: NOT a
         # roofline fraction, since point location reaches the same result without doing them.
         "roofline": {"kernel": search_kernel, "bound": "hbm",

@@ -236,7 +236,8 @@ int32_t hqmq_encode_given_thresholds(const hqmq_params *params, const void *x_de
 
 /* hqmq_encode_given_thresholds for n_tensors tensors of one shape in one call (e.g. the new K and
  * V rows of every layer of a generation step): up to 32 tensors per kernel launch, arguments as in
- * hqmq_encode_batch plus thr_dev, a HOST array of n_tensors DEVICE pointers to fp64 [H]. */
+ * hqmq_encode_batch plus thr_dev, a HOST array of n_tensors DEVICE pointers to fp64 [H] (tensors of up to
+ * 64 rows: up to 64 per launch). */
 int32_t hqmq_encode_batch_given_thresholds(const hqmq_params *params, int32_t n_tensors,
                                            const void *const *x_dev, const float *const *sec_dev,
                                            const double *const *thr_dev, const hqmq_encoded *enc,
@@ -297,7 +298,9 @@ int32_t hqmq_shard_median_region(const hqmq_params *params, int32_t pass, uint64
  *   phase_events    NULL, or 4 hipEvent_t as in hqmq_encode_timed (entries may be NULL): [0] is
  *            recorded before the first launch, [1..3] after the select / search / outlier-list
  *            phase of EVERY group of 32 tensors, so with more than 32 tensors they hold the times
- *            of the last group; time groups of at most 32 with one call each.
+ *            of the last group; time groups of at most 32 with one call each.  Tensors of up to 64
+ *            rows with extraction off may take one launch for 64 of them, which is all three phases:
+ *            [1] is then recorded with [0], [2] and [3] after the last.
  * Errors: as hqmq_encode; INVALID_ARG also for n_tensors <= 0 or a null array. */
 int32_t hqmq_encode_batch(const hqmq_params *params, int32_t n_tensors, const void *const *x_dev,
                           const float *const *sec_dev, const hqmq_encoded *enc,

@@ -145,15 +145,17 @@ static Geometry make_geometry(const hqmq_params *p)
     return g;
 }
 
-// The search of the general path: the box index (a launch of 12 to 30 us, 1.1 us per head beyond some 25 heads, then a
-// search that hardly depends on S) from chunks per head x (S + 32) = 6.3 million on, the matrix screen below.  Whole
-// encodes of 4 tensors with 8 heads of 128 elements, screen / index in us: S = 256: 92 / 90 at T = 512, 118 / 102 at
-// 1024, 355 / 199 at 4096; S = 64: 87 / 94 at 1536, 116 / 110 at 3072, 209 / 183 at 4096; S = 16: 90 / 94 at 3072,
-// 176 / 168 at 4096, 272 / 203 at 16384.  With 64 heads the two meet at the same lengths within a fifth, with 8 earlier.
-// A workgroup copies the whole index for rows of one (batch entry, head) only, so their chunks x (S + 32) have to reach 2^17:
-// search of 2 tensors with 8 heads and many batch entries, screen / index in us: S = 256: 194 / 334 at B = 1024, T = 4, 143 /
-// 190 at 512 x 8, 278 / 200 at 512 x 16; S = 64: 115 / 277 at 1024 x 8, 195 / 296 at 1024 x 16, 179 / 181 at 512 x 32, 176 /
-// 123 at 256 x 64; S = 16: 64 / 95 at 256 x 32, 62 / 68 at 128 x 64, 62 / 56 at 64 x 128.
+// The search of the general path: the box index (built beside the select's sweep, or where a head has at most 1024 rows in a
+// launch of its own, of 12 to 25 us; then a search that hardly depends on S) from chunks per head x (S + 32) = 6.3 million on, the
+// matrix screen below.  Whole encodes with heads of 128 elements, screen / index in us.  4 tensors of 8 heads: S = 256: 53 / 60 at
+// T = 512, 68 / 64 at 683, 87 / 66 at 1024, 266 / 91 at 4096; S = 64: 60 / 62 at 1100, 66 / 63 at 1536, 78 / 68 at 2048, 123 / 77 at
+// 4096; S = 16: 48 / 50 at 1100, 59 / 56 at 2048, 75 / 70 at 3072, 88 / 68 at 4096.  Of 64 heads the two meet earlier (S = 256: 85 / 84
+// at 512; S = 16: 68 / 68 at 1100), of fewer later: 8 heads S = 256: 41 / 45 at 1024, 53 / 49 at 1100; S = 64: 43 / 41 at 2048; S = 16:
+// 45 / 42 at 4096; 2 heads S = 256: 29 / 43 at 1024, 50 / 45 at 4096; S = 16: 38 / 38 at 8192.
+// A workgroup copies the whole index for rows of one (batch entry, head) only, so their chunks x (S + 32) have to reach 2^17: two
+// tensors with 8 heads and many batch entries: S = 256: 384 / 472 at B = 1024, T = 4, 238 / 253 at 512 x 8, 360 / 270 at 512 x 16; S =
+// 64: 353 / 464 at 1024 x 8, 427 / 481 at 1024 x 16, 285 / 256 at 512 x 32, 219 / 144 at 256 x 64; S = 16: 102 / 113 at 256 x 32, 93 /
+// 82 at 128 x 64, 88 / 67 at 64 x 128.
 static bool use_cells(const Geometry &g)
 {
     const uint64_t work = (uint64_t)g.T * g.n_c * (uint64_t)(g.S + 32);

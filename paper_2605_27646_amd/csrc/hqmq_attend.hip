@@ -9,7 +9,8 @@
 //     takes 16 rows of a tile; the encoded rows of K and of V arrive with coalesced loads issued one
 //     tile ahead and are re-distributed through LDS as in the stand-alone decode;
 //   * both products run on v_mfma_f32_16x16x16_f16, and the lane-to-chunk assignment of each decode
-//     is the operand layout of its product, so no value crosses lanes:
+//     is the operand layout of its product, so no value crosses lanes (k_attend_partial; k_attend_joint,
+//     below, gives a lane neighbouring chunks instead, with q and the output columns to match):
 //       scores  S[row][head]  = K_hat[16 rows x 128] * Q^T : lane (row = l % 16, j = l / 16) decodes
 //               chunks 4 m + j, m = 0..7, i.e. exactly the four k-values it owes to product m;
 //       values  O[head][dim] += P^T[head x 16 rows] * V_hat : lane (n = l % 16, j) decodes chunks
@@ -875,7 +876,7 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
 
         uint2 p_hi = make_uint2(0u, 0u), p_lo = make_uint2(0u, 0u);
         if (nrows > 0) {
-            // ---- scores: lane (row n16, j4) supplies chunks 4 m + j4 ------------------------------------
+            // ---- scores: lane (row n16, j4) supplies chunks kM j4 + m ------------------------------------
             float4_t sc = float4_t{0.f, 0.f, 0.f, 0.f};
             auto scores = [&](auto fast_tag) {
                 // The careful form is rare: its lane indices are made opaque so that the compiler does
@@ -982,7 +983,7 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         if (more)
             open_windows(nn);
 
-        // ---- weighted values: lane (n16, j4) supplies chunks n16 and n16 + 16 of rows 4 j4 + i -----------
+        // ---- weighted values: lane (n16, j4) supplies chunks kU n16 + u of rows 4 j4 + i -------------------
         if (nrows > 0) {
             auto weighted_values = [&](auto fast_tag) {
                 int n16 = n16_, j4 = j4_;
@@ -1061,7 +1062,7 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         nrows = nn;
     }
 
-    // ---- merge: the row groups of a wave (sum of l_run over j4), then the 4 waves -----------------------
+    // ---- merge: the row groups of a wave (sum of l_run over j4), then the 8 waves -----------------------
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
     __syncthreads();  // every wave is done with its staging area

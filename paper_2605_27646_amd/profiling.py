@@ -86,11 +86,11 @@ kernel ({per_launch:g} tensors per launch unless noted)       calls     avg (us)
 (% time is of all GPU kernels in the process, including torch's generators for the synthetic inputs.)
 
 bench.py line of the same build (python bench.py --workload {wl}; {d['warmup']} warm-up + {d['steps']} timed steps; HIP-event times on the launch stream):
-  search phase (box index and search): avg {rf['avg_launch_ms'] * 1e3:.1f} us for {per_launch:g} tensors (median {rf['median_launch_ms'] * 1e3:.1f}, min {rf['min_launch_ms'] * 1e3:.1f}; {rf['avg_launch_ms'] * 1e3 / per_launch:.1f} us per tensor)  ->  {rf['achieved']:.0f} GB/s of 8000 = {rf['frac'] * 100:.1f} % ({rf['bytes_per_chunk']:.2f} B per chunk, {chunks:,} chunks per tensor);
+  search phase: avg {rf['avg_launch_ms'] * 1e3:.1f} us for {per_launch:g} tensors (median {rf['median_launch_ms'] * 1e3:.1f}, min {rf['min_launch_ms'] * 1e3:.1f}; {rf['avg_launch_ms'] * 1e3 / per_launch:.1f} us per tensor)  ->  {rf['achieved']:.0f} GB/s of 8000 = {rf['frac'] * 100:.1f} % ({rf['bytes_per_chunk']:.2f} B per chunk, {chunks:,} chunks per tensor);
       the exhaustive closed form ({fe32['flops_per_chunk']:g} flop per chunk) would run at {fe32['achieved']:.1f} TFLOP/s = {fe32['ratio_to_fp32_peak']:.3f} x the 157.3 fp32 peak (the metric's yardstick, not a roofline fraction)
   decode kernel: avg launch {rd['avg_launch_ms'] * 1e3:.1f} us for {rd['tensors_per_launch']:g} tensors (median {rd['median_launch_ms'] * 1e3:.1f}, min {rd['min_launch_ms'] * 1e3:.1f}; {rd['avg_launch_ms'] * 1e3 / rd['tensors_per_launch']:.1f} us per tensor)  ->  {rd['achieved']:.0f} GB/s of 8000 = {rd['frac'] * 100:.1f} % ({rd['bytes_per_chunk']:.2f} B per chunk)
   encode {d['encode_elems_per_s']:.3e} elems/s, decode {d['decode_elems_per_s']:.3e} elems/s, encode+decode {d['value']:.3e} elems/s ({d['ms_per_step']:.1f} ms per step)
-  encode phases per tensor: median select {d['encode_phase_ms_per_tensor']['median_select'] * 1e3:.1f} us ({d['median_select_GBs']:.0f} GB/s over the {d['median_select_reads']:.4g} reads of the tensor it makes), search + quantise + pack {d['encode_phase_ms_per_tensor']['search_quantise_pack'] * 1e3:.1f} us, outlier scan + gather {d['encode_phase_ms_per_tensor']['outlier_scan_gather'] * 1e3:.1f} us
+  encode phases per tensor: median select, with the box index built beside its sweep, {d['encode_phase_ms_per_tensor']['median_select'] * 1e3:.1f} us ({d['median_select_GBs']:.0f} GB/s over the {d['median_select_reads']:.4g} reads of the tensor it makes), search + quantise + pack {d['encode_phase_ms_per_tensor']['search_quantise_pack'] * 1e3:.1f} us, outlier scan + gather {d['encode_phase_ms_per_tensor']['outlier_scan_gather'] * 1e3:.1f} us
   outlier fraction {d['outlier_fraction']:.4f}, stored bits per element {d['bits_per_element_stored']:.3f}""")
     if has_att:
         at = d["attend"]
