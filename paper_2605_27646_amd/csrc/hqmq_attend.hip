@@ -52,15 +52,6 @@ static_assert(kStageWords % 4 == 0 && kSideWords % 4 == 0, "16-byte LDS reads of
 
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // LDS serves the instructions of one wave in order; this only stops the compiler from moving
-    // LDS accesses of other lanes' data across the point.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One tile's encoded rows of one side on their way from memory to LDS.  Every lane loads, past the tile's end its last
 // word again: no lane mask per load, and the bases stay scalar.  Rows that are not there get a scale of zero and no flags:
 // whatever their code words say, they decode to zeros.
@@ -102,6 +93,60 @@ __device__ __forceinline__ void stage_tile(TileRegs<kNc> &t, uint32_t *stage, in
         stage[kStageWords + lane] = t.fw;
         stage[kStageWords + kStageRows + lane] = t.sg;
         stage[kStageWords + 2 * kStageRows + lane] = t.ro;
+    }
+}
+
+// Outlier payloads of a wave's 16 rows: one contiguous window of the list, its first 128 entries copied to LDS (zeros for
+// entries beyond the list's capacity).  The first 64 are requested half a tile ahead, from the tile's registers (offset of the
+// first row, offset + count of the last); the next 64 (rare) are copied when the tile is staged; a still larger window (more
+// than a quarter of the chunks flagged) sends the tile down the careful path, which reads the list.
+struct Window {
+    uint32_t base, n, in_list;  // in_list: entries that the list has room for
+    uint2 mine;                 // entry `lane` of the window, on its way to LDS
+};
+template <int kNc>
+__device__ __forceinline__ Window window_of(const AttendSide &s, const TileRegs<kNc> &t, int nr)
+{
+    Window wd;
+    wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
+    const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, nr - 1);
+    const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, nr - 1);
+    wd.n = ro_l + __popc(fw_l) - wd.base;
+    wd.in_list = (uint64_t)wd.base < s.outlier_capacity ? (uint32_t)min((uint64_t)wd.n, s.outlier_capacity - wd.base) : 0u;
+    return wd;
+}
+// Unconditional load (a conditional one would be waited for on the spot): lanes past the window or the list's capacity re-read
+// a neighbour's entry; a wave without outliers reads 8 harmless bytes of the offset array.  Nothing looks at the entry before
+// it is staged.
+__device__ __forceinline__ void request_window(const AttendSide &s, Window &wd, int lane)
+{
+    const uint2 *src = wd.in_list ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base : reinterpret_cast<const uint2 *>(s.row_off);
+    wd.mine = src[min((uint32_t)lane, wd.in_list ? wd.in_list - 1u : 0u)];
+}
+// Both sides' bounds before either request: looking at the second side's offsets after the first request would wait for that
+// too (0.7 us per tile).
+template <int kNc>
+__device__ __forceinline__ void request_windows(const AttendArgs &a, const TileRegs<kNc> &tk, const TileRegs<kNc> &tv, int nr, int lane,
+                                                Window &wk, Window &wv)
+{
+    if (nr > 0) {
+        wk = window_of(a.k, tk, nr);
+        wv = window_of(a.v, tv, nr);
+        request_window(a.k, wk, lane);
+        request_window(a.v, wv, lane);
+    } else {
+        wk.n = wv.n = wk.in_list = wv.in_list = 0u;
+    }
+}
+__device__ __forceinline__ void stage_window(const AttendSide &s, const Window &wd, uint32_t *stage, int lane)
+{
+    uint2 *st_pay = reinterpret_cast<uint2 *>(stage + kStageWords + 3 * kStageRows);
+    st_pay[lane] = (uint32_t)lane < wd.in_list ? wd.mine : make_uint2(0u, 0u);
+    if (wd.n > 64u) {  // wave-uniform and rare: more than 64 outliers in 16 rows
+        for (uint32_t k = 64u + lane; k < min(wd.n, (uint32_t)kPaySlots); k += 64u) {
+            const uint64_t at = (uint64_t)wd.base + k;
+            st_pay[k] = at < s.outlier_capacity ? reinterpret_cast<const uint2 *>(s.outliers)[at] : make_uint2(0u, 0u);
+        }
     }
 }
 
@@ -219,56 +264,8 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
     const uint32_t code_mask = (1u << w) - 1u, idx_mask = (1u << w_idx) - 1u;
     const float inv_L = g.inv_L;
 
-    // Outlier payloads of a wave's 16 rows: one contiguous window of the list, its first 128 entries
-    // copied to LDS (zeros for entries beyond the list's capacity).  The first 64 are requested half
-    // a tile ahead, from the tile's registers (offset of the first row, offset + count of the last);
-    // the next 64 (rare) are copied when the tile is staged; a still larger window (more than a
-    // quarter of the chunks flagged) sends the tile down the careful path, which reads the list.
-    struct Window {
-        uint32_t base, n, in_list;  // in_list: entries that the list has room for
-        uint2 mine;                 // entry `lane` of the window, on its way to LDS
-    };
-    auto window_of = [&](const AttendSide &s, const TileRegs<kNc> &t, int nr) {
-        Window wd;
-        wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
-        const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, nr - 1);
-        const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, nr - 1);
-        wd.n = ro_l + __popc(fw_l) - wd.base;
-        wd.in_list = (uint64_t)wd.base < s.outlier_capacity ? (uint32_t)min((uint64_t)wd.n, s.outlier_capacity - wd.base) : 0u;
-        return wd;
-    };
-    // unconditional load (a conditional one would be waited for on the spot): lanes past the window or the list's capacity
-    // re-read a neighbour's entry; a wave without outliers reads 8 harmless bytes of the offset array.  Nothing looks at the
-    // entry before it is staged.
-    auto request = [&](const AttendSide &s, Window &wd) {
-        const uint2 *src = wd.in_list ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
-                                      : reinterpret_cast<const uint2 *>(s.row_off);
-        wd.mine = src[min((uint32_t)lane, wd.in_list ? wd.in_list - 1u : 0u)];
-    };
-    // Both sides' bounds before either request: looking at the second side's offsets after the first request would wait for
-    // that too (0.7 us per tile).
     Window wk = {}, wvw = {};
-    auto open_windows = [&](int nr) {
-        if (nr > 0) {
-            wk = window_of(a.k, tk, nr);
-            wvw = window_of(a.v, tv, nr);
-            request(a.k, wk);
-            request(a.v, wvw);
-        } else {
-            wk.n = wvw.n = wk.in_list = wvw.in_list = 0u;
-        }
-    };
-    auto stage_window = [&](const AttendSide &s, const Window &wd, uint32_t *stage) {
-        uint2 *st_pay = reinterpret_cast<uint2 *>(stage + kStageWords + 3 * kStageRows);
-        st_pay[lane] = (uint32_t)lane < wd.in_list ? wd.mine : make_uint2(0u, 0u);
-        if (wd.n > 64u) {  // wave-uniform and rare: more than 64 outliers in 16 rows
-            for (uint32_t k = 64u + lane; k < min(wd.n, (uint32_t)kPaySlots); k += 64u) {
-                const uint64_t at = (uint64_t)wd.base + k;
-                st_pay[k] = at < s.outlier_capacity ? reinterpret_cast<const uint2 *>(s.outliers)[at]
-                                                    : make_uint2(0u, 0u);
-            }
-        }
-    };
+    auto open_windows = [&](int nr) { request_windows(a, tk, tv, nr, lane, wk, wvw); };
 
     // One chunk of `row` as the library's decode returns it (four fp16 values, two dwords), in three
     // steps so that the LDS round trips of neighbouring chunks overlap: the code, then the table
@@ -355,8 +352,8 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
         // ---- this tile's rows and payload windows into LDS; the next tile's rows requested -----------
         stage_tile(tk, stage_k, nrows, lane);
         stage_tile(tv, stage_v, nrows, lane);
-        stage_window(a.k, wk, stage_k);
-        stage_window(a.v, wvw, stage_v);
+        stage_window(a.k, wk, stage_k, lane);
+        stage_window(a.v, wvw, stage_v, lane);
         wave_lds_sync();
         const uint32_t base_k = wk.base, base_v = wvw.base;
         // a product r_hat * c_i can leave the fp16 range only when the row's scale is within a factor
@@ -727,56 +724,8 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
     const uint32_t div_shift = 32u - (uint32_t)__clz((int)(48u * (uint32_t)g.S * (uint32_t)g.S));
     const uint32_t div_mul = ((1u << div_shift) + (uint32_t)g.S - 1u) / (uint32_t)g.S;
 
-    // Outlier payloads of a wave's 16 rows: one contiguous window of the list, its first 128 entries
-    // copied to LDS (zeros for entries beyond the list's capacity).  The first 64 are requested half
-    // a tile ahead, from the tile's registers (offset of the first row, offset + count of the last);
-    // the next 64 (rare) are copied when the tile is staged; a still larger window (more than a
-    // quarter of the chunks flagged) sends the tile down the careful path, which reads the list.
-    struct Window {
-        uint32_t base, n, in_list;  // in_list: entries that the list has room for
-        uint2 mine;                 // entry `lane` of the window, on its way to LDS
-    };
-    auto window_of = [&](const AttendSide &s, const TileRegs<kNc> &t, int nr) {
-        Window wd;
-        wd.base = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, 0);
-        const uint32_t ro_l = (uint32_t)__builtin_amdgcn_readlane((int)t.ro, nr - 1);
-        const uint32_t fw_l = (uint32_t)__builtin_amdgcn_readlane((int)t.fw, nr - 1);
-        wd.n = ro_l + __popc(fw_l) - wd.base;
-        wd.in_list = (uint64_t)wd.base < s.outlier_capacity ? (uint32_t)min((uint64_t)wd.n, s.outlier_capacity - wd.base) : 0u;
-        return wd;
-    };
-    // unconditional load (a conditional one would be waited for on the spot): lanes past the window or the list's capacity
-    // re-read a neighbour's entry; a wave without outliers reads 8 harmless bytes of the offset array.  Nothing looks at the
-    // entry before it is staged.
-    auto request = [&](const AttendSide &s, Window &wd) {
-        const uint2 *src = wd.in_list ? reinterpret_cast<const uint2 *>(s.outliers) + wd.base
-                                      : reinterpret_cast<const uint2 *>(s.row_off);
-        wd.mine = src[min((uint32_t)lane, wd.in_list ? wd.in_list - 1u : 0u)];
-    };
-    // Both sides' bounds before either request: looking at the second side's offsets after the first request would wait for
-    // that too (0.7 us per tile).
     Window wk = {}, wvw = {};
-    auto open_windows = [&](int nr) {
-        if (nr > 0) {
-            wk = window_of(a.k, tk, nr);
-            wvw = window_of(a.v, tv, nr);
-            request(a.k, wk);
-            request(a.v, wvw);
-        } else {
-            wk.n = wvw.n = wk.in_list = wvw.in_list = 0u;
-        }
-    };
-    auto stage_window = [&](const AttendSide &s, const Window &wd, uint32_t *stage) {
-        uint2 *st_pay = reinterpret_cast<uint2 *>(stage + kStageWords + 3 * kStageRows);
-        st_pay[lane] = (uint32_t)lane < wd.in_list ? wd.mine : make_uint2(0u, 0u);
-        if (wd.n > 64u) {  // wave-uniform and rare: more than 64 outliers in 16 rows
-            for (uint32_t k = 64u + lane; k < min(wd.n, (uint32_t)kPaySlots); k += 64u) {
-                const uint64_t at = (uint64_t)wd.base + k;
-                st_pay[k] = at < s.outlier_capacity ? reinterpret_cast<const uint2 *>(s.outliers)[at]
-                                                    : make_uint2(0u, 0u);
-            }
-        }
-    };
+    auto open_windows = [&](int nr) { request_windows(a, tk, tv, nr, lane, wk, wvw); };
 
     // One chunk as the library's decode returns it (four fp16 values, two dwords), in three steps so that the LDS round
     // trips of neighbouring chunks overlap: the primary's entry of the look-up table and the payload slot (pre), the table
@@ -857,8 +806,8 @@ __global__ __launch_bounds__(kJointThreads, 1) void k_attend_joint(Geometry g, A
         // ---- this tile's rows and payload windows into LDS; the next tile's rows requested -----------
         stage_tile(tk, stage_k, nrows, lane);
         stage_tile(tv, stage_v, nrows, lane);
-        stage_window(a.k, wk, stage_k);
-        stage_window(a.v, wvw, stage_v);
+        stage_window(a.k, wk, stage_k, lane);
+        stage_window(a.v, wvw, stage_v, lane);
         wave_lds_sync();
         const uint32_t base_k = wk.base, base_v = wvw.base;
         // a product r_hat * c_i can leave the fp16 range only when the row's scale is within a factor

@@ -341,6 +341,15 @@ __device__ __forceinline__ int row_of_chunk(int q, const Shape &g)
     return g.n_c == 1 ? q : (int)__umulhi((uint32_t)q, g.n_c_magic);
 }
 
+__device__ __forceinline__ void wave_lds_sync()
+{
+    // LDS serves the instructions of one wave in order; this only stops the compiler from moving
+    // LDS accesses of other lanes' data across the point.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The lanes for which p holds (__ballot takes an integer, which costs two vector instructions).
 __device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // This lane's bit of a mask of the wave.

@@ -8,15 +8,6 @@ namespace hqmq {
 
 namespace {
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // LDS serves the instructions of one wave in order; this only stops the compiler from moving
-    // LDS accesses of other lanes' data across the point.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int kCtrl>
 __device__ __forceinline__ unsigned long long dpp_move64(unsigned long long v)
 {
