@@ -86,3 +86,38 @@ def test_graph_replays_match_eager():
         # eager work of the program's own between the replays
         path()
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_calls_go_to_the_current_stream(raw, monkeypatch):
+    """The stream that a call without one takes is torch's current one, from the handle that this torch gives directly or, where
+    it does not, from a Stream object: on the default stream, on another, in another thread and while a graph is captured."""
+    import threading
+
+    from paper_2605_27646_amd import binding
+    if not raw:
+        monkeypatch.setattr(binding, "_raw_stream", None)
+    elif binding._raw_stream is None:
+        pytest.skip("this torch has no handle without a Stream object")
+
+    def agrees():
+        return binding._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+
+    assert agrees()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert agrees() and binding._stream_ptr(None) == side.cuda_stream
+        seen = []
+        t = threading.Thread(target=lambda: seen.append((agrees(), binding._stream_ptr(None))))
+        t.start()
+        t.join()
+        assert seen[0][0] and seen[0][1] != side.cuda_stream
+        assert binding._stream_ptr(side) == side.cuda_stream
+    assert agrees() and binding._stream_ptr(None) != side.cuda_stream
+    graph = torch.cuda.CUDAGraph()
+    buf = torch.zeros(4, device="cuda:0")
+    with torch.cuda.graph(graph):
+        assert agrees()
+        buf.add_(1.0)
+    graph.replay()
+    torch.cuda.synchronize()
