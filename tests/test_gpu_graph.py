@@ -88,6 +88,66 @@ def test_graph_replays_match_eager():
         torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("n,B,H,T,D,S,given", [
+    (2, 1, 2, 6000, 128, 64, False),   # sweep with the box index beside it
+    (1, 2, 3, 1537, 100, 96, False),   # the same for any row length, decode included
+    (1, 2, 2, 1100, 128, 16, False),   # sweep alone, matrix screen
+    (3, 1, 8, 1, 128, 256, True),      # rows of a generation step: one launch
+    (3, 2, 8, 5, 96, 48, True),        # two launches
+    (2, 1, 2, 5000, 128, 128, True),   # thresholds known: the index in a launch of its own
+])
+def test_graph_replays_of_the_encodes_forms(n, B, H, T, D, S, given):
+    xs = [workloads.make_tensor(workloads.Workload("graph", 910 + i, 1, B, H, T, D, S, sigma_g=0.8), 0, 0, "cpu").to(DEV)
+          for i in range(n)]
+    cb = hq.hqmq_build_codebooks(1, n, H, S).to(DEV)
+    secs = [cb[i, 0].contiguous() for i in range(n)]
+    params = hq.params_for(xs[0], S)
+    encs = [hq.alloc_encoded(params, DEV, outlier_capacity=B * H * T * ((D + 3) // 4)) for _ in range(n)]
+    ws = hq.alloc_batch_workspace(params, n, DEV)
+    batch = hq.EncodeBatch(params, xs, secs, encs, ws)
+    thrs = hq.ThresholdBatch(batch, [torch.full((H,), 6.0, dtype=torch.float64, device=DEV)] * n) if given else None
+    outs = [torch.empty_like(x) for x in xs]
+    dec = hq.DecodeBatch(params, encs, secs, outs)
+
+    def path():
+        if given:
+            hq.hqmq_encode_batch_given_thresholds(batch, thrs)
+        else:
+            hq.hqmq_encode_batch(batch)
+        hq.hqmq_decode_batch(dec)
+
+    def state():
+        return [t for e, o in zip(encs, outs) for t in (e.codes, e.sigma, e.flags, e.row_off, e.n_outliers, e.status, o)]
+
+    def snapshot():
+        torch.cuda.synchronize()
+        return [(t.view(torch.int16) if t.dtype == torch.float16 else t).clone() for t in state()]
+
+    hq.hqmq_init()
+    path()
+    want = snapshot()
+    assert all(int(e.n_outliers[-1]) > 0 for e in encs)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        path()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        path()
+    for rep in range(3):
+        for t in state():
+            t.fill_(-1)
+        ws.fill_(0x77)
+        torch.cuda.synchronize()
+        graph.replay()
+        for a, b in zip(snapshot(), want):
+            assert torch.equal(a, b), rep
+        path()
+        torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("raw", [True, False])
 def test_calls_go_to_the_current_stream(raw, monkeypatch):
     """The stream that a call without one takes is torch's current one, from the handle that this torch gives directly or, where
