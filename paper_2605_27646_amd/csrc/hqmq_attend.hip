@@ -40,7 +40,7 @@ constexpr int kStageRows = 16;                      // rows per wave and tile
 constexpr int kMaxW = 24;                           // w = w_idx + b_r <= 16 + 8
 constexpr int kStageWords = kStageRows * kMaxW + 4; // + padding: a 2-word window may start at the last word
 constexpr int kPaySlots = 128;                      // outlier payloads of a wave's 16 rows kept in LDS
-constexpr int kSideWords = kStageWords + 3 * kStageRows + 2 * kPaySlots + 4;  // one side (K or V) of one wave
+constexpr int kSideWords = kStageWords + 3 * kStageRows + 2 * kPaySlots;  // one side (K or V) of one wave
 constexpr float kNegBig = -1.0e30f;                 // "no row seen yet" (finite, so differences stay finite)
 constexpr int kRedStride = 2 + 128;                 // one partial state: maximum, sum, 128 weighted values
 constexpr int kAttendTargetBlocks = 512;            // two resident workgroups per compute unit
@@ -80,7 +80,7 @@ __device__ __forceinline__ void load_tile(TileRegs<kNc> &t, const AttendSide &s,
 }
 
 // LDS image of one side: code words [16 rows][row_words] | room for reads past the last | flag words [16] | scales [16] |
-// offsets [16] | payload window [128] x 8 bytes | one slot more, read and not used
+// offsets [16] | payload window [128] x 8 bytes; k_attend_joint reads a slot past it, of what follows, and does not use it
 template <int kNc>
 __device__ __forceinline__ void stage_tile(TileRegs<kNc> &t, uint32_t *stage, int nrows, int lane)
 {
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void k_attend_partial(Geometry g, A
 // first's, twice per tile, 38.6 and 23.4.  Parts left out, 8 x 32768 x 128: no loads after the first tile 28, no
 // reconstruction 16, neither 9, of which the set-up 3.4, the tables 0.7 and the partial sums 1.6.
 // grid = (n_splits, B*H), block = 512.
-// dynamic LDS: max(lut [48] uint2 | table K [13 S][4] f32 | table V | staging [8 waves][K, V][kSideWords] u32,
+// dynamic LDS: max(lut [48] uint2 | table K [13 S][4] f32 | table V | staging [8 waves][K, V][kSideWords] u32 | 2 u32,
 //                  merge buffer [8 waves][G][130] f32)
 // ---------------------------------------------------------------------------------------
 constexpr int kJointWaves = 8;
@@ -1147,7 +1147,7 @@ static size_t joint_lds_bytes(const Geometry &g, int G, int *table_floats)
     const int tf = 13 * g.S * 4;
     if (table_floats)
         *table_floats = tf;
-    const size_t loop = (2 * 48 + 2 * (size_t)tf + (size_t)kJointWaves * 2 * kSideWords) * sizeof(float);
+    const size_t loop = (2 * 48 + 2 * (size_t)tf + (size_t)kJointWaves * 2 * kSideWords + 2) * sizeof(float);  // + the slot past the last
     const size_t merge = (size_t)kJointWaves * G * kRedStride * sizeof(float);
     return loop > merge ? loop : merge;
 }

@@ -212,6 +212,19 @@ def test_encode_decode_reject_bad_arguments_without_touching_the_gpu(lib):
     assert lib.hqmq_last_hip_error() == 0
 
 
+@pytest.mark.parametrize("D", [64, 96, 128])
+def test_largest_codebook_of_the_table_form(lib, D):
+    """The form with tables holds up to 286 secondaries, and its workspace half the splits of the other form's: callers have
+    allocated for either."""
+    def size(S, flags=0):
+        p = hq.HqmqParams(B=1, H=8, T=32768, D=D, stride_b=8 * 32768 * D, stride_h=32768 * D, stride_t=D, S=S, b_r=6, C=3.0, flags=flags)
+        return hq.hqmq_attend_workspace_bytes(p, 32)
+
+    for flags in (0, hq.HQMQ_FLAG_ATTEND_TABLES):
+        assert size(286, flags) == size(256, flags) == size(16, flags)
+        assert size(287, flags) == 2 * size(286, flags)
+
+
 def test_build_codebooks_matches_the_oracles_generator(lib):
     for seed in (0, 1, 7, 42, 1337):
         mine = hq.hqmq_build_codebooks(seed, 3, 4, 48).numpy()

@@ -325,10 +325,11 @@ def test_attend_windows_larger_than_the_lds_slots():
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129])
-@pytest.mark.parametrize("D,S,T", [(128, 256, 37), (96, 85, 16), (64, 24, 145)])
+@pytest.mark.parametrize("D,S,T", [(128, 256, 37), (96, 85, 16), (64, 24, 145), (128, 286, 145)])
 def test_attend_window_sizes(D, S, T, n):
     """Outlier windows of 16 rows at the edges of what a wave holds (a lane's entry, 64; the slots, 128), among them the last
-    chunks of the window and of a row; other rows of the tile without outliers, the last tile of 5, 16 or 1 rows."""
+    chunks of the window and of a row; other rows of the tile without outliers, the last tile of 5, 16 or 1 rows; the largest
+    codebook whose tables fit."""
     B, H, Hq, b_r = 1, 2, 6, 4
     gen = torch.Generator().manual_seed(100 * n + D)
     nc = D // 4
