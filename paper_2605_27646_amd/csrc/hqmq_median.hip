@@ -425,6 +425,10 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
 // A workgroup's sample: pieces of 8 chunks (64 bytes) of 128 rows per step, so that chunks of one row, which are alike
 // where the rows differ in scale, are few among it; every row's piece follows the one before, turned once more per round,
 // at an odd stride of rows, so that structures of a power-of-two period in either direction do not alias with the sample.
+// The parts of a head take the sampled rows in turn, and the turn goes round (each part once first, with one more step per
+// round): a part that took every eighth would see two of a period's 16 rows only, and its ends, 1/8 of the average, moved the
+// range past the median of heads with one row of 16 ten times smaller (select of two tensors with 8 such heads of 32768 rows 140
+// us, 60 so).
 // The range ends at the sample's ranks four standard deviations of a binomial count (sqrt(n) / 2 each) below and above its
 // middle one, for n chunks of all parts, whose ends are averaged: the whole head's median falls outside it about once in
 // 16000 heads of independent chunks.
@@ -468,7 +472,10 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
         const uint32_t pieces = (uint32_t)(g.n_c + kPieceChunks - 1) / kPieceChunks;
         const uint32_t inverse = ((1u << 20) + pieces - 1u) / pieces;  // i / pieces = i * inverse >> 20 for i below 2^12
         static_assert(kPieceRows * kSteps * 2 + kMaxParts < 1 << 12, "j + part + j / pieces");
-        uint32_t j = tid / kPieceChunks, r = (j * parts + part) * stride;
+        static_assert(kPieceRows % (kMaxParts * kMaxParts) == 0, "the turn of a thread's rows is the same in every step");
+        uint32_t j = tid / kPieceChunks;
+        const uint32_t turn = (part + j + (j >> (__ffs((int)parts) - 1))) & (parts - 1u);
+        uint32_t r = (j * parts + turn) * stride;
         const uint32_t more = kPieceRows * parts * stride;
         const _Float16 *row = tn.x + (int64_t)h * g.sh;
         RowWalk walk(g, r, more);
