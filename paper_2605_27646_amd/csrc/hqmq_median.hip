@@ -276,15 +276,21 @@ __device__ __forceinline__ double threshold_of(unsigned long long median_bits, f
 // per chunk and 32 rows per step, all requested before the first is used.  A histogram of the squared norms in fp32 (exact
 // squares, three rounded additions: within 3 * 2^-24 of the fp64 sum), exponent and 9 mantissa bits; the fp64 median lies in
 // the bin that holds the rank, or within that error of its ends, and what is below the bin by more than twice the error is
-// below the median: only the chunks in and 8 units around the bin (some 25 of 32768 smooth ones) get an fp64 norm, and one
-// wave ranks them by counting.  More of them (values that repeat): select_rank among them.
+// below the median: only the chunks in and 8 units around the bin (some 25 of 32768 smooth ones) get an fp64 norm, and a
+// thread for each ranks them by counting.  More than 256 (values that repeat or lie close together): all norms in fp64, in
+// registers, and select_rank between the least and the most of them.  Select of 8 tensors with 8 such heads of 1024 rows, in us,
+// all norms in fp64 / fp32 and select_rank over the bin with norms taken again in each round / so: multiples of 1 48 / 59 / 39, of
+// 1/4 25 / 33 / 26, constant 154 / 162 / 51, chunks of one norm 33 / 54 / 43.
 // Bound by that compute unit's loads and latency: 12 us for 1024 rows, 6.4 for 256 and fewer; with every norm in fp64, a
 // second histogram, addresses multiplied out per step and scans through LDS 17 and 8.7.
 // grid = (H, 1, tensors), 1024 threads.
 // ---------------------------------------------------------------------------------------
 constexpr int kHeadBits = 9, kHeadShift = 23 - kHeadBits;
-constexpr uint32_t kHeadBase = (79u << kHeadBits) - 1u;  // fp32 exponents 79 (2^-48) to 162; bin 0: zero, the last: not finite
+// fp32 exponents 79 (2^-48) to 162; bin 0: zero, the last: not finite.  Even, so that the bins on either side of a power of two,
+// which hold all norms of unit chunks, are counted in two words.
+constexpr uint32_t kHeadBase = (79u << kHeadBits) - 2u;
 constexpr int kHeadBins = 84 << kHeadBits, kHeadWords = kHeadBins / 2;
+constexpr int kHeadFew = 256;        // keys that are ranked by counting
 constexpr uint32_t kHeadSlack = 8u;  // twice the error of a norm in fp32, in units of the last place
 static_assert(kHeadRows * kChunksPerRow < 1 << 16, "two counters share a word");
 
@@ -298,6 +304,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
     static_assert(kHeadWords % kSelectThreads == 0 && kRankBins <= kHeadWords, "bins tile the block; the histograms share memory");
     __shared__ __align__(16) uint32_t hist[kHeadWords];
     __shared__ RankScratch sc;
+    __shared__ unsigned long long few[kHeadFew];
     const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
     const bool active = kFull || c < g.n_c;
     half4_t v[kSteps];
@@ -382,18 +389,19 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
                     at = atomicAdd(&sc.n_few, n);
                 at = (__builtin_amdgcn_readfirstlane((int)at) & 0xffffu) +
                      __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                if (near && at < (uint32_t)kFew)
-                    sc.few[at] = key_of(chunk_norm2(v[u]));
+                if (near && at < (uint32_t)kHeadFew)
+                    few[at] = key_of(chunk_norm2(v[u]));
             }
         }
         __syncthreads();
         const uint32_t count = sc.n_few & 0xffffu, left = rank - (below_bin - (sc.n_few >> 16));
-        if (count <= (uint32_t)kFew) {
+        if (count <= (uint32_t)kHeadFew) {
             if ((uint32_t)tid < count) {
-                const unsigned long long mine = sc.few[tid];
+                const unsigned long long mine = few[tid];
                 uint32_t less = 0;
+#pragma unroll 4
                 for (uint32_t j = 0; j < count; ++j) {
-                    const unsigned long long other = sc.few[j];
+                    const unsigned long long other = few[j];
                     less += other < mine || (other == mine && j < (uint32_t)tid) ? 1u : 0u;
                 }
                 if (less == left)
@@ -402,16 +410,36 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
             __syncthreads();
             median = sc.result;
         } else {
-            __syncthreads();  // select_rank clears the count that every thread has to read before
+            // values that repeat: between the ends of what is there, a single value at once
+            unsigned long long wide[kSteps], least_inverse = 0ull, most = 0ull;
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u) {
+                const bool near = key[u] - f_lo <= f_span;
+                const unsigned long long k = key_of(chunk_norm2(v[u]));
+                wide[u] = near ? k : ~0ull;  // outside every range of keys
+                least_inverse = umax64(least_inverse, ~wide[u]);
+                most = umax64(most, near ? k : 0ull);
+            }
+            least_inverse = wave_umax64(least_inverse);
+            most = wave_umax64(most);
+            __syncthreads();  // every thread has read the count, which select_rank clears
+            if (lane == 0) {
+                few[2 * wv] = least_inverse;
+                few[2 * wv + 1] = most;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kW; ++k) {
+                least_inverse = umax64(least_inverse, few[2 * k]);
+                most = umax64(most, few[2 * k + 1]);
+            }
             median = select_rank(
                 [&](auto f) {
 #pragma unroll
                     for (int u = 0; u < kSteps; ++u)
-                        if (key[u] - f_lo <= f_span)
-                            f(key_of(chunk_norm2(v[u])));
+                        f(wide[u]);
                 },
-                key_of((double)__uint_as_float(f_lo - kHeadSlack)), key_of((double)__uint_as_float(f_lo + f_span + kHeadSlack)),
-                left, hist, sc);
+                ~least_inverse, most, left, hist, sc);
         }
     }
     if (tid == 0)
