@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2605_27646_amd as hq
 
-NEAR_TIE = 1e-6          # score gap below which two codewords count as tied (spec rule)
+NEAR_TIE = 1e-6          # score gap below which two codewords count as tied
 RECON_TOL = 1e-3         # max-abs reconstruction error relative to the chunk norm
 
 
