@@ -826,6 +826,33 @@ def test_time_of_the_select_of_periodic_rows(T, period):
     assert times[1] < 1.5 * times[0]
 
 
+@pytest.mark.parametrize("n,B,H,T,D,S,most", [(16, 4, 8, 35, 64, 384, 1.32), (8, 1, 64, 25, 64, 512, 1.75), (32, 1, 8, 10, 96, 512, 1.45)])
+def test_time_of_encoding_short_segments_of_large_codebooks(n, B, H, T, D, S, most):
+    """Short segments whose workgroups copy up to 72 KB of operands: a call with the select and the general search against one
+    with known thresholds, whose workgroups have 64 rows (1.14, 1.34 and 1.21 times as long measured; 1.49, 2.26 and 1.71 with
+    as few rows per workgroup as the number of workgroups allows)."""
+    xs = [_lognormal_tensor(B, H, T, seed=i, D=D).to(DEV) for i in range(n)]
+    secs = [_sec(i, H, S)[0].to(DEV) for i in range(n)]
+    params = hq.params_for(xs[0], S)
+    encs = [hq.alloc_encoded(params, DEV) for _ in range(n)]
+    batch = hq.EncodeBatch(params, xs, secs, encs, hq.alloc_batch_workspace(params, n, DEV))
+    thrs = hq.ThresholdBatch(batch, [torch.full((H,), 100.0, dtype=torch.float64, device=DEV)] * n)
+    times = []
+    for call in (lambda: hq.hqmq_encode_batch(batch), lambda: hq.hqmq_encode_batch_given_thresholds(batch, thrs)):
+        best = float("inf")
+        for _ in range(10):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 10)
+        times.append(best)
+    print(f"{1e3 * times[0]:.1f} us, thresholds known {1e3 * times[1]:.1f} us", flush=True)
+    assert times[0] < most * times[1]
+
+
 def _encode_ms(x, sec):
     """Shortest of several encodes of a device tensor, in ms."""
     params = hq.params_for(x, sec.shape[1])
