@@ -177,22 +177,25 @@ static int screen_rows(const Geometry &g, int n)
     if (large)
         return kSearchRowsLarge;
     // Few workgroups: down to 8 rows each, while a launch then has at most 2048, two waves still get a pass of 64 chunks, and by
-    // this estimate (ns) the search gains: the passes of a workgroup's busiest wave, for every round of workgroups and, as those of
-    // a compute unit share its SIMDs, for every one of them; with operands to copy, times the rows that there is room for, as a
-    // nearly empty last workgroup takes a good part of a full one's time.  Fitted to whole encodes of 2000 shapes (S = 1 to 512, D =
-    // 4 to 128) with 64, 32, 16 and 8 rows.  Of 1500 others 3 are more than 8 % slower than with 64 rows, where by the counts alone
-    // 64 were (up to 62 %: they copy 70 KB of operands for 8 rows, in several rounds, and split 10 rows in two); of 300 with more than
-    // 512 secondaries 2, were 14.  64 / 32 / 16 / 8 rows in us (by the counts, so): 8 heads of 128 elements, S = 16, T = 1024 38
-    // / 31 / 28 / 28 (8, 8); S = 256, T = 256 64 / 42 / 31 / 25 (8, 8); 512 heads of 64, S = 384, T = 35 51 / 75 / 66 / 86 (16, 64);
-    // 256 of 96, S = 512, T = 10 31 / 31 / 30 / 42 (8, 16); 128 of 90, S = 512, T = 127 89 / 73 / 90 / 97 (8, 32).
+    // this estimate the search gains: the passes of a workgroup's busiest wave, for every round of workgroups and, as those of a
+    // compute unit share its SIMDs, for every one of them.  In ns with operands to copy, and then times the rows that there is room
+    // for, as a nearly empty last workgroup takes a good part of a full one's time; in passes beyond 512 secondaries.  Fitted to
+    // whole encodes of 2000 shapes (S = 1 to 512, D = 4 to 128) with 64, 32, 16 and 8 rows.  Of 1500 others 3 are more than 8 %
+    // slower than with 64 rows, where by the counts alone 64 were (up to 62 %: they copy 70 KB of operands for 8 rows, in several
+    // rounds, and split 10 rows in two); of 300 with more than 512 secondaries 3, were 14.  64 / 32 / 16 / 8 rows in us (by the
+    // counts, so): 8 heads of 128 elements, S = 16, T = 1024 38 / 31 / 28 / 28 (8, 8); S = 256, T = 256 64 / 42 / 31 / 25 (8, 8);
+    // 512 heads of 64, S = 384, T = 35 51 / 75 / 66 / 86 (16, 64); 256 of 96, S = 512, T = 10 31 / 31 / 30 / 42 (8, 16); 128 of 90,
+    // S = 512, T = 127 89 / 73 / 90 / 97 (8, 32).
     const auto estimate = [&](int rows) {
         const int64_t per_seg = (g.T + rows - 1) / rows, wgs = (int64_t)n * g.B * g.H * per_seg;
         const int chunks = (g.T < rows ? g.T : rows) * g.n_c;
         const double passes = (chunks + 64 * kSearchWaves - 1) / (64 * kSearchWaves);
-        const size_t fit = kLdsPerCu / search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, rows);
-        const double per_cu = (double)((wgs + 255) / 256), rounds = std::max(1.0, per_cu / (double)std::min<size_t>(fit, 4));
-        const double ns = rounds * passes * (1460 + 8.9 * g.S) + per_cu * (240 + 5.4 * passes * g.S);
-        return per_seg > 1 && g.A16 > 0 ? ns * (double)(per_seg * rows) / g.T : ns;
+        const size_t lds_fit = kLdsPerCu / search_lds_bytes(g.S16, g.A16, g.D, g.row_words, kSearchWaves, rows);
+        const double fit = (double)std::min<size_t>(lds_fit, g.A16 > 0 ? 4 : 8), per_cu = (double)((wgs + 255) / 256);
+        if (g.A16 == 0)
+            return passes * (std::ceil(per_cu / fit) + 0.25 * per_cu);
+        const double ns = std::max(1.0, per_cu / fit) * passes * (1460 + 8.9 * g.S) + per_cu * (240 + 5.4 * passes * g.S);
+        return per_seg > 1 ? ns * (double)(per_seg * rows) / g.T : ns;
     };
     int rows = kSearchRowsSmall;
     double least = estimate(rows);
