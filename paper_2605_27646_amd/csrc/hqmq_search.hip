@@ -355,7 +355,11 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
         bs = min(first + 2 * bt, g.S - 1);
     }
     // the unclear chunks, one at a time: every lane scores the secondaries lane, lane + 64, ...; the key
-    // orders by score, then by descending s (scores are positive, so their bit patterns order like them)
+    // orders by score, then by descending s (scores are positive, so their bit patterns order like them).
+    // Without a screen they are all of them, two steps of 64 secondaries at a time (the last one over again past the end): with
+    // a bound per lane it was bound by latency, and the same instructions have taken 3 to 9 % longer at another place in the code.
+    // In us, before / now: 40 tensors of 16 x 3 rows of 64, S = 600 138 / 120, S = 2730 456 / 382; two of 8 x 2000 rows of 96, S =
+    // 1024 791 / 766.
     unsigned long long todo = __ballot(unclear);
     while (todo) {  // wave-uniform
         const int src = __ffsll((long long)todo) - 1;
@@ -365,10 +369,18 @@ __device__ __forceinline__ uint32_t search_codeword(const Geometry &g, int lane,
         const float e2 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u2), src));
         const float e3 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(u3), src));
         unsigned long long key = 0ull;
-        for (int s = lane; s < g.S; s += 64) {
+        const auto score = [&](int s) {
             float v0, v1, v2, v3;
             const float sc = score_secondary(secl + 4 * s, e0, e1, e2, e3, v0, v1, v2, v3);
             key = umax64(key, ((unsigned long long)__float_as_uint(sc) << 32) | (0xffffffffu - (uint32_t)s));
+        };
+        if (kScreen) {
+            for (int s = lane; s < g.S; s += 64)
+                score(s);
+        } else {
+#pragma unroll 2
+            for (int s0 = 0; s0 < g.S; s0 += 64)
+                score(min(s0 + lane, g.S - 1));
         }
         key = wave_umax64(key);
         if (lane == src)

@@ -74,6 +74,8 @@ def _lognormal_tensor(B, H, T, seed, sigma_g=0.5, D=128):
     (1, 2, 70, 600, 6),        # past it: every chunk scores all secondaries in fp32
     (2, 1, 20, 2730, 8),       # largest supported S (24 S = 65520) and b_r: 24-bit code words
     (1, 1, 300, 1024, 4),      # power of two above the screen's limit; 256-row workgroups
+    (1, 2, 40, 513, 6),        # steps of 64 secondaries: nine, the last of one
+    (1, 2, 41, 640, 6),        # ten
 ])
 def test_encode_decode_parity_small(B, H, T, S, b_r):
     print(f"case B={B} H={H} T={T} S={S} b_r={b_r}", flush=True)
@@ -241,6 +243,7 @@ def test_other_workloads_full_size(name, layer, role):
     (124, 1, 1, 70, 512, 8),     # the most LDS the general search can ask for
     (96, 1, 2, 40, 700, 6),      # unscreened search at 24 chunks per row
     (64, 1, 1, 30, 2730, 8),     # largest S at 16 chunks per row
+    (96, 1, 2, 23, 577, 6),      # ten steps of 64 secondaries, the last of one
     (64, 1, 2, 4100, 192, 4),    # 256-row workgroups at 16 chunks per row, ragged last workgroup
 ])
 def test_other_head_dimensions_small(D, B, H, T, S, b_r):
