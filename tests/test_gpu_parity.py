@@ -73,7 +73,7 @@ def _lognormal_tensor(B, H, T, seed, sigma_g=0.5, D=128):
     (1, 1, 40, 512, 8),        # largest S that is screened on the matrix cores, largest b_r
     (1, 2, 70, 600, 6),        # past it: every chunk scores all secondaries in fp32
     (2, 1, 20, 2730, 8),       # largest supported S (24 S = 65520) and b_r: 24-bit code words
-    (1, 1, 300, 1024, 4),      # power of two above the screen's limit; 256-row workgroups
+    (1, 1, 300, 1024, 4),      # power of two above the screen's limit
     (1, 2, 40, 513, 6),        # steps of 64 secondaries: nine, the last of one
     (1, 2, 41, 640, 6),        # ten
 ])
@@ -238,7 +238,7 @@ def test_other_workloads_full_size(name, layer, role):
     (100, 2, 2, 90, 33, 5),      # multiple of 4, strides not multiples of 8
     (126, 1, 1, 130, 256, 6),    # 32 chunks like the full row, but through the general path
     (124, 1, 3, 2100, 64, 6),    # 31 chunks; long enough for the 256-row search workgroups
-    (96, 1, 1, 2100, 256, 6),    # long, but the tables leave no room for 256-row workgroups: 8 waves, 64 rows
+    (96, 1, 1, 2100, 256, 6),    # long, but the tables leave no room for 256-row workgroups: 64 rows
     (96, 1, 1, 70, 512, 8),      # largest S and b_r at 24 chunks per row
     (124, 1, 1, 70, 512, 8),     # the most LDS the general search can ask for
     (96, 1, 2, 40, 700, 6),      # unscreened search at 24 chunks per row
