@@ -536,7 +536,7 @@ static int32_t encode_impl(const hqmq_params *params, int32_t n_tensors, const v
             gs.cell_groups = c.groups;
             gs.cell_used = c.used;
             gs.cell_words = (24 * g.S + 31) / 32;
-            gs.cand_room = g.cand_cap - cell_index_keys(c);
+            gs.cand_room = g.cand_cap - cell_index_keys(c, g.H, g.S16, gs.cell_words);
             // the most rows per workgroup (its copy of the index is made once) that leave 512 workgroups
             const auto blocks = [&](int rows) { return (int64_t)n * g.B * g.H * ((g.T + rows - 1) / rows); };
             gs.search_rows = blocks(kSearchRowsHuge) >= 512 ? kSearchRowsHuge : blocks(kSearchRowsLarge) >= 512 ? kSearchRowsLarge : kSearchRowsSmall;

@@ -113,8 +113,30 @@ inline CellShape cell_shape_for(int S)
 // functions and lists lie in the first 64 KiB of LDS: their addresses fit 16 bits
 static_assert(((13 * kScreenMaxS) / 5 + 99 + 1) * 16 + 5120 * 8 < 65536, "16-bit LDS addresses");
 __host__ __device__ inline size_t cell_head_bytes(int n) { return ((size_t)n * n * n * 2 + 15) / 16 * 16; }
-// A head's index in candidate keys: at most 7120 (S = 512) of 32768 and more.
-inline int cell_index_keys(const CellShape &c) { return (int)((cell_head_bytes(c.n) + 15) / 16 * 2) + c.groups; }
+// Where the heads' indexes lie: what they are counted in, and the codewords that their lists name with their functions, in the
+// memory of the matrix screen's operands, which such a search does not use; lists and boxes of each behind its candidate list,
+// and the functions with them where the former has no room (S <= 16).
+struct CellOffsets {  // bytes, of the first head
+    size_t id, function, end;
+};
+__host__ __device__ inline CellOffsets cell_offsets(int H, int words, int used)
+{
+    CellOffsets o;
+    o.id = ((size_t)H * (1 + words) * 4 + 15) / 16 * 16;
+    o.function = o.id + (size_t)H * used * 4;
+    o.end = o.function + (size_t)H * (used + 1) * 16;
+    return o;
+}
+__host__ __device__ inline bool cell_functions_behind_lists(int H, int S16, const CellOffsets &o)
+{
+    return o.end > (size_t)H * S16 * kATiles * 64 * 16;
+}
+// In candidate keys: at most 7120 (S = 512) of 32768 and more.
+inline int cell_index_keys(const CellShape &c, int H, int S16, int words)
+{
+    const int functions = cell_functions_behind_lists(H, S16, cell_offsets(H, words, c.used)) ? 2 * (c.used + 1) : 0;
+    return (int)(cell_head_bytes(c.n) / 16 * 2) + c.groups + functions;
+}
 
 // The rows per workgroup that a workspace is sized for (its arrays of workgroup totals): no launch takes fewer without
 // finding its own place for the totals.  A size that callers have allocated for, so it stays.
@@ -155,8 +177,8 @@ struct Workspace {
     unsigned long long *cand;      // [H][cand_cap]
     uint32_t *block_sum;           // [B*H*n_search_blocks_per_seg] outliers per search workgroup
     uint32_t *block_pre;           // same shape, exclusive prefix
-    uint32_t *cell_state;          // [H][1 + cell_words] counter and used bits of the search's box index; the boxes and
-                                   // lists themselves take the end of the candidate list's memory (cand_room)
+    char *cell_state;              // counters and used bits of the search's box index, its codewords (cell_offsets); the boxes
+                                   // and lists themselves take the end of the candidate list's memory (cand_room)
     uint4 *aop;                    // [H][kATiles * S16][64] MFMA A operands of the search, built once per call
 };
 
@@ -223,7 +245,7 @@ __device__ __forceinline__ Workspace carve_workspace(char *base, const Workspace
     ws.cand = reinterpret_cast<unsigned long long *>(base + o.cand);
     ws.block_sum = reinterpret_cast<uint32_t *>(base + o.block_sum);
     ws.block_pre = reinterpret_cast<uint32_t *>(base + o.block_pre);
-    ws.cell_state = reinterpret_cast<uint32_t *>(base + o.aop);
+    ws.cell_state = base + o.aop;
     ws.aop = reinterpret_cast<uint4 *>(base + o.aop);
     return ws;
 }

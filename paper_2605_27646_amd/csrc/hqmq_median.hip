@@ -210,7 +210,7 @@ __device__ __forceinline__ void reset_head(const Geometry &g, const Workspace &w
         build_operands(g, ws, tn.sec, h, tid, threads);
     else
         for (int i = tid; i < 1 + g.cell_words; i += threads)
-            ws.cell_state[(size_t)h * (1 + g.cell_words) + i] = 0;
+            cell_index_of(g, ws, h).n_groups[i] = 0;  // and the bits behind it
     if (tid == 0) {
         enc.n_outliers[h] = 0;
         if (h == 0) {
@@ -931,25 +931,35 @@ __device__ __forceinline__ void each_key(const Geometry &g, const _Float16 *x, i
 // The head of a workgroup.  Workgroups go to the eight XCDs in turn and there to the 32 compute units in turn: the next head
 // for the next part, and one more after every 256 workgroups, so that neither the first parts of all heads nor the parts of
 // one head share an XCD or a compute unit (64 parts of one head: 187 us for the call's select on half the compute units, 140).
-__device__ __forceinline__ int missed_head(const Geometry &g)
+__device__ __forceinline__ int missed_head(const Geometry &g, uint32_t part)
 {
-    return (int)((blockIdx.x + blockIdx.z + gridDim.x * gridDim.y * blockIdx.z / 256u) % (uint32_t)g.H);
+    return (int)((blockIdx.x + part + gridDim.x * gridDim.y * part / 256u) % (uint32_t)g.H);
 }
-__device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t &first, uint32_t &last)
+__device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t part, uint32_t parts, uint32_t &first, uint32_t &last)
 {
     const uint64_t R = (uint64_t)g.B * g.T;
-    first = (uint32_t)(R * blockIdx.z / gridDim.z);
-    last = (uint32_t)(R * (blockIdx.z + 1) / gridDim.z);
+    first = (uint32_t)(R * part / parts);
+    last = (uint32_t)(R * (part + 1) / parts);
 }
 
-// The histogram.  grid = (H, tensors, missed_parts()).
+// The histogram.  A launch that mostly has nothing to do: the box index that was built beside the sweep is finished in it
+// (kFinishParts first workgroups of every head; 0 without an index).  grid = (H, tensors, finish_parts + missed_parts()).
 template <bool kFull>
-__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, uint32_t finish_parts)
 {
     const EncodeTensor &tn = batch.t[blockIdx.y];
     const Workspace ws = carve_workspace(tn.ws, wo);
     __shared__ uint32_t hist[kBins0];
-    const int h = missed_head(g);
+    static_assert(kFinishThreads == kSelectThreads && kFinishWords <= kBins0, "the same workgroup and memory");
+    if (blockIdx.z < finish_parts) {  // uniform
+        const int h = blockIdx.x;
+        const CellIndex ix = cell_index_of(g, ws, h);
+        finish_cells<kFinishParts>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)blockIdx.z,
+                                   CellPlaces{ix.list, reinterpret_cast<uint2 *>(ix.head), ix.id, ix.function}, hist);
+        return;
+    }
+    const uint32_t part = blockIdx.z - finish_parts;
+    const int h = missed_head(g, part);
     uint32_t bucket, rank_in, n, first, last;
     bool inside;
     const KeptCounts kept(ws, h);
@@ -960,7 +970,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
         hist[i] = 0;
     __syncthreads();
-    part_of_rows(g, first, last);
+    part_of_rows(g, part, gridDim.z - finish_parts, first, last);
     each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) {
         if (look.counts(key))
             atomicAdd(&hist[look.bin_of(key)], 1u);
@@ -995,7 +1005,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
     __shared__ RankScratch sc;
     __shared__ unsigned long long least, most;
     __shared__ uint32_t n_staged, list_at, arrived;
-    const int h = missed_head(g), tid = threadIdx.x;
+    const int h = missed_head(g, blockIdx.z), tid = threadIdx.x;
     uint32_t rank = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
     unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
     const bool selects = blockIdx.z == 0;  // the workgroups that start first
@@ -1051,7 +1061,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
             }
             __syncthreads();
             uint32_t first, last;
-            part_of_rows(g, first, last);
+            part_of_rows(g, blockIdx.z, gridDim.z, first, last);
             unsigned long long my_least = ~0ull, my_most = 0ull;
             auto flush = [&] {  // by the whole workgroup
                 __syncthreads();
@@ -1524,7 +1534,8 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
         else
             hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(sweep * m), dim3(kCountThreads), 0, stream, g, wo, rest, rows, m);
     }
-    hipLaunchKernelGGL(k_select_digit<kFull>, parts, block, 0, stream, g, wo, batch);
+    const uint32_t finish_parts = g.cell_n > 0 ? kFinishParts : 0;
+    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, finish_parts + parts.z), block, 0, stream, g, wo, batch, finish_parts);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }
 

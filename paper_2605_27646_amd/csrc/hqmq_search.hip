@@ -1006,10 +1006,11 @@ hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStre
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32.  Either way the codeword is the best one, or the fp32 search's choice
 // between codewords whose scores differ by no more than its own rounding.
-// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 127 by the index (and 14 beside the
-// select's sweep).  Bound by VALU issue (282 instructions per 64 chunks, 115 of them in the list loop: the longest of
-// 64 lists has 3.4 groups of four on average), LDS busy half of the time.  145 us and 327 instructions with fp64 norms of
-// every chunk, ballots of integers, the fold by all sixteen products and the rows' state stored row by row.
+// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 118 by the index (and 14 beside the
+// select's sweep).  Bound by VALU issue (250 instructions per 64 chunks, 113 of them in the list loop: the longest of
+// 64 lists has 3.3 groups of four on average), LDS busy half of the time.  129 us and 282 instructions with the index finished by
+// every workgroup (finish_cells), 145 and 327 with fp64 norms of every chunk, ballots of integers, the fold by all sixteen products
+// and the rows' state stored row by row.
 // What a codebook costs whose lists do not fit (secondaries close together or equal) stands at the fall-back in cell_codeword.
 // ---------------------------------------------------------------------------------------------------------------
 
@@ -1030,7 +1031,6 @@ constexpr float kCellShrink = 1.0f - 4.0e-6f;  // keeps the box numbers of y = -
 // The search numbers the element P_0 that it folds with by 4 f + 16 for f = p_0 / 4 + p_1 / 2 + p_2 + 2 p_3 in twice its
 // components: odd from 1 to 31 for the half-integer elements, even for the axis elements.  It needs the index of P_0 P_p' in
 // the order of the primaries: [fold][p'], rows of 32 bytes.
-constexpr int kFolds = 33;
 struct FoldTable {
     alignas(16) uint8_t at[kFolds * 32];
 };
@@ -1066,32 +1066,8 @@ __global__ __launch_bounds__(kCellThreads) void k_cells(Geometry g, WorkspaceOff
     const EncodeTensor &tn = batch.t[blockIdx.z];
     build_cells(g, carve_workspace(tn.ws, wo), tn.sec, blockIdx.y, blockIdx.x, lds);
 }
-
 namespace {
 
-// LDS image of a head's index during the search, at the start of the workgroup's LDS.  List entries and box heads are
-// LDS addresses, so that neither takes arithmetic (the first two arrays end below 2^16, checked by the host).
-struct CellTables {
-    uint32_t base;    // address of the codeword functions (c_1, c_2, c_3, c_0) [cell_used + 1]; the last never wins
-    uint32_t list;    // [cell_groups] groups of four addresses of functions, the first two ascending in the last group of a list
-    uint32_t head;    // [n^3] u16 address of the box's first group
-    uint32_t id;      // [cell_used] p' << 16 | s of the codeword
-    uint32_t mul;     // [kFolds][32] u8: FoldTable
-    uint32_t sec;     // [S][4] the head's secondaries
-    uint32_t end;
-};
-__host__ __device__ inline CellTables cell_tables(const Geometry &g, uint32_t base)
-{
-    CellTables t;
-    t.base = base;
-    t.list = t.base + ((uint32_t)g.cell_used + 1u) * 16u;
-    t.head = t.list + (uint32_t)g.cell_groups * 8u;
-    t.id = t.head + (uint32_t)cell_head_bytes(g.cell_n);
-    t.mul = t.id + (uint32_t)g.cell_used * 4u;
-    t.sec = t.mul + (uint32_t)kFolds * 32u;
-    t.end = t.sec + (uint32_t)g.S * 16u;
-    return t;
-}
 template <typename T>
 __device__ __forceinline__ T lds_at(uint32_t address)
 {
@@ -1219,99 +1195,57 @@ __device__ __forceinline__ uint32_t cell_codeword(const Geometry &g, const CellT
     return of_mask(live) ? ((uint32_t)rq << g.w_idx) | (__umul24(p, (uint32_t)g.S) + s) : 0u;
 }
 
-// A head's index from the workspace into LDS: lists (entries k become addresses), boxes, and the functions of the
-// codewords that lists name.  `bits` [2 * cell_words + 1] u32 is scratch.  Ends with a barrier.
+// A head's index from the workspace into LDS, with the folds and the secondaries.  A finished one 16 bytes at a time, all
+// requested before the first is written; else it is finished on the way (bits: scratch).  Ends with a barrier.
 template <int kThreadsS>
-__device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &ws, int h, const float *sec_h,
-                                           const CellTables &ct, uint32_t *bits)
+__device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &ws, int h, const float *sec_h, const CellTables &ct,
+                                           bool finished, uint32_t *bits)
 {
-    const int tid = threadIdx.x, lane = tid & 63;
+    static_assert(kThreadsS == kFinishThreads, "finish_cells");
+    const int tid = threadIdx.x;
+    if (!finished) {  // uniform
+        if (tid < kFolds * 2)
+            lds_ptr<uint4>(ct.mul)[tid] = reinterpret_cast<const uint4 *>(kFoldTable.at)[tid];
+        if (tid < g.S)
+            lds_ptr<uint4>(ct.sec)[tid] = reinterpret_cast<const uint4 *>(sec_h)[tid];
+        // its first barrier comes before it looks at the secondaries
+        finish_cells<1>(g, ws, lds_ptr<float4_t>(ct.sec), h, 0,
+                        CellPlaces{lds_ptr<uint2>(ct.list), lds_ptr<uint2>(ct.head), lds_ptr<uint32_t>(ct.id), lds_ptr<float4_t>(ct.base)}, bits);
+        __syncthreads();
+        return;
+    }
     const CellIndex ix = cell_index_of(g, ws, h);
-    const int nw = g.cell_words, used_cap = g.cell_used;
-    uint32_t *pre = bits + nw;  // [nw], then the number of codewords in use
-    float4_t *table = lds_ptr<float4_t>(ct.base), *secl = lds_ptr<float4_t>(ct.sec);
-    uint2 *list = lds_ptr<uint2>(ct.list);
-    uint32_t *head = lds_ptr<uint32_t>(ct.head), *id = lds_ptr<uint32_t>(ct.id);
-    for (int s = tid; s < g.S; s += kThreadsS)
-        secl[s] = reinterpret_cast<const float4_t *>(sec_h)[s];
-    for (int i = tid; i < kFolds * 32 / 4; i += kThreadsS)
-        lds_ptr<uint32_t>(ct.mul)[i] = reinterpret_cast<const uint32_t *>(kFoldTable.at)[i];
-    if (tid < 64) {  // exclusive prefix of the used bits, nw <= 6 * 64 words
-        uint32_t w[6], sum = 0;
+    constexpr int kMax = 5120 * 8 + 20 * 20 * 20 * 2;  // bytes of the largest lists and boxes
+    constexpr int kLists = (kMax / 16 + kThreadsS - 1) / kThreadsS, kFunctions = 2;
+    static_assert((13 * kScreenMaxS / 5 + 99) / 4 * 4 + 1 <= kFunctions * kThreadsS && kScreenMaxS <= kThreadsS, "loads of a thread");
+    const int n_lists = (int)(ct.id - ct.list) / 16, n_functions = g.cell_used + 1, n_ids = g.cell_used / 4, n_folds = kFolds * 2;
+    uint4 lists[kLists], functions[kFunctions], ids = {}, folds = {}, secondaries = {};
 #pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            const int i = 6 * lane + j;
-            w[j] = i < nw ? ix.used[i] : 0u;
-            sum += __popc(w[j]);
-        }
-        uint32_t inc = sum;
+    for (int u = 0; u < kLists; ++u)
+        lists[u] = reinterpret_cast<const uint4 *>(ix.list)[min(tid + u * kThreadsS, n_lists - 1)];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = __shfl_up(inc, d, 64);
-            if (lane >= d)
-                inc += o;
-        }
-        uint32_t run = inc - sum;
+    for (int u = 0; u < kFunctions; ++u)
+        functions[u] = reinterpret_cast<const uint4 *>(ix.function)[min(tid + u * kThreadsS, n_functions - 1)];
+    if (tid < n_ids)
+        ids = reinterpret_cast<const uint4 *>(ix.id)[tid];
+    if (tid < n_folds)
+        folds = reinterpret_cast<const uint4 *>(kFoldTable.at)[tid];
+    if (tid < g.S)
+        secondaries = reinterpret_cast<const uint4 *>(sec_h)[tid];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            const int i = 6 * lane + j;
-            if (i < nw) {
-                bits[i] = w[j];
-                pre[i] = run;
-            }
-            run += __popc(w[j]);
-        }
-        if (lane == 63)
-            pre[nw] = inc;
-    }
-    __syncthreads();
-    const int n_used = (int)pre[nw];
-    const bool whole = n_used <= used_cap;  // else no box gets a list
-    {
-        const uint2 *src = reinterpret_cast<const uint2 *>(ix.head);
-        const int words = g.cell_n * g.cell_n * g.cell_n / 4;  // n is a multiple of 4
-        auto address = [&](uint32_t group) { return ct.list + 8u * (whole ? min(group, (uint32_t)g.cell_groups - 1u) : 0u); };
-        for (int i = tid; i < words; i += kThreadsS) {
-            const uint2 v = src[i];
-            head[2 * i] = address(v.x & 0xffffu) | (address(v.x >> 16) << 16);
-            head[2 * i + 1] = address(v.y & 0xffffu) | (address(v.y >> 16) << 16);
-        }
-    }
-    const uint32_t S = (uint32_t)g.S, n_code = 24u * S;
-    for (int i = tid; i < nw; i += kThreadsS) {
-        uint32_t left = bits[i], at = pre[i];
-        for (; left; left &= left - 1u, ++at) {
-            const uint32_t k = 32u * (uint32_t)i + (uint32_t)__ffs((int)left) - 1u;
-            const uint32_t p = (uint32_t)((float)k * g.inv_S);  // k / S
-            if (at < (uint32_t)used_cap && k < n_code)
-                id[at] = (p << 16) | (k - p * S);
-        }
-    }
-    const int n_groups = min((int)*ix.n_groups + 1, g.cell_groups);
-    const uint32_t pad = ct.base + 16u * (uint32_t)used_cap;
-    auto address_of = [&](uint32_t k) -> uint32_t {  // a pad, or a group that belongs to no list: the function that never wins
-        if (k >= n_code)
-            return pad;
-        return min(ct.base + 16u * (pre[k >> 5] + (uint32_t)__popc(bits[k >> 5] & ((1u << (k & 31u)) - 1u))), pad);
-    };
-    for (int i = tid; i < n_groups; i += kThreadsS) {
-        const uint2 raw = ix.list[i];
-        const uint32_t a = address_of(raw.x & 0x7fffu), b = address_of(raw.x >> 16);
-        const uint32_t low = min(a, b), high = max(a, b);  // equal: pads
-        list[i] = make_uint2(raw.x & 0x8000u ? low | (high << 16) : high | (low << 16),
-                             address_of(raw.y & 0xffffu) | (address_of(raw.y >> 16) << 16));
-    }
-    __syncthreads();
-    for (int i = tid; i <= used_cap; i += kThreadsS) {
-        float4_t f = {0.f, 0.f, 0.f, -1.0e30f};
-        if (i < n_used && i < used_cap) {
-            const uint32_t v = id[i];
-            f = codeword_function((int)(v >> 16), secl[v & 0xffffu]);
-        }
-        table[i] = f;
-    }
-    if (n_used == 0 && tid == 0)
-        id[0] = 0;  // what a chunk without a list reads before the fp32 search
+    for (int u = 0; u < kLists; ++u)
+        if (tid + u * kThreadsS < n_lists)
+            lds_ptr<uint4>(ct.list)[tid + u * kThreadsS] = lists[u];
+#pragma unroll
+    for (int u = 0; u < kFunctions; ++u)
+        if (tid + u * kThreadsS < n_functions)
+            lds_ptr<uint4>(ct.base)[tid + u * kThreadsS] = functions[u];
+    if (tid < n_ids)
+        lds_ptr<uint4>(ct.id)[tid] = ids;
+    if (tid < n_folds)
+        lds_ptr<uint4>(ct.mul)[tid] = folds;
+    if (tid < g.S)
+        lds_ptr<uint4>(ct.sec)[tid] = secondaries;
     __syncthreads();
 }
 
@@ -1323,14 +1257,13 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
 // kFull: rows of 128 elements.
 // Dynamic LDS: cell_lds_bytes().
 template <int kRows, int kSlot, bool kFull>
-__global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch)
+__global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int cells_finished)
 {
     constexpr int kWaves = 16;
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
-    extern __shared__ float4_t cell_smem[];
-    const CellTables ct = cell_tables(g, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float4_t *)cell_smem);
+    const CellTables ct = cell_tables(g);
     uint2 *state = lds_ptr<uint2>(ct.end);                           // of a row: flag word, scale
     uint32_t *pack = reinterpret_cast<uint32_t *>(state + kRows);
 
@@ -1338,7 +1271,7 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seg = blockIdx.y, b = seg / g.H, h = seg % g.H;
     const int t0 = blockIdx.x * kRows;
-    load_cells<64 * kWaves>(g, ws, h, tn.sec + (size_t)h * g.S * 4, ct, reinterpret_cast<uint32_t *>(state));  // scratch
+    load_cells<64 * kWaves>(g, ws, h, tn.sec + (size_t)h * g.S * 4, ct, cells_finished != 0, reinterpret_cast<uint32_t *>(state));  // scratch
 
     const double thr = ws.thr[h];
     // a squared norm in fp32 differs from the fp64 one by at most 3 * 2^-24 of it: outside these it decides
@@ -1483,6 +1416,11 @@ hipError_t prepare_search_kernels()
     for (const void *f : variants)
         if (err == hipSuccess)
             err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsPerCu);
+    hipFuncAttributes cells;  // the index in the workspace holds LDS addresses from 0 on
+    if (err == hipSuccess)
+        err = hipFuncGetAttributes(&cells, variants[4]);
+    if (err == hipSuccess && cells.sharedSizeBytes != 0)
+        err = hipErrorInvalidConfiguration;
     return err;
 }
 
@@ -1501,6 +1439,7 @@ hipError_t launch_search_fused(const Geometry &g, const WorkspaceOffsets &wo, co
     return hipGetLastError();
 }
 
+// cells_built: the select's launches have built and finished the box index.
 hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const EncodeBatch &batch, int n_tensors,
                          bool cells_built, hipStream_t stream)
 {
@@ -1514,13 +1453,13 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
 #define HQMQ_LAUNCH_CELLS(R)                                                                                             \
     do {                                                                                                             \
         if (full_rows)                                                                                               \
-            hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch);    \
+            hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \
         else if (g.n_c > 21)                                                                                         \
-            hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);   \
+            hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
         else if (g.n_c <= 16 && g.n_c > 12)                                                                          \
-            hipLaunchKernelGGL((k_search_cells<R, 16, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);   \
+            hipLaunchKernelGGL((k_search_cells<R, 16, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
         else                                                                                                         \
-            hipLaunchKernelGGL((k_search_cells<R, 0, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch);    \
+            hipLaunchKernelGGL((k_search_cells<R, 0, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \
     } while (0)
         if (g.search_rows == kSearchRowsHuge)
             HQMQ_LAUNCH_CELLS(kSearchRowsHuge);

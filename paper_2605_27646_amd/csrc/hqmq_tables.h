@@ -212,21 +212,54 @@ __device__ __forceinline__ bool meets_octahedron(float m1, float m2, float m3, f
     return (fmaxf(fabsf(m1) - h, 0.f) + fmaxf(fabsf(m2) - h, 0.f)) + fmaxf(fabsf(m3) - h, 0.f) <= 1.0001f;
 }
 
-struct CellIndex {        // parts of one head's index in the workspace
-    uint16_t *head;       // [n^3] first group of the box's list; 0 = no list
+struct CellIndex {        // parts of one head's index in the workspace; finish_cells turns lists and boxes into LDS addresses
     uint2 *list;          // [cell_groups] groups of four 16-bit entries k = p S + s; group 0 belongs to no list
+    uint16_t *head;       // [n^3] first group of the box's list; 0 = no list; behind the lists, as in LDS
     uint32_t *n_groups;   // groups handed out beyond group 0
     uint32_t *used;       // [cell_words] bit k: codeword k is in some list
+    uint32_t *id;         // [cell_used] p << 16 | s of the codewords in use, ascending
+    float4_t *function;   // [cell_used + 1] their functions
 };
 __device__ __forceinline__ CellIndex cell_index_of(const Geometry &g, const Workspace &ws, int h)
 {
     CellIndex ix;
     char *base = reinterpret_cast<char *>(ws.cand + (size_t)h * g.cand_cap + g.cand_room);
-    ix.head = reinterpret_cast<uint16_t *>(base);
-    ix.list = reinterpret_cast<uint2 *>(base + cell_head_bytes(g.cell_n));
-    ix.n_groups = ws.cell_state + (size_t)h * (1 + g.cell_words);
+    ix.list = reinterpret_cast<uint2 *>(base);
+    ix.head = reinterpret_cast<uint16_t *>(ix.list + g.cell_groups);
+    const CellOffsets at = cell_offsets(g.H, g.cell_words, g.cell_used);
+    ix.n_groups = reinterpret_cast<uint32_t *>(ws.cell_state) + (size_t)h * (1 + g.cell_words);
     ix.used = ix.n_groups + 1;
+    ix.id = reinterpret_cast<uint32_t *>(ws.cell_state + at.id) + (size_t)h * g.cell_used;
+    ix.function = cell_functions_behind_lists(g.H, g.S16, at)
+                      ? reinterpret_cast<float4_t *>(reinterpret_cast<char *>(ix.head) + cell_head_bytes(g.cell_n))
+                      : reinterpret_cast<float4_t *>(ws.cell_state + at.function) + (size_t)h * (g.cell_used + 1);
     return ix;
+}
+
+// LDS image of a head's index during the search, at the start of the workgroup's LDS (address 0: the kernel has no static LDS,
+// checked by the host).  List entries and box heads are LDS addresses, so that neither takes arithmetic (the first two arrays
+// end below 2^16, checked by the host).
+struct CellTables {
+    uint32_t base;    // address of the codeword functions (c_1, c_2, c_3, c_0) [cell_used + 1]; the last never wins
+    uint32_t list;    // [cell_groups] groups of four addresses of functions, the first two ascending in the last group of a list
+    uint32_t head;    // [n^3] u16 address of the box's first group
+    uint32_t id;      // [cell_used] p' << 16 | s of the codeword
+    uint32_t mul;     // [kFolds][32] u8: FoldTable
+    uint32_t sec;     // [S][4] the head's secondaries
+    uint32_t end;
+};
+constexpr int kFolds = 33;
+__host__ __device__ inline CellTables cell_tables(const Geometry &g)
+{
+    CellTables t;
+    t.base = 0;
+    t.list = t.base + ((uint32_t)g.cell_used + 1u) * 16u;
+    t.head = t.list + (uint32_t)g.cell_groups * 8u;
+    t.id = t.head + (uint32_t)cell_head_bytes(g.cell_n);
+    t.mul = t.id + (uint32_t)g.cell_used * 4u;
+    t.sec = t.mul + (uint32_t)kFolds * 32u;
+    t.end = t.sec + (uint32_t)g.S * 16u;
+    return t;
 }
 
 }  // namespace
@@ -534,6 +567,109 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
     for (int j = tid; j < nc; j += kCellThreads)
         if ((lds.cused[j >> 5] >> (j & 31)) & 1u)
             atomicOr(&ix.used[lds.ck[j] >> 5], 1u << (lds.ck[j] & 31));
+}
+
+// The built index in the form that the search reads from LDS: entries k become addresses, and the functions of the codewords that
+// lists name are tabulated.  Where the select follows the build, its launches have room for that (kFinishParts workgroups of 1024
+// threads per head, in place): done by each of the search's workgroups for itself it was 500 of a wave's 4500 instructions for 512
+// rows, and more than the search for 64.  A launch of its own for it takes what it saves (32 tensors of 8 heads of 1024 rows, S =
+// 256, known thresholds: 262 us, 246 without), so without a select each workgroup does it into its LDS.
+// bits: LDS, scratch.
+constexpr int kFinishThreads = 1024, kFinishParts = 4;
+constexpr int kFinishWords = 2 * (24 * kScreenMaxS / 32) + 1;  // of LDS
+struct CellPlaces {
+    uint2 *list;
+    uint2 *head;
+    uint32_t *id;
+    float4_t *function;
+};
+template <int kParts>
+__device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace &ws, const float4_t *sec_h, int h, int part,
+                                             const CellPlaces to, uint32_t *bits)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const CellIndex ix = cell_index_of(g, ws, h);
+    const CellTables ct = cell_tables(g);
+    const int nw = g.cell_words, used_cap = g.cell_used;
+    uint32_t *pre = bits + nw;  // [nw], then the number of codewords in use
+    if (tid < 64) {  // exclusive prefix of the used bits, nw <= 6 * 64 words
+        uint32_t w[6], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int i = 6 * lane + j;
+            w[j] = i < nw ? ix.used[i] : 0u;
+            sum += __popc(w[j]);
+        }
+        const uint32_t inc = wave_scan(sum);
+        uint32_t run = inc - sum;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int i = 6 * lane + j;
+            if (i < nw) {
+                bits[i] = w[j];
+                pre[i] = run;
+            }
+            run += __popc(w[j]);
+        }
+        if (lane == 63)
+            pre[nw] = inc;
+    }
+    const int first = part * kFinishThreads + tid;
+    constexpr int kStep = kParts * kFinishThreads;
+    __syncthreads();
+    const int n_used = (int)pre[nw];
+    const bool whole = n_used <= used_cap;  // else no box gets a list
+    {
+        const uint2 *head = reinterpret_cast<const uint2 *>(ix.head);
+        const int words = g.cell_n * g.cell_n * g.cell_n / 4;  // n is a multiple of 4
+        auto address = [&](uint32_t group) { return ct.list + 8u * (whole ? min(group, (uint32_t)g.cell_groups - 1u) : 0u); };
+        for (int i = first; i < words; i += kStep) {
+            const uint2 v = head[i];
+            to.head[i] = make_uint2(address(v.x & 0xffffu) | (address(v.x >> 16) << 16), address(v.y & 0xffffu) | (address(v.y >> 16) << 16));
+        }
+    }
+    const uint32_t S = (uint32_t)g.S, n_code = 24u * S;
+    auto place_of = [&](uint32_t k) { return pre[k >> 5] + (uint32_t)__popc(bits[k >> 5] & ((1u << (k & 31u)) - 1u)); };
+    const int n_groups = min((int)*ix.n_groups + 1, g.cell_groups);
+    const uint32_t pad = ct.base + 16u * (uint32_t)used_cap;
+    auto address_of = [&](uint32_t k) {  // a pad, or a group that belongs to no list: the function that never wins
+        return k < n_code ? min(ct.base + 16u * place_of(k), pad) : pad;
+    };
+    for (int i = first; i < n_groups; i += kStep) {
+        const uint2 raw = ix.list[i];
+        const uint32_t a = address_of(raw.x & 0x7fffu), b = address_of(raw.x >> 16);
+        const uint32_t low = min(a, b), high = max(a, b);  // equal: pads
+        to.list[i] = make_uint2(raw.x & 0x8000u ? low | (high << 16) : high | (low << 16),
+                                address_of(raw.y & 0xffffu) | (address_of(raw.y >> 16) << 16));
+    }
+    const int n_functions = min(n_used, used_cap);
+    if (kParts > 1) {
+        for (uint32_t k = (uint32_t)first; k < n_code; k += kStep) {
+            if ((bits[k >> 5] >> (k & 31u)) & 1u) {
+                const uint32_t at = place_of(k), p = (uint32_t)((float)k * g.inv_S), s = k - p * S;  // k / S
+                if (at < (uint32_t)used_cap) {
+                    to.id[at] = (p << 16) | s;
+                    to.function[at] = codeword_function((int)p, sec_h[s]);
+                }
+            }
+        }
+    } else {  // a tenth of the codewords is in use: one step for their functions where a thread per codeword would take six
+        for (int i = tid; i < nw; i += kFinishThreads) {
+            uint32_t left = bits[i], at = pre[i];
+            for (; left; left &= left - 1u, ++at) {
+                const uint32_t k = 32u * (uint32_t)i + (uint32_t)__ffs((int)left) - 1u, p = (uint32_t)((float)k * g.inv_S);
+                if (at < (uint32_t)used_cap && k < n_code)
+                    to.id[at] = (p << 16) | (k - p * S);
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < n_functions; i += kFinishThreads)
+            to.function[i] = codeword_function((int)(to.id[i] >> 16), sec_h[to.id[i] & 0xffffu]);
+    }
+    for (int i = n_functions + first; i <= used_cap; i += kStep)
+        to.function[i] = float4_t{0.f, 0.f, 0.f, -1.0e30f};
+    if (n_used == 0 && first == 0)
+        to.id[0] = 0;  // what a chunk without a list reads before the fp32 search
 }
 
 }  // namespace hqmq

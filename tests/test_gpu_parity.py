@@ -1054,6 +1054,29 @@ def test_box_index_built_beside_the_select(kind, D, B, T, S):
     assert np.array_equal(thr.cpu().numpy().view(np.uint64), ((c * c) * e.m2).view(np.uint64))
 
 
+@pytest.mark.parametrize("S,D,kind", [(1, 128, "random"), (16, 128, "random"), (17, 96, "random"), (256, 128, "twice"), (512, 124, "random")])
+def test_box_index_finished_by_the_select_or_by_the_search(S, D, kind):
+    """Behind a select the index is finished once per head, with known thresholds by each workgroup of the search: the same
+    bytes.  Codebooks whose functions lie behind the lists (up to 16 secondaries) and in the operands' memory."""
+    H, T = 3, -(-(3 << 21) // ((S + 32) * ((D + 3) // 4))) + 5
+    x = _lognormal_tensor(1, H, T, seed=S, D=D).to(DEV)
+    sec = torch.from_numpy(_index_codebook(kind, S, H)).to(DEV)
+    params = hq.params_for(x, S)
+    ws = hq.alloc_workspace(params, DEV)
+    first, again = hq.alloc_encoded(params, DEV), hq.alloc_encoded(params, DEV)
+    ws.fill_(0xAB)
+    hq.hqmq_encode(params, x, sec, first, ws)
+    thr = hq.hqmq_thresholds(params, ws)
+    ws.fill_(0x5A)
+    hq.hqmq_encode_given_thresholds(params, x, sec, thr, again, ws)
+    torch.cuda.synchronize()
+    total = int(first.n_outliers[-1])
+    for a, b in ((again.codes, first.codes), (again.flags, first.flags), (again.row_off, first.row_off),
+                 (again.n_outliers, first.n_outliers), (again.sigma.view(torch.int16), first.sigma.view(torch.int16)),
+                 (again.outliers[:total].view(torch.int16), first.outliers[:total].view(torch.int16))):
+        assert torch.equal(a, b)
+
+
 def test_box_index_of_more_heads_than_a_launch_holds():
     """32 tensors of 4100 heads whose index has 125 workgroups each: more threads than one axis of a grid takes.  Every tensor's
     bytes are those of a call of its own.  (50 GB, most of it workspace; the heads share their rows, the tensors their inputs.)"""
