@@ -1006,10 +1006,11 @@ hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStre
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32.  Either way the codeword is the best one, or the fp32 search's choice
 // between codewords whose scores differ by no more than its own rounding.
-// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 118 by the index (and 14 beside the
-// select's sweep).  Bound by VALU issue (250 instructions per 64 chunks, 113 of them in the list loop: the longest of
-// 64 lists has 3.3 groups of four on average), LDS busy half of the time.  129 us and 282 instructions with the index finished by
-// every workgroup (finish_cells), 145 and 327 with fp64 norms of every chunk, ballots of integers, the fold by all sixteen products
+// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 114 by the index (and 14 beside the
+// select's sweep).  Bound by VALU issue (257 instructions per 64 chunks, 113 of them in the list loop: the longest of
+// 64 lists has 3.3 groups of four on average; the VALUs are busy for 97 % of the time), LDS for 61 % of it (list entries read one
+// by one, without the instructions that take them apart: 139 us).  118 us and 262 with the rows of one pass at a time, 129 and 282
+// with the index finished by every workgroup (finish_cells), 145 and 327 with fp64 norms of every chunk, ballots of integers, the fold by all sixteen products
 // and the rows' state stored row by row.
 // What a codebook costs whose lists do not fit (secondaries close together or equal) stands at the fall-back in cell_codeword.
 // ---------------------------------------------------------------------------------------------------------------
@@ -1251,6 +1252,9 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
 
 }  // namespace
 
+// A value that all lanes have, in a scalar register.
+__device__ __forceinline__ float scalar(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
 // 16 waves and kRows rows per workgroup; a wave takes several whole rows at a time, one lane per chunk: kSlot = 32 or 16
 // lanes per row, the lanes past the row's chunks idle (row maxima are then DPP steps), or kSlot = 0 for rows that would
 // leave many idle: 64 / n_c rows next to one another.
@@ -1275,104 +1279,153 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
 
     const double thr = ws.thr[h];
     // a squared norm in fp32 differs from the fp64 one by at most 3 * 2^-24 of it: outside these it decides
-    const float thr_sure = (float)thr * (1.f + 0x1p-21f), thr_perhaps = (float)thr * (1.f - 0x1p-21f);
-    const double Lq = (double)((1 << g.b_r) - 1);
+    const float thr_sure = scalar((float)thr * (1.f + 0x1p-21f)), thr_perhaps = scalar((float)thr * (1.f - 0x1p-21f));
     const int n_c = kFull ? kChunksPerRow : g.n_c, row_words = kFull ? g.w : g.row_words;
     const int slot = kSlot ? kSlot : n_c;
     const int rows_pass = 64 / slot;
-    const int rl = lane / slot, c = lane - rl * slot;  // the lane's row of the pass and chunk of the row
+    const int rl = lane / slot, c = lane - rl * slot;  // the lane's row of a pass and chunk of the row
     const int n_rows = min(kRows, g.T - t0);         // >= 1 by the grid's size
     uint32_t *my_pack = pack + wv * 64;              // rows_pass * row_words <= 64 words: w <= 22 as S <= kScreenMaxS
-    const _Float16 *rows = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * rows_pass) * g.st;
-    const int64_t row_step = (int64_t)(kWaves * rows_pass) * g.st;
-    const uint32_t own_chunk = 2u * (uint32_t)rl * (uint32_t)g.st + 8u * (uint32_t)c;  // kFull: bytes, below 2^32 (launch_search)
+    // Two passes at a time where there are rows enough for all waves: the steps that every lane of a row takes alike (scale,
+    // its reciprocal, what is kept of a row) are then taken once, the even lanes for the first pass and the odd for the second.
+    constexpr int kPasses = kSlot && kRows * kSlot >= kWaves * 64 * 2 ? 2 : 1;
+    const bool second = kPasses == 2 && of_mask(0xaaaaaaaaaaaaaaaaull);
+    const _Float16 *rows = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * kPasses * rows_pass) * g.st;
+    const int64_t row_step = (int64_t)(kWaves * kPasses * rows_pass) * g.st;
+    // Lanes without a chunk, and rows past the end, load another once more: they are masked where it matters.
+    const bool mine = kFull || (rl < rows_pass && c < n_c);
+    const unsigned long long in_slot = kFull ? ~0ull : ballot(mine);
+    const uint32_t first_chunk = mine ? 8u * (uint32_t)c : 0u;
+    const uint32_t own_chunk = (mine ? 2u * (uint32_t)rl * (uint32_t)g.st : 0u) + first_chunk;  // kSlot: bytes, below 2^32 (launch_search)
     const int64_t row0 = (int64_t)seg * g.T + t0;
-    const float Lf = (float)Lq;
-    for (int r0 = wv * rows_pass; r0 < n_rows; r0 += kWaves * rows_pass, rows += row_step) {  // wave-uniform
-        const int r = r0 + rl;
-        const bool valid = (kFull || (rl < rows_pass && c < n_c)) && r < n_rows;
-        half4_t xv = {0, 0, 0, 0};
-        if (kFull)  // the second row past the end: the first once more
-            xv = load_chunk(reinterpret_cast<const _Float16 *>(reinterpret_cast<const char *>(rows) + (r0 + 1 < n_rows ? own_chunk : 8u * (uint32_t)c)));
-        else if (valid)
-            xv = load_row_chunk<false>(rows + (int64_t)rl * g.st, c, g);
-        const Chunk4 x = {opaque((float)xv[0]), opaque((float)xv[1]), opaque((float)xv[2]), opaque((float)xv[3])};
-        const float r2f = fmaf(x.x3, x.x3, fmaf(x.x2, x.x2, fmaf(x.x1, x.x1, x.x0 * x.x0)));  // squares are exact: three roundings
-        // Predicates of the whole wave are kept as masks: combined on the scalar unit, they cost no vector instruction.
-        unsigned long long flags = ballot(r2f > thr_sure);
-        if (flags != ballot(r2f > thr_perhaps))  // a ten-millionth of the chunks
-            flags = ballot(chunk_norm2(x) > thr);
-        if (!kFull)
-            flags &= ballot(valid);
-        const bool flagged = of_mask(flags);
-        if (g.check_finite) {  // uniform
-            const bool bad = valid && chunk_nonfinite(x);
-            if (ballot(bad) != 0ull && lane == 0)
-                atomicOr(enc.status, HQMQ_STATUS_NONFINITE);
+    auto *pass_codes = (__attribute__((address_space(1))) uint32_t *)(enc.codes + (row0 + wv * kPasses * rows_pass) * row_words);
+    const uint32_t code_step = (uint32_t)(kWaves * kPasses * rows_pass * row_words);
+    const float Lf = scalar((float)((1 << g.b_r) - 1)), surely = scalar(0.5f - (6e-7f * Lf + 1e-6f));
+    // where the lane's code goes in a pass's words: the word's LDS address and, below it, the bit in the word
+    const uint32_t bit = (uint32_t)(rl * row_words * 32 + c * g.w);
+    uint32_t place = ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t *)(my_pack + (bit >> 5)) << 5) | (bit & 31u);
+    // The largest of a row's values, in every lane of the row; of both passes' in their lanes.
+    auto row_max = [&](auto first, auto other) {
+        if (kSlot) {  // after each step the running maxima are uniform over a block twice as large
+            first = fmax(first, dpp_move<0xB1>(first));  // quad_perm [1, 0, 3, 2]
+            if (kPasses == 2) {
+                other = fmax(other, dpp_move<0xB1>(other));
+                first = second ? other : first;
+            }
+            first = fmax(first, dpp_move<0x4E>(first));   // quad_perm [2, 3, 0, 1]
+            first = fmax(first, dpp_move<0x124>(first));  // row_ror 4
+            first = fmax(first, dpp_move<0x128>(first));  // row_ror 8
+            return kSlot == 32 ? max_across_16(first) : first;
         }
+        for (int d = 1; d < n_c; d <<= 1) {
+            const auto o = __shfl(first, lane + d, 64);
+            first = c + d < n_c ? fmax(first, o) : first;
+        }
+        return __shfl(first, lane - c, 64);
+    };
+    // a value of the row in all its lanes
+    auto of_pass = [&](auto v, int p) { return kPasses == 1 ? v : p ? dpp_move<0xF5>(v) : dpp_move<0xA0>(v); };  // quad_perm [1, 1, 3, 3], [0, 0, 2, 2]
+    for (int r0 = wv * kPasses * rows_pass; r0 < n_rows; r0 += kWaves * kPasses * rows_pass, rows += row_step, pass_codes += code_step) {  // wave-uniform
+        Chunk4 x[kPasses];
+        float r2f[kPasses];
+        unsigned long long flags[kPasses];
+        half4_t xv[kPasses];
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int first = r0 + p * rows_pass;  // of the pass's rows
+            const _Float16 *at = first < n_rows ? rows + (int64_t)(p * rows_pass) * g.st : rows;
+            const bool in = kFull ? first + 1 < n_rows : rl < n_rows - first;
+            const _Float16 *own = kSlot ? reinterpret_cast<const _Float16 *>(reinterpret_cast<const char *>(at) + (in ? own_chunk : first_chunk))
+                                        : at + (in && mine ? (int64_t)rl * g.st : 0) + first_chunk / 2;
+            if (kFull || g.vec_ok) {
+                xv[p] = load_chunk(own);
+            } else {
+                xv[p] = half4_t{0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (first_chunk / 2 + e < (uint32_t)g.D)
+                        xv[p][e] = own[e];
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            x[p] = Chunk4{opaque((float)xv[p][0]), opaque((float)xv[p][1]), opaque((float)xv[p][2]), opaque((float)xv[p][3])};
+            r2f[p] = fmaf(x[p].x3, x[p].x3, fmaf(x[p].x2, x[p].x2, fmaf(x[p].x1, x[p].x1, x[p].x0 * x[p].x0)));  // squares are exact: three roundings
+            // Predicates of the whole wave are kept as masks: combined on the scalar unit, they cost no vector instruction.
+            flags[p] = ballot(r2f[p] > thr_sure);
+            if (flags[p] != ballot(r2f[p] > thr_perhaps))  // a ten-millionth of the chunks
+                flags[p] = ballot(chunk_norm2(x[p]) > thr);
+            flags[p] &= in_slot;
+            if (g.check_finite) {  // uniform
+                if (ballot(chunk_nonfinite(x[p])) != 0ull && lane == 0)
+                    atomicOr(enc.status, HQMQ_STATUS_NONFINITE);
+            }
+        }
+        constexpr int kLast = kPasses - 1;
+        auto counts = [&](int p) { return of_mask(in_slot & ~flags[p]); };  // for the scale
         // The row's scale, sigma_of_row_max of the largest r^2: the fp32 maximum is within 3 * 2^-24 of the fp64 one and decides
         // unless its square root lies next to a rounding boundary; then the fp64 maximum is taken as well.
         // r^2 is 0 or at least 2^-48: the fp32 value is zero for a zero chunk only.
-        auto row_max = [&](auto v) {
-            if (kSlot) {  // after each step the running maxima are uniform over a block twice as large, so the mirrors pair the right blocks
-                v = fmax(v, dpp_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
-                v = fmax(v, dpp_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
-                v = fmax(v, dpp_move<0x141>(v));  // row_half_mirror
-                v = fmax(v, dpp_move<0x140>(v));  // row_mirror
-                return kSlot == 32 ? max_across_16(v) : v;
-            }
-            for (int d = 1; d < n_c; d <<= 1) {
-                const auto o = __shfl(v, lane + d, 64);
-                v = c + d < n_c ? fmax(v, o) : v;
-            }
-            return __shfl(v, lane - c, 64);
-        };
-        const float sf = fminf(__builtin_amdgcn_sqrtf(row_max(flagged ? 0.f : r2f)), 65504.f);  // 1 ulp
+        const float sf = fminf(__builtin_amdgcn_sqrtf(row_max(counts(0) ? r2f[0] : 0.f, counts(kLast) ? r2f[kLast] : 0.f)), 65504.f);  // 1 ulp
         uint16_t sigma16 = __builtin_bit_cast(uint16_t, (_Float16)sf);
         const bool unsure_scale = scale_unsure(sf);
         if (ballot(unsure_scale)) {
-            const double exact = row_max(flagged ? 0.0 : chunk_norm2(x));
+            const double exact = row_max(counts(0) ? chunk_norm2(x[0]) : 0.0, counts(kLast) ? chunk_norm2(x[kLast]) : 0.0);
             if (unsure_scale)
                 sigma16 = double_to_half_rne_sat(sqrt(exact));
         }
-        const float r_f = __builtin_amdgcn_sqrtf(r2f);
-        unsigned long long live = ballot(r2f != 0.f) & ~flags;
-        if (!kFull)
-            live &= ballot(valid);
-        // radius_code
-        int rq = 0;
+        // radius codes per unit of norm; a scale of zero gives the code 0
+        const float per_norm = sigma16 != 0 ? Lf * __builtin_amdgcn_rcpf((float)__builtin_bit_cast(_Float16, sigma16)) : 0.f;
+        // what is kept of the rows: lane 0 of a row for the first pass, lane 1 for the second
         {
-            const float q = fminf(r_f * Lf * __builtin_amdgcn_rcpf((float)__builtin_bit_cast(_Float16, sigma16)), Lf);
-            const float whole = rintf(q);
-            rq = sigma16 != 0 ? (int)whole : 0;
-            const unsigned long long unsure = live & ballot(sigma16 != 0) & ballot(fabsf(q - whole) > 0.5f - (6e-7f * Lf + 1e-6f));
-            if (unsure) {
-                if (of_mask(unsure))
-                    rq = radius_code_exact(chunk_norm2(x), sigma16, Lq);
+            const int r = r0 + (second ? rows_pass : 0) + rl;
+            uint32_t word = 0;
+            if (kFull) {
+                const uint32_t low = second ? (uint32_t)flags[kLast] : (uint32_t)flags[0];
+                const uint32_t high = second ? (uint32_t)(flags[kLast] >> 32) : (uint32_t)(flags[0] >> 32);
+                word = lane >= 32 ? high : low;
+            } else {
+                const unsigned long long both = second ? flags[kLast] : flags[0];
+                word = (uint32_t)(both >> ((unsigned)(rl * slot) & 63u)) & (uint32_t)((1ull << n_c) - 1ull);
             }
-        }
-        my_pack[lane] = 0;  // after the previous pass's reads of it: LDS serves a wave in order
-        const uint32_t code = cell_codeword(g, ct, lane, x, live, rq);
-        wave_lds_sync();
-        if (code) {
-            const uint32_t bitpos = (uint32_t)c * g.w;
-            const uint32_t sh = bitpos & 31;
-            uint32_t *d0 = my_pack + rl * row_words + (bitpos >> 5);
-            atomicOr(d0, code << sh);
-            if (sh + g.w > 32)
-                atomicOr(d0 + 1, code >> (32 - sh));
-        }
-        wave_lds_sync();
-        // the pass's rows are neighbours, and so are their code words
-        uint32_t *codes = enc.codes + (row0 + r0) * row_words;
-        if (lane < min(rows_pass, n_rows - r0) * row_words)
-            codes[(uint32_t)lane] = my_pack[lane];
-        if (kFull) {
-            const uint32_t word = of_mask(~0ull << 32) ? (uint32_t)(flags >> 32) : (uint32_t)flags;
-            if (of_mask(r0 + 1 < n_rows ? 1ull | 1ull << 32 : 1ull))
+            if (c < kPasses && (kFull || rl < rows_pass) && r < n_rows)
                 state[r] = make_uint2(word, sigma16);
-        } else if (valid && c == 0) {
-            state[r] = make_uint2((uint32_t)(flags >> ((unsigned)(rl * slot) & 63u)) & (uint32_t)((1ull << n_c) - 1ull), sigma16);
+        }
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int first = r0 + p * rows_pass;
+            if (p > 0 && first >= n_rows)  // uniform
+                break;
+            const unsigned long long live = in_slot & ballot(r2f[p] != 0.f) & ~flags[p];
+            // radius_code
+            int rq;
+            {
+                const float q = fminf(__builtin_amdgcn_sqrtf(r2f[p]) * of_pass(per_norm, p), Lf), whole = rintf(q);
+                rq = (int)whole;
+                const unsigned long long unsure = live & ballot(fabsf(q - whole) > surely);
+                if (unsure) {
+                    const uint16_t own = (uint16_t)of_pass((int)sigma16, p);
+                    if (of_mask(unsure))
+                        rq = radius_code_exact(chunk_norm2(x[p]), own, (double)opaque(Lf));  // not kept in 64 bits for all passes
+                }
+            }
+            asm volatile("" : "+v"(place));  // one register for all passes, not one for its word's address as well
+            my_pack[lane] = 0;  // after the previous pass's reads of it: LDS serves a wave in order
+            const uint32_t code = cell_codeword(g, ct, lane, x[p], live, rq);
+            wave_lds_sync();
+            if (code) {
+                const uint64_t shifted = (uint64_t)code << (place & 63u);
+                uint32_t *d0 = lds_ptr<uint32_t>(place >> 5);
+                atomicOr(d0, (uint32_t)shifted);
+                if (shifted >> 32)
+                    atomicOr(d0 + 1, (uint32_t)(shifted >> 32));
+            }
+            wave_lds_sync();
+            // the pass's rows are neighbours, and so are their code words
+            auto *codes = pass_codes + (uint32_t)(p * rows_pass * row_words);
+            asm volatile("" : "+s"(codes));  // a lane's offset to a scalar base, not an address per lane
+            if (lane < min(rows_pass, n_rows - first) * row_words)
+                codes[(uint32_t)lane] = my_pack[lane];
         }
     }
     __syncthreads();
@@ -1446,7 +1499,7 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
     dim3 grid((g.T + g.search_rows - 1) / g.search_rows, g.B * g.H, (unsigned)n_tensors);
     const bool full = g.D == 4 * kChunksPerRow;
     if (g.cell_n > 0) {
-        const bool full_rows = full && g.st < (1ll << 29);  // 32-bit offsets inside a pass
+        const bool narrow = g.st < (1ll << 29), full_rows = full && narrow;  // 32-bit offsets inside a pass
         if (!cells_built)
             hipLaunchKernelGGL(k_cells, dim3(cell_blocks(g), g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
         const size_t lds_cells = cell_lds_bytes(g);
@@ -1454,9 +1507,9 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
     do {                                                                                                             \
         if (full_rows)                                                                                               \
             hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \
-        else if (g.n_c > 21)                                                                                         \
+        else if (narrow && g.n_c > 21)                                                                                         \
             hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
-        else if (g.n_c <= 16 && g.n_c > 12)                                                                          \
+        else if (narrow && g.n_c <= 16 && g.n_c > 12)                                                                          \
             hipLaunchKernelGGL((k_search_cells<R, 16, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
         else                                                                                                         \
             hipLaunchKernelGGL((k_search_cells<R, 0, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \

@@ -1077,6 +1077,29 @@ def test_box_index_finished_by_the_select_or_by_the_search(S, D, kind):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("D,T", [(128, 8), (100, 10)])
+def test_box_index_search_of_rows_far_apart(D, T):
+    """Rows 2^29 elements apart, past what a pass's 32-bit offsets reach: the bytes of the same rows side by side."""
+    B, H, S, step = 64, 1, 512, 1 << 29
+    x = _lognormal_tensor(B, H, T, seed=T, sigma_g=0.8, D=D).to(DEV)
+    sec = _sec(9, H, S)[0].to(DEV)
+    near = gpu_encode(x, sec)
+    store = torch.empty((T - 1) * step + B * 128, dtype=torch.float16, device=DEV)
+    far = store.as_strided((B, H, T, D), (128, 128 * B, step, 1))
+    far.copy_(x)
+    got = gpu_encode(far, sec)
+    for name in ("codes", "sigma", "flags", "row_off", "n_out", "outliers"):
+        assert np.array_equal(getattr(got, name), getattr(near, name)), name
+
+
+@pytest.mark.parametrize("T,D", [(33023, 128), (33025, 128), (33026, 128), (33027, 96), (70000, 61), (64, 128), (67, 128)])
+def test_box_index_search_takes_rows_two_passes_at_a_time(T, D):
+    """Rows that end one to three behind a wave's pair of passes, heads of few rows in many batch entries: every row's scale,
+    flags and radius codes."""
+    B = 1 if T > 1000 else 24
+    _roundtrip(_lognormal_tensor(B, 1, T, seed=T, sigma_g=0.8, D=D), S=192, rows=np.arange(0, B * T, 5), check_decode=False)
+
+
 def test_box_index_of_more_heads_than_a_launch_holds():
     """32 tensors of 4100 heads whose index has 125 workgroups each: more threads than one axis of a grid takes.  Every tensor's
     bytes are those of a call of its own.  (50 GB, most of it workspace; the heads share their rows, the tensors their inputs.)"""
