@@ -281,8 +281,9 @@ __device__ __forceinline__ double threshold_of(unsigned long long median_bits, f
 // registers, and select_rank between the least and the most of them.  Select of 8 tensors with 8 such heads of 1024 rows, in us,
 // all norms in fp64 / fp32 and select_rank over the bin with norms taken again in each round / so: multiples of 1 48 / 59 / 39, of
 // 1/4 25 / 33 / 26, constant 154 / 162 / 51, chunks of one norm 33 / 54 / 43.
-// Bound by that compute unit's loads and latency: 12 us for 1024 rows, 6.4 for 256 and fewer; with every norm in fp64, a
-// second histogram, addresses multiplied out per step and scans through LDS 17 and 8.7.
+// Bound by that compute unit's loads and latency: 10.6 us for 1024 rows of 128 elements, which a lane loads 16 bytes at a time
+// (12.3 with 8), 6.2 for 256 and fewer; with every norm in fp64, a second histogram, addresses multiplied out per step and scans
+// through LDS 17 and 8.7.
 // grid = (H, 1, tensors), 1024 threads.
 // ---------------------------------------------------------------------------------------
 constexpr int kHeadBits = 9, kHeadShift = 23 - kHeadBits;
@@ -308,17 +309,29 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
     const uint32_t R = (uint32_t)g.B * (uint32_t)g.T;
     const bool active = kFull || c < g.n_c;
     half4_t v[kSteps];
+    // kFull: two chunks of a row per load, 16 lanes to a row and 64 rows to two steps
+    constexpr int kWide = kFull ? 2 : 1, kLanes = kChunksPerRow / kWide, kStepRows = kSelectThreads / kLanes;
+    const uint32_t first_row = (uint32_t)tid / kLanes;
     {
-        uint32_t r = tid >> 5;
+        uint32_t r = first_row;
         const _Float16 *row = tn.x + (int64_t)h * g.sh;
-        RowWalk walk(g, r, 32u);
+        RowWalk walk(g, r, kStepRows);
         row += walk.first;
 #pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
+        for (int u = 0; u < kSteps; u += kWide) {
             v[u] = half4_t{0, 0, 0, 0};
-            if (active && r < R)
-                v[u] = load_row_chunk<kFull>(row, c, g);
-            r += 32;
+            if (kFull) {
+                v[u + kWide - 1] = v[u];
+                if (r < R) {
+                    typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+                    const half8_t two = *reinterpret_cast<const half8_t *>(row + 8 * (tid % kLanes));
+                    v[u] = half4_t{two[0], two[1], two[2], two[3]};
+                    v[u + kWide - 1] = half4_t{two[4], two[5], two[6], two[7]};
+                }
+            } else if (active && r < R) {
+                v[u] = load_row_chunk<false>(row, c, g);
+            }
+            r += kStepRows;
             row += walk.step;
             if (g.B > 1)
                 row += walk.over_end(g);
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_head(Geometry g, Work
     uint32_t key[kSteps];
 #pragma unroll
     for (int u = 0; u < kSteps; ++u) {
-        const bool in = active && (uint32_t)(tid >> 5) + 32u * u < R;
+        const bool in = active && first_row + (uint32_t)(kStepRows * (u / kWide)) < R;
         const float x0 = (float)v[u][0], x1 = (float)v[u][1], x2 = (float)v[u][2], x3 = (float)v[u][3];
         key[u] = in ? __float_as_uint(fmaf(x3, x3, fmaf(x2, x2, fmaf(x1, x1, x0 * x0)))) & 0x7fffffffu : ~0u;
         if (in) {
