@@ -44,8 +44,8 @@ struct SelectPlan {
     uint32_t below;              // keys below the predicted range
     uint32_t n_cand, n_done;     // where the kept keys did not answer: keys sent to the candidate list (they may exceed
                                  // cand_cap) and workgroups done with it,
-    uint32_t pad;
-    unsigned long long least, most;  // and the smallest and largest of these keys
+    uint32_t selected;           // they did
+    unsigned long long least, most;  // the smallest and largest of the candidate list's keys
 };
 
 // Shape and addressing of one tensor, passed by value to every kernel.

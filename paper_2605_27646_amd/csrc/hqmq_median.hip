@@ -12,7 +12,7 @@
 // (select_rank).  The prediction decides which keys are kept, never the result.
 //   heads of at most 1024 rows   one workgroup selects from its registers (k_select_head)
 //   longer heads                 k_select_predict (a workgroup per head), k_select_count (the sweep, HBM-bound),
-//                                k_select_digit (only where the prediction missed), k_select_finish
+//                                k_select_digit (the selection), k_select_finish (only where the prediction missed)
 // For a head whose prediction missed, or whose list overflowed, k_select_digit makes a histogram of 8192 equal parts of the
 // predicted range, or of a first digit of all keys, and k_select_finish collects the keys of the bin that holds the median;
 // every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
@@ -955,19 +955,55 @@ __device__ __forceinline__ void part_of_rows(const Geometry &g, uint32_t part, u
     last = (uint32_t)(R * (part + 1) / parts);
 }
 
-// The histogram.  A launch that mostly has nothing to do: the box index that was built beside the sweep is finished in it
-// (kFinishParts first workgroups of every head; 0 without an index).  grid = (H, tensors, finish_parts + missed_parts()).
+// The key of the given rank of a list of n kept keys, by one workgroup; bins: LDS, kRankBins.
+__device__ __forceinline__ unsigned long long select_kept(const unsigned long long *list, uint32_t n, uint32_t rank, const Buckets &range,
+                                                          uint32_t *bins, RankScratch &sc)
+{
+    const int tid = threadIdx.x;
+    constexpr int kHeld = 8;  // keys per thread that stay in registers
+    if (range.span == 0ull)
+        return range.lo;
+    if (n <= kHeld * kSelectThreads) {
+        unsigned long long key[kHeld];
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u)
+            key[u] = u * kSelectThreads + tid < n ? list[u * kSelectThreads + tid] : ~0ull;  // outside every range of keys
+        return select_rank(
+            [&](auto f) {
+#pragma unroll
+                for (int u = 0; u < kHeld; ++u)
+                    if (u * kSelectThreads < n)  // uniform
+                        f(key[u]);
+            },
+            range.lo, range.lo + range.span, rank, bins, sc);
+    }
+    return select_rank(
+        [&](auto f) {
+            for (uint32_t i = tid; i < n; i += kSelectThreads)
+                f(list[i]);
+        },
+        range.lo, range.lo + range.span, rank, bins, sc);
+}
+
+// For a head whose kept keys hold the wanted rank, the first workgroup selects from their list; for any other, all of them make
+// the histogram.  The box index that was built beside the sweep is finished in the same launch (kFinishParts first workgroups of
+// every head; 0 without an index), beside the selection: with that in k_select_finish, which now has nothing left to do for such a
+// head, the encode of two [1, 8, 32768, 128] tensors took 178.6 us instead of 176.2, of one [2, 4, 1537, 100] 43.5 instead of 40.3.
+// Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, finish_parts + missed_parts()).
 template <bool kFull>
-__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, uint32_t finish_parts)
+__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, uint32_t finish_parts,
+                                                                 float C)
 {
     const EncodeTensor &tn = batch.t[blockIdx.y];
     const Workspace ws = carve_workspace(tn.ws, wo);
     __shared__ uint32_t hist[kBins0];
+    __shared__ RankScratch sc;
+    static_assert(kRankBins <= kBins0, "the histograms share their memory");
     static_assert(kFinishThreads == kSelectThreads && kFinishWords <= kBins0, "the same workgroup and memory");
     if (blockIdx.z < finish_parts) {  // uniform
         const int h = blockIdx.x;
         const CellIndex ix = cell_index_of(g, ws, h);
-        finish_cells<kFinishParts>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)blockIdx.z,
+        finish_cells<true>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)blockIdx.z, (int)finish_parts,
                                    CellPlaces{ix.list, reinterpret_cast<uint2 *>(ix.head), ix.id, ix.function}, hist);
         return;
     }
@@ -977,8 +1013,17 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     bool inside;
     const KeptCounts kept(ws, h);
     const Buckets range(g, ws, h);
-    if (find_kept(g, kept, range, (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n, inside))
+    if (find_kept(g, kept, range, (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2), bucket, rank_in, n, inside)) {  // uniform
+        if (part != 0)
+            return;
+        const unsigned long long median =
+            select_kept(ws.cand + (size_t)h * g.cand_cap + bucket * bucket_capacity(g), n, rank_in, range, hist, sc);
+        if (threadIdx.x == 0) {
+            ws.thr[h] = threshold_of(median, C);
+            ws.plan[h].selected = 1u;
+        }
         return;
+    }
     const SecondLook look(range, inside);
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
         hist[i] = 0;
@@ -995,12 +1040,12 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
 }
 
 // ---------------------------------------------------------------------------------------
-// finish: one workgroup of a head selects from the list that holds the wanted rank.  If there is none, all of the
-// head's workgroups collect the keys of the histogram's bin that holds it, and the last of them to end selects among
-// these.  If they were too many, the bin mostly holds a single value (a coarsely quantised tensor), which is the median;
-// else the last workgroup selects among the head's raw rows: slow, exact, and only for such inputs.
-// 5.5 us for 8 heads of 2^20 chunks.  A call with heads that were missed (16 heads of 2^20 chunks, 8 of 2^22): 30 and 60 us
-// more, with a list that overflowed 75 and 120, with half the keys of one value 165 and 290.
+// finish, for a head without a list that holds the wanted rank: all of its workgroups collect the keys of the histogram's bin that
+// holds it, and the last of them to end selects among these.  If they were too many, the bin mostly holds a single value (a
+// coarsely quantised tensor), which is the median; else the last workgroup selects among the head's raw rows: slow, exact, and
+// only for such inputs.
+// A call with heads that were missed (16 heads of 2^20 chunks, 8 of 2^22): 30 and 60 us more, with a list that overflowed 75 and
+// 120, with half the keys of one value 165 and 290.
 // Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, missed_parts()).
 // ---------------------------------------------------------------------------------------
 constexpr int kVmcnt0 = 0x0f70;  // s_waitcnt vmcnt(0), the other counters at their largest
@@ -1022,125 +1067,99 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_finish(Geometry g, Wo
     uint32_t rank = (uint32_t)(((uint64_t)g.B * g.T * g.n_c - 1) / 2);
     unsigned long long *cand = ws.cand + (size_t)h * g.cand_cap;
     const bool selects = blockIdx.z == 0;  // the workgroups that start first
+    // done by k_select_digit: one scalar load, not all that find_kept looks at (0.9 us of those 40.3)
+    if (*(const __attribute__((address_space(4))) uint32_t *)(uintptr_t)&ws.plan[h].selected)
+        return;
     unsigned long long median;
     const KeptCounts kept(ws, h);
     const Buckets range(g, ws, h);
     uint32_t bucket, rank_in, n;
     bool inside;
-    if (find_kept(g, kept, range, rank, bucket, rank_in, n, inside)) {  // uniform
+    (void)find_kept(g, kept, range, rank, bucket, rank_in, n, inside);
+    SelectPlan &plan = ws.plan[h];
+    const SecondLook look(range, inside);
+    uint32_t bin, before;
+    unsigned long long lo, hi;
+    rank = look.rank_of(rank, plan.below);
+    pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank, sc.pick, bin, before);
+    rank -= before;
+    if (!look.bounds(bin, lo, hi, median)) {
         if (!selects)
             return;
-        const unsigned long long *list = cand + bucket * bucket_capacity(g);
-        constexpr int kHeld = 8;  // keys per thread that stay in registers
-        if (range.span == 0ull) {
-            median = range.lo;
-        } else if (n <= kHeld * kSelectThreads) {
-            unsigned long long key[kHeld];
-#pragma unroll
-            for (int u = 0; u < kHeld; ++u)
-                key[u] = u * kSelectThreads + tid < n ? list[u * kSelectThreads + tid] : ~0ull;  // outside every range of keys
-            median = select_rank(
-                [&](auto f) {
-#pragma unroll
-                    for (int u = 0; u < kHeld; ++u)
-                        if (u * kSelectThreads < n)  // uniform
-                            f(key[u]);
-                },
-                range.lo, range.lo + range.span, rank_in, bins, sc);
-        } else {
+    } else {
+        if (tid == 0) {
+            least = ~0ull;
+            most = 0ull;
+            n_staged = 0u;
+        }
+        __syncthreads();
+        uint32_t first, last;
+        part_of_rows(g, blockIdx.z, gridDim.z, first, last);
+        unsigned long long my_least = ~0ull, my_most = 0ull;
+        auto flush = [&] {  // by the whole workgroup
+            __syncthreads();
+            if (tid == 0)
+                list_at = atomicAdd(&plan.n_cand, n_staged);
+            __syncthreads();
+            for (uint32_t i = tid; i < n_staged; i += kSelectThreads)
+                if (list_at + i < (uint32_t)g.cand_room)
+                    cand[list_at + i] = staged[i];
+            __syncthreads();
+            if (tid == 0)
+                n_staged = 0u;
+            __syncthreads();
+        };
+        each_key<kFull>(
+            g, tn.x, h, first, last,
+            [&](unsigned long long key) {
+                if (look.counts(key) && look.bin_of(key) == bin) {
+                    my_least = key < my_least ? key : my_least;
+                    my_most = key > my_most ? key : my_most;
+                    staged[atomicAdd(&n_staged, 1u)] = key;
+                }
+            },
+            [&] {
+                __syncthreads();
+                if (n_staged > (uint32_t)kStaged)  // uniform: nobody adds before flush's barrier or the next
+                    flush();
+                else
+                    __syncthreads();
+            });
+        flush();
+        if (my_least <= my_most) {
+            atomicMin(&least, my_least);
+            atomicMax(&most, my_most);
+        }
+        __syncthreads();
+        if (tid == 0 && least <= most) {
+            atomicMin(&plan.least, least);
+            atomicMax(&plan.most, most);
+        }
+        // The list and its ends before the arrival: every wave waits for its own stores, then one thread makes the whole
+        // workgroup's visible (a fence by each of the 16 waves writes the L2 back 16 times: 200 us for 512 workgroups).
+        __builtin_amdgcn_s_waitcnt(kVmcnt0);
+        __syncthreads();
+        if (tid == 0) {
+            __threadfence();
+            arrived = atomicAdd(&plan.n_done, 1u);
+        }
+        __syncthreads();
+        if (arrived != gridDim.z - 1u)
+            return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        n = __hip_atomic_load(&plan.n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        lo = __hip_atomic_load(&plan.least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        hi = __hip_atomic_load(&plan.most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n <= (uint32_t)g.cand_room)
             median = select_rank(
                 [&](auto f) {
                     for (uint32_t i = tid; i < n; i += kSelectThreads)
-                        f(list[i]);
+                        f(cand[i]);
                 },
-                range.lo, range.lo + range.span, rank_in, bins, sc);
-        }
-    } else {
-        SelectPlan &plan = ws.plan[h];
-        const SecondLook look(range, inside);
-        uint32_t bin, before;
-        unsigned long long lo, hi;
-        rank = look.rank_of(rank, plan.below);
-        pick_bin<kBins0, kSelectThreads>(ws.hist0 + (size_t)h * kBins0, rank, sc.pick, bin, before);
-        rank -= before;
-        if (!look.bounds(bin, lo, hi, median)) {
-            if (!selects)
-                return;
-        } else {
-            if (tid == 0) {
-                least = ~0ull;
-                most = 0ull;
-                n_staged = 0u;
-            }
-            __syncthreads();
-            uint32_t first, last;
-            part_of_rows(g, blockIdx.z, gridDim.z, first, last);
-            unsigned long long my_least = ~0ull, my_most = 0ull;
-            auto flush = [&] {  // by the whole workgroup
-                __syncthreads();
-                if (tid == 0)
-                    list_at = atomicAdd(&plan.n_cand, n_staged);
-                __syncthreads();
-                for (uint32_t i = tid; i < n_staged; i += kSelectThreads)
-                    if (list_at + i < (uint32_t)g.cand_room)
-                        cand[list_at + i] = staged[i];
-                __syncthreads();
-                if (tid == 0)
-                    n_staged = 0u;
-                __syncthreads();
-            };
-            each_key<kFull>(
-                g, tn.x, h, first, last,
-                [&](unsigned long long key) {
-                    if (look.counts(key) && look.bin_of(key) == bin) {
-                        my_least = key < my_least ? key : my_least;
-                        my_most = key > my_most ? key : my_most;
-                        staged[atomicAdd(&n_staged, 1u)] = key;
-                    }
-                },
-                [&] {
-                    __syncthreads();
-                    if (n_staged > (uint32_t)kStaged)  // uniform: nobody adds before flush's barrier or the next
-                        flush();
-                    else
-                        __syncthreads();
-                });
-            flush();
-            if (my_least <= my_most) {
-                atomicMin(&least, my_least);
-                atomicMax(&most, my_most);
-            }
-            __syncthreads();
-            if (tid == 0 && least <= most) {
-                atomicMin(&plan.least, least);
-                atomicMax(&plan.most, most);
-            }
-            // The list and its ends before the arrival: every wave waits for its own stores, then one thread makes the whole
-            // workgroup's visible (a fence by each of the 16 waves writes the L2 back 16 times: 200 us for 512 workgroups).
-            __builtin_amdgcn_s_waitcnt(kVmcnt0);
-            __syncthreads();
-            if (tid == 0) {
-                __threadfence();
-                arrived = atomicAdd(&plan.n_done, 1u);
-            }
-            __syncthreads();
-            if (arrived != gridDim.z - 1u)
-                return;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            n = __hip_atomic_load(&plan.n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            lo = __hip_atomic_load(&plan.least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            hi = __hip_atomic_load(&plan.most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (n <= (uint32_t)g.cand_room)
-                median = select_rank(
-                    [&](auto f) {
-                        for (uint32_t i = tid; i < n; i += kSelectThreads)
-                            f(cand[i]);
-                    },
-                    lo, hi, rank, bins, sc);
-            else  // at once where lo == hi
-                median = select_rank([&](auto f) { each_key<kFull>(g, tn.x, h, 0u, (uint32_t)g.B * (uint32_t)g.T, f); }, lo, hi, rank,
-                                     bins, sc);
-        }
+                lo, hi, rank, bins, sc);
+        else  // at once where lo == hi
+            median = select_rank([&](auto f) { each_key<kFull>(g, tn.x, h, 0u, (uint32_t)g.B * (uint32_t)g.T, f); }, lo, hi, rank,
+                                 bins, sc);
     }
     if (tid == 0)
         ws.thr[h] = threshold_of(median, C);
@@ -1547,8 +1566,9 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
         else
             hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(sweep * m), dim3(kCountThreads), 0, stream, g, wo, rest, rows, m);
     }
-    const uint32_t finish_parts = g.cell_n > 0 ? kFinishParts : 0;
-    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, finish_parts + parts.z), block, 0, stream, g, wo, batch, finish_parts);
+    // of a head's index: more than one round of workgroups takes longer than fewer of them with more to do
+    const uint32_t heads_all = n * (uint32_t)g.H, finish_parts = g.cell_n == 0 ? 0u : heads_all <= 64u ? kFinishParts : heads_all <= 128u ? 2u : 1u;
+    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, finish_parts + parts.z), block, 0, stream, g, wo, batch, finish_parts, C);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }
 

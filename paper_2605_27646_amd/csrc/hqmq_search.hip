@@ -1210,7 +1210,7 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
         if (tid < g.S)
             lds_ptr<uint4>(ct.sec)[tid] = reinterpret_cast<const uint4 *>(sec_h)[tid];
         // its first barrier comes before it looks at the secondaries
-        finish_cells<1>(g, ws, lds_ptr<float4_t>(ct.sec), h, 0,
+        finish_cells<false>(g, ws, lds_ptr<float4_t>(ct.sec), h, 0, 1,
                         CellPlaces{lds_ptr<uint2>(ct.list), lds_ptr<uint2>(ct.head), lds_ptr<uint32_t>(ct.id), lds_ptr<float4_t>(ct.base)}, bits);
         __syncthreads();
         return;

@@ -570,8 +570,8 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
 }
 
 // The built index in the form that the search reads from LDS: entries k become addresses, and the functions of the codewords that
-// lists name are tabulated.  Where the select follows the build, its launches have room for that (kFinishParts workgroups of 1024
-// threads per head, in place): done by each of the search's workgroups for itself it was 500 of a wave's 4500 instructions for 512
+// lists name are tabulated.  Where the select follows the build, its launches have room for that (up to kFinishParts workgroups of
+// 1024 threads per head, in place): done by each of the search's workgroups for itself it was 500 of a wave's 4500 instructions for 512
 // rows, and more than the search for 64.  A launch of its own for it takes what it saves (32 tensors of 8 heads of 1024 rows, S =
 // 256, known thresholds: 262 us, 246 without), so without a select each workgroup does it into its LDS.
 // bits: LDS, scratch.
@@ -583,8 +583,8 @@ struct CellPlaces {
     uint32_t *id;
     float4_t *function;
 };
-template <int kParts>
-__device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace &ws, const float4_t *sec_h, int h, int part,
+template <bool kShared>  // by `parts` workgroups, or else by one
+__device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace &ws, const float4_t *sec_h, int h, int part, int parts,
                                              const CellPlaces to, uint32_t *bits)
 {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -615,7 +615,7 @@ __device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace 
             pre[nw] = inc;
     }
     const int first = part * kFinishThreads + tid;
-    constexpr int kStep = kParts * kFinishThreads;
+    const int step = kShared ? parts * kFinishThreads : kFinishThreads;
     __syncthreads();
     const int n_used = (int)pre[nw];
     const bool whole = n_used <= used_cap;  // else no box gets a list
@@ -623,7 +623,7 @@ __device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace 
         const uint2 *head = reinterpret_cast<const uint2 *>(ix.head);
         const int words = g.cell_n * g.cell_n * g.cell_n / 4;  // n is a multiple of 4
         auto address = [&](uint32_t group) { return ct.list + 8u * (whole ? min(group, (uint32_t)g.cell_groups - 1u) : 0u); };
-        for (int i = first; i < words; i += kStep) {
+        for (int i = first; i < words; i += step) {
             const uint2 v = head[i];
             to.head[i] = make_uint2(address(v.x & 0xffffu) | (address(v.x >> 16) << 16), address(v.y & 0xffffu) | (address(v.y >> 16) << 16));
         }
@@ -635,7 +635,7 @@ __device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace 
     auto address_of = [&](uint32_t k) {  // a pad, or a group that belongs to no list: the function that never wins
         return k < n_code ? min(ct.base + 16u * place_of(k), pad) : pad;
     };
-    for (int i = first; i < n_groups; i += kStep) {
+    for (int i = first; i < n_groups; i += step) {
         const uint2 raw = ix.list[i];
         const uint32_t a = address_of(raw.x & 0x7fffu), b = address_of(raw.x >> 16);
         const uint32_t low = min(a, b), high = max(a, b);  // equal: pads
@@ -643,8 +643,8 @@ __device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace 
                                 address_of(raw.y & 0xffffu) | (address_of(raw.y >> 16) << 16));
     }
     const int n_functions = min(n_used, used_cap);
-    if (kParts > 1) {
-        for (uint32_t k = (uint32_t)first; k < n_code; k += kStep) {
+    if (kShared) {
+        for (uint32_t k = (uint32_t)first; k < n_code; k += step) {
             if ((bits[k >> 5] >> (k & 31u)) & 1u) {
                 const uint32_t at = place_of(k), p = (uint32_t)((float)k * g.inv_S), s = k - p * S;  // k / S
                 if (at < (uint32_t)used_cap) {
@@ -666,7 +666,7 @@ __device__ __forceinline__ void finish_cells(const Geometry &g, const Workspace 
         for (int i = tid; i < n_functions; i += kFinishThreads)
             to.function[i] = codeword_function((int)(to.id[i] >> 16), sec_h[to.id[i] & 0xffffu]);
     }
-    for (int i = n_functions + first; i <= used_cap; i += kStep)
+    for (int i = n_functions + first; i <= used_cap; i += step)
         to.function[i] = float4_t{0.f, 0.f, 0.f, -1.0e30f};
     if (n_used == 0 && first == 0)
         to.id[0] = 0;  // what a chunk without a list reads before the fp32 search

@@ -1100,6 +1100,27 @@ def test_box_index_search_takes_rows_two_passes_at_a_time(T, D):
     _roundtrip(_lognormal_tensor(B, 1, T, seed=T, sigma_g=0.8, D=D), S=192, rows=np.arange(0, B * T, 5), check_decode=False)
 
 
+@pytest.mark.parametrize("n,H", [(2, 32), (5, 13), (4, 32), (3, 43)])
+def test_box_index_finished_for_many_heads(n, H):
+    """64, 65, 128 and 129 heads in a launch: four, two and one workgroups finish a head's index.  Each tensor's bytes are those
+    of a call of its own."""
+    T, S = 2100, 64
+    cb = hq.hqmq_build_codebooks(6, n, H, S)
+    xs = [_lognormal_tensor(1, H, T, seed=500 + i, sigma_g=0.8).to(DEV) for i in range(n)]
+    secs = [cb[i, 0].contiguous().to(DEV) for i in range(n)]
+    params = hq.params_for(xs[0], S)
+    encs, ws = [hq.alloc_encoded(params, DEV) for _ in range(n)], hq.alloc_batch_workspace(params, n, DEV)
+    ws.fill_(0xAB)
+    hq.hqmq_encode_batch(hq.EncodeBatch(params, xs, secs, encs, ws))
+    torch.cuda.synchronize()
+    for i in range(n):
+        g = gpu_encode(xs[i], secs[i])
+        total = int(g.n_out[-1])
+        assert torch.equal(encs[i].codes, g.bufs.codes) and torch.equal(encs[i].flags, g.bufs.flags), i
+        assert torch.equal(encs[i].n_outliers, g.bufs.n_outliers) and torch.equal(encs[i].row_off, g.bufs.row_off), i
+        assert torch.equal(encs[i].outliers[:total].view(torch.int16), g.bufs.outliers[:total].view(torch.int16)), i
+
+
 def test_box_index_of_more_heads_than_a_launch_holds():
     """32 tensors of 4100 heads whose index has 125 workgroups each: more threads than one axis of a grid takes.  Every tensor's
     bytes are those of a call of its own.  (50 GB, most of it workspace; the heads share their rows, the tensors their inputs.)"""
