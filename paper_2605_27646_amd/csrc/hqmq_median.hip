@@ -638,7 +638,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
 __device__ __forceinline__ uint32_t bucket_capacity(const Geometry &g) { return (uint32_t)g.cand_room / kBuckets; }
 struct Buckets {
     unsigned long long lo, span;  // keys
-    float scale;
+    float scale, first, last;     // their values
     __device__ __forceinline__ Buckets(const Geometry &g, const Workspace &ws, int h)
     {
         // sums over the parts in pairs, so that equal ends sum up exactly
@@ -651,10 +651,9 @@ struct Buckets {
             return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
         };
         static_assert(kMaxParts == 8, "a part per lane of the sum");
-        float first = sum8(own.x), last = sum8(own.y);
         // exact, if the parts agree on a single value; else their ends are 4 units of the last place wide
-        first *= 1.0f / (float)n;
-        last *= 1.0f / (float)n;
+        first = sum8(own.x) * (1.0f / (float)n);
+        last = sum8(own.y) * (1.0f / (float)n);
         lo = key_of((double)first);
         span = key_of((double)last) - lo;
         scale = (float)kBuckets / (last - first);  // not used for a single value
@@ -730,20 +729,25 @@ struct SecondLook {
 };
 
 // The sweep: keys below the predicted range are counted, those in it kept, staged in LDS so that a workgroup updates each
-// list's counter once.  HBM-bound: two [1, 8, 32768, 128] tensors in 29 us, 4.6 TB/s; one of 131072 rows in 57, 4.7.
+// list's counter once.  Norms in fp32 tell nearly all chunks apart; what may be in the range waits in a queue of the wave for its
+// key in fp64.  Two [1, 8, 32768, 128] tensors with the smallest index beside it in 30 us, 4.5 TB/s, one of 131072 rows in 47, 5.7
+// (all keys in fp64: 31 and 53; with no arithmetic but the norms 24 and 42); where every chunk waits, in a tensor of two
+// norms only, the select of both takes 220, was 214.
 // A thread has eight loads of 16 bytes (rows of 128 elements) or of a chunk in flight, next to one another over the rows.
 // kCells: workgroups in between build the search's box index, which needs the secondaries only, while the others wait for
 // their rows; a quarter of the sweep's alternates with them, eight by eight (one for each XCD), the rest follows (half, three
-// quarters, all: within 1 %).  The two launches one after the other / together, in us: 16 heads of 32768 rows, S = 256, 51 /
-// 43; 8 heads of 131072, 76 / 58; 64 heads of 8192 rows of 96 elements, S = 192, 81 / 80 (bound by VALU issue); 4 heads of
-// 3074 rows of 100, S = 96, 23 / 14.
+// quarters, all: within 1 %).  The two launches one after the other / together / together with the norms in fp32, in us:
+// 16 heads of 32768 rows, S = 256, 51 / 43 / 37; 8 heads of 131072, 76 / 58 / 50; 64 heads of 8192 rows of 96 elements, S = 192,
+// 81 / 74 / 68 (bound by VALU issue); 4 heads of 3074 rows of 100, S = 96, 23 / 14 / 13.
 // `rows` of one (b, h) segment per workgroup; grid: cell_blocks() * H * n_tensors, rounded up to 8, and ceil(T / rows) * B * H *
 // n_tensors, likewise.
 constexpr int kCountThreads = kCellThreads;
 constexpr int kCountRows = 512;  // of a workgroup, at most
-constexpr int kStageKeys = 192;  // keys a workgroup stages per list
+constexpr int kStageKeys = 144;  // keys a workgroup stages per list
+constexpr int kQueue = 256;      // chunks a wave queues up
 struct CountStage {              // LDS
     unsigned long long staged[kBuckets][kStageKeys];
+    uint2 queue[kCountThreads / 64][kQueue];         // of each wave: chunks whose keys are wanted
     uint32_t n_staged[kBuckets], n_below;            // n_staged: all keys of the list, also those past the stage
     uint32_t n_direct[kBuckets], full[kBuckets];     // those of them that the list's counter has; the list is full
 };
@@ -816,19 +820,70 @@ __global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, Work
                 lists[k * cap + at] = key;
         }
     };
-    uint32_t below = 0, equal = 0;
-    auto take = [&](const half4_t v, bool in) {
+    // A squared norm in fp32 differs from the fp64 one by at most 3 * 2^-24 of it: below the range or above it by more than that it
+    // needs no other.  The rest, some 5 in 100 chunks, queue up until a wave has 64, which then get their keys together.
+    const float under = range.first * (1.0f - 0x1p-21f), over = range.last * (1.0f + 0x1p-21f);
+    const bool single = range.span == 0ull;  // uniform; a range of one value: its keys may be all there are, and only their number counts
+    const int lane = tid & 63;
+    uint2 *queue = st.queue[tid / 64];
+    uint32_t below = 0, equal = 0, queued = 0;  // of the wave
+    auto keep = [&](const half4_t v, bool in) {
         const unsigned long long key = key_of(chunk_norm2(v)) & kKeyMask;
-        below += in && key < range.lo ? 1u : 0u;
+        below += (uint32_t)__popcll(ballot(in && key < range.lo));
         if (in && range.holds(key)) {
-            if (range.span == 0ull) {
-                ++equal;
-            } else {
-                const uint32_t k = range.of(key), pos = atomicAdd(&st.n_staged[k], 1u);
-                if (pos < (uint32_t)kStageKeys)
-                    st.staged[k][pos] = key;
-                else if (!*(volatile uint32_t *)&st.full[k])
-                    append(k, key);
+            const uint32_t k = range.of(key), pos = atomicAdd(&st.n_staged[k], 1u);
+            if (pos < (uint32_t)kStageKeys)
+                st.staged[k][pos] = key;
+            else if (!*(volatile uint32_t *)&st.full[k])
+                append(k, key);
+        }
+    };
+    auto keep_queued = [&](uint32_t n) {        // the last n, at most 64
+        wave_lds_sync();
+        queued -= n;
+        const bool mine = (uint32_t)lane < n;
+        keep(__builtin_bit_cast(half4_t, queue[mine ? queued + lane : 0u]), mine);
+        wave_lds_sync();
+    };
+    // Queues up a wave's chunks whose keys are wanted; false, and nothing done, if they don't fit.  A chunk of infinities (what
+    // lanes without one have) is above every range.
+    auto take = [&](const half4_t v) {
+        const float x0 = (float)v[0], x1 = (float)v[1], x2 = (float)v[2], x3 = (float)v[3];
+        const float r2 = fmaf(x3, x3, fmaf(x2, x2, fmaf(x1, x1, x0 * x0)));
+        const unsigned long long less = ballot(r2 < under);
+        unsigned long long wanted = ballot(r2 <= over) & ~less;
+        const bool fits = queued + (uint32_t)__popcll(wanted) <= (uint32_t)kQueue;
+        wanted = fits ? wanted : 0ull;
+        below += fits ? (uint32_t)__popcll(less) : 0u;
+        if (of_mask(wanted))
+            queue[queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(wanted >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)wanted, 0u))] =
+                __builtin_bit_cast(uint2, v);
+        queued += (uint32_t)__popcll(wanted);
+        return fits;
+    };
+    auto take_single = [&](const half4_t v) {
+        const unsigned long long key = key_of(chunk_norm2(v)) & kKeyMask;
+        below += (uint32_t)__popcll(ballot(key < range.lo));
+        equal += (uint32_t)__popcll(ballot(key == range.lo));
+    };
+    const _Float16 inf = __builtin_bit_cast(_Float16, (uint16_t)0x7c00);
+    const half4_t none = {inf, inf, inf, inf};
+    // Empties the queue, and keeps what it had no room for, again from memory, four in flight.  (Emptied at each of the places where
+    // it may be full, the code of that alone was 25 KB.)
+    auto settle = [&](uint32_t left, auto again) {
+        while (queued >= 64u)  // uniform, as the next
+            keep_queued(64u);
+        while (left) {
+            half4_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = left ? again(__ffs((int)left) - 1) : none;
+                left &= left - 1u;  // 0 stays 0
+            }
+#pragma unroll 1
+            for (int k = 0; k < 4; ++k) {
+                keep(v[0], true);
+                v[0] = v[1], v[1] = v[2], v[2] = v[3];
             }
         }
     };
@@ -837,46 +892,72 @@ __global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, Work
         typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
         constexpr int kPieces = kChunksPerRow / 2, kStep = kCountThreads / kPieces;  // 16-byte pieces of a row, rows per load
         const _Float16 *at = base + (int64_t)(tid / kPieces) * g.st + 8 * (tid % kPieces);
-        for (int r = tid / kPieces; r - tid / kPieces < n_rows; r += kLoads * kStep, at += (int64_t)(kLoads * kStep) * g.st) {
-            half8_t v[kLoads];
+        for (int r0 = 0; r0 < n_rows; r0 += kLoads * kStep, at += (int64_t)(kLoads * kStep) * g.st) {
+            half8_t two[kLoads];
+            if (r0 + kLoads * kStep <= n_rows) {  // uniform
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u)
+                    two[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    two[u] = half8_t{inf, inf, inf, inf, inf, inf, inf, inf};
+                    if (r0 + tid / kPieces + kStep * u < n_rows)
+                        two[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
+                }
+            }
+            if (single) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    take_single(half4_t{two[u][0], two[u][1], two[u][2], two[u][3]});
+                    take_single(half4_t{two[u][4], two[u][5], two[u][6], two[u][7]});
+                }
+                continue;
+            }
+            uint32_t left = 0;
 #pragma unroll
             for (int u = 0; u < kLoads; ++u) {
-                v[u] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-                if (r + kStep * u < n_rows)
-                    v[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
+                left |= take(half4_t{two[u][0], two[u][1], two[u][2], two[u][3]}) ? 0u : 1u << (2 * u);
+                left |= take(half4_t{two[u][4], two[u][5], two[u][6], two[u][7]}) ? 0u : 2u << (2 * u);
             }
-#pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                const bool in = r + kStep * u < n_rows;
-                take(half4_t{v[u][0], v[u][1], v[u][2], v[u][3]}, in);
-                take(half4_t{v[u][4], v[u][5], v[u][6], v[u][7]}, in);
-            }
+            settle(left, [&](int i) {
+                const int r = kStep * (i >> 1);
+                return r0 + tid / kPieces + r < n_rows ? load_chunk(at + (int64_t)r * g.st + 4 * (i & 1)) : none;
+            });
         }
     } else {
         const int n_chunks = n_rows * g.n_c;
+        auto load = [&](int q) {
+            if (q >= n_chunks)
+                return none;
+            const int r = row_of_chunk(q, g);
+            return load_row_chunk<false>(base + (int64_t)r * g.st, q - r * g.n_c, g);
+        };
         for (int q0 = 0; q0 < n_chunks; q0 += kLoads * kCountThreads) {  // uniform
             half4_t v[kLoads];
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                const int q = q0 + u * kCountThreads + tid;
-                v[u] = half4_t{0, 0, 0, 0};
-                if (q < n_chunks) {
-                    const int r = row_of_chunk(q, g);
-                    v[u] = load_row_chunk<false>(base + (int64_t)r * g.st, q - r * g.n_c, g);
-                }
+            for (int u = 0; u < kLoads; ++u)
+                v[u] = load(q0 + u * kCountThreads + tid);
+            if (single) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u)
+                    take_single(v[u]);
+                continue;
             }
+            uint32_t left = 0;
 #pragma unroll
             for (int u = 0; u < kLoads; ++u)
-                take(v[u], q0 + u * kCountThreads + tid < n_chunks);
+                left |= take(v[u]) ? 0u : 1u << u;
+            settle(left, [&](int i) { return load(q0 + i * kCountThreads + tid); });
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1)
-        below += __shfl_xor(below, d, 64);
-    if ((tid & 63) == 0)
+    if (queued)
+        keep_queued(queued);
+    if (lane == 0) {
         atomicAdd(&st.n_below, below);
-    if (equal)
-        atomicAdd(&st.n_staged[0], equal);
+        if (equal)
+            atomicAdd(&st.n_staged[0], equal);
+    }
     __syncthreads();
     if (range.span == 0ull) {
         if (tid == 0 && st.n_staged[0])

@@ -684,6 +684,36 @@ def test_select_of_repeating_norms(kind, B, T, D):
         assert (m2 == 0.0).all()
 
 
+@pytest.mark.parametrize("B,T,D", [(1, 1025, 128), (1, 8192, 128), (2, 5003, 128), (3, 700, 44), (1, 6001, 96), (1, 16385, 64)])
+@pytest.mark.parametrize("steps", [0, 40])
+def test_select_of_sorted_rows(steps, B, T, D):
+    """Rows in the order of their norms: all that the median's neighbourhood holds comes to a few waves of the sweep, in numbers
+    around and far above what each queues up; in distinct values, and in 40 of them.  In rows that lie apart, thresholds bit for
+    bit."""
+    H, S = 2, 1
+    gen = torch.Generator().manual_seed(T)
+    size = torch.linspace(0.5, 2.0, T).view(1, 1, T, 1, 1)
+    if steps:
+        size = torch.round(size * steps) / steps
+        x = torch.ones(B, H, T, D // 4, 4)
+    else:
+        x = torch.randn(B, H, T, D // 4, 4, generator=gen)
+        x = x / x.norm(dim=-1, keepdim=True)
+    x = (x * size).view(B, H, T, D).half()
+    x[:, 1] = x[:, 1].flip(1)
+    sec_t, sec = _sec(4, H, S)
+    m2 = oracle.encode(_bits(x), sec, rows=np.arange(0, 1)).m2
+    x_dev = torch.zeros(B, H, T, D + 8, dtype=torch.float16, device=DEV)[..., :D]
+    x_dev.copy_(x)
+    params = hq.params_for(x_dev, S)
+    ws = hq.alloc_workspace(params, DEV)
+    ws.fill_(0x5A)
+    hq.hqmq_encode(params, x_dev, sec_t.to(DEV), hq.alloc_encoded(params, DEV), ws)
+    thr = hq.hqmq_thresholds(params, ws).cpu().numpy()
+    c = float(np.float32(3.0))
+    assert np.array_equal(thr.view(np.uint64), ((c * c) * m2).view(np.uint64))
+
+
 def _head_with_cluster(R, D, k, gen):
     """fp16 [R, D] with k chunks around the median whose squared norms are neighbours on either side of 1, steps of 2e-9
     apart (up to 30 of them share an fp32 value); of the others one half is smaller, one larger."""
