@@ -44,7 +44,7 @@ struct SelectPlan {
     uint32_t below;              // keys below the predicted range
     uint32_t n_cand, n_done;     // where the kept keys did not answer: keys sent to the candidate list (they may exceed
                                  // cand_cap) and workgroups done with it,
-    uint32_t selected;           // they did
+    uint32_t selected;           // the kept keys answered: k_select_finish has nothing to do
     unsigned long long least, most;  // the smallest and largest of the candidate list's keys
 };
 

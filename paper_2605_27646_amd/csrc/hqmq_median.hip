@@ -979,10 +979,10 @@ __global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, Work
 }
 
 // ---------------------------------------------------------------------------------------
-// For a head whose kept keys do not answer: gridDim.z workgroups share its rows (of all batch entries one after the other).
-// Every other head's workgroups return at once, but their launch takes time too: 512 workgroups in all, at least 4 for a long
-// head and at most one per 256 rows.  (16 per head: the two launches took 42 us instead of 14 for 512 heads of 1400 rows, and
-// 287 instead of 77 where 8 heads of 131072 were missed, on half the chip.)
+// Workgroups that share the rows of a head whose kept keys do not answer (of all batch entries one after the other).  Every other
+// head's return at once, but for the first in k_select_digit, which selects; but their launch takes time too: 512 workgroups in
+// all, at least 4 for a long head and at most one per 256 rows.  (16 per head: the two launches took 42 us instead of 14 for 512
+// heads of 1400 rows, and 287 instead of 77 where 8 heads of 131072 were missed, on half the chip.)
 // ---------------------------------------------------------------------------------------
 static int missed_parts(const Geometry &g, unsigned n_tensors)
 {
@@ -1067,13 +1067,17 @@ __device__ __forceinline__ unsigned long long select_kept(const unsigned long lo
 }
 
 // For a head whose kept keys hold the wanted rank, the first workgroup selects from their list; for any other, all of them make
-// the histogram.  The box index that was built beside the sweep is finished in the same launch (kFinishParts first workgroups of
-// every head; 0 without an index), beside the selection: with that in k_select_finish, which now has nothing left to do for such a
+// the histogram.  The box index that was built beside the sweep is finished in the same launch (finish_parts workgroups of every
+// head; 0 without an index), beside the selection: with that in k_select_finish, which now has nothing left to do for such a
 // head, the encode of two [1, 8, 32768, 128] tensors took 178.6 us instead of 176.2, of one [2, 4, 1537, 100] 43.5 instead of 40.3.
-// Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, finish_parts + missed_parts()).
+// These come last: the others fill the chip with two workgroups per compute unit, and those of missed heads keep their
+// places (the launch in us, 16 missed heads of 32768 rows alike within a row: 24.4 with them first, 17.0 so; half zero rows 41, 40).
+// Two per compute unit take at most 96 scalar registers per wave, hence the launch bound (100 left it one: 32 instead of 26 for
+// 16 heads in steps of 1/8, 92 instead of 73 for 8 heads of 131072 rows, half of them zero).
+// Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, missed_parts() + finish_parts).
 template <bool kFull>
-__global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, uint32_t finish_parts,
-                                                                 float C)
+__global__ __launch_bounds__(kSelectThreads, 8) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
+                                                                    uint32_t finish_parts, float C)
 {
     const EncodeTensor &tn = batch.t[blockIdx.y];
     const Workspace ws = carve_workspace(tn.ws, wo);
@@ -1081,14 +1085,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     __shared__ RankScratch sc;
     static_assert(kRankBins <= kBins0, "the histograms share their memory");
     static_assert(kFinishThreads == kSelectThreads && kFinishWords <= kBins0, "the same workgroup and memory");
-    if (blockIdx.z < finish_parts) {  // uniform
+    const uint32_t parts = gridDim.z - finish_parts, part = blockIdx.z;
+    if (part >= parts) {  // uniform
         const int h = blockIdx.x;
         const CellIndex ix = cell_index_of(g, ws, h);
-        finish_cells<true>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)blockIdx.z, (int)finish_parts,
+        finish_cells<true>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)(part - parts), (int)finish_parts,
                                    CellPlaces{ix.list, reinterpret_cast<uint2 *>(ix.head), ix.id, ix.function}, hist);
         return;
     }
-    const uint32_t part = blockIdx.z - finish_parts;
     const int h = missed_head(g, part);
     uint32_t bucket, rank_in, n, first, last;
     bool inside;
@@ -1109,7 +1113,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_digit(Geometry g, Wor
     for (int i = threadIdx.x; i < kBins0; i += kSelectThreads)
         hist[i] = 0;
     __syncthreads();
-    part_of_rows(g, part, gridDim.z - finish_parts, first, last);
+    part_of_rows(g, part, parts, first, last);
     each_key<kFull>(g, tn.x, h, first, last, [&](unsigned long long key) {
         if (look.counts(key))
             atomicAdd(&hist[look.bin_of(key)], 1u);
@@ -1647,9 +1651,14 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
         else
             hipLaunchKernelGGL((k_select_count<kFull, false>), dim3(sweep * m), dim3(kCountThreads), 0, stream, g, wo, rest, rows, m);
     }
-    // of a head's index: more than one round of workgroups takes longer than fewer of them with more to do
-    const uint32_t heads_all = n * (uint32_t)g.H, finish_parts = g.cell_n == 0 ? 0u : heads_all <= 64u ? kFinishParts : heads_all <= 128u ? 2u : 1u;
-    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, finish_parts + parts.z), block, 0, stream, g, wo, batch, finish_parts, C);
+    // Workgroups that finish a head's index: a step of theirs is 1024 of its 24 S codewords and of up to 5120 list groups, and
+    // all heads' lie beside one another, two per compute unit.  The launch in us by 1 / 2 / 4 / 8 of them, heads of 4100 rows: S = 256:
+    // 8 heads 8.4 / 5.7 / 5.2 / 5.3, 64 heads 10.6 / 7.8 / 7.3 / 7.2, 128 heads 11.0 / 10.0 / 9.0 / 10.2, 256 heads 15.2 / 14.2 / 15.5 /
+    // 18.0; S = 64: 16 heads 6.4 / 5.8 / 5.7 / 5.8, 256 heads 9.9 / 10.2 / 11.6 / 14.5; S = 16: 16 heads 5.4 / 5.9 / 5.3 / 5.7, 128
+    // heads 6.0 / 6.0 / 7.1 / 8.5.
+    const uint32_t heads_all = n * (uint32_t)g.H;
+    const uint32_t finish_parts = g.cell_n == 0 ? 0u : std::max(1u, std::min({(uint32_t)(g.S + 31) / 32u, 512u / heads_all, kFinishParts}));
+    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, parts.z + finish_parts), block, 0, stream, g, wo, batch, finish_parts, C);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }
 

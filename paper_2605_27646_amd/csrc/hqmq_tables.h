@@ -575,7 +575,8 @@ __device__ __forceinline__ void build_cells(const Geometry &g, const Workspace &
 // rows, and more than the search for 64.  A launch of its own for it takes what it saves (32 tensors of 8 heads of 1024 rows, S =
 // 256, known thresholds: 262 us, 246 without), so without a select each workgroup does it into its LDS.
 // bits: LDS, scratch.
-constexpr int kFinishThreads = 1024, kFinishParts = 4;
+constexpr int kFinishThreads = 1024;
+constexpr uint32_t kFinishParts = 8;
 constexpr int kFinishWords = 2 * (24 * kScreenMaxS / 32) + 1;  // of LDS
 struct CellPlaces {
     uint2 *list;

@@ -1132,8 +1132,8 @@ def test_box_index_search_takes_rows_two_passes_at_a_time(T, D):
 
 @pytest.mark.parametrize("n,H", [(2, 32), (5, 13), (4, 32), (3, 43)])
 def test_box_index_finished_for_many_heads(n, H):
-    """64, 65, 128 and 129 heads in a launch: four, two and one workgroups finish a head's index.  Each tensor's bytes are those
-    of a call of its own."""
+    """64, 65, 128 and 129 heads in a launch, two workgroups of which finish a head's index.  Each tensor's bytes are those of a
+    call of its own."""
     T, S = 2100, 64
     cb = hq.hqmq_build_codebooks(6, n, H, S)
     xs = [_lognormal_tensor(1, H, T, seed=500 + i, sigma_g=0.8).to(DEV) for i in range(n)]
@@ -1149,6 +1149,34 @@ def test_box_index_finished_for_many_heads(n, H):
         assert torch.equal(encs[i].codes, g.bufs.codes) and torch.equal(encs[i].flags, g.bufs.flags), i
         assert torch.equal(encs[i].n_outliers, g.bufs.n_outliers) and torch.equal(encs[i].row_off, g.bufs.row_off), i
         assert torch.equal(encs[i].outliers[:total].view(torch.int16), g.bufs.outliers[:total].view(torch.int16)), i
+
+
+@pytest.mark.parametrize("n,H,S", [(1, 2, 512), (2, 8, 97), (5, 13, 256), (3, 43, 225), (32, 17, 65)])
+def test_box_index_finished_beside_a_second_look(n, H, S):
+    """2 to 544 heads in a launch, eight to one workgroups of which finish a head's index, in one step or several, while others make
+    the histograms of the heads that are half zeros: one in three, and in the last tensor all.  Each tensor's bytes are those of a
+    call of its own."""
+    T = 2100
+    cb = hq.hqmq_build_codebooks(8, n, H, S)
+    xs = [_lognormal_tensor(1, H, T, seed=700 + i, sigma_g=0.8) for i in range(n)]
+    for i, x in enumerate(xs):
+        x[:, :: 3 if i + 1 < n else 1, T // 2 :] = 0
+    xs = [x.to(DEV) for x in xs]
+    secs = [cb[i, 0].contiguous().to(DEV) for i in range(n)]
+    params = hq.params_for(xs[0], S)
+    encs, ws = [hq.alloc_encoded(params, DEV) for _ in range(n)], hq.alloc_batch_workspace(params, n, DEV)
+    ws.fill_(0xAB)
+    hq.hqmq_encode_batch(hq.EncodeBatch(params, xs, secs, encs, ws))
+    torch.cuda.synchronize()
+    for i in range(n):
+        g = gpu_encode(xs[i], secs[i])
+        total = int(g.n_out[-1])
+        assert torch.equal(encs[i].codes, g.bufs.codes) and torch.equal(encs[i].flags, g.bufs.flags), i
+        assert torch.equal(encs[i].n_outliers, g.bufs.n_outliers) and torch.equal(encs[i].row_off, g.bufs.row_off), i
+        assert torch.equal(encs[i].outliers[:total].view(torch.int16), g.bufs.outliers[:total].view(torch.int16)), i
+        if H * n <= 16:
+            xb, sec = _bits(xs[i].cpu()), secs[i].cpu().numpy()
+            compare_encode(g, oracle.encode(xb, sec, rows=np.arange(0, H * T, 29)), xb, sec)
 
 
 def test_box_index_of_more_heads_than_a_launch_holds():
