@@ -484,6 +484,7 @@ constexpr int kPredictBins = 84 << kPredictBits;
 constexpr int kBuckets = 16;
 constexpr int kBucketPitch = kBins1 / kBuckets;  // words between the counters: atomics to one line wait for each other
 constexpr int kMaxParts = 8;
+constexpr uint32_t kDenseBit = 1u << 31;  // sign of a part's lower end: the range holds a large share of the sample
 __host__ __device__ __forceinline__ int predict_parts(const Geometry &g)
 {
     const uint64_t n_h = (uint64_t)g.B * g.T * g.n_c;
@@ -572,6 +573,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
     uint32_t f_lo = bin_lo == 0u ? 0u : (bin_lo + kPredictBase) << kPredictShift;
     uint32_t f_hi = bin_hi == 0u ? 0u : ((bin_hi + kPredictBase) << kPredictShift) | ((1u << kPredictShift) - 1u);
     const uint32_t n_lo = hist[bin_lo];
+    bool dense = false;
     if (n_lo + hist[bin_hi] > n / 64u) {  // uniform: concentrated or coarse data
         __syncthreads();
         for (int i = tid; i < 2 * kBins1; i += kSelectThreads)
@@ -597,6 +599,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
                 b = n_lo + rank_hi - before_hi;
             },
             pick, sub_lo, before, sub_hi, before);
+        // a range holds no more than a few per cent of the sample besides what shares the parts at its ends
+        dense = 8u * (hist[sub_lo] + hist[sub_hi]) > 3u * n;
         if (bin_lo != 0u)
             f_lo |= sub_lo << kSubShift;
         if (bin_hi != 0u)
@@ -629,7 +633,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_predict(Geometry g, W
             f_lo = f_lo <= 4u ? 0u : f_lo - 4u;
             f_hi += 4u;
         }
-        predicted_ends(ws, h)[part] = make_float2(__uint_as_float(f_lo), __uint_as_float(f_hi));
+        predicted_ends(ws, h)[part] = make_float2(__uint_as_float(f_lo | (dense ? kDenseBit : 0u)), __uint_as_float(f_hi));
     }
 }
 
@@ -639,11 +643,13 @@ __device__ __forceinline__ uint32_t bucket_capacity(const Geometry &g) { return 
 struct Buckets {
     unsigned long long lo, span;  // keys
     float scale, first, last;     // their values
+    bool dense;                   // wanted by many of the chunks
     __device__ __forceinline__ Buckets(const Geometry &g, const Workspace &ws, int h)
     {
         // sums over the parts in pairs, so that equal ends sum up exactly
         const int n = predict_parts(g), lane = threadIdx.x & 63;
         const float2 own = lane < n ? predicted_ends(ws, h)[lane] : make_float2(0.0f, 0.0f);
+        dense = ballot((__float_as_uint(own.x) & kDenseBit) != 0u) != 0ull;
         auto sum8 = [](float v) {  // of the first eight lanes
             v += dpp_move<0xb1>(v);   // neighbours
             v += dpp_move<0x4e>(v);   // pairs
@@ -652,7 +658,7 @@ struct Buckets {
         };
         static_assert(kMaxParts == 8, "a part per lane of the sum");
         // exact, if the parts agree on a single value; else their ends are 4 units of the last place wide
-        first = sum8(own.x) * (1.0f / (float)n);
+        first = sum8(fabsf(own.x)) * (1.0f / (float)n);
         last = sum8(own.y) * (1.0f / (float)n);
         lo = key_of((double)first);
         span = key_of((double)last) - lo;
@@ -730,9 +736,11 @@ struct SecondLook {
 
 // The sweep: keys below the predicted range are counted, those in it kept, staged in LDS so that a workgroup updates each
 // list's counter once.  Norms in fp32 tell nearly all chunks apart; what may be in the range waits in a queue of the wave for its
-// key in fp64.  Two [1, 8, 32768, 128] tensors with the smallest index beside it in 30 us, 4.5 TB/s, one of 131072 rows in 47, 5.7
-// (all keys in fp64: 31 and 53; with no arithmetic but the norms 24 and 42); where every chunk waits, in a tensor of two
-// norms only, the select of both takes 220, was 214.
+// key in fp64.  Two [1, 8, 32768, 128] tensors with the smallest index beside it in 29 us, 4.6 TB/s, one of 131072 rows in 47, 5.7
+// (all keys in fp64: 31 and 53; with no arithmetic but the norms 24 and 42).
+// Where most chunks are wanted the queue only adds to the work.  Two values of norms and nothing else / half zeros / two close
+// values in 40 of 100 chunks, all queued up and all not, us: those two tensors 63, 56 / 60, 55 / 44, 36; two [1, 8, 16384, 96]
+// 32, 28 / 31, 28 / 24, 25; the long one 121, 99 / 110, 97 / 94, 105; in 25 of 100 chunks 34, 34 / 20, 25 / 66, 92.
 // A thread has eight loads of 16 bytes (rows of 128 elements) or of a chunk in flight, next to one another over the rows.
 // kCells: workgroups in between build the search's box index, which needs the secondaries only, while the others wait for
 // their rows; a quarter of the sweep's alternates with them, eight by eight (one for each XCD), the rest follows (half, three
@@ -752,7 +760,7 @@ struct CountStage {              // LDS
     uint32_t n_direct[kBuckets], full[kBuckets];     // those of them that the list's counter has; the list is full
 };
 template <bool kFull, bool kCells>
-__global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows,
+__global__ __launch_bounds__(kCountThreads, 6) void k_select_count(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int rows,
                                                                 uint32_t n_tensors)
 {
     constexpr size_t kLds = kCells && sizeof(CellBuild) > sizeof(CountStage) ? sizeof(CellBuild) : sizeof(CountStage);
@@ -887,42 +895,61 @@ __global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, Work
             }
         }
     };
-    constexpr int kLoads = 8;
+    // A wave takes the keys of all chunks at once, none of them queued, where the prediction's sample says that three in eight are
+    // wanted, or from the step on after one that left three of eight loads over.  A loop for each way: inside one loop the other
+    // ways cost the usual one 2 % of the sweep.
+    constexpr int kLoads = 8, kMany = 3;
     if (kFull) {
         typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
         constexpr int kPieces = kChunksPerRow / 2, kStep = kCountThreads / kPieces;  // 16-byte pieces of a row, rows per load
         const _Float16 *at = base + (int64_t)(tid / kPieces) * g.st + 8 * (tid % kPieces);
-        for (int r0 = 0; r0 < n_rows; r0 += kLoads * kStep, at += (int64_t)(kLoads * kStep) * g.st) {
-            half8_t two[kLoads];
-            if (r0 + kLoads * kStep <= n_rows) {  // uniform
+        int r0 = 0;
+        auto steps = [&](auto f) {  // until f says no
+            for (bool more = true; more && r0 < n_rows; r0 += kLoads * kStep, at += (int64_t)(kLoads * kStep) * g.st) {  // uniform
+                half8_t two[kLoads];
+                if (r0 + kLoads * kStep <= n_rows) {  // uniform
 #pragma unroll
-                for (int u = 0; u < kLoads; ++u)
-                    two[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kLoads; ++u) {
-                    two[u] = half8_t{inf, inf, inf, inf, inf, inf, inf, inf};
-                    if (r0 + tid / kPieces + kStep * u < n_rows)
+                    for (int u = 0; u < kLoads; ++u)
                         two[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
-                }
-            }
-            if (single) {
+                } else {
 #pragma unroll
-                for (int u = 0; u < kLoads; ++u) {
-                    take_single(half4_t{two[u][0], two[u][1], two[u][2], two[u][3]});
-                    take_single(half4_t{two[u][4], two[u][5], two[u][6], two[u][7]});
+                    for (int u = 0; u < kLoads; ++u) {
+                        two[u] = half8_t{inf, inf, inf, inf, inf, inf, inf, inf};
+                        if (r0 + tid / kPieces + kStep * u < n_rows)
+                            two[u] = *reinterpret_cast<const half8_t *>(at + (int64_t)(kStep * u) * g.st);
+                    }
                 }
-                continue;
+                more = f([&](int i) {
+                    const half8_t v = two[i >> 1];
+                    return i & 1 ? half4_t{v[4], v[5], v[6], v[7]} : half4_t{v[0], v[1], v[2], v[3]};
+                });
             }
-            uint32_t left = 0;
+        };
+        if (single) {
+            steps([&](auto chunk) {
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                left |= take(half4_t{two[u][0], two[u][1], two[u][2], two[u][3]}) ? 0u : 1u << (2 * u);
-                left |= take(half4_t{two[u][4], two[u][5], two[u][6], two[u][7]}) ? 0u : 2u << (2 * u);
-            }
-            settle(left, [&](int i) {
-                const int r = kStep * (i >> 1);
-                return r0 + tid / kPieces + r < n_rows ? load_chunk(at + (int64_t)r * g.st + 4 * (i & 1)) : none;
+                for (int i = 0; i < 2 * kLoads; ++i)
+                    take_single(chunk(i));
+                return true;
+            });
+        } else {
+            if (!range.dense)
+                steps([&](auto chunk) {
+                    uint32_t left = 0;
+#pragma unroll
+                    for (int i = 0; i < 2 * kLoads; ++i)
+                        left |= take(chunk(i)) ? 0u : 1u << i;
+                    settle(left, [&](int i) {
+                        const int r = kStep * (i >> 1);
+                        return r0 + tid / kPieces + r < n_rows ? load_chunk(at + (int64_t)r * g.st + 4 * (i & 1)) : none;
+                    });
+                    return __popc(left) < 2 * kMany;
+                });
+            steps([&](auto chunk) {
+#pragma unroll
+                for (int i = 0; i < 2 * kLoads; ++i)
+                    keep(chunk(i), true);
+                return true;
             });
         }
     } else {
@@ -933,22 +960,39 @@ __global__ __launch_bounds__(kCountThreads) void k_select_count(Geometry g, Work
             const int r = row_of_chunk(q, g);
             return load_row_chunk<false>(base + (int64_t)r * g.st, q - r * g.n_c, g);
         };
-        for (int q0 = 0; q0 < n_chunks; q0 += kLoads * kCountThreads) {  // uniform
-            half4_t v[kLoads];
-#pragma unroll
-            for (int u = 0; u < kLoads; ++u)
-                v[u] = load(q0 + u * kCountThreads + tid);
-            if (single) {
+        int q0 = 0;
+        auto steps = [&](auto f) {  // as above
+            for (bool more = true; more && q0 < n_chunks; q0 += kLoads * kCountThreads) {  // uniform
+                half4_t v[kLoads];
 #pragma unroll
                 for (int u = 0; u < kLoads; ++u)
-                    take_single(v[u]);
-                continue;
+                    v[u] = load(q0 + u * kCountThreads + tid);
+                more = f([&](int u) { return v[u]; });
             }
-            uint32_t left = 0;
+        };
+        if (single) {
+            steps([&](auto chunk) {
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u)
-                left |= take(v[u]) ? 0u : 1u << u;
-            settle(left, [&](int i) { return load(q0 + i * kCountThreads + tid); });
+                for (int u = 0; u < kLoads; ++u)
+                    take_single(chunk(u));
+                return true;
+            });
+        } else {
+            if (!range.dense)
+                steps([&](auto chunk) {
+                    uint32_t left = 0;
+#pragma unroll
+                    for (int u = 0; u < kLoads; ++u)
+                        left |= take(chunk(u)) ? 0u : 1u << u;
+                    settle(left, [&](int i) { return load(q0 + i * kCountThreads + tid); });
+                    return __popc(left) < kMany;
+                });
+            steps([&](auto chunk) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u)
+                    keep(chunk(u), true);
+                return true;
+            });
         }
     }
     if (queued)
@@ -1071,7 +1115,8 @@ __device__ __forceinline__ unsigned long long select_kept(const unsigned long lo
 // head; 0 without an index), beside the selection: with that in k_select_finish, which now has nothing left to do for such a
 // head, the encode of two [1, 8, 32768, 128] tensors took 178.6 us instead of 176.2, of one [2, 4, 1537, 100] 43.5 instead of 40.3.
 // These come last: the others fill the chip with two workgroups per compute unit, and those of missed heads keep their
-// places (the launch in us, 16 missed heads of 32768 rows alike within a row: 24.4 with them first, 17.0 so; half zero rows 41, 40).
+// places (the launch in us, 16 missed heads of 32768 rows alike within a row: 24.4 with them first, 17.0 so; half zero rows 41, 40;
+// that last tensor's encode 39.8 with them first, 40.0 so).
 // Two per compute unit take at most 96 scalar registers per wave, hence the launch bound (100 left it one: 32 instead of 26 for
 // 16 heads in steps of 1/8, 92 instead of 73 for 8 heads of 131072 rows, half of them zero).
 // Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, missed_parts() + finish_parts).

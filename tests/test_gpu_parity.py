@@ -714,6 +714,40 @@ def test_select_of_sorted_rows(steps, B, T, D):
     assert np.array_equal(thr.view(np.uint64), ((c * c) * m2).view(np.uint64))
 
 
+@pytest.mark.parametrize("kind", ["sorted", "two", "zeros", "near"])
+@pytest.mark.parametrize("B,H,T,D", [(1, 64, 4999, 128), (1, 64, 6001, 44), (2, 40, 4100, 127), (1, 2, 1153, 128), (3, 1, 700, 61)])
+def test_select_of_heads_whose_chunks_are_wanted(kind, B, H, T, D):
+    """Heads, and stretches of rows in them, in which the sweep wants most chunks: where the prediction says so before the first
+    step, and where a workgroup of several steps sees it in its first.  Each kind in every third head, the others smooth;
+    thresholds bit for bit."""
+    gen = torch.Generator(device=DEV).manual_seed(T + D)
+    n_c = -(-D // 4)
+    y = torch.randn(B, H, T, n_c, 4, generator=gen, device=DEV)
+    u = torch.rand(B, H, T, n_c, 1, generator=gen, device=DEV)
+    few = y[:, ::3]
+    if kind == "sorted":
+        few = few / few.norm(dim=-1, keepdim=True) * torch.linspace(0.5, 2.0, T, device=DEV).view(1, 1, T, 1, 1)
+    elif kind == "two":
+        few = torch.where(u[:, ::3] < 0.5, 1.0, 2.0).expand_as(few)
+    elif kind == "zeros":
+        few = few * (u[:, ::3] < 0.5)
+    else:  # half of the chunks close to 1, some of the values in fp32 twins
+        v = u[:, ::3]
+        near = 1.0 + torch.round(v * 64.0) / 1024.0
+        few = torch.where(v < 0.25, 0.5 * v, torch.where(v > 0.75, 2.0 * v, near)) * torch.tensor([1.0, 0.0, 0.0, 0.0], device=DEV)
+    y[:, ::3] = few
+    x = y.reshape(B, H, T, 4 * n_c)[..., :D].half()
+    z = torch.nn.functional.pad(x, (0, 4 * n_c - D)).view(B, H, T, n_c, 4).double()
+    r2 = ((z[..., 0] * z[..., 0] + z[..., 1] * z[..., 1]) + z[..., 2] * z[..., 2]) + z[..., 3] * z[..., 3]
+    m2 = r2.transpose(0, 1).reshape(H, -1).sort(1).values[:, (B * T * n_c - 1) // 2]
+    params = hq.params_for(x, 16)
+    ws = hq.alloc_workspace(params, DEV)
+    ws.fill_(0x5A)
+    hq.hqmq_encode(params, x.contiguous(), _sec(4, H, 16)[0].to(DEV), hq.alloc_encoded(params, DEV), ws)
+    thr = hq.hqmq_thresholds(params, ws)
+    assert torch.equal(thr.view(torch.int64), (9.0 * m2).view(torch.int64))
+
+
 def _head_with_cluster(R, D, k, gen):
     """fp16 [R, D] with k chunks around the median whose squared norms are neighbours on either side of 1, steps of 2e-9
     apart (up to 30 of them share an fp32 value); of the others one half is smaller, one larger."""
