@@ -1114,13 +1114,13 @@ __device__ __forceinline__ unsigned long long select_kept(const unsigned long lo
 // the histogram.  The box index that was built beside the sweep is finished in the same launch (finish_parts workgroups of every
 // head; 0 without an index), beside the selection: with that in k_select_finish, which now has nothing left to do for such a
 // head, the encode of two [1, 8, 32768, 128] tensors took 178.6 us instead of 176.2, of one [2, 4, 1537, 100] 43.5 instead of 40.3.
-// These come last: the others fill the chip with two workgroups per compute unit, and those of missed heads keep their
-// places (the launch in us, 16 missed heads of 32768 rows alike within a row: 24.4 with them first, 17.0 so; half zero rows 41, 40;
-// that last tensor's encode 39.8 with them first, 40.0 so).
+// kFinishFirst: these come first, where all workgroups lie beside one another, two per compute unit (that last tensor's encode 40.7,
+// 41.0 with them last); else last, so that those of missed heads keep their places (the launch in us, 16 missed heads of 32768
+// rows alike within a row: 24.4 with them first, 17.0 so; half zero rows 41, 40).
 // Two per compute unit take at most 96 scalar registers per wave, hence the launch bound (100 left it one: 32 instead of 26 for
 // 16 heads in steps of 1/8, 92 instead of 73 for 8 heads of 131072 rows, half of them zero).
 // Writes thr[h] = fl(fl(C*C) * median).  grid = (H, tensors, missed_parts() + finish_parts).
-template <bool kFull>
+template <bool kFull, bool kFinishFirst>
 __global__ __launch_bounds__(kSelectThreads, 8) void k_select_digit(Geometry g, WorkspaceOffsets wo, EncodeBatch batch,
                                                                     uint32_t finish_parts, float C)
 {
@@ -1130,11 +1130,11 @@ __global__ __launch_bounds__(kSelectThreads, 8) void k_select_digit(Geometry g, 
     __shared__ RankScratch sc;
     static_assert(kRankBins <= kBins0, "the histograms share their memory");
     static_assert(kFinishThreads == kSelectThreads && kFinishWords <= kBins0, "the same workgroup and memory");
-    const uint32_t parts = gridDim.z - finish_parts, part = blockIdx.z;
-    if (part >= parts) {  // uniform
+    const uint32_t parts = gridDim.z - finish_parts, part = blockIdx.z - (kFinishFirst ? finish_parts : 0u);
+    if (kFinishFirst ? blockIdx.z < finish_parts : part >= parts) {  // uniform
         const int h = blockIdx.x;
         const CellIndex ix = cell_index_of(g, ws, h);
-        finish_cells<true>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)(part - parts), (int)finish_parts,
+        finish_cells<true>(g, ws, reinterpret_cast<const float4_t *>(tn.sec) + (size_t)h * g.S, h, (int)(kFinishFirst ? blockIdx.z : part - parts), (int)finish_parts,
                                    CellPlaces{ix.list, reinterpret_cast<uint2 *>(ix.head), ix.id, ix.function}, hist);
         return;
     }
@@ -1703,7 +1703,11 @@ static void launch_select_for(const Geometry &g, const WorkspaceOffsets &wo, con
     // heads 6.0 / 6.0 / 7.1 / 8.5.
     const uint32_t heads_all = n * (uint32_t)g.H;
     const uint32_t finish_parts = g.cell_n == 0 ? 0u : std::max(1u, std::min({(uint32_t)(g.S + 31) / 32u, 512u / heads_all, kFinishParts}));
-    hipLaunchKernelGGL(k_select_digit<kFull>, dim3(g.H, n, parts.z + finish_parts), block, 0, stream, g, wo, batch, finish_parts, C);
+    const dim3 all(g.H, n, parts.z + finish_parts);
+    if (heads_all * all.z <= 512u)
+        hipLaunchKernelGGL((k_select_digit<kFull, true>), all, block, 0, stream, g, wo, batch, finish_parts, C);
+    else
+        hipLaunchKernelGGL((k_select_digit<kFull, false>), all, block, 0, stream, g, wo, batch, finish_parts, C);
     hipLaunchKernelGGL(k_select_finish<kFull>, parts, block, 0, stream, g, wo, batch, C);
 }
 
