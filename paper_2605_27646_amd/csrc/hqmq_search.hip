@@ -35,6 +35,8 @@
 //
 // That is the search of short tensors.  Long ones locate a chunk's direction in a box index over the codewords
 // (k_cells, k_search_cells below), which replaces the scan over all S secondaries.
+#include <algorithm>
+
 #include "hqmq_tables.h"
 
 namespace hqmq {
@@ -1255,15 +1257,18 @@ __device__ __forceinline__ void load_cells(const Geometry &g, const Workspace &w
 // A value that all lanes have, in a scalar register.
 __device__ __forceinline__ float scalar(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 
+constexpr int kCellWaves = 16;  // of a workgroup
+constexpr int cell_passes(int rows, int slot) { return slot > 0 && rows * slot >= kCellWaves * 64 * 2 ? 2 : 1; }
+
 // 16 waves and kRows rows per workgroup; a wave takes several whole rows at a time, one lane per chunk: kSlot = 32 or 16
 // lanes per row, the lanes past the row's chunks idle (row maxima are then DPP steps), or kSlot = 0 for rows that would
 // leave many idle: 64 / n_c rows next to one another.
 // kFull: rows of 128 elements.
 // Dynamic LDS: cell_lds_bytes().
-template <int kRows, int kSlot, bool kFull>
+template <int kRows, int kSlot, bool kFull, int kPasses = cell_passes(kRows, kSlot)>
 __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceOffsets wo, EncodeBatch batch, int cells_finished)
 {
-    constexpr int kWaves = 16;
+    constexpr int kWaves = kCellWaves;
     const EncodeTensor &tn = batch.t[blockIdx.z];
     const Workspace ws = carve_workspace(tn.ws, wo);
     const EncodedPtrs enc = tn.enc;
@@ -1286,9 +1291,9 @@ __global__ __launch_bounds__(1024, 8) void k_search_cells(Geometry g, WorkspaceO
     const int rl = lane / slot, c = lane - rl * slot;  // the lane's row of a pass and chunk of the row
     const int n_rows = min(kRows, g.T - t0);         // >= 1 by the grid's size
     uint32_t *my_pack = pack + wv * 64;              // rows_pass * row_words <= 64 words: w <= 22 as S <= kScreenMaxS
-    // Two passes at a time where there are rows enough for all waves: the steps that every lane of a row takes alike (scale,
-    // its reciprocal, what is kept of a row) are then taken once, the even lanes for the first pass and the odd for the second.
-    constexpr int kPasses = kSlot && kRows * kSlot >= kWaves * 64 * 2 ? 2 : 1;
+    // Two passes at a time where a workgroup has rows enough for all waves (launch_search): the steps that every lane of a row
+    // takes alike (scale, its reciprocal, what is kept of a row) are then taken once, the even lanes for the first pass and the odd
+    // for the second.
     const bool second = kPasses == 2 && of_mask(0xaaaaaaaaaaaaaaaaull);
     const _Float16 *rows = tn.x + (int64_t)b * g.sb + (int64_t)h * g.sh + (int64_t)(t0 + wv * kPasses * rows_pass) * g.st;
     const int64_t row_step = (int64_t)(kWaves * kPasses * rows_pass) * g.st;
@@ -1450,6 +1455,8 @@ hipError_t prepare_search_kernels()
                               reinterpret_cast<const void *>(k_search_flat<>),
                               reinterpret_cast<const void *>(k_search<false, false>),
                               reinterpret_cast<const void *>(k_search_flat<false, false>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true, 1>),
+                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false, 1>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
                               reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
@@ -1503,23 +1510,34 @@ hipError_t launch_search(const Geometry &g, const WorkspaceOffsets &wo, const En
         if (!cells_built)
             hipLaunchKernelGGL(k_cells, dim3(cell_blocks(g), g.H, (unsigned)n_tensors), dim3(kCellThreads), 0, stream, g, wo, batch);
         const size_t lds_cells = cell_lds_bytes(g);
-#define HQMQ_LAUNCH_CELLS(R)                                                                                             \
+#define HQMQ_LAUNCH_CELLS(...) \
+    hipLaunchKernelGGL((k_search_cells<__VA_ARGS__>), grid, dim3(64 * kCellWaves), lds_cells, stream, g, wo, batch, cells_built)
+#define HQMQ_LAUNCH_CELLS_OF(R, ...)                                                                                 \
     do {                                                                                                             \
         if (full_rows)                                                                                               \
-            hipLaunchKernelGGL((k_search_cells<R, 32, true>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \
-        else if (narrow && g.n_c > 21)                                                                                         \
-            hipLaunchKernelGGL((k_search_cells<R, 32, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
-        else if (narrow && g.n_c <= 16 && g.n_c > 12)                                                                          \
-            hipLaunchKernelGGL((k_search_cells<R, 16, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);   \
+            HQMQ_LAUNCH_CELLS(R, 32, true, ##__VA_ARGS__);                                                           \
+        else if (narrow && g.n_c > 21)                                                                               \
+            HQMQ_LAUNCH_CELLS(R, 32, false, ##__VA_ARGS__);                                                          \
+        else if (narrow && g.n_c <= 16 && g.n_c > 12)                                                                \
+            HQMQ_LAUNCH_CELLS(R, 16, false, ##__VA_ARGS__);                                                          \
         else                                                                                                         \
-            hipLaunchKernelGGL((k_search_cells<R, 0, false>), grid, dim3(1024), lds_cells, stream, g, wo, batch, cells_built);    \
+            HQMQ_LAUNCH_CELLS(R, 0, false, ##__VA_ARGS__);                                                           \
     } while (0)
-        if (g.search_rows == kSearchRowsHuge)
-            HQMQ_LAUNCH_CELLS(kSearchRowsHuge);
-        else if (g.search_rows == kSearchRowsLarge)
-            HQMQ_LAUNCH_CELLS(kSearchRowsLarge);
+        // The form for the rows that a workgroup has, not for those that it may have: up to two per wave in single passes, for which
+        // pairs would leave half of the waves without any (eight for 16 rows, four so); and the forms for more rows hold
+        // more in scalar registers than there are.  Known thresholds, 8 heads of two tensors, S = 256, the form for 512 rows / this
+        // one, call in us: 512 batch entries of 16 rows of 128 elements 243 / 230, 256 of 32 122 / 117, 128 of 64 87 / 83, 341 of 24
+        // rows of 96 184 / 169, 256 of 32 rows of 64 114 / 99, 113 of 72 rows of 128 89 / 88.
+        const int most = std::min(g.T, g.search_rows);
+        if (most > kSearchRowsLarge)
+            HQMQ_LAUNCH_CELLS_OF(kSearchRowsHuge);
+        else if (most > kSearchRowsSmall)
+            HQMQ_LAUNCH_CELLS_OF(kSearchRowsLarge);
+        else if (most > kCellWaves * 2)
+            HQMQ_LAUNCH_CELLS_OF(kSearchRowsSmall);
         else
-            HQMQ_LAUNCH_CELLS(kSearchRowsSmall);
+            HQMQ_LAUNCH_CELLS_OF(kSearchRowsSmall, 1);
+#undef HQMQ_LAUNCH_CELLS_OF
 #undef HQMQ_LAUNCH_CELLS
         return hipGetLastError();
     }

@@ -1164,6 +1164,31 @@ def test_box_index_search_takes_rows_two_passes_at_a_time(T, D):
     _roundtrip(_lognormal_tensor(B, 1, T, seed=T, sigma_g=0.8, D=D), S=192, rows=np.arange(0, B * T, 5), check_decode=False)
 
 
+@pytest.mark.parametrize("D,T", [(128, 15), (128, 32), (128, 33), (128, 64), (128, 65), (127, 31), (96, 19), (96, 33), (96, 65), (64, 29), (64, 32),
+                                 (64, 64), (64, 65), (61, 63), (40, 46), (40, 65)])
+def test_box_index_search_of_many_short_segments(D, T):
+    """513 batch entries of one head, few rows each, which a search of up to 512 rows per workgroup takes in the form for these few:
+    every form's last rows, with thresholds from the select and known ones (the index finished once, and by each workgroup)."""
+    B, S = 513, 256
+    x = _lognormal_tensor(B, 1, T, seed=T + D, sigma_g=0.8, D=D)
+    sec_t, sec = _sec(5, 1, S)
+    xb = _bits(x)
+    rows = np.unique(np.concatenate([np.arange(0, B * T, 23), np.arange(1, 40) * T - 1, [B * T - 1]]))
+    e = oracle.encode(xb, sec, rows=rows)
+    x_dev, sec_dev = x.to(DEV), sec_t.to(DEV)
+    g = gpu_encode(x_dev, sec_dev)
+    compare_encode(g, e, xb, sec)
+    ws = hq.alloc_workspace(g.params, DEV)
+    thr = torch.from_numpy((9.0 * e.m2).astype(np.float64)).to(DEV)
+    again = hq.alloc_encoded(g.params, DEV)
+    hq.hqmq_encode_given_thresholds(g.params, x_dev, sec_dev, thr, again, ws)
+    total = int(g.n_out[-1])
+    for a, b in ((again.codes, g.bufs.codes), (again.flags, g.bufs.flags), (again.row_off, g.bufs.row_off),
+                 (again.n_outliers, g.bufs.n_outliers), (again.sigma.view(torch.int16), g.bufs.sigma.view(torch.int16)),
+                 (again.outliers[:total].view(torch.int16), g.bufs.outliers[:total].view(torch.int16))):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("n,H", [(2, 32), (5, 13), (4, 32), (3, 43)])
 def test_box_index_finished_for_many_heads(n, H):
     """64, 65, 128 and 129 heads in a launch, two workgroups of which finish a head's index.  Each tensor's bytes are those of a
