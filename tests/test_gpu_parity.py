@@ -1141,10 +1141,12 @@ def test_box_index_finished_by_the_select_or_by_the_search(S, D, kind):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("D,T", [(128, 8), (100, 10)])
-def test_box_index_search_of_rows_far_apart(D, T):
-    """Rows 2^29 elements apart, past what a pass's 32-bit offsets reach: the bytes of the same rows side by side."""
-    B, H, S, step = 64, 1, 512, 1 << 29
+@pytest.mark.parametrize("D,T,step", [(128, 8, 1 << 29), (100, 10, 1 << 29), (128, 8, (1 << 29) - 8), (100, 10, (1 << 29) - 8),
+                                      (64, 16, (1 << 29) - 8), (64, 16, 1 << 29)])
+def test_box_index_search_of_rows_far_apart(D, T, step):
+    """Rows 2^29 elements apart, past what a pass's 32-bit offsets reach, and just below, where those of four rows pass 2^31: the
+    bytes of the same rows side by side."""
+    B, H, S = 64, 1, 512
     x = _lognormal_tensor(B, H, T, seed=T, sigma_g=0.8, D=D).to(DEV)
     sec = _sec(9, H, S)[0].to(DEV)
     near = gpu_encode(x, sec)
