@@ -157,16 +157,6 @@ inline int search_rows_for(int T, int S16, int A16, int D, int row_words)
     return kSearchRowsSmall;
 }
 
-// Dynamic LDS of one workgroup of the search with the box index.
-inline size_t cell_lds_bytes(const Geometry &g)
-{
-    const size_t tables = ((size_t)g.cell_used + 1) * 16 + (size_t)g.S * 16 + cell_head_bytes(g.cell_n) +
-                          (size_t)g.cell_groups * 8 + (size_t)g.cell_used * 4 + 33 * 32;
-    const size_t scratch = (size_t)g.cell_words * 8 + 4;
-    const size_t rows = 16 * 64 * 4 + (size_t)g.search_rows * 8;
-    return tables + (rows > scratch ? rows : scratch);
-}
-
 // Workspace carve-up (device pointers into the caller's workspace).
 struct Workspace {
     SelectState *state;            // [H]

@@ -1260,6 +1260,13 @@ __device__ __forceinline__ float scalar(float v) { return __int_as_float(__built
 constexpr int kCellWaves = 16;  // of a workgroup
 constexpr int cell_passes(int rows, int slot) { return slot > 0 && rows * slot >= kCellWaves * 64 * 2 ? 2 : 1; }
 
+// Dynamic LDS of a workgroup: the index, then the rows' state and the waves' words, in whose place it is finished.
+inline size_t cell_lds_bytes(const Geometry &g)
+{
+    const size_t rows = kCellWaves * 64 * 4 + (size_t)g.search_rows * 8, scratch = (size_t)g.cell_words * 8 + 4;
+    return cell_tables(g).end + std::max(rows, scratch);
+}
+
 // 16 waves and kRows rows per workgroup; a wave takes several whole rows at a time, one lane per chunk: kSlot = 32 or 16
 // lanes per row, the lanes past the row's chunks idle (row maxima are then DPP steps), or kSlot = 0 for rows that would
 // leave many idle: 64 / n_c rows next to one another.
@@ -1454,21 +1461,21 @@ hipError_t prepare_search_kernels()
     const void *variants[] = {reinterpret_cast<const void *>(k_search<>),
                               reinterpret_cast<const void *>(k_search_flat<>),
                               reinterpret_cast<const void *>(k_search<false, false>),
-                              reinterpret_cast<const void *>(k_search_flat<false, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true, 1>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false, 1>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 0, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, true>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 16, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 0, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, true>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 16, false>),
-                              reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 0, false>)};
+                              reinterpret_cast<const void *>(k_search_flat<false, false>)};
+    const void *cells[] = {reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true, 1>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false, 1>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, true>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 32, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 16, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsSmall, 0, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, true>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 32, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 16, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsLarge, 0, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, true>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 32, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 16, false>),
+                           reinterpret_cast<const void *>(k_search_cells<kSearchRowsHuge, 0, false>)};
     hipError_t err = hipSuccess;
     for (const void *f : fused)
         if (err == hipSuccess)
@@ -1476,11 +1483,15 @@ hipError_t prepare_search_kernels()
     for (const void *f : variants)
         if (err == hipSuccess)
             err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsPerCu);
-    hipFuncAttributes cells;  // the index in the workspace holds LDS addresses from 0 on
-    if (err == hipSuccess)
-        err = hipFuncGetAttributes(&cells, variants[4]);
-    if (err == hipSuccess && cells.sharedSizeBytes != 0)
-        err = hipErrorInvalidConfiguration;
+    for (const void *f : cells) {
+        hipFuncAttributes own;
+        if (err == hipSuccess)
+            err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsPerCu);
+        if (err == hipSuccess)
+            err = hipFuncGetAttributes(&own, f);
+        if (err == hipSuccess && own.sharedSizeBytes != 0)  // the index in the workspace holds LDS addresses from 0 on
+            err = hipErrorInvalidConfiguration;
+    }
     return err;
 }
 
