@@ -753,9 +753,17 @@ constexpr int kCountThreads = kCellThreads;
 constexpr int kCountRows = 512;  // of a workgroup, at most
 constexpr int kStageKeys = 144;  // keys a workgroup stages per list
 constexpr int kQueue = 256;      // chunks a wave queues up
+constexpr int kStageDense = kStageKeys + kCountThreads / 64 * kQueue / kBuckets;  // where no wave has a queue
 struct CountStage {              // LDS
-    unsigned long long staged[kBuckets][kStageKeys];
-    uint2 queue[kCountThreads / 64][kQueue];         // of each wave: chunks whose keys are wanted
+    union {
+        struct {
+            unsigned long long staged[kBuckets][kStageKeys];
+            uint2 queue[kCountThreads / 64][kQueue];  // of each wave: chunks whose keys are wanted
+        };
+        // Two values of norms in 128 rows of 12 elements fill 192 places of two lists: sweep of 8 heads of 20000 such rows 12 us
+        // with fewer, 8 with these.
+        unsigned long long dense[kBuckets][kStageDense];
+    };
     uint32_t n_staged[kBuckets], n_below;            // n_staged: all keys of the list, also those past the stage
     uint32_t n_direct[kBuckets], full[kBuckets];     // those of them that the list's counter has; the list is full
 };
@@ -834,14 +842,17 @@ __global__ __launch_bounds__(kCountThreads, 6) void k_select_count(Geometry g, W
     const bool single = range.span == 0ull;  // uniform; a range of one value: its keys may be all there are, and only their number counts
     const int lane = tid & 63;
     uint2 *queue = st.queue[tid / 64];
+    const bool wide = !kFull && range.dense;  // rows of 128 elements fill any number
+    const uint32_t stage = wide ? kStageDense : kStageKeys;
+    auto staged = [&](uint32_t k, uint32_t pos) -> unsigned long long & { return wide ? st.dense[k][pos] : st.staged[k][pos]; };
     uint32_t below = 0, equal = 0, queued = 0;  // of the wave
     auto keep = [&](const half4_t v, bool in) {
         const unsigned long long key = key_of(chunk_norm2(v)) & kKeyMask;
         below += (uint32_t)__popcll(ballot(in && key < range.lo));
         if (in && range.holds(key)) {
             const uint32_t k = range.of(key), pos = atomicAdd(&st.n_staged[k], 1u);
-            if (pos < (uint32_t)kStageKeys)
-                st.staged[k][pos] = key;
+            if (pos < stage)
+                staged(k, pos) = key;
             else if (!*(volatile uint32_t *)&st.full[k])
                 append(k, key);
         }
@@ -1012,10 +1023,10 @@ __global__ __launch_bounds__(kCountThreads, 6) void k_select_count(Geometry g, W
             st.full[tid] = atomicAdd(&count[tid * kBucketPitch], st.n_staged[tid] - st.n_direct[tid]);
         __syncthreads();
         for (int k = tid / 64; k < kBuckets; k += kCountThreads / 64) {
-            const uint32_t n = min(st.n_staged[k], (uint32_t)kStageKeys), at = st.full[k];
+            const uint32_t n = min(st.n_staged[k], stage), at = st.full[k];
             for (uint32_t i = tid & 63; i < n; i += 64)
                 if (at + i < cap)
-                    lists[k * cap + at + i] = st.staged[k][i];
+                    lists[k * cap + at + i] = staged(k, i);
         }
     }
     if (tid == 0 && st.n_below)

@@ -715,7 +715,7 @@ def test_select_of_sorted_rows(steps, B, T, D):
 
 
 @pytest.mark.parametrize("kind", ["sorted", "two", "zeros", "near"])
-@pytest.mark.parametrize("B,H,T,D", [(1, 64, 4999, 128), (1, 64, 6001, 44), (2, 40, 4100, 127), (1, 2, 1153, 128), (3, 1, 700, 61)])
+@pytest.mark.parametrize("B,H,T,D", [(1, 64, 4999, 128), (1, 64, 6001, 44), (2, 40, 4100, 127), (1, 2, 1153, 128), (3, 1, 700, 61), (1, 8, 2501, 12)])
 def test_select_of_heads_whose_chunks_are_wanted(kind, B, H, T, D):
     """Heads, and stretches of rows in them, in which the sweep wants most chunks: where the prediction says so before the first
     step, and where a workgroup of several steps sees it in its first.  Each kind in every third head, the others smooth;
