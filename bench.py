@@ -25,7 +25,10 @@ if ROOT not in sys.path:
 METRIC = "HQMQ encode/decode elems/sec at 1 GPU; % of fp32-compute (enc) / HBM (dec) roofline"
 PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 matrix (and packed vector) peak
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E peak
-PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # plain (unpacked) VALU lane-operations per second, in 1e12
+# VALU lane-operations per second, in 1e12, of the instructions that issue fastest: a wave's fp32 additions, multiplications and
+# FMAs, 32-bit additions, logic, right shifts and moves take 2 cycles of a SIMD (2.4 measured); minima, maxima, compares,
+# selects, conversions, three-operand integer forms and DPP 4 (4.2 measured), reciprocals and square roots 8.
+PEAK_VALU_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 
 PROFILES = os.path.join(ROOT, "profiles")
 
@@ -213,8 +216,9 @@ def main() -> int:
         v = prof.get((kernel, "traffic_bytes_per_tensor"))
         return None if v is None else v * per_launch
 
-    # What the search kernel executes, from the committed instruction counters: the share of the chip's VALU issue
-    # slots it fills at the measured launch time (256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, plain instructions).
+    # What the search kernel executes, from the committed instruction counters: its VALU lane-operations at the measured launch
+    # time against the fastest rate of issue (a lower bound of the time that the VALUs are busy for: two thirds of its
+    # instructions are of the kinds that issue at half that rate).
     valu_chunk = prof.get((search_kernel, "valu_lane_operations_per_chunk"))
     executed = {"source": prof.get(("source", "instruction_counters")), "valu_lane_operations_per_chunk": valu_chunk,
                 "valu_issue_frac": None}

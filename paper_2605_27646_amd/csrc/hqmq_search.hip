@@ -1008,9 +1008,10 @@ hipError_t launch_append(const AppendShape &g, const AppendBatch &batch, hipStre
 // 5.5 S operations; best and runner-up decide as in the screen above: a chunk whose two best lie within kCellBand
 // is searched again over all S secondaries in fp32.  Either way the codeword is the best one, or the fp32 search's choice
 // between codewords whose scores differ by no more than its own rounding.
-// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 114 by the index (and 14 beside the
-// select's sweep).  Bound by VALU issue (257 instructions per 64 chunks, 113 of them in the list loop: the longest of
-// 64 lists has 3.3 groups of four on average; the VALUs are busy for 97 % of the time), LDS for 61 % of it (list entries read one
+// Measured, two [1, 8, 32768, 128] tensors in a call, S = 256: 1017 us (matrix screen), 114 by the index (and 7 beside the
+// select's sweep).  Bound by VALU issue: 258 instructions per 64 chunks, 113 of them in the list loop (the longest of 64 lists has
+// 3.3 groups of four on average), 1.01 per SIMD and four cycles.  A third of them, additions, multiplications and moves, issue in
+// 2.4 cycles, the others in 4.2: the VALUs are busy for some nine tenths of the time, LDS for 65 % (list entries read one
 // by one, without the instructions that take them apart: 139 us).  118 us and 262 with the rows of one pass at a time, 129 and 282
 // with the index finished by every workgroup (finish_cells), 145 and 327 with fp64 norms of every chunk, ballots of integers, the fold by all sixteen products
 // and the rows' state stored row by row.

@@ -10,8 +10,8 @@
     rocprofv3 --pmc FETCH_SIZE --output-format csv -d <raw_dir> -o fetch -- \
         python3 <repo>/bench.py --workload W --steps 1 --warmup 0 --layers 2 --no-cpu-baseline --no-append --calibrate-copy
     rocprofv3 --pmc WRITE_SIZE --output-format csv -d <raw_dir> -o write -- (the same bench.py arguments)
-    rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_BUSY_CYCLES SQ_WAVE_CYCLES \
-        SQ_INSTS_SALU SQ_INSTS_LDS --output-format csv -d <raw_dir> -o insts -- \
+    rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_IDX_ACTIVE \
+        SQ_INSTS_SALU SQ_INSTS_LDS GRBM_GUI_ACTIVE --output-format csv -d <raw_dir> -o insts -- \
         python3 <repo>/bench.py --workload W --steps 1 --warmup 0 --layers 1 --no-cpu-baseline --no-append --q-heads-per-kv 0
 
 Writes profiles/hot_path_kernels_W.txt, profiles/hbm_traffic_W.txt and profiles/instruction_counters_W.txt.  The
@@ -27,8 +27,7 @@ import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-N_SIMD = 256 * 4
-CLOCK_GHZ = 2.4
+N_SIMD, N_CU, N_XCD = 256 * 4, 256, 8
 
 
 def short(name: str) -> str:
@@ -171,26 +170,25 @@ measured per tensor: search {s[0] + s[1]:.1f} MB ({s[0]:.1f} read + {s[1]:.1f} w
         ic = counters(f"{raw}/insts_counter_collection.csv")
         lines = [f"""Instruction counters of the hot-path kernels, workload {wl} ({shape} fp16 tensors, S = {cfg['S']}, b_r = {cfg['b_r']}), MI355X:
 one rocprofv3 PMC pass over a 1-layer run (2 tensors: every encode / decode kernel is ONE launch over both).  Counters are
-sums over the launch.  SQ_ACTIVE_INST_VALU counts in units of 4 cycles; with {N_SIMD} SIMDs and a nominal {CLOCK_GHZ} GHz clock
-"VALU busy" below is 4 x SQ_ACTIVE_INST_VALU / {N_SIMD} cycles, i.e. the time every SIMD's vector ALU would be busy if the work
-were spread evenly; "launch" is the kernel's average duration in the kernel trace of the same build (32 tensors per launch),
-scaled to the 2 tensors of this run.
+sums over the launch; "cycles" are those for which the chip was active for it (GRBM_GUI_ACTIVE / {N_XCD}, start and end of the launch
+included), of the same launch as the others.  "VALU per 4" is SQ_ACTIVE_INST_VALU per SIMD and four of these cycles: it counts one
+per instruction, two for reciprocals and square roots, and is no share of time.  A wave's fp32 additions, multiplications and FMAs,
+32-bit additions, logic, right shifts and moves issue in 2.4 cycles (1.7 per 4 in kernels of nothing else), all others in 4.2
+(0.95 per 4).  "LDS" is the share of the cycles for which the LDS of a compute unit serves indexed accesses.
 
 command (run from /tmp with TMPDIR=/tmp):
-  rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_INSTS_SALU SQ_INSTS_LDS --output-format csv -d <out> -o insts -- python3 bench.py --workload {wl} --steps 1 --warmup 0 --layers 1 --no-cpu-baseline --no-append --q-heads-per-kv 0
+  rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_IDX_ACTIVE SQ_INSTS_SALU SQ_INSTS_LDS GRBM_GUI_ACTIVE --output-format csv -d <out> -o insts -- python3 bench.py --workload {wl} --steps 1 --warmup 0 --layers 1 --no-cpu-baseline --no-append --q-heads-per-kv 0
 
-kernel                              waves   VALU/wave   MFMA/wave   SALU/wave    LDS/wave   VALU busy (us)   launch (us, 2 tensors)   busy / launch"""]
-        trace_us = {short(r["Name"]): float(r["AverageNs"]) / 1e3 / per_launch * 2 for r in rows}
+kernel                                  waves   VALU/wave   MFMA/wave   SALU/wave    LDS/wave       cycles   VALU per 4     LDS"""]
         figs = []
         for k, c in ic.items():
             if "hqmq" not in k or not c.get("SQ_WAVES"):
                 continue
             wv = c["SQ_WAVES"]
-            busy_us = 4 * c["SQ_ACTIVE_INST_VALU"] / N_SIMD / (CLOCK_GHZ * 1e3)
-            t = trace_us.get(short(k))
-            lines.append(f"{short(k):32s} {wv:8.0f} {c['SQ_INSTS_VALU'] / wv:11.1f} {c['SQ_INSTS_MFMA'] / wv:11.2f} "
-                         f"{c['SQ_INSTS_SALU'] / wv:11.1f} {c['SQ_INSTS_LDS'] / wv:11.1f} {busy_us:16.1f} "
-                         + (f"{t:24.1f} {busy_us / t:15.2f}" if t else ""))
+            cycles = c["GRBM_GUI_ACTIVE"] / N_XCD
+            lines.append(f"{short(k):36s} {wv:8.0f} {c['SQ_INSTS_VALU'] / wv:11.1f} {c['SQ_INSTS_MFMA'] / wv:11.2f} "
+                         f"{c['SQ_INSTS_SALU'] / wv:11.1f} {c['SQ_INSTS_LDS'] / wv:11.1f} {cycles:12.0f} "
+                         f"{4 * c['SQ_ACTIVE_INST_VALU'] / N_SIMD / cycles:12.2f} {c['SQ_LDS_IDX_ACTIVE'] / N_CU / cycles:7.2f}")
             if base(k) == rf["kernel"]:
                 figs.append((base(k), 64 * c["SQ_INSTS_VALU"] / (2 * chunks)))
         lines.append("")
