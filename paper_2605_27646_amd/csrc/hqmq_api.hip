@@ -148,15 +148,18 @@ static Geometry make_geometry(const hqmq_params *p)
 
 // The search of the general path: the box index (built beside the select's sweep, or where a head has at most 1024 rows in a
 // launch of its own, of 12 to 25 us; then a search that hardly depends on S) from chunks per head x (S + 32) = 6.3 million on, the
-// matrix screen below.  Whole encodes with heads of 128 elements, screen / index in us.  4 tensors of 8 heads: S = 256: 53 / 60 at
-// T = 512, 68 / 64 at 683, 87 / 66 at 1024, 266 / 91 at 4096; S = 64: 60 / 62 at 1100, 66 / 63 at 1536, 78 / 68 at 2048, 123 / 77 at
-// 4096; S = 16: 48 / 50 at 1100, 59 / 56 at 2048, 75 / 70 at 3072, 88 / 68 at 4096.  Of 64 heads the two meet earlier (S = 256: 85 / 84
-// at 512; S = 16: 68 / 68 at 1100), of fewer later: 8 heads S = 256: 41 / 45 at 1024, 53 / 49 at 1100; S = 64: 43 / 41 at 2048; S = 16:
-// 45 / 42 at 4096; 2 heads S = 256: 29 / 43 at 1024, 50 / 45 at 4096; S = 16: 38 / 38 at 8192.
+// matrix screen below.  Whole encodes with heads of 128 elements, screen / index in us.  4 tensors of 8 heads: S = 256: 55 / 60 at
+// T = 512, 70 / 64 at 683, 85 / 65 at 1024, 262 / 89 at 4096; S = 64: 58 / 57 at 1100, 62 / 58 at 1536, 75 / 61 at 2048, 119 / 74 at
+// 4096; S = 16: 46 / 46 at 1100, 57 / 50 at 2048, 72 / 59 at 3072, 84 / 64 at 4096.  Of 64 heads the two meet earlier (S = 256: 83 / 86
+// at 512; S = 16: 66 / 60 at 1100), of fewer later: 8 heads S = 256: 37 / 43 at 1024, 50 / 46 at 1100; S = 64: 38 / 38 at 2048; S = 16:
+// 42 / 40 at 4096; 2 heads S = 256: 27 / 41 at 1024, 45 / 42 at 4096; S = 16: 34 / 36 at 8192.
 // A workgroup copies the whole index for rows of one (batch entry, head) only, so their chunks x (S + 32) have to reach 2^17: two
-// tensors with 8 heads and many batch entries: S = 256: 384 / 472 at B = 1024, T = 4, 238 / 253 at 512 x 8, 360 / 270 at 512 x 16; S =
-// 64: 353 / 464 at 1024 x 8, 427 / 481 at 1024 x 16, 285 / 256 at 512 x 32, 219 / 144 at 256 x 64; S = 16: 102 / 113 at 256 x 32, 93 /
-// 82 at 128 x 64, 88 / 67 at 64 x 128.
+// tensors with 8 heads and many batch entries: S = 256: 400 / 384 at B = 1024, T = 4, 245 / 201 at 512 x 8, 362 / 214 at 512 x 16; S =
+// 64: 360 / 394 at 1024 x 8, 433 / 410 at 1024 x 16, 289 / 217 at 512 x 32, 217 / 117 at 256 x 64; S = 16: 102 / 96 at 256 x 32, 90 /
+// 73 at 128 x 64, 84 / 61 at 64 x 128.  With known thresholds, where each of the search's workgroups finishes the index for itself:
+// 186 / 209 at S = 256, 512 x 8, 304 / 224 at 512 x 16; 230 / 208 at S = 64, 512 x 32; 62 / 51 at S = 16, 64 x 128; 4 tensors of 8 heads
+// 45 / 49 at S = 64, T = 1536, 51 / 50 at S = 16, 3072.
+// (Both lines were laid when every call did that: behind a select they now lie up to 20 % too high for 4 tensors and more.)
 static bool use_cells(const Geometry &g)
 {
     const uint64_t work = (uint64_t)g.T * g.n_c * (uint64_t)(g.S + 32);

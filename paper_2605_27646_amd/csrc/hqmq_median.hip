@@ -11,8 +11,8 @@
 // they lie, and the wanted rank is located in the one list that holds it by histograms over ever narrower ranges
 // (select_rank).  The prediction decides which keys are kept, never the result.
 //   heads of at most 1024 rows   one workgroup selects from its registers (k_select_head)
-//   longer heads                 k_select_predict (a workgroup per head), k_select_count (the sweep, HBM-bound),
-//                                k_select_digit (the selection), k_select_finish (only where the prediction missed)
+//   longer heads                 k_select_predict (one to eight workgroups per head), k_select_count (the sweep), k_select_digit (the
+//                                selection), k_select_finish (only where the prediction missed)
 // For a head whose prediction missed, or whose list overflowed, k_select_digit makes a histogram of 8192 equal parts of the
 // predicted range, or of a first digit of all keys, and k_select_finish collects the keys of the bin that holds the median;
 // every other head's workgroups leave at once.  The first digit is made of the exponent and 6 mantissa bits (the squares of
